@@ -5,38 +5,41 @@
 // (8 consecutive k per lane), so tiles go global -> LDS -> registers as 16-byte pieces
 // with no transposition anywhere.
 //
-// Tiling.  A workgroup of WGM x WGN wavefronts owns a BM x BN tile of the output (BM tokens,
+// Tiling.  A workgroup of WGM x WGN (x WGK) wavefronts owns a BM x BN tile of the output (BM tokens,
 // BN out-features); a wavefront owns TM x TN MFMA tiles of 32x32 with fp32 accumulators in
 // registers.  The MFMA is issued with W as its first operand and u as its second, so a lane
 // ends up holding, for one token, 4 consecutive out-features per accumulator group.
 // The main configuration is 192 x 384 with eight wavefronts (2 x 4, each 96 x 96): the
-// accumulators fill half of the compute unit's register file.  What sets the tile size is the
-// path from L2 into the compute units: it delivers well under 100 bytes per clock to a CU, so a
-// tile has to do about 128 flop per byte fetched, which 192 x 384 does (and 384 divides the
-// model's widths 1152, 3456 and 4608).  Two wavefronts share a SIMD: one wavefront alone can draw
-// only about 30 B/clk from the LDS, less than its matrix core eats.
+// accumulators fill half of the compute unit's register file and a tile does 128 flop per byte
+// fetched (384 divides the model's widths 1152, 3456 and 4608).  Small tiles also run eight
+// wavefronts, two per SIMD, so that one's LDS reads run under the other's MFMAs: WGK = 2 gives
+// each half of every k-step to a different set of wavefronts, whose partial sums meet in LDS once
+// per tile.
 //
-// Operand path.  k is walked in steps of 32.  Tiles go global -> LDS with 16-byte
-// global_load_lds: no staging registers, no ds_write, and the loads of k-step i+NS-1 are in
-// flight while k-step i is multiplied (NS LDS stages of (BM+BN) rows x 64 B).  A wave-wide
-// load places lane l's piece at LDS base + 16 l, i.e. 16 consecutive 64-byte rows.  The LDS
-// of this chip has 64 banks (256 B per clock): the four 16-byte chunks of row r are stored
-// at slot chunk ^ ((r >> 2) & 3), so the 16 lanes that a ds_read_b128 serves per clock (16
-// consecutive rows, same chunk) touch 16 different 16-byte bank groups.  Since the load
-// instruction fixes where each lane's piece lands, the swizzle is applied to the GLOBAL
-// address each lane fetches from.  The (BM+BN)/16 loads of a k-step are dealt to the wavefronts
-// round-robin; when they do not divide evenly the first wavefronts issue one more, and the k
-// loop is compiled once per count, because completion is tracked with the vector-memory
-// counter, which retires loads in order: before the barrier of k-step i each wave waits until
-// at most its loads of the later k-steps are outstanding, so past the barrier stage i+1 is
-// complete.  A k tail (k not a multiple of 32) is zero-filled by pointing the lanes past
-// the end of the row at a block of zeros.
+// Operand path.  k is walked in steps of 64, i.e. whole 128-byte cache lines of every operand row:
+// a row piece of 64 bytes (32 of k) costs the path from L2 into the CU as much as a whole line does
+// (measured with a load-only loop over the tiles of 192 x 384, all CUs busy: 58 bytes per ns and CU
+// with 64-byte pieces, 96 with 128-byte ones), and that path is what the k loop waits for.  Tiles go
+// global -> LDS with 16-byte buffer loads: no staging registers, no ds_write; the resource descriptor
+// carries the tile's base and what is left of the matrix, so rows past the end are not fetched, and a
+// lane needs one offset per operand for the whole kernel.  The loads of NS k-steps are in flight in
+// NS LDS stages; the stream of k-steps runs on into the workgroup's next tile, so a tile's epilogue
+// runs while the first operands of the next one arrive.  Completion is tracked with the
+// vector-memory counter, which retires in order: before the barrier of k-step i each wavefront waits
+// until only its loads of later k-steps are outstanding, so past the barrier stage i+1 is complete.
+// A wave-wide load places lane l's piece at LDS base + 16 l, i.e. 8 consecutive 128-byte rows.  The
+// LDS of this chip has 64 banks (256 B per clock): 16-byte chunk c of row r is stored at slot
+// c ^ ((r >> 1) & 7), so the 16 lanes that a ds_read_b128 serves per clock (16 consecutive rows, same
+// chunk) touch 16 different 16-byte bank groups.  Since the load instruction fixes where each lane's
+// piece lands, the swizzle is applied to the GLOBAL address each lane fetches from.  A k tail (k not a
+// multiple of 64) is zero-filled by pointing the lanes past the end of the row past the end of the
+// buffer.
 //
 // Tile order.  Persistent workgroups; see tile_sequence_index.
 //
-// Epilogue.  The accumulators are staged through LDS (free once the k loop is done), 32 rows
-// per wavefront at a time, so that global memory is written in whole-row pieces, 16 bytes per
-// lane, instead of 8-byte pieces scattered over 32 rows: bf16 store; GELU(tanh form) + bf16
+// Epilogue.  Each wavefront stages its accumulators, 32 token rows at a time, through a part of the
+// last k-step's LDS stage that is its own (no barrier between the pieces), so that global memory is
+// written in row pieces of 64 bytes and more, 16 bytes per lane: bf16 store; GELU(tanh form) + bf16
 // store; gated residual update of the fp32 stream (x += gate_b * (acc + bias)), optionally
 // also storing bf16(x).
 #include "ddit_common.hpp"
@@ -46,10 +49,9 @@
 
 namespace {
 
-constexpr int BK = 32;        // k per pipeline step (bf16 elements)
-constexpr int ROW = 64;       // bytes per LDS row
-
-__device__ __attribute__((aligned(16))) const unsigned int k_zero_block[4] = {0u, 0u, 0u, 0u};
+constexpr int BK = 64;         // k per pipeline step (bf16 elements)
+constexpr int ROW = 128;       // bytes per LDS row
+constexpr int BIAS_SLOTS = 4;  // tiles whose bias may be in LDS at once (see GemmCfg::MIN_STEPS)
 
 struct GemmParams {
   const bf16_t *u; int64_t ld_u;
@@ -62,6 +64,7 @@ struct GemmParams {
   const float *gate_c6; int64_t gate_c6_stride;
   int64_t tokens_per_sample;
   int tiles_m; int tiles_n; int group_w; int total_tiles; int rounds;
+  int plain;   // row strides below 2^26 elements: a row group's offsets fit 32 bits
 };
 
 // A grouped launch: one token matrix u against G weight matrices of the same shape [group_n, k], each
@@ -95,9 +98,11 @@ __device__ __forceinline__ void lds_barrier() {
 // 16-byte LDS reads that the compiler does not see as LDS reads.  It guards every LDS read it
 // knows of with a wait for ALL outstanding vector-memory operations (it cannot tell the
 // direct-to-LDS loads from stores), which in the epilogues would make each read wait for the round
-// trip of the stores issued just before it.  The epilogues read only what the workgroup itself
-// staged behind a barrier, so no vector-memory wait is needed there.
+// trip of the stores issued just before it.  The epilogues read only what the same wavefront has
+// staged (LDS operations of a wavefront complete in order), so no vector-memory wait is needed there.
 typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
+typedef int intx4 __attribute__((ext_vector_type(4)));
+typedef unsigned int uintx2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ unsigned lds_offset(const void *p) {
   return (unsigned)(uintptr_t)(__attribute__((address_space(3))) const void *)p;
 }
@@ -107,11 +112,15 @@ __device__ __forceinline__ void lds_read2_b128(uintx4 (&v)[2], unsigned a0, unsi
                : "v"(a0), "v"(a1)
                : "memory");
 }
-__device__ __forceinline__ void lds_read3_b128(uintx4 (&v)[3], unsigned a0, unsigned a1, unsigned a2) {
-  asm volatile("ds_read_b128 %0, %3\n\tds_read_b128 %1, %4\n\tds_read_b128 %2, %5\n\ts_waitcnt lgkmcnt(0)"
-               : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2])
-               : "v"(a0), "v"(a1), "v"(a2)
-               : "memory");
+// four 32x32 fp32 row pieces: 8 rows of PITCH bytes further each
+template <int STEP>
+__device__ __forceinline__ void lds_read4_b128(uintx4 (&v)[4], unsigned a) {
+  asm volatile(
+      "ds_read_b128 %0, %4\n\tds_read_b128 %1, %4 offset:%5\n\tds_read_b128 %2, %4 offset:%6\n\t"
+      "ds_read_b128 %3, %4 offset:%7\n\ts_waitcnt lgkmcnt(0)"
+      : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3])
+      : "v"(a), "n"(STEP), "n"(2 * STEP), "n"(3 * STEP)
+      : "memory");
 }
 // the tile's bias for this lane: 4 consecutive features (8 bytes) at each of four 8-feature steps
 __device__ __forceinline__ void lds_read4_b64(uint2 (&v)[4], unsigned a) {
@@ -170,312 +179,376 @@ __device__ __forceinline__ void decode_tile(const GemmParams &p, int L, int &til
   tile_n = g * p.group_w + (r - tile_m * bw);
 }
 
-template <int WGM, int WGN, int TM, int TN, int NS>
+template <int WGM, int WGN, int WGK, int TM, int TN, int NS>
 struct GemmCfg {
-  static constexpr int WGM_ = WGM;
-  static constexpr int NW = WGM * WGN;                       // wavefronts per workgroup
+  static constexpr int NW = WGM * WGN * WGK;                 // wavefronts per workgroup
   static constexpr int NT = 64 * NW;
   static constexpr int BM = WGM * TM * 32;
   static constexpr int BN = WGN * TN * 32;
   static constexpr int STAGE = (BM + BN) * ROW;
-  static constexpr int MAIN_BYTES = NS * STAGE;
-  static constexpr int PASS_ROWS = WGM * 32;                 // rows staged per pass of the fp32 epilogue
-  static constexpr int PITCH_BF16 = BN * 2 + 16;             // epilogue staging row pitches
-  static constexpr int PITCH_F32 = BN * 4 + 16;
-  static constexpr int EPI_BYTES = PASS_ROWS * PITCH_F32;
-  static constexpr int SMEM = MAIN_BYTES > EPI_BYTES ? MAIN_BYTES : EPI_BYTES;
-  static constexpr int GATE_BYTES = 2 * BN * 4;              // gate vectors of two samples, past the stages
-  static constexpr int BIAS_BYTES = BN * 2;                  // the tile's bias, past the gates
-  static constexpr int EXTRA_BYTES = GATE_BYTES + BIAS_BYTES;
-  // the bf16 epilogues stage one row-tile of every wavefront at a time inside the LAST TWO stages,
-  // so that the first stages can already receive the next tile's operands
-  static constexpr int EARLY_STEPS = NS - 2;                 // k-steps of the next tile fetched before the epilogue
-  static constexpr int BF16_STAGING = EARLY_STEPS * STAGE;
-  static_assert(PASS_ROWS * PITCH_BF16 <= 2 * STAGE, "a pass of the bf16 epilogue must fit two stages");
+  static constexpr int NJU = BM / 8 / NW, NJW = BN / 8 / NW; // wave-wide loads (8 rows each) per wavefront and k-step
+  static constexpr int NJ = NJU + NJW;
+  static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "the rows of both operands divide over the wavefronts");
+  static_assert(NW % 2 == 0, "a wavefront's loads share one swizzle");
+  static_assert(WGK == 1 || (WGK == 2 && TM * TN > 0), "at most two k halves");
+  static constexpr int SUBS = 4 / WGK;                       // MFMA groups of 16 k per wavefront and k-step
+  // WGK = 2: each wavefront gives the accumulators it does not write out to its partner through LDS
+  static constexpr int XCH_TILES = WGK == 2 ? WGM * WGN * TM * TN : 0;
+  static constexpr int XCH_PER_STAGE = STAGE / 4096;
+  // The stages of a tile's last DEFER k-steps are used by its epilogue; their refill waits until it is done.
+  static constexpr int FW = TN * 32;                         // a wavefront's out-features
+  static constexpr int PITCH_F32 = 32 * 4 + 16;              // staged row pitches: 32 features fp32,
+  static constexpr int bf16_pitch(int na) { return na * 64 + 16; }   // na * 32 features bf16
+  static constexpr int EPI_WAVE = 32 * (PITCH_F32 > bf16_pitch(TN) || WGK == 2 ? PITCH_F32 : bf16_pitch(TN));
+  static constexpr int XCH_STAGES = WGK == 2 ? (XCH_TILES + XCH_PER_STAGE - 1) / XCH_PER_STAGE : 0;
+  static constexpr int EPI_STAGES = (NW + STAGE / EPI_WAVE - 1) / (STAGE / EPI_WAVE);
+  static constexpr int DEFER = XCH_STAGES > EPI_STAGES ? XCH_STAGES : EPI_STAGES;
+  static_assert(DEFER < NS, "at least one stage keeps prefetching under the epilogue");
+  // A tile takes at least this many k-steps (missing ones are zero-filled), so that the load stream is
+  // never more than BIAS_SLOTS - 1 tiles ahead of the tile being multiplied.
+  static constexpr int MIN_STEPS = (NS + BIAS_SLOTS - 2) / (BIAS_SLOTS - 1) > DEFER ? (NS + BIAS_SLOTS - 2) / (BIAS_SLOTS - 1) : DEFER;
+  static constexpr int BIAS_BYTES = BIAS_SLOTS * BN * 2;
+  static constexpr int SMEM = NS * STAGE + BIAS_BYTES;
+  // Residual update: a wavefront writes OWN MFMA tiles; where their rows of x fit the registers beside the
+  // accumulators they are fetched when the tile begins, else a few at a time under the epilogue.
+  static constexpr int OWN = (TM * TN + WGK - 1) / WGK;
+  static constexpr bool X_EARLY = TM * TN <= 4;
   static_assert(BN / 8 <= 64, "one wavefront fetches the tile's bias");
-  static constexpr int NI = (BM + BN) / 16;                  // wave-wide loads per k-step (16 rows each)
-  static constexpr int NJ_LO = NI / NW;                      // loads per wavefront per k-step ...
-  static constexpr int N_HI = NI % NW;                       // ... one more for the first N_HI wavefronts
-  static constexpr int NJ_HI = NJ_LO + (N_HI ? 1 : 0);
-  static_assert(BM % 16 == 0 && BN % 16 == 0, "tile rows come in sixteens");
-  static_assert((NS - 2) * NJ_HI < 64 && NS >= 3, "pipeline depth");
+  static_assert((NS - 1) * NJ < 64 && NS >= 2, "pipeline depth");
 };
 
-// Epilogue of one output tile.  acc[a][b][4g+e] = C[token tb + l32][feature fb + 8g + 4 lh + e]
-// (bias already inside).  Pass b stages accumulator row-tile b of every wavefront (32 rows per
-// wavefront row) and writes those rows out.  `smem` is free once the k loop is done; the caller
-// guarantees no read of it is pending.  Ends with every thread past a barrier after its last read
-// of the staging area.
-template <class C, int TM, int TN, int EPI>
-__device__ __forceinline__ void gemm_epilogue(floatx16 (&acc)[TN][TM], unsigned char *smem, const float *smem_gate,
-                                              const GemmParams &p, int64_t my_row0, int my_col0, int64_t my_sample0,
-                                              int tid, int wm, int wn, int l32, int lh, bf16_t *my_out, int my_shift) {
-  constexpr int BN = C::BN, NT = C::NT, PR = C::PASS_ROWS;
-  const unsigned stage_base = lds_offset(smem);
-  const int rl_stage = wm * 32 + l32;   // this lane's row inside a pass
-  if constexpr (EPI != 2) {
-    // Pass b: every wavefront stages its row-tile b (32 token rows x its features); everyone writes
-    // those WGM*32 rows out.
-    constexpr int CPR = BN / 8;   // 16-byte chunks per tile row
-    constexpr int ITERS = PR * CPR / NT;
-    static_assert(PR * CPR % NT == 0 && (ITERS == 4 || ITERS == 6), "row pieces per thread and pass");
-    constexpr int G = ITERS / 2;  // pieces per LDS read group
-    unsigned char *const stg = smem + C::BF16_STAGING;
-    const unsigned stg_base = lds_offset(stg);
-#pragma unroll
-    for (int b = 0; b < TM; ++b) {
-      // bias is inside; (+ GELU), round to bf16, stage
-#pragma unroll
-      for (int a = 0; a < TN; ++a)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int fl = wn * (TN * 32) + a * 32 + 8 * g + 4 * lh;   // feature inside the tile
-          float v0 = acc[a][b][4 * g + 0], v1 = acc[a][b][4 * g + 1], v2 = acc[a][b][4 * g + 2],
-                v3 = acc[a][b][4 * g + 3];
-          if (EPI == 1) {
-            v0 = gelu_tanh_f(v0); v1 = gelu_tanh_f(v1); v2 = gelu_tanh_f(v2); v3 = gelu_tanh_f(v3);
-          }
-          bf16x4 o;
-          o[0] = (bf16_t)v0; o[1] = (bf16_t)v1; o[2] = (bf16_t)v2; o[3] = (bf16_t)v3;
-          *reinterpret_cast<bf16x4 *>(stg + rl_stage * C::PITCH_BF16 + fl * 2) = o;
-        }
-      lds_barrier();
-#pragma unroll
-      for (int it0 = 0; it0 < ITERS; it0 += G) {
-        uintx4 piece[G];
-        unsigned la[G];
-#pragma unroll
-        for (int j = 0; j < G; ++j) {
-          const int idx = tid + NT * (it0 + j);
-          const int rl = idx / CPR, c = idx - rl * CPR;
-          la[j] = stg_base + rl * C::PITCH_BF16 + c * 16;
-        }
-        if constexpr (G == 2) lds_read2_b128(piece, la[0], la[1]);
-        else lds_read3_b128(piece, la[0], la[1], la[2]);
-#pragma unroll
-        for (int j = 0; j < G; ++j) {
-          const int idx = tid + NT * (it0 + j);
-          const int rl = idx / CPR, c = idx - rl * CPR;          // rl = 32 * wave-row + row
-          const int64_t tok = my_row0 + (rl >> 5) * (TM * 32) + b * 32 + (rl & 31);
-          const int f = my_col0 + c * 8;
-          // streaming store: the output is not read again by this launch, and a plain store would push
-          // the operand lines that other workgroups still re-read out of the L2
-          if (tok < p.N && f < p.n)
-            __builtin_nontemporal_store(piece[j], reinterpret_cast<uintx4 *>(my_out + tok * p.ld_out + (f - my_shift)));
-        }
-      }
-      lds_barrier();   // staged rows are read by other waves until here
-    }
-  } else {
-    // gated residual: gate * (acc + bias) is staged; the update of x happens on the way out, on
-    // whole-row pieces
-    constexpr int CPR = BN / 4;       // float4 chunks per tile row
-    constexpr int ITERS = PR * CPR / NT;
-    static_assert(PR * CPR % NT == 0 && ITERS % 2 == 0, "row pieces must divide evenly over the threads, in pairs");
-    const int64_t sample1_tok = (my_sample0 + 1) * p.tokens_per_sample;   // first token of the tile's second sample
-    float *const x_tile = p.resid + my_row0 * (int64_t)p.n + my_col0;
-    // The reads of x run DEPTH groups (of G row pieces per thread) ahead of their use, across the
-    // passes: memory requests complete in order, loads and stores alike, so a group's loads are
-    // issued BEFORE the stores of the groups processed while they are in flight, and waiting for
-    // them never waits for a store.  The piece indices start from an opaque copy of the thread
-    // index: otherwise the compiler hoists every address out of the tile loop and keeps them in
-    // registers across the k loop.
-    constexpr int G = ITERS % 4 == 0 ? 4 : 2;
-    constexpr int GP = ITERS / G;            // groups per pass
-    constexpr int NG = TM * GP;              // groups per tile
-    constexpr int DEPTH = NG < 3 ? NG : 3;
-    int tq = tid;
-    asm volatile("" : "+v"(tq));
-    float4 xr[DEPTH][G];
-    auto issue_x = [&](int g, int slot) {
-      const int b = g / GP, u0 = (g - b * GP) * G;
-      int tg = tq;
-      asm volatile("" : "+v"(tg));   // per group: nothing of its index arithmetic is shared or kept
-#pragma unroll
-      for (int j = 0; j < G; ++j) {
-        const int idx = tg + NT * (u0 + j);
-        const int rl = idx / CPR, c = idx - rl * CPR;
-        const int trow = (rl >> 5) * (TM * 32) + b * 32 + (rl & 31);   // row inside the tile
-        const bool ok = my_row0 + trow < p.N && my_col0 + c * 4 < p.n;
-        xr[slot][j] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (ok) {   // x is touched once per launch: streaming load and store keep it out of the operands' way
-          const floatx4 t = __builtin_nontemporal_load(reinterpret_cast<const floatx4 *>(x_tile + (trow * p.n + c * 4)));
-          xr[slot][j] = make_float4(t[0], t[1], t[2], t[3]);
-        }
-      }
-    };
-#pragma unroll
-    for (int g = 0; g < DEPTH; ++g) issue_x(g, g);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int b = 0; b < TM; ++b) {
-      {
-        const int64_t tok = my_row0 + wm * (TM * 32) + b * 32 + l32;
-        const int64_t ds = tok - sample1_tok;                      // >= 0: second sample of the tile (or beyond)
-        const bool far = p.gate_tab && ds >= p.tokens_per_sample;  // tile over more than two samples (tiny shapes)
-        const float *grow = smem_gate + (ds >= 0 ? BN : 0);
-        const float *gfar = nullptr;                               // this row's c6 gate vector when `far`
-        if (far && p.gate_c6) {
-          int64_t smp = my_sample0 + 1, t = sample1_tok + p.tokens_per_sample;
-          const int64_t tk = tok < p.N ? tok : p.N - 1;
-          while (t <= tk) { ++smp; t += p.tokens_per_sample; }
-          // rows past the end of a problem that ends inside the tile's first sample would name a
-          // sample that does not exist (their result is never stored, but the read must stay inside c6)
-          const int64_t last = (p.N - 1) / p.tokens_per_sample;
-          if (smp > last) smp = last;
-          gfar = p.gate_c6 + smp * p.gate_c6_stride;
-        }
-#pragma unroll
-        for (int a = 0; a < TN; ++a)
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const int fl = wn * (TN * 32) + a * 32 + 8 * g + 4 * lh;
-            float4 gt = make_float4(1.f, 1.f, 1.f, 1.f);
-            if (p.gate_tab) {
-              gt = *reinterpret_cast<const float4 *>(grow + fl);
-              if (far) {
-                int f = my_col0 + fl;
-                if (f > p.n - 4) f = p.n - 4;
-                gt = *reinterpret_cast<const float4 *>(p.gate_tab + f);
-                if (gfar) {
-                  const float4 gc = *reinterpret_cast<const float4 *>(gfar + f);
-                  gt.x += gc.x; gt.y += gc.y; gt.z += gc.z; gt.w += gc.w;
-                }
-              }
-            }
-            *reinterpret_cast<float4 *>(smem + rl_stage * C::PITCH_F32 + fl * 4) =
-                make_float4(acc[a][b][4 * g + 0] * gt.x, acc[a][b][4 * g + 1] * gt.y, acc[a][b][4 * g + 2] * gt.z,
-                            acc[a][b][4 * g + 3] * gt.w);
-            __builtin_amdgcn_sched_barrier(0);   // keeps the gate reads from piling up in registers
-          }
-      }
-      lds_barrier();
-      // update of x on whole-row pieces
-#pragma unroll
-      for (int i = 0; i < GP; ++i) {
-        const int g = b * GP + i, slot = g % DEPTH, u0 = i * G;
-        uintx4 piece[G];
-        int tg = tq;
-        asm volatile("" : "+v"(tg));
-#pragma unroll
-        for (int j = 0; j < G; j += 2) {
-          uintx4 two[2];
-          unsigned la[2];
-#pragma unroll
-          for (int e2 = 0; e2 < 2; ++e2) {
-            const int idx = tg + NT * (u0 + j + e2);
-            const int rl = idx / CPR, c = idx - rl * CPR;
-            la[e2] = stage_base + rl * C::PITCH_F32 + c * 16;
-          }
-          lds_read2_b128(two, la[0], la[1]);
-          piece[j] = two[0];
-          piece[j + 1] = two[1];
-        }
-#pragma unroll
-        for (int j = 0; j < G; ++j) {
-          const int idx = tg + NT * (u0 + j);
-          const int rl = idx / CPR, c = idx - rl * CPR;
-          const int trow = (rl >> 5) * (TM * 32) + b * 32 + (rl & 31);   // row inside the tile
-          if (my_row0 + trow < p.N && my_col0 + c * 4 < p.n) {
-            float4 r = xr[slot][j];
-            r.x += __uint_as_float(piece[j][0]); r.y += __uint_as_float(piece[j][1]);
-            r.z += __uint_as_float(piece[j][2]); r.w += __uint_as_float(piece[j][3]);
-            floatx4 rv;
-            rv[0] = r.x; rv[1] = r.y; rv[2] = r.z; rv[3] = r.w;
-            __builtin_nontemporal_store(rv, reinterpret_cast<floatx4 *>(x_tile + (trow * p.n + c * 4)));
-            if (p.out) {
-              bf16x4 o;
-              o[0] = (bf16_t)r.x; o[1] = (bf16_t)r.y; o[2] = (bf16_t)r.z; o[3] = (bf16_t)r.w;
-              __builtin_nontemporal_store(o, reinterpret_cast<bf16x4 *>(p.out + (my_row0 + trow) * p.ld_out + my_col0 + c * 4));
-            }
-          }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        if (g + DEPTH < NG) issue_x(g + DEPTH, slot);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      lds_barrier();   // the staging area is rewritten by the next pass / the next tile's loads
+// the same pointer in every lane, said so that the compiler believes it (a resource it thinks might differ between
+// lanes costs a loop around every load)
+__device__ __forceinline__ void *uniform_ptr(const void *q) {
+  const uint64_t v = (uint64_t)q;
+  const uint64_t lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)v);
+  const uint64_t hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(v >> 32));
+  return (void *)(hi << 32 | lo);
+}
+
+// One output tile as the epilogue sees it.
+struct TileOut {
+  int64_t row0; int col0;      // first token, first out-feature
+  bf16_t *out; int shift;      // output of the tile's problem; its first out-feature
+  unsigned smp0;               // sample of the first token ...
+  bool one_sample;             // ... and of all of them
+};
+
+// The sample a token belongs to (token counts stay below 2^30).
+__device__ __forceinline__ unsigned sample_of(const GemmParams &p, int64_t tok) {
+  return p.tokens_per_sample > 0x7fffffff ? 0u : (unsigned)tok / (unsigned)p.tokens_per_sample;
+}
+
+// Rows of the residual stream and gate vectors of a wavefront's tiles, fetched before they are needed: lane l of a
+// group of 8 rows holds four features of row l / 8.
+template <int OWN, int TN>
+struct XRows {
+  float4 x[OWN][4];
+  float4 gate[TN];
+};
+
+// gate vector of a sample at this lane's features (f4 .. f4 + 3) of the MFMA column that starts at feature col
+__device__ __forceinline__ float4 gate_vector(const GemmParams &p, unsigned smp, int f) {
+  float4 g = make_float4(1.f, 1.f, 1.f, 1.f);
+  if (p.gate_tab) {
+    if (f > p.n - 4) f = p.n - 4;                 // past the edge: what is there, not used
+    g = *reinterpret_cast<const float4 *>(p.gate_tab + f);
+    if (p.gate_c6) {
+      const float4 c = *reinterpret_cast<const float4 *>(p.gate_c6 + (int64_t)smp * p.gate_c6_stride + f);
+      g.x += c.x; g.y += c.y; g.z += c.z; g.w += c.w;
     }
   }
+  return g;
+}
+
+// Writes out the MFMA tiles T0 .. T1-1 of this wavefront (tile t = b * TN + a covers the wavefront's token
+// rows 32 b .. 32 b + 31 and out-features 32 a .. 32 a + 31; acc[a][b][4g+e] = C[token l32][feature
+// 8g + 4 lh + e] of it, bias inside).  `stg`: this wavefront's staging bytes (LDS offset); nothing here
+// synchronises with other wavefronts.
+// FULL: the whole tile lies inside the problem and (residual update) inside one sample: straight-line code.
+template <class C, int TM, int TN, int EPI, int T0, int T1, bool FULL>
+__device__ __forceinline__ void gemm_epilogue_as(floatx16 (&acc)[TN][TM], unsigned stg, unsigned char *stg_ptr,
+                                              const GemmParams &p, const TileOut &to, int lane, int wm, int wn, unsigned smp0,
+                                                 bool one_sample, const XRows<C::OWN, TN> &early) {
+  const int l32 = lane & 31, lh = lane >> 5;
+  const int64_t row_w = to.row0 + wm * (TM * 32);   // the wavefront's first token and out-feature
+  const int col_w = to.col0 + wn * (TN * 32);
+  if constexpr (EPI != 2) {
+    // rows of AG * 64 bytes: the whole width of the wavefront where it owns all of it, else one MFMA tile
+    constexpr int AG = (T0 == 0 && T1 == TM * TN) ? TN : 1;
+    constexpr int PITCH = C::bf16_pitch(AG), CPR = AG * 4, ITERS = AG * 2;
+    unsigned char *const o0 = reinterpret_cast<unsigned char *>(uniform_ptr(to.out + row_w * p.ld_out + (col_w - to.shift)));
+#pragma unroll
+    for (int t = T0; t < T1; t += AG) {
+      const int b = t / TN, a0 = t - b * TN;
+      asm volatile("" : "+v"(lane));   // nothing of a piece's index arithmetic is kept in registers for the next
+      // bias is inside; (+ GELU), round to bf16, stage
+#pragma unroll
+      for (int a = 0; a < AG; ++a)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          bf16x4 o;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            float v = acc[a0 + a][b][4 * g + e];
+            if (EPI == 1) v = gelu_tanh_f(v);
+            o[e] = (bf16_t)v;
+          }
+          *reinterpret_cast<bf16x4 *>(stg_ptr + l32 * PITCH + (a * 32 + 8 * g + 4 * lh) * 2) = o;
+        }
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("" ::: "memory");   // the reads below are not visible as LDS reads: keep them after the writes
+#pragma unroll
+      for (int i0 = 0; i0 < ITERS; i0 += 2) {
+        uintx4 piece[2];
+        unsigned la[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const int idx = lane + 64 * (i0 + j), rl = idx / CPR, c = idx - rl * CPR;
+          la[j] = stg + rl * PITCH + c * 16;
+        }
+        lds_read2_b128(piece, la[0], la[1]);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const int idx = lane + 64 * (i0 + j), rl = idx / CPR, c = idx - rl * CPR;
+          const int64_t tok = row_w + b * 32 + rl;
+          const int f = col_w + a0 * 32 + c * 8;
+          // streaming store: the output is not read again by this launch, and a plain store would push
+          // the operand lines that other workgroups still re-read out of the L2
+          if (FULL) {
+            const unsigned place = ((unsigned)rl * (unsigned)p.ld_out + (unsigned)(c * 8)) * 2u;
+            __builtin_nontemporal_store(piece[j], reinterpret_cast<uintx4 *>(o0 + ((int64_t)(b * 32) * p.ld_out + a0 * 32) * 2 + place));
+          } else if (tok < p.N && f < p.n) {
+            __builtin_nontemporal_store(piece[j], reinterpret_cast<uintx4 *>(to.out + tok * p.ld_out + (f - to.shift)));
+          }
+        }
+      }
+    }
+  } else {
+    // Gated residual update.  One MFMA tile at a time is staged as it is; on the way out a lane holds four
+    // consecutive features of a row (8 lanes a row of 128 bytes, 8 rows per instruction), so the
+    // stream is read and written in whole lines.  The reads of x run DEPTH tiles ahead of their use: memory
+    // requests complete in order, loads and stores alike, so a tile's loads are issued BEFORE the stores of
+    // the tiles processed while they are in flight, and waiting for them never waits for a store.
+    constexpr bool EARLY = C::X_EARLY;
+    constexpr int DEPTH = EARLY ? T1 - T0 : !FULL ? 1 : (T1 - T0 < 3 ? T1 - T0 : 3);
+    int r8 = lane >> 3, f4 = (lane & 7) * 4;
+    // this wavefront's corner of the stream and of its bf16 copy, and this lane's place in a group of 8 rows
+    unsigned char *const x0 = reinterpret_cast<unsigned char *>(uniform_ptr(p.resid + row_w * p.n + col_w));
+    unsigned char *const o0 = reinterpret_cast<unsigned char *>(uniform_ptr(p.out + (p.out ? row_w * p.ld_out + col_w : 0)));
+    const unsigned lane_x = (unsigned)(r8 * p.n + f4) * 4u, lane_o = ((unsigned)r8 * (unsigned)p.ld_out + f4) * 2u;
+    float4 xr[DEPTH][4];
+    auto issue_x = [&](int t, int slot) {
+      const int b = t / TN, a = t - b * TN;
+      if constexpr (!FULL) asm volatile("" : "+v"(r8), "+v"(f4));   // nothing of a tile's index arithmetic is kept for the next
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const floatx4 *src;
+        if constexpr (FULL) {
+          src = reinterpret_cast<const floatx4 *>(x0 + ((int64_t)(b * 32 + 8 * i) * p.n + a * 32) * 4 + lane_x);
+        } else {   // lanes past the edge read what is there and do not use it
+          int64_t tok = row_w + b * 32 + 8 * i + r8;
+          int f = col_w + a * 32 + f4;
+          if (tok > p.N - 1) tok = p.N - 1;
+          if (f > p.n - 4) f = p.n - 4;
+          src = reinterpret_cast<const floatx4 *>(p.resid + tok * p.n + f);
+        }
+        // x is touched once per launch: streaming load and store keep it out of the operands' way
+        const floatx4 v = __builtin_nontemporal_load(src);
+        xr[slot][i] = make_float4(v[0], v[1], v[2], v[3]);
+      }
+    };
+    float4 gate[TN];
+    if constexpr (EARLY) {
+#pragma unroll
+      for (int d = 0; d < DEPTH; ++d)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) xr[d][i] = early.x[d][i];
+#pragma unroll
+      for (int a = 0; a < TN; ++a) gate[a] = early.gate[a];
+    } else if constexpr (FULL) {
+#pragma unroll
+      for (int d = 0; d < DEPTH; ++d) issue_x(T0 + d, d);
+#pragma unroll
+      for (int a = 0; a < TN; ++a) gate[a] = gate_vector(p, smp0, col_w + a * 32 + f4);
+    }
+#pragma unroll
+    for (int t = T0; t < T1; ++t) {
+      const int b = t / TN, a = t - b * TN, slot = (t - T0) % DEPTH;
+      if constexpr (!FULL && !EARLY) issue_x(t, slot);
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        floatx4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = acc[a][b][4 * g + e];
+        *reinterpret_cast<floatx4 *>(stg_ptr + l32 * C::PITCH_F32 + (8 * g + 4 * lh) * 4) = v;
+      }
+      asm volatile("" ::: "memory");
+      uintx4 piece[4];
+      lds_read4_b128<8 * C::PITCH_F32>(piece, stg + r8 * C::PITCH_F32 + f4 * 4);
+      auto update = [&](int i, float4 g) {
+        floatx4 r;
+        r[0] = xr[slot][i].x + g.x * __uint_as_float(piece[i][0]);
+        r[1] = xr[slot][i].y + g.y * __uint_as_float(piece[i][1]);
+        r[2] = xr[slot][i].z + g.z * __uint_as_float(piece[i][2]);
+        r[3] = xr[slot][i].w + g.w * __uint_as_float(piece[i][3]);
+        return r;
+      };
+      auto copy_of = [](floatx4 r) {
+        bf16x4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = (bf16_t)r[e];
+        return o;
+      };
+      if constexpr (FULL) {
+        floatx4 r[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          r[i] = update(i, gate[a]);
+          __builtin_nontemporal_store(r[i], reinterpret_cast<floatx4 *>(x0 + ((int64_t)(b * 32 + 8 * i) * p.n + a * 32) * 4 + lane_x));
+        }
+        if (p.out) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            __builtin_nontemporal_store(copy_of(r[i]), reinterpret_cast<bf16x4 *>(o0 + ((int64_t)(b * 32 + 8 * i) * p.ld_out + a * 32) * 2 + lane_o));
+        }
+      } else {
+        float4 g0 = make_float4(1.f, 1.f, 1.f, 1.f);
+        if (one_sample) g0 = EARLY ? gate[a] : gate_vector(p, smp0, col_w + a * 32 + f4);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int64_t tok = row_w + b * 32 + 8 * i + r8;
+          const int f = col_w + a * 32 + f4;
+          if (tok < p.N && f < p.n) {
+            const floatx4 r = update(i, one_sample ? g0 : gate_vector(p, sample_of(p, tok), f));
+            __builtin_nontemporal_store(r, reinterpret_cast<floatx4 *>(p.resid + tok * p.n + f));
+            if (p.out) __builtin_nontemporal_store(copy_of(r), reinterpret_cast<bf16x4 *>(p.out + tok * p.ld_out + f));
+          }
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (FULL && !EARLY) {
+        if (t + DEPTH < T1) issue_x(t + DEPTH, slot);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+}
+
+template <class C, int TM, int TN, int EPI, int T0, int T1>
+__device__ __forceinline__ void gemm_epilogue(floatx16 (&acc)[TN][TM], unsigned stg, unsigned char *stg_ptr,
+                                              const GemmParams &p, const TileOut &to, int lane, int wm, int wn,
+                                              const XRows<C::OWN, TN> &early) {
+  const bool inside = p.plain && to.row0 + C::BM <= p.N && to.col0 + C::BN <= p.n;
+  const unsigned smp0 = to.smp0;
+  const bool one_sample = to.one_sample;
+  if (inside && one_sample)
+    gemm_epilogue_as<C, TM, TN, EPI, T0, T1, true>(acc, stg, stg_ptr, p, to, lane, wm, wn, smp0, one_sample, early);
+  else
+    gemm_epilogue_as<C, TM, TN, EPI, T0, T1, false>(acc, stg, stg_ptr, p, to, lane, wm, wn, smp0, one_sample, early);
 }
 
 typedef __attribute__((address_space(3))) void *lds_ptr_t;
 typedef __attribute__((address_space(1))) const void *gbl_ptr_t;
 
-template <int NJ_>
-struct LoadCount { static constexpr int value = NJ_; };
-
-template <int WGM, int WGN, int TM, int TN, int NS, int EPI, class GT>
-__global__ __launch_bounds__(WGM *WGN * 64, 2) void k_gemm_bf16(GemmParams p, GT gt) {
-  using C = GemmCfg<WGM, WGN, TM, TN, NS>;
+template <int WGM, int WGN, int WGK, int TM, int TN, int NS, int EPI, class GT>
+__global__ __launch_bounds__(WGM *WGN *WGK * 64, 2) void k_gemm_bf16(GemmParams p, GT gt) {
+  using C = GemmCfg<WGM, WGN, WGK, TM, TN, NS>;
   constexpr bool GROUPED = !std::is_same<GT, NoGroups>::value;
   static_assert(!GROUPED || EPI != 2, "grouped launches write bf16 outputs");
-  constexpr int BM = C::BM, BN = C::BN, STAGE = C::STAGE, NW = C::NW;
-  constexpr int NFRAG = TM + TN, NMFMA = TM * TN;
-  constexpr int AHEAD = NS - 1;          // k-steps in flight ahead of the one being multiplied
-  // The bf16 epilogues stage in the last two LDS stages only, so the next tile's first k-steps are
-  // fetched while the current tile is written out; the fp32 epilogue needs the whole LDS.
-  constexpr bool EARLY_FETCH = EPI != 2;
+  constexpr int BM = C::BM, BN = C::BN, STAGE = C::STAGE, NW = C::NW, NJ = C::NJ, NJU = C::NJU, SUBS = C::SUBS;
+  constexpr int NFRAG = TM + TN, NMFMA = TM * TN, DEFER = C::DEFER;
+  // a k-step's loads are issued in two parts: after the barrier that frees their stage, and under the
+  // next k-step's first MFMAs
+  constexpr int LA = (NJ + 1) / 2;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  float *smem_gate = reinterpret_cast<float *>(smem + C::SMEM);
-  unsigned char *smem_bias = smem + C::SMEM + C::GATE_BYTES;
+  unsigned char *const smem_bias = smem + NS * STAGE;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / WGN, wn = wave - wm * WGN;
+  const int wk = WGK == 2 ? wave / (WGM * WGN) : 0;
+  const int wt = wave - wk * (WGM * WGN);
+  const int wm = wt / WGN, wn = wt - wm * WGN;
   const int l32 = lane & 31, lh = lane >> 5;
-  const int nk = (p.k + BK - 1) / BK;
-  const int nk_full = p.k / BK;
+  const int nk = (p.k + BK - 1) / BK > C::MIN_STEPS ? (p.k + BK - 1) / BK : C::MIN_STEPS;
 
-  // fragment reads: row (tile*32 + l32) of 64 B, chunk (2 kk + lh) at slot chunk ^ ((row >> 2) & 3)
+  // fragment reads: row (tile*32 + l32) of 128 B, chunk 2 sub + lh at slot chunk ^ ((row >> 1) & 7)
   const int frag_u = (wm * (TM * 32) + l32) * ROW;
   const int frag_w = BM * ROW + (wn * (TN * 32) + l32) * ROW;
-  int coff[2];
+  int coff[SUBS];
 #pragma unroll
-  for (int kk = 0; kk < 2; ++kk) coff[kk] = ((kk * 2 + lh) ^ ((l32 >> 2) & 3)) << 4;
-  // loads: this wave's j-th instruction is number g = wave + NW j of the k-step and covers tile rows
-  // 16 g .. 16 g + 15 (token rows first, then W rows); this lane: row lane/4, slot lane%4
-  const int ld_row = lane >> 2;
-  const int ld_chunk = ((lane & 3) ^ ((ld_row >> 2) & 3)) * 8;   // element offset of the global chunk to fetch
+  for (int s = 0; s < SUBS; ++s) coff[s] = ((2 * (wk * SUBS + s) + lh) ^ ((l32 >> 1) & 7)) << 4;
+  // loads: this wave's j-th instruction covers tile rows 8 (wave + NW j) .. + 7 of the token rows (j < NJU) or of
+  // the W rows; this lane: row lane/8 of the eight, slot lane%8
+  const int ld_row = wave * 8 + (lane >> 3);
+  const int ld_chunk = (lane & 7) ^ ((ld_row >> 1) & 7);          // the global 16-byte chunk that lands in this slot
+  const unsigned voff_u = (unsigned)ld_row * (unsigned)p.ld_u * 2u + ld_chunk * 16;
+  const unsigned voff_w = (unsigned)ld_row * (unsigned)p.k * 2u + ld_chunk * 16;
   const unsigned bias_lds = lds_offset(smem_bias) + (wn * (TN * 32) + 4 * lh) * 2;
 
-  // W, bias, output and first out-feature of the problem that the tile being FETCHED belongs to
-  const bf16_t *W_tile = p.W, *bias_tile = p.bias;
-  bf16_t *out_tile = p.out;
-  int shift_tile = 0;
+  // ---- the load stream: k-steps of this workgroup's tiles, one after the other, stage by stage.  Past the
+  // last tile it goes on with resources of length zero (nothing is fetched), so the loops need no branches
+  // and the counts of outstanding loads stay the same.
+  int ld_round = 0, ld_k = 0;           // the next k-step to fetch
+  const bf16_t *ld_u = p.u, *ld_W = p.W;   // operands of its tile: first row ...
+  int64_t tot_u = 0, tot_w = 0;         // ... and bytes from there to the matrix's last element (below 2^32)
+  const int64_t du = (int64_t)p.ld_u * (NW * 16), dw = (int64_t)p.k * (NW * 16);   // bytes between a wave's loads
 
-  // The whole tile loop, compiled per NJ = this wavefront's loads per k-step.
-  auto run = [&](auto nj_tag) {
-    constexpr int NJ = decltype(nj_tag)::value;
-    constexpr int PENDING = (NS - 2) * NJ;   // loads that may still be outstanding when k-step i+1 is needed
-    int src_off[NJ];                         // element offset of this lane's piece at k = 0 (u or W, by instruction)
+  // Start of a tile's operand stream: its place, and its bias (one wavefront fetches it, ahead of everything
+  // else, so it has landed when k-step 0 has).
+  auto ld_tile = [&](int tile) {
+    if (tile < 0) { tot_u = tot_w = 0; return; }
+    int tm, tn;
+    decode_tile(p, tile, tm, tn);
+    const int64_t row0 = (int64_t)tm * BM;
+    int f0 = tn * BN, n_all = p.n;
+    const bf16_t *bias = p.bias;
+    ld_W = p.W;
+    if constexpr (GROUPED) {
+      const int g = f0 / gt.group_n;
+      ld_W = gt.W[g]; bias = gt.bias[g];
+      f0 -= g * gt.group_n; n_all = gt.group_n;
+    }
+    ld_u = p.u + row0 * p.ld_u;
+    ld_W += (int64_t)f0 * p.k;
+    tot_u = ((p.N - row0 - 1) * p.ld_u + p.k) * 2;
+    tot_w = (int64_t)(n_all - f0) * p.k * 2;
+    if (bias && wave == 0 && lane < BN / 8) {
+      int f = f0 + lane * 8;
+      if (f > n_all - 8) f = n_all - 8;         // overhanging features: a valid address, never stored
+      __builtin_amdgcn_global_load_lds((gbl_ptr_t)(bias + f), (lds_ptr_t)(smem_bias + (ld_round % BIAS_SLOTS) * (BN * 2)), 16, 0, 0);
+    }
+  };
+  // loads J0 .. J1-1 of the current k-step of the stream into stage ST; each instruction has a resource that
+  // starts at its eight rows
+  auto ld_issue = [&](auto j0_tag, auto j1_tag, int st) {
+    constexpr int J0 = decltype(j0_tag)::value, J1 = decltype(j1_tag)::value;
+    const int k0 = __builtin_amdgcn_readfirstlane(ld_k * (BK * 2));     // bytes
+    const bool in = ld_k * BK + ld_chunk * 8 < p.k;   // past the row's end: fetch nothing, write zeros
+    const unsigned vu = in ? voff_u : 0xfffffff0u, vw = in ? voff_w : 0xfffffff0u;
+#pragma unroll
+    for (int j = J0; j < J1; ++j) {
+      const bool is_u = j < NJU;
+      const int64_t off = is_u ? du * j : dw * (j - NJU), left = (is_u ? tot_u : tot_w) - off;
+      const unsigned lim = (unsigned)left & ~(unsigned)(left >> 63);
+      const unsigned char *base = reinterpret_cast<const unsigned char *>(is_u ? ld_u : ld_W) + off;
+      __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(base), 0, __builtin_amdgcn_readfirstlane((int)lim), 0x00020000);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr_t)(smem + st * STAGE + (wave + NW * j) * 1024), 16, is_u ? vu : vw, k0, 0, 0);
+    }
+  };
+  auto ld_advance = [&]() {
+    if (++ld_k < nk) return;
+    ld_k = 0;
+    ++ld_round;
+    ld_tile(ld_round < p.rounds ? tile_sequence_index(p, ld_round) : -1);
+  };
+  using J_0 = std::integral_constant<int, 0>;
+  using J_A = std::integral_constant<int, LA>;
+  using J_N = std::integral_constant<int, NJ>;
 
-#define DL_ISSUE(KT, ST)                                                                           \
+#define DL_READ_FRAGS(BUF, ST, S)                                                                  \
   do {                                                                                             \
-    const int k0_ = (KT) * BK;                                                                     \
-    unsigned char *sb_ = smem + (ST) * STAGE + wave * 1024;                                        \
-    _Pragma("unroll") for (int j = 0; j < NJ; ++j) {                                               \
-      const bf16_t *src_ = ((wave + NW * j) * 16 < BM ? p.u : W_tile) + src_off[j] + k0_;          \
-      __builtin_amdgcn_global_load_lds((gbl_ptr_t)src_, (lds_ptr_t)(sb_ + j * (NW * 1024)), 16, 0, 0); \
-    }                                                                                              \
-  } while (0)
-
-    // the last, partial k-step: lanes whose chunk starts at or past k fetch zeros instead
-#define DL_ISSUE_TAIL(KT, ST)                                                                      \
-  do {                                                                                             \
-    const int k0_ = (KT) * BK;                                                                     \
-    const bool in_ = k0_ + ld_chunk < p.k;                                                         \
-    unsigned char *sb_ = smem + (ST) * STAGE + wave * 1024;                                        \
-    _Pragma("unroll") for (int j = 0; j < NJ; ++j) {                                               \
-      const bf16_t *src_ = ((wave + NW * j) * 16 < BM ? p.u : W_tile) + src_off[j] + k0_;          \
-      if (!in_) src_ = reinterpret_cast<const bf16_t *>(k_zero_block);                             \
-      __builtin_amdgcn_global_load_lds((gbl_ptr_t)src_, (lds_ptr_t)(sb_ + j * (NW * 1024)), 16, 0, 0); \
-    }                                                                                              \
-  } while (0)
-
-#define DL_READ_FRAGS(BUF, ST, KK)                                                                 \
-  do {                                                                                             \
-    const unsigned char *sb_ = smem + (ST) * STAGE + coff[KK];                                     \
+    const unsigned char *sb_ = smem + (ST) * STAGE + coff[S];                                      \
     _Pragma("unroll") for (int b = 0; b < TM; ++b)                                                 \
         uf[BUF][b] = *reinterpret_cast<const bf16x8 *>(sb_ + frag_u + b * 32 * ROW);               \
     _Pragma("unroll") for (int a = 0; a < TN; ++a)                                                 \
@@ -489,94 +562,72 @@ __global__ __launch_bounds__(WGM *WGN * 64, 2) void k_gemm_bf16(GemmParams p, GT
             acc[a][b] = mfma32(wf[BUF][a], uf[BUF][b], acc[a][b]);                                 \
   } while (0)
 
-#define NEXT_STAGE(S) ((S) + 1 == NS ? 0 : (S) + 1)
+  int tile = tile_sequence_index(p, 0);
+  if (tile < 0) return;
+  ld_tile(tile);
+  // the first NS k-steps, less the second part of the last one (the first k-step of the loop issues that)
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    if (s + 1 < NS) {
+      ld_issue(J_0{}, J_N{}, s);
+      ld_advance();
+    } else {
+      ld_issue(J_0{}, J_A{}, s);
+    }
+  }
+  wait_vmcnt<(NS - 2) * NJ + LA>();   // k-step 0 (and the bias) has landed
+  lds_barrier();
 
-    // Start of a tile's operand stream: source offsets, the tile's bias (one wavefront fetches it,
-    // ahead of everything else, so it has landed when k-step 0 has), k-steps 0 .. AHEAD-1.
-    auto begin_tile = [&](int64_t row0, int col0, int first_steps) {
-      int n_lim = p.n;             // out-features of the tile's problem
-      if constexpr (GROUPED) {
-        const int g = col0 / gt.group_n;
-        W_tile = gt.W[g]; bias_tile = gt.bias[g]; out_tile = gt.out[g];
-        shift_tile = g * gt.group_n;
-        n_lim = gt.group_n;
-      }
-      const int lcol0 = col0 - shift_tile;   // the tile's first out-feature inside its problem
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        const int R = (wave + NW * j) * 16 + ld_row;
-        if (R < BM) {
-          int64_t t = row0 + R;
-          if (t > p.N - 1) t = p.N - 1;           // overhanging rows re-read the last row; never stored
-          src_off[j] = (int)(t * p.ld_u) + ld_chunk;
-        } else {
-          int f = lcol0 + R - BM;
-          if (f > n_lim - 1) f = n_lim - 1;
-          src_off[j] = f * p.k + ld_chunk;
-        }
-      }
-      if (bias_tile && wave == 0 && lane < BN / 8) {
-        int f = lcol0 + lane * 8;
-        if (f > n_lim - 8) f = n_lim - 8;         // overhanging features: a valid address, never stored
-        __builtin_amdgcn_global_load_lds((gbl_ptr_t)(bias_tile + f), (lds_ptr_t)smem_bias, 16, 0, 0);
-      }
-#pragma unroll
-      for (int s = 0; s < AHEAD; ++s) {
-        if (s >= first_steps) break;
-        if (s < nk_full) DL_ISSUE(s, s);
-        else if (s < nk) DL_ISSUE_TAIL(s, s);
-      }
-    };
-    // the remaining k-steps of the first AHEAD, once the epilogue has left the last stages
-    auto finish_begin = [&](int first_steps) {
-#pragma unroll
-      for (int s = 0; s < AHEAD; ++s) {
-        if (s < first_steps) continue;
-        if (s < nk_full) DL_ISSUE(s, s);
-        else if (s < nk) DL_ISSUE_TAIL(s, s);
-      }
-    };
-
-    int tile = tile_sequence_index(p, 0);
-    if (tile < 0) return;
+  int st = 0;                 // stage of the k-step being multiplied
+  for (int round = 0;; ++round) {
     int tile_m, tile_n;
     decode_tile(p, tile, tile_m, tile_n);
-    int64_t row0 = (int64_t)tile_m * BM;
-    int col0 = tile_n * BN;
-    begin_tile(row0, col0, AHEAD);
-
-    for (int round = 0;; ++round) {
-      int64_t sample0 = 0;
-      if (EPI == 2 && p.gate_tab) {
-        sample0 = row0 / p.tokens_per_sample;
-        if (tid < 2 * (BN / 4)) {
-          const int which = tid / (BN / 4), c = tid - which * (BN / 4);
-          int f = col0 + 4 * c;
-          if (f > p.n - 4) f = p.n - 4;
-          float4 gt = *reinterpret_cast<const float4 *>(p.gate_tab + f);
-          if (p.gate_c6) {
-            int64_t smp = sample0 + which;
-            const int64_t last = (p.N - 1) / p.tokens_per_sample;
-            if (smp > last) smp = last;
-            const float4 gc = *reinterpret_cast<const float4 *>(p.gate_c6 + smp * p.gate_c6_stride + f);
-            gt.x += gc.x; gt.y += gc.y; gt.z += gc.z; gt.w += gc.w;
-          }
-          *reinterpret_cast<float4 *>(smem_gate + tid * 4) = gt;
-        }
+    TileOut to;
+    to.row0 = (int64_t)tile_m * BM; to.col0 = tile_n * BN; to.out = p.out; to.shift = 0;
+    to.smp0 = 0; to.one_sample = true;
+    XRows<C::OWN, TN> early;
+    if constexpr (EPI == 2) {
+      if (p.gate_tab && p.gate_c6) {
+        to.smp0 = sample_of(p, to.row0);
+        to.one_sample = to.smp0 == sample_of(p, (to.row0 + BM < p.N ? to.row0 + BM : p.N) - 1);
       }
-      // k-step 0 (and the bias) must have landed; up to AHEAD-1 later steps may be pending
-      if (nk >= AHEAD) wait_vmcnt<PENDING>();
-      else wait_vmcnt<0>();
-      lds_barrier();
-
-      // the accumulators start from the bias
-      floatx16 acc[TN][TM];
+      if constexpr (C::X_EARLY) {
+        // this wavefront's rows of x and gates, behind the loads in flight: they have arrived long before the epilogue
+        const int64_t row_w = to.row0 + wm * (TM * 32) + (lane >> 3);
+        const int col_w = to.col0 + wn * (TN * 32) + (lane & 7) * 4;
+#pragma unroll
+        for (int d = 0; d < C::OWN; ++d) {
+          int t = wk * C::OWN + d;
+          if (t > NMFMA - 1) t = NMFMA - 1;
+          const int b = t / TN, a = t - b * TN;
+          int f = col_w + a * 32;
+          if (f > p.n - 4) f = p.n - 4;            // lanes past the edge read what is there and do not use it
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            int64_t tok = row_w + b * 32 + 8 * i;
+            if (tok > p.N - 1) tok = p.N - 1;
+            const floatx4 v = __builtin_nontemporal_load(reinterpret_cast<const floatx4 *>(p.resid + tok * p.n + f));
+            early.x[d][i] = make_float4(v[0], v[1], v[2], v[3]);
+          }
+        }
+#pragma unroll
+        for (int a = 0; a < TN; ++a) early.gate[a] = gate_vector(p, to.smp0, col_w + a * 32);
+      }
+    }
+    // the accumulators start from the bias (those of the first k half)
+    floatx16 acc[TN][TM];
+    {
+      const bf16_t *bias = p.bias;
+      if constexpr (GROUPED) {
+        const int g = to.col0 / gt.group_n;
+        bias = gt.bias[g]; to.out = gt.out[g]; to.shift = g * gt.group_n;
+      }
 #pragma unroll
       for (int a = 0; a < TN; ++a) {
         uint2 bq[4];
 #pragma unroll
         for (int g = 0; g < 4; ++g) bq[g] = make_uint2(0u, 0u);
-        if (GROUPED ? bias_tile != nullptr : p.bias != nullptr) lds_read4_b64(bq, bias_lds + a * 64);
+        if (bias && wk == 0) lds_read4_b64(bq, bias_lds + (round % BIAS_SLOTS) * (BN * 2) + a * 64);
 #pragma unroll
         for (int b = 0; b < TM; ++b)
 #pragma unroll
@@ -587,90 +638,126 @@ __global__ __launch_bounds__(WGM *WGN * 64, 2) void k_gemm_bf16(GemmParams p, GT
             acc[a][b][4 * g + 3] = __uint_as_float(bq[g].y & 0xffff0000u);
           }
       }
-
-      bf16x8 uf[2][TM], wf[2][TN];
-      DL_READ_FRAGS(0, 0, 0);
-      int kt = 0;
-      int st = 0;                 // stage of k-step kt
-      int st_new = AHEAD;         // stage that k-step kt + AHEAD goes to (== stage of kt-1)
-      // ---- steady state: k-step kt + AHEAD exists and is a full step; no branches, issue order pinned.
-      // Each half issues one MFMA first, then the LDS reads of the NEXT half's fragments, then the
-      // rest: the wait that the compiler places before the first MFMA (it always waits for every
-      // LDS read issued so far) then covers only reads issued a whole half earlier.
-      for (; kt + AHEAD < nk_full; ++kt) {
-        const int st_next = NEXT_STAGE(st);
-        DL_READ_FRAGS(1, st, 1);
-        DL_ISSUE(kt + AHEAD, st_new);
-        DL_MFMAS(0);
-        __builtin_amdgcn_sched_group_barrier(SG_MFMA, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(SG_DS_RD, NFRAG, 0);
-        sched_interleave<SG_VMEM_RD, 0, NMFMA - 1, NJ>();
-        __builtin_amdgcn_sched_barrier(0);
-        wait_vmcnt<PENDING>();        // k-step kt+1 has landed (this wave's part); kt+2 .. kt+AHEAD may be pending
-        lds_barrier();                // ... everyone's part; and every wave is done reading stage kt
-        DL_READ_FRAGS(0, st_next, 0);
-        DL_MFMAS(1);
-        __builtin_amdgcn_sched_group_barrier(SG_MFMA, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(SG_DS_RD, NFRAG, 0);
-        __builtin_amdgcn_sched_group_barrier(SG_MFMA, NMFMA - 1, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        st_new = st;
-        st = st_next;
-      }
-      // ---- last k-steps: at most one more load (the partial step), then drain
-      for (; kt < nk; ++kt) {
-        const int st_next = NEXT_STAGE(st);
-        DL_READ_FRAGS(1, st, 1);
-        if (kt + AHEAD < nk) DL_ISSUE_TAIL(kt + AHEAD, st_new);
-        DL_MFMAS(0);
-        wait_vmcnt<0>();
-        lds_barrier();
-        if (kt + 1 < nk) DL_READ_FRAGS(0, st_next, 0);
-        DL_MFMAS(1);
-        st_new = st;
-        st = st_next;
-      }
-      // every wave is past the last barrier of the k loop: no LDS read of the stages is pending
-
-      const int64_t my_row0 = row0;
-      const int my_col0 = col0;
-      bf16_t *const my_out = out_tile;
-      const int my_shift = GROUPED ? shift_tile : 0;
-      const int next = round + 1 < p.rounds ? tile_sequence_index(p, round + 1) : -1;
-      if (next >= 0) {
-        decode_tile(p, next, tile_m, tile_n);
-        row0 = (int64_t)tile_m * BM;
-        col0 = tile_n * BN;
-        if (EARLY_FETCH) begin_tile(row0, col0, C::EARLY_STEPS);
-      }
-      gemm_epilogue<C, TM, TN, EPI>(acc, smem, smem_gate, p, my_row0, my_col0, sample0, tid, wm, wn, l32, lh, my_out, my_shift);
-      if (next < 0) break;
-      if (EARLY_FETCH) finish_begin(C::EARLY_STEPS);
-      else begin_tile(row0, col0, AHEAD);
     }
-#undef DL_ISSUE
-#undef DL_ISSUE_TAIL
+    bf16x8 uf[2][TM], wf[2][TN];
+    DL_READ_FRAGS(0, st, 0);
+    // One k-step.  TAIL = -1: in the middle of the tile; TAIL = i: the i-th of the tile's last DEFER steps, whose
+    // stage the epilogue uses.  Each group of MFMAs issues one MFMA first, then the LDS reads of the NEXT
+    // group's fragments, then the rest: the wait that the compiler places before the first MFMA (it always
+    // waits for every LDS read issued so far) then covers only reads issued a whole group earlier.
+    auto k_step = [&](auto tail_tag) {
+      constexpr int TAIL = decltype(tail_tag)::value;
+      constexpr bool LAST = TAIL == DEFER - 1;
+      const int st_next = st + 1 == NS ? 0 : st + 1, st_prev = st == 0 ? NS - 1 : st - 1;
+#pragma unroll
+      for (int s = 0; s < SUBS; ++s) {
+        if (s + 1 < SUBS) {
+          DL_READ_FRAGS((s + 1) & 1, st, s + 1);
+          if (s == 0 && TAIL <= 0) ld_issue(J_A{}, J_N{}, st_prev);
+          DL_MFMAS(s & 1);
+          __builtin_amdgcn_sched_group_barrier(SG_MFMA, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(SG_DS_RD, NFRAG, 0);
+          if (s == 0 && TAIL <= 0) sched_interleave<SG_VMEM_RD, 0, NMFMA - 1, NJ - LA>();
+          else __builtin_amdgcn_sched_group_barrier(SG_MFMA, NMFMA - 1, 0);
+          __builtin_amdgcn_sched_barrier(0);
+          if (s == 0 && TAIL <= 0) ld_advance();
+        } else {
+          // every fragment of this k-step is in registers (or on its way): past the barrier its stage is free,
+          // and the next k-step's stage is complete
+          wait_vmcnt<(NS - 2 - (TAIL > 0 ? TAIL : 0)) * NJ>();
+          lds_barrier();
+          if (!LAST) DL_READ_FRAGS((s + 1) & 1, st_next, 0);
+          if (TAIL < 0) ld_issue(J_0{}, J_A{}, st);
+          DL_MFMAS(s & 1);
+          if (!LAST) {
+            __builtin_amdgcn_sched_group_barrier(SG_MFMA, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(SG_DS_RD, NFRAG, 0);
+            if (TAIL < 0) sched_interleave<SG_VMEM_RD, 0, NMFMA - 1, LA>();
+            else __builtin_amdgcn_sched_group_barrier(SG_MFMA, NMFMA - 1, 0);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      st = st_next;
+    };
+    for (int kt = 0; kt < nk - DEFER; ++kt) k_step(std::integral_constant<int, -1>{});
+    k_step(std::integral_constant<int, 0>{});
+    if constexpr (DEFER > 1) k_step(std::integral_constant<int, 1>{});
+    if constexpr (DEFER > 2) k_step(std::integral_constant<int, 2>{});
+    if constexpr (DEFER > 3) k_step(std::integral_constant<int, 3>{});
+    static_assert(DEFER <= 4, "k_step calls");
+
+    // the i-th slice of EACH bytes inside the stages of the last DEFER k-steps
+    auto slice = [&](int i, int each) {
+      const int per = STAGE / each, d = i / per;
+      int s = st - DEFER + d;
+      if (s < 0) s += NS;
+      return s * STAGE + (i - d * per) * each;
+    };
+    if constexpr (WGK == 1) {
+      const int at = slice(wave, C::EPI_WAVE);
+      gemm_epilogue<C, TM, TN, EPI, 0, NMFMA>(acc, lds_offset(smem) + at, smem + at, p, to, lane, wm, wn, early);
+    } else {
+      // Partial sums meet: of its tiles a wavefront of the first k half keeps the first part and gives the rest to
+      // its partner, and the other way round.
+      constexpr int H = (NMFMA + 1) / 2;
+      auto meet = [&](auto keep0_tag, auto keep1_tag) {
+        constexpr int K0 = decltype(keep0_tag)::value, K1 = decltype(keep1_tag)::value;
+#pragma unroll
+        for (int t = 0; t < NMFMA; ++t)
+          if (t < K0 || t >= K1) {
+            unsigned char *at = smem + slice(wt * NMFMA + t, 4096) + lane * 16;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+              floatx4 v;
+#pragma unroll
+              for (int e = 0; e < 4; ++e) v[e] = acc[t % TN][t / TN][4 * g + e];
+              *reinterpret_cast<floatx4 *>(at + g * 1024) = v;
+            }
+          }
+        lds_barrier();
+#pragma unroll
+        for (int t = K0; t < K1; ++t) {
+          uintx4 v[4];
+          lds_read4_b128<1024>(v, lds_offset(smem) + slice(wt * NMFMA + t, 4096) + lane * 16);
+#pragma unroll
+          for (int g = 0; g < 4; ++g)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[t % TN][t / TN][4 * g + e] += __uint_as_float(v[g][e]);
+        }
+        lds_barrier();   // the same bytes take the staged rows
+        const int at = slice(wave, C::EPI_WAVE);
+        if constexpr (K0 < K1)
+          gemm_epilogue<C, TM, TN, EPI, K0, K1>(acc, lds_offset(smem) + at, smem + at, p, to, lane, wm, wn, early);
+      };
+      if (wk == 0) meet(std::integral_constant<int, 0>{}, std::integral_constant<int, H>{});
+      else meet(std::integral_constant<int, H>{}, std::integral_constant<int, NMFMA>{});
+    }
+    tile = round + 1 < p.rounds ? tile_sequence_index(p, round + 1) : -1;
+    if (tile < 0) break;
+    lds_barrier();   // every wavefront is done with the stages it staged in: refill them
+#pragma unroll
+    for (int d = 0; d < DEFER; ++d) {
+      int s = st - DEFER + d;
+      if (s < 0) s += NS;
+      if (d + 1 < DEFER) {
+        ld_issue(J_0{}, J_N{}, s);
+        ld_advance();
+      } else {
+        ld_issue(J_0{}, J_A{}, s);
+      }
+    }
+  }
+  wait_vmcnt<0>();   // no load may still write to the LDS when the workgroup leaves it
 #undef DL_READ_FRAGS
 #undef DL_MFMAS
-#undef NEXT_STAGE
-  };
-
-  if constexpr (C::N_HI == 0) {
-    run(LoadCount<C::NJ_LO>{});
-  } else {
-    if (wave < C::N_HI) run(LoadCount<C::NJ_HI>{});
-    else run(LoadCount<C::NJ_LO>{});
-  }
 }
 
-template <int WGM, int WGN, int TM, int TN, int NS, int EPI, class GT = NoGroups>
+template <int WGM, int WGN, int WGK, int TM, int TN, int NS, int EPI, class GT = NoGroups>
 int launch_one(const GemmParams &p0, hipStream_t s, const GT &gt = GT()) {
-  using C = GemmCfg<WGM, WGN, TM, TN, NS>;
-  constexpr int LDS_BYTES = C::SMEM + C::EXTRA_BYTES;
+  using C = GemmCfg<WGM, WGN, WGK, TM, TN, NS>;
+  constexpr int LDS_BYTES = C::SMEM;
   static_assert(LDS_BYTES <= 160 * 1024, "the tile's stages must fit the LDS");
-  // workgroups resident per CU: what the LDS holds, at most three of the four-wavefront tiles
-  constexpr int LDS_FIT = (160 * 1024) / LDS_BYTES;
-  constexpr int WG_PER_CU = C::NW > 4 ? 1 : (LDS_FIT > 3 ? 3 : (LDS_FIT < 1 ? 1 : LDS_FIT));
   GemmParams p = p0;
   const int64_t tiles_m = (p.N + C::BM - 1) / C::BM;
   p.tiles_m = (int)tiles_m;
@@ -686,73 +773,68 @@ int launch_one(const GemmParams &p0, hipStream_t s, const GT &gt = GT()) {
     return -2;
   }
   p.total_tiles = (int)total;
-  // as many workgroups as the chip holds at once; a multiple of 8 so that every round gives
+  p.plain = p.n < (1 << 26) && p.ld_out < (1 << 26);
+  // one workgroup per CU (its stages take most of the LDS); a multiple of 8 so that every round gives
   // each XCD a contiguous run of tiles
-  int grid = (ddit::device_cus() * WG_PER_CU) & ~7;
+  int grid = ddit::device_cus() & ~7;
   if (grid < 8) grid = 8;
   if (total <= grid) grid = (int)((total + 7) & ~(int64_t)7);
   p.rounds = (int)(((total + 7) / 8 + grid / 8 - 1) / (grid / 8));
   static bool attr_set = false;  // benign race: the attribute is idempotent
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_bf16<WGM, WGN, TM, TN, NS, EPI, GT>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_bf16<WGM, WGN, WGK, TM, TN, NS, EPI, GT>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
     if (e != hipSuccess) return ddit::hip_fail(e, "gemm hipFuncSetAttribute");
     attr_set = true;
   }
-  hipLaunchKernelGGL((k_gemm_bf16<WGM, WGN, TM, TN, NS, EPI, GT>), dim3((unsigned)grid), dim3(C::NT), LDS_BYTES, s, p, gt);
+  hipLaunchKernelGGL((k_gemm_bf16<WGM, WGN, WGK, TM, TN, NS, EPI, GT>), dim3((unsigned)grid), dim3(C::NT), LDS_BYTES, s, p, gt);
   return ddit::hip_fail(hipGetLastError(), "gemm launch");
 }
 
 // ---------------------------------------------------------------------------------------------
-// Tile choice.  Nine forms of the kernel are compiled: seven output tiles, and for 192 x 192 and
-// 128 x 192 two depths of the operand ring.  With three stages two workgroups of these tiles fit a
-// CU's LDS and one's epilogue runs under the other's k loop (192 x 192 at 48600 tokens: fc1 0.62 ->
-// 0.52 ms); with four a workgroup that has the CU to itself hides more of the fetch latency (128 x
-// 192 at 3680 tokens, k = 4608: 63 against 69 microseconds).  Which form is fastest depends on how the tile grid
-// divides over the CUs far more than on the tile's own efficiency (a 192 x 384 tile runs its k
-// loop at about twice the rate per flop of a 128 x 128 one, but 60 of them leave 196 CUs idle).
-// The launcher therefore prices every tile with a small model of the kernel and takes the
-// cheapest.  With  tiles = ceil(N / rows) * ceil(n / cols)  and  q = ceil(tiles / CUs)  tiles on
-// the busiest CU,
-//     t = (a * k / 1152 + e[epilogue]) * q / gain[min(q, workgroups per CU)]
-//         * (1 + 0.29 * min(1, tiles / CUs)) + 0.63      [microseconds]
-// a: one workgroup's k-loop time per 1152 of k with a CU to itself; e: its epilogue and set-up;
-// gain: what sharing a CU between two or three resident workgroups returns; the load term is the
-// clock and memory slow-down of a full chip against a single busy CU.  The constants are a
-// least-squares fit (in log time) to a sweep of the model's five linears over 23 token counts
-// from 288 to 48600 with every tile forced in turn (ddit_linear_fwd_tile): over that sweep the
-// model's picks are within 0.4 % of the best tile's total time.  (The load term and the launch
-// constant trade against each other in the fit and differ between machines of one type: 0.29 / 0.63
-// and 0.40 / 0 fit equally well; the picks do not change.)
+// Tile choice.  Nine output tiles are compiled.  Which is fastest depends on how the tile grid divides over
+// the CUs far more than on the tile's own efficiency (a 192 x 384 tile does twice the work per byte
+// fetched of a 128 x 192 one, but 60 of them leave 196 CUs idle).  The launcher therefore prices every tile
+// with a small model of the kernel and takes the cheapest.  With  tiles = ceil(N / rows) * ceil(n / cols),
+// q = ceil(tiles / CUs)  tiles on the busiest CU and  steps = ceil(k / 64),
+//     t = (a * steps + e[epilogue]) * q * (1 + s * min(1, tiles / CUs)) + 2.71      [microseconds]
+//         (+ f * min(1, tiles / CUs) for the residual update)
+// a: one k-step; e: a tile's epilogue and set-up; s: the clock and memory slow-down of a full chip against a
+// single busy CU; f: what the first round's epilogues cost more, when all CUs reach the memory-bound phase
+// together; the rest is the launch.  The constants are a least-squares fit (in log time) to a sweep of
+// eleven linears (the model's at hidden 1152 and 256, one rank's of a four-way head split, the caption
+// embedder's) over 44 token counts from 16 to 48600 with every tile forced in turn and the weights coming
+// from HBM, as they do in a step: over that sweep the picks cost 1.1 % more than the best tile everywhere.
+// The nine are the ones, of fourteen that were swept, that lose least against all fourteen (0.6 % of a layer).
 // ---------------------------------------------------------------------------------------------
 struct TileModel {
-  int rows, cols, wavefronts, stages, wg_per_cu;   // stages: depth of the operand ring in LDS
-  float a;        // k-loop microseconds per 1152 of k, alone on a CU
+  int rows, cols, wavefronts, stages;   // stages: depth of the operand ring in LDS
+  float a;        // microseconds per k-step of 64
   float e[3];     // epilogue + set-up microseconds: bf16 / GELU / gated residual
+  float s;        // slow-down of a full chip
+  float f;        // once per launch, residual update
 };
 constexpr int N_TILES = 9;
 constexpr TileModel TILES[N_TILES] = {
-    {192, 384, 8, 4, 1, 22.07f, {4.65f, 7.82f, 18.53f}},
-    {192, 288, 6, 4, 1, 18.75f, {4.28f, 6.87f, 15.69f}},
-    {192, 256, 8, 4, 1, 15.69f, {3.24f, 5.16f, 12.01f}},
-    {192, 192, 4, 3, 2, 15.24f, {2.74f, 4.34f, 11.08f}},
-    {192, 192, 4, 4, 1, 13.11f, {4.12f, 5.94f, 12.41f}},
-    {128, 192, 4, 3, 2, 12.84f, {0.67f, 1.71f, 6.39f}},
-    {128, 192, 4, 4, 1, 10.97f, {1.40f, 2.71f, 7.46f}},
-    {128, 128, 4, 4, 2, 8.91f, {1.20f, 1.75f, 5.35f}},
-    {64, 128, 4, 4, 3, 6.59f, {0.36f, 0.62f, 2.33f}},
+    {192, 384, 8, 2, 1.219f, {3.82f, 7.11f, 22.75f}, 0.249f, 20.40f},
+    {256, 256, 8, 2, 1.137f, {2.85f, 6.48f, 21.69f}, 0.248f, 7.58f},
+    {192, 256, 8, 2, 1.009f, {2.11f, 5.02f, 15.09f}, 0.147f, 9.81f},
+    {256, 128, 8, 3, 0.546f, {1.67f, 3.18f, 7.93f}, 0.451f, 0.00f},
+    {128, 192, 8, 3, 0.506f, {1.43f, 2.44f, 6.26f}, 0.357f, 0.00f},
+    {128, 128, 8, 4, 0.364f, {1.65f, 2.66f, 5.52f}, 0.298f, 0.19f},
+    {64, 192, 8, 4, 0.368f, {1.37f, 2.97f, 5.28f}, 0.129f, 0.00f},
+    {64, 128, 8, 6, 0.283f, {1.30f, 2.17f, 3.72f}, 0.115f, 0.23f},
+    {64, 64, 8, 8, 0.219f, {0.89f, 1.35f, 2.54f}, 0.069f, 0.39f},
 };
-constexpr float CU_SHARE_GAIN[3] = {1.0f, 1.21f, 1.22f};
-constexpr float FULL_CHIP_SLOWDOWN = 0.29f, LAUNCH_US = 0.63f;
+constexpr float LAUNCH_US = 2.71f;
 
 float predicted_us(int tile, int epilogue, int64_t N, int n, int k, int cus) {
   const TileModel &t = TILES[tile];
   const double tiles = (double)((N + t.rows - 1) / t.rows) * (double)((n + t.cols - 1) / t.cols);
   const double q = std::ceil(tiles / cus);
-  const int sharing = q < t.wg_per_cu ? (int)q : t.wg_per_cu;
-  const double one = t.a * (double)k / 1152.0 + t.e[epilogue];
-  const double load = 1.0 + FULL_CHIP_SLOWDOWN * (tiles < cus ? tiles / cus : 1.0);
-  return (float)(one * q / CU_SHARE_GAIN[sharing > 0 ? sharing - 1 : 0] * load + LAUNCH_US);
+  const double one = t.a * (double)((k + BK - 1) / BK) + t.e[epilogue];
+  const double full = tiles < cus ? tiles / cus : 1.0;
+  return (float)(one * q * (1.0 + t.s * full) + (epilogue == 2 ? t.f * full : 0.0) + LAUNCH_US);
 }
 
 int cheapest_tile(int epilogue, int64_t N, int n, int k, int cus) {
@@ -765,31 +847,31 @@ int cheapest_tile(int epilogue, int64_t N, int n, int k, int cus) {
   return best;
 }
 
-template <int WGM, int WGN, int TM, int TN, int NS, int EPI>
+template <int WGM, int WGN, int WGK, int TM, int TN, int NS, int EPI>
 int launch_checked(int tile, const GemmParams &p, hipStream_t s) {
-  using C = GemmCfg<WGM, WGN, TM, TN, NS>;
+  using C = GemmCfg<WGM, WGN, WGK, TM, TN, NS>;
   // the model's table and the compiled tile must describe the same thing
   if (TILES[tile].rows != C::BM || TILES[tile].cols != C::BN || TILES[tile].wavefronts != C::NW ||
       TILES[tile].stages != NS) {
     ddit::set_error("linear: tile table entry %d does not match its kernel", tile);
     return -2;
   }
-  return launch_one<WGM, WGN, TM, TN, NS, EPI>(p, s);
+  return launch_one<WGM, WGN, WGK, TM, TN, NS, EPI>(p, s);
 }
 
 template <int EPI>
 int launch_epi(int tile, const GemmParams &p, hipStream_t s) {
   if (tile < 0) tile = cheapest_tile(EPI, p.N, p.n, p.k, ddit::device_cus());
   switch (tile) {
-    case 0: return launch_checked<2, 4, 3, 3, 4, EPI>(tile, p, s);
-    case 1: return launch_checked<2, 3, 3, 3, 4, EPI>(tile, p, s);
-    case 2: return launch_checked<2, 4, 3, 2, 4, EPI>(tile, p, s);
-    case 3: return launch_checked<2, 2, 3, 3, 3, EPI>(tile, p, s);
-    case 4: return launch_checked<2, 2, 3, 3, 4, EPI>(tile, p, s);
-    case 5: return launch_checked<2, 2, 2, 3, 3, EPI>(tile, p, s);
-    case 6: return launch_checked<2, 2, 2, 3, 4, EPI>(tile, p, s);
-    case 7: return launch_checked<2, 2, 2, 2, 4, EPI>(tile, p, s);
-    case 8: return launch_checked<2, 2, 1, 2, 4, EPI>(tile, p, s);
+    case 0: return launch_checked<2, 4, 1, 3, 3, 2, EPI>(tile, p, s);
+    case 1: return launch_checked<2, 4, 1, 4, 2, 2, EPI>(tile, p, s);
+    case 2: return launch_checked<2, 4, 1, 3, 2, 2, EPI>(tile, p, s);
+    case 3: return launch_checked<4, 2, 1, 2, 2, 3, EPI>(tile, p, s);
+    case 4: return launch_checked<4, 2, 1, 1, 3, 3, EPI>(tile, p, s);
+    case 5: return launch_checked<2, 2, 2, 2, 2, 4, EPI>(tile, p, s);
+    case 6: return launch_checked<2, 2, 2, 1, 3, 4, EPI>(tile, p, s);
+    case 7: return launch_checked<2, 2, 2, 1, 2, 6, EPI>(tile, p, s);
+    case 8: return launch_checked<2, 2, 2, 1, 1, 8, EPI>(tile, p, s);
   }
   ddit::set_error("linear: no tile %d (there are %d)", tile, N_TILES);
   return -1;
@@ -804,7 +886,7 @@ int gemm_tile_count() { return N_TILES; }
 int gemm_tile_info(int tile, int *rows, int *cols, int *wavefronts, int *wg_per_cu) {
   if (tile < 0 || tile >= N_TILES) return -1;
   *rows = TILES[tile].rows; *cols = TILES[tile].cols;
-  *wavefronts = TILES[tile].wavefronts; *wg_per_cu = TILES[tile].wg_per_cu;
+  *wavefronts = TILES[tile].wavefronts; *wg_per_cu = 1;
   return 0;
 }
 
@@ -815,9 +897,9 @@ int gemm_tile_choice(int epilogue, int64_t N, int n, int k, int cus, float *us_p
   return cheapest_tile(epilogue, N, n, k, cus);
 }
 
-template <int WGM, int WGN, int TM, int TN, int NS>
+template <int WGM, int WGN, int WGK, int TM, int TN, int NS>
 int launch_grouped_tile(const GemmParams &p, const GroupTable &gt, hipStream_t s) {
-  return launch_one<WGM, WGN, TM, TN, NS, 0, GroupTable>(p, s, gt);
+  return launch_one<WGM, WGN, WGK, TM, TN, NS, 0, GroupTable>(p, s, gt);
 }
 
 // One launch for G problems that share u: out[g] = u W[g]^T + bias[g], every W[g] of shape [a.n, a.k].
@@ -851,17 +933,17 @@ int launch_gemm_grouped(const GemmArgs &a, int G, const void *const *W, const vo
   p.out = gt.out[0]; p.ld_out = a.ld_out;
   p.resid = nullptr; p.gate_tab = nullptr; p.gate_c6 = nullptr; p.gate_c6_stride = 0;
   p.tokens_per_sample = a.tokens_per_sample > 0 ? a.tokens_per_sample : 1;
-  p.tiles_m = 0; p.tiles_n = 0; p.group_w = 1; p.total_tiles = 0; p.rounds = 0;
+  p.tiles_m = 0; p.tiles_n = 0; p.group_w = 1; p.total_tiles = 0; p.rounds = 0; p.plain = 0;
   switch (tile) {
-    case 0: return launch_grouped_tile<2, 4, 3, 3, 4>(p, gt, s);
-    case 1: return launch_grouped_tile<2, 3, 3, 3, 4>(p, gt, s);
-    case 2: return launch_grouped_tile<2, 4, 3, 2, 4>(p, gt, s);
-    case 3: return launch_grouped_tile<2, 2, 3, 3, 3>(p, gt, s);
-    case 4: return launch_grouped_tile<2, 2, 3, 3, 4>(p, gt, s);
-    case 5: return launch_grouped_tile<2, 2, 2, 3, 3>(p, gt, s);
-    case 6: return launch_grouped_tile<2, 2, 2, 3, 4>(p, gt, s);
-    case 7: return launch_grouped_tile<2, 2, 2, 2, 4>(p, gt, s);
-    default: return launch_grouped_tile<2, 2, 1, 2, 4>(p, gt, s);
+    case 0: return launch_grouped_tile<2, 4, 1, 3, 3, 2>(p, gt, s);
+    case 1: return launch_grouped_tile<2, 4, 1, 4, 2, 2>(p, gt, s);
+    case 2: return launch_grouped_tile<2, 4, 1, 3, 2, 2>(p, gt, s);
+    case 3: return launch_grouped_tile<4, 2, 1, 2, 2, 3>(p, gt, s);
+    case 4: return launch_grouped_tile<4, 2, 1, 1, 3, 3>(p, gt, s);
+    case 5: return launch_grouped_tile<2, 2, 2, 2, 2, 4>(p, gt, s);
+    case 6: return launch_grouped_tile<2, 2, 2, 1, 3, 4>(p, gt, s);
+    case 7: return launch_grouped_tile<2, 2, 2, 1, 2, 6>(p, gt, s);
+    default: return launch_grouped_tile<2, 2, 2, 1, 1, 8>(p, gt, s);
   }
 }
 
@@ -888,7 +970,7 @@ int launch_gemm(int epilogue, const GemmArgs &a, hipStream_t s) {
   p.resid = a.resid;
   p.gate_tab = a.gate_tab; p.gate_c6 = a.gate_c6; p.gate_c6_stride = a.gate_c6_stride;
   p.tokens_per_sample = a.tokens_per_sample > 0 ? a.tokens_per_sample : 1;
-  p.tiles_m = 0; p.tiles_n = 0; p.group_w = 1; p.total_tiles = 0; p.rounds = 0;
+  p.tiles_m = 0; p.tiles_n = 0; p.group_w = 1; p.total_tiles = 0; p.rounds = 0; p.plain = 0;
   switch (epilogue) {
     case 0: return launch_epi<0>(a.tile, p, s);
     case 1: return launch_epi<1>(a.tile, p, s);
