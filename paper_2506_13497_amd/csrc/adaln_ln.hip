@@ -10,27 +10,31 @@
 
 namespace {
 
-constexpr int ROWS_PER_WAVE = 4;
-
-// CHUNKS = float4 chunks per lane; D <= 256*CHUNKS.  A wavefront takes ROWS_PER_WAVE consecutive
-// token rows and keeps the sample's (1 + scale) and shift vectors in registers across them: read
-// per row they would be four more vectors of D floats against one row of x, and although they come
-// from cache, that traffic through the CU's vector cache then costs as much time as the HBM side.
-template <int CHUNKS>
+// CHUNKS = float4 chunks per lane; D <= 256*CHUNKS.  A wavefront takes ROWS (1 or 2) consecutive token
+// rows.  The sample's (1 + scale) and shift vectors, four vectors of D floats to read against one row of x,
+// are formed once per workgroup and kept in LDS: read per row, or per wavefront, that traffic through the
+// CU's vector cache costs as much time as the HBM side.  Rows of another sample than the workgroup's first
+// row (the last rows of a sample, tiny shapes) read theirs from memory.
+template <int CHUNKS, int ROWS, bool STREAM>
 __global__ __launch_bounds__(256) void k_modulated_layernorm(const float *__restrict__ x,
                                                              const float *__restrict__ tab,
                                                              const float *__restrict__ c6, int which, int64_t N,
                                                              int64_t tokens_per_sample, int D, float eps,
                                                              bf16_t *__restrict__ out) {
+  extern __shared__ __attribute__((aligned(16))) float4 mod[];   // [2][nchunk]: 1 + scale, shift
   const int lane = threadIdx.x & 63;
-  const int64_t row0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * ROWS_PER_WAVE;
-  if (row0 >= N) return;
+  const int64_t wg_row0 = (int64_t)blockIdx.x * (4 * ROWS);
+  const int64_t row0 = wg_row0 + (threadIdx.x >> 6) * ROWS;
   const int nchunk = D >> 2;
   const float4 *t_shift = reinterpret_cast<const float4 *>(tab + (int64_t)(3 * which) * D);
   const float4 *t_scale = reinterpret_cast<const float4 *>(tab + (int64_t)(3 * which + 1) * D);
-  float4 sc1[CHUNKS], sh[CHUNKS];   // 1 + scale, shift of sample b_cur
-  int64_t b_cur = -1;
-  const int64_t row_end = row0 + ROWS_PER_WAVE < N ? row0 + ROWS_PER_WAVE : N;
+  auto modulation = [&](int64_t b, int c, float4 &sc1, float4 &sh) {
+    const float4 *c_shift = reinterpret_cast<const float4 *>(c6 + b * 6 * (int64_t)D + (int64_t)(3 * which) * D);
+    const float4 *c_scale = reinterpret_cast<const float4 *>(c6 + b * 6 * (int64_t)D + (int64_t)(3 * which + 1) * D);
+    const float4 ts = t_shift[c], tc = t_scale[c], cs = c_shift[c], cc = c_scale[c];
+    sh = make_float4(ts.x + cs.x, ts.y + cs.y, ts.z + cs.z, ts.w + cs.w);
+    sc1 = make_float4(1.f + (tc.x + cc.x), 1.f + (tc.y + cc.y), 1.f + (tc.z + cc.z), 1.f + (tc.w + cc.w));
+  };
   // the first row's loads are issued before the modulation vectors are fetched
   float4 v[CHUNKS];
   auto load_row = [&](int64_t row) {
@@ -39,29 +43,21 @@ __global__ __launch_bounds__(256) void k_modulated_layernorm(const float *__rest
     for (int j = 0; j < CHUNKS; ++j) {
       const int c = lane + 64 * j;
       v[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (c < nchunk) {   // each row is read once and written once: streaming accesses
-        const floatx4 t = __builtin_nontemporal_load(xr + c);
+      if (c < nchunk) {
+        const floatx4 t = STREAM ? __builtin_nontemporal_load(xr + c) : xr[c];
         v[j] = make_float4(t[0], t[1], t[2], t[3]);
       }
     }
   };
-  load_row(row0);
+  if (row0 < N) load_row(row0);
+  const int64_t b_wg = wg_row0 / tokens_per_sample;
+  for (int c = threadIdx.x; c < nchunk; c += 256) modulation(b_wg, c, mod[c], mod[nchunk + c]);
+  __syncthreads();
+  if (row0 >= N) return;
+  const int64_t row_end = row0 + ROWS < N ? row0 + ROWS : N;
+  const int64_t wg_sample_end = (b_wg + 1) * tokens_per_sample;
+#pragma unroll 1
   for (int64_t row = row0; row < row_end; ++row) {
-    const int64_t b = row / tokens_per_sample;
-    if (b != b_cur) {
-      b_cur = b;
-      const float4 *c_shift = reinterpret_cast<const float4 *>(c6 + b * 6 * (int64_t)D + (int64_t)(3 * which) * D);
-      const float4 *c_scale = reinterpret_cast<const float4 *>(c6 + b * 6 * (int64_t)D + (int64_t)(3 * which + 1) * D);
-#pragma unroll
-      for (int j = 0; j < CHUNKS; ++j) {
-        const int c = lane + 64 * j;
-        if (c < nchunk) {
-          const float4 ts = t_shift[c], tc = t_scale[c], cs = c_shift[c], cc = c_scale[c];
-          sh[j] = make_float4(ts.x + cs.x, ts.y + cs.y, ts.z + cs.z, ts.w + cs.w);
-          sc1[j] = make_float4(1.f + (tc.x + cc.x), 1.f + (tc.y + cc.y), 1.f + (tc.z + cc.z), 1.f + (tc.w + cc.w));
-        }
-      }
-    }
     float s = 0.f;
 #pragma unroll
     for (int j = 0; j < CHUNKS; ++j) s += (v[j].x + v[j].y) + (v[j].z + v[j].w);   // chunks past D hold zeros
@@ -74,18 +70,22 @@ __global__ __launch_bounds__(256) void k_modulated_layernorm(const float *__rest
       if (lane + 64 * j < nchunk) ss += (dv[j].x * dv[j].x + dv[j].y * dv[j].y) + (dv[j].z * dv[j].z + dv[j].w * dv[j].w);
     }
     // the next row is on its way while this one is reduced and written
-    if (row + 1 < row_end) load_row(row + 1);
+    if (ROWS > 1 && row + 1 < row_end) load_row(row + 1);
     const float rstd = rsqrtf(wave_sum(ss) / (float)D + eps);
     bf16x4 *orow = reinterpret_cast<bf16x4 *>(out + row * (int64_t)D);
+    const bool here = row < wg_sample_end;
 #pragma unroll
     for (int j = 0; j < CHUNKS; ++j) {
       const int c = lane + 64 * j;
       if (c < nchunk) {
+        float4 sc1, sh;
+        if (here) { sc1 = mod[c]; sh = mod[nchunk + c]; }
+        else modulation(row / tokens_per_sample, c, sc1, sh);
         bf16x4 o;
-        o[0] = (bf16_t)(dv[j].x * rstd * sc1[j].x + sh[j].x);
-        o[1] = (bf16_t)(dv[j].y * rstd * sc1[j].y + sh[j].y);
-        o[2] = (bf16_t)(dv[j].z * rstd * sc1[j].z + sh[j].z);
-        o[3] = (bf16_t)(dv[j].w * rstd * sc1[j].w + sh[j].w);
+        o[0] = (bf16_t)(dv[j].x * rstd * sc1.x + sh.x);
+        o[1] = (bf16_t)(dv[j].y * rstd * sc1.y + sh.y);
+        o[2] = (bf16_t)(dv[j].z * rstd * sc1.z + sh.z);
+        o[3] = (bf16_t)(dv[j].w * rstd * sc1.w + sh.w);
         __builtin_nontemporal_store(o, orow + c);
       }
     }
@@ -96,20 +96,32 @@ __global__ __launch_bounds__(256) void k_modulated_layernorm(const float *__rest
 
 namespace ddit {
 
+template <int CHUNKS, int ROWS, bool STREAM>
+void launch_ln(const float *x, const float *tab, const float *c6, int which, int64_t N, int64_t tps, int D, float eps,
+               bf16_t *o, hipStream_t s) {
+  const unsigned lds = 2u * (unsigned)D * 4u;   // at most 32 KB
+  hipLaunchKernelGGL((k_modulated_layernorm<CHUNKS, ROWS, STREAM>), dim3((unsigned)((N + 4 * ROWS - 1) / (4 * ROWS))),
+                     dim3(256), lds, s, x, tab, c6, which, N, tps, D, eps, o);
+}
+template <int CHUNKS>
+void launch_ln(const float *x, const float *tab, const float *c6, int which, int64_t N, int64_t tps, int D, float eps,
+               bf16_t *o, hipStream_t s) {
+  // A wavefront with a second row hides its latency behind the first one's reductions; below 8192 rows there are
+  // not four wavefronts per SIMD and the second row only makes the launch longer.  D = 1152, 1 / 2 rows: 256 rows
+  // 3.5 / 4.8 us, 2304 rows 5.6 / 6.2 us, 12960 rows 19.6 / 19.8 us, 48600 rows 53.1 / 50.1 us (6.7 TB/s).
+  // A stream too large for the memory-side cache is read past the L2, which keeps other launches' weights.
+  if (N < 8192) launch_ln<CHUNKS, 1, false>(x, tab, c6, which, N, tps, D, eps, o, s);
+  else if (N * (int64_t)D <= (int64_t)24 << 20) launch_ln<CHUNKS, 2, false>(x, tab, c6, which, N, tps, D, eps, o, s);
+  else launch_ln<CHUNKS, 2, true>(x, tab, c6, which, N, tps, D, eps, o, s);
+}
+
 int launch_modulated_layernorm(const float *x, const float *ada_table, const float *c6, int which, int64_t N,
                                int64_t tokens_per_sample, int D, float eps, void *out, hipStream_t s) {
   if (N == 0) return 0;
-  const unsigned grid = (unsigned)((N + 4 * ROWS_PER_WAVE - 1) / (4 * ROWS_PER_WAVE));
   bf16_t *o = reinterpret_cast<bf16_t *>(out);
-  if (D <= 256 * 2)
-    hipLaunchKernelGGL(k_modulated_layernorm<2>, dim3(grid), dim3(256), 0, s, x, ada_table, c6, which, N,
-                       tokens_per_sample, D, eps, o);
-  else if (D <= 256 * 5)
-    hipLaunchKernelGGL(k_modulated_layernorm<5>, dim3(grid), dim3(256), 0, s, x, ada_table, c6, which, N,
-                       tokens_per_sample, D, eps, o);
-  else if (D <= 256 * 16)
-    hipLaunchKernelGGL(k_modulated_layernorm<16>, dim3(grid), dim3(256), 0, s, x, ada_table, c6, which, N,
-                       tokens_per_sample, D, eps, o);
+  if (D <= 256 * 2) launch_ln<2>(x, ada_table, c6, which, N, tokens_per_sample, D, eps, o, s);
+  else if (D <= 256 * 5) launch_ln<5>(x, ada_table, c6, which, N, tokens_per_sample, D, eps, o, s);
+  else if (D <= 256 * 16) launch_ln<16>(x, ada_table, c6, which, N, tokens_per_sample, D, eps, o, s);
   else {
     set_error("D=%d: hidden size above 4096 is not supported by the LayerNorm kernel", D);
     return -2;
