@@ -15,13 +15,14 @@ namespace {
 // are formed once per workgroup and kept in LDS: read per row, or per wavefront, that traffic through the
 // CU's vector cache costs as much time as the HBM side.  Rows of another sample than the workgroup's first
 // row (the last rows of a sample, tiny shapes) read theirs from memory.
-template <int CHUNKS, int ROWS, bool STREAM>
-__global__ __launch_bounds__(256) void k_modulated_layernorm(const float *__restrict__ x,
+// SUM: a residual update that came as partial sums is added to the row first, and the row written back.
+template <int CHUNKS, int ROWS, bool STREAM, bool SUM>
+__global__ __launch_bounds__(256) void k_modulated_layernorm(float *__restrict__ x,
                                                              const float *__restrict__ tab,
                                                              const float *__restrict__ c6, int which, int64_t N,
                                                              int64_t tokens_per_sample, int D, float eps,
-                                                             bf16_t *__restrict__ out) {
-  extern __shared__ __attribute__((aligned(16))) float4 mod[];   // [2][nchunk]: 1 + scale, shift
+                                                             bf16_t *__restrict__ out, ddit::PendingSum pend) {
+  extern __shared__ __attribute__((aligned(16))) float4 mod[];   // [2 (+ 1)][nchunk]: 1 + scale, shift (, gate of the pending update)
   const int lane = threadIdx.x & 63;
   const int64_t wg_row0 = (int64_t)blockIdx.x * (4 * ROWS);
   const int64_t row0 = wg_row0 + (threadIdx.x >> 6) * ROWS;
@@ -34,6 +35,15 @@ __global__ __launch_bounds__(256) void k_modulated_layernorm(const float *__rest
     const float4 ts = t_shift[c], tc = t_scale[c], cs = c_shift[c], cc = c_scale[c];
     sh = make_float4(ts.x + cs.x, ts.y + cs.y, ts.z + cs.z, ts.w + cs.w);
     sc1 = make_float4(1.f + (tc.x + cc.x), 1.f + (tc.y + cc.y), 1.f + (tc.z + cc.z), 1.f + (tc.w + cc.w));
+  };
+  auto pending_gate = [&](int64_t b, int c) {
+    float4 g = make_float4(1.f, 1.f, 1.f, 1.f);
+    if (pend.gate_tab) {
+      g = reinterpret_cast<const float4 *>(pend.gate_tab)[c];
+      const float4 h = reinterpret_cast<const float4 *>(pend.gate_c6 + b * pend.gate_c6_stride)[c];
+      g.x += h.x; g.y += h.y; g.z += h.z; g.w += h.w;
+    }
+    return g;
   };
   // the first row's loads are issued before the modulation vectors are fetched
   float4 v[CHUNKS];
@@ -50,14 +60,45 @@ __global__ __launch_bounds__(256) void k_modulated_layernorm(const float *__rest
     }
   };
   if (row0 < N) load_row(row0);
+  float4 add[CHUNKS];   // SUM: the row's pending update, before its gate
+  if constexpr (SUM) {
+    static_assert(ROWS == 1, "one row per wavefront");
+    if (row0 < N)
+#pragma unroll
+      for (int j = 0; j < CHUNKS; ++j) {
+        const int c = lane + 64 * j;
+        add[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (c < nchunk)
+          for (int q = 0; q < pend.parts; ++q) {
+            const float4 t = reinterpret_cast<const float4 *>(pend.part + q * pend.part_stride + row0 * (int64_t)D)[c];
+            add[j].x += t.x; add[j].y += t.y; add[j].z += t.z; add[j].w += t.w;
+          }
+      }
+  }
   const int64_t b_wg = wg_row0 / tokens_per_sample;
-  for (int c = threadIdx.x; c < nchunk; c += 256) modulation(b_wg, c, mod[c], mod[nchunk + c]);
+  for (int c = threadIdx.x; c < nchunk; c += 256) {
+    modulation(b_wg, c, mod[c], mod[nchunk + c]);
+    if constexpr (SUM) mod[2 * nchunk + c] = pending_gate(b_wg, c);
+  }
   __syncthreads();
   if (row0 >= N) return;
   const int64_t row_end = row0 + ROWS < N ? row0 + ROWS : N;
   const int64_t wg_sample_end = (b_wg + 1) * tokens_per_sample;
 #pragma unroll 1
   for (int64_t row = row0; row < row_end; ++row) {
+    const bool here = row < wg_sample_end;
+    if constexpr (SUM) {
+      floatx4 *xw = reinterpret_cast<floatx4 *>(x + row * (int64_t)D);
+#pragma unroll
+      for (int j = 0; j < CHUNKS; ++j) {
+        const int c = lane + 64 * j;
+        if (c < nchunk) {
+          const float4 g = here ? mod[2 * nchunk + c] : pending_gate(row / tokens_per_sample, c);
+          v[j] = make_float4(v[j].x + g.x * add[j].x, v[j].y + g.y * add[j].y, v[j].z + g.z * add[j].z, v[j].w + g.w * add[j].w);
+          xw[c] = floatx4{v[j].x, v[j].y, v[j].z, v[j].w};
+        }
+      }
+    }
     float s = 0.f;
 #pragma unroll
     for (int j = 0; j < CHUNKS; ++j) s += (v[j].x + v[j].y) + (v[j].z + v[j].w);   // chunks past D hold zeros
@@ -73,7 +114,6 @@ __global__ __launch_bounds__(256) void k_modulated_layernorm(const float *__rest
     if (ROWS > 1 && row + 1 < row_end) load_row(row + 1);
     const float rstd = rsqrtf(wave_sum(ss) / (float)D + eps);
     bf16x4 *orow = reinterpret_cast<bf16x4 *>(out + row * (int64_t)D);
-    const bool here = row < wg_sample_end;
 #pragma unroll
     for (int j = 0; j < CHUNKS; ++j) {
       const int c = lane + 64 * j;
@@ -96,32 +136,35 @@ __global__ __launch_bounds__(256) void k_modulated_layernorm(const float *__rest
 
 namespace ddit {
 
-template <int CHUNKS, int ROWS, bool STREAM>
-void launch_ln(const float *x, const float *tab, const float *c6, int which, int64_t N, int64_t tps, int D, float eps,
-               bf16_t *o, hipStream_t s) {
-  const unsigned lds = 2u * (unsigned)D * 4u;   // at most 32 KB
-  hipLaunchKernelGGL((k_modulated_layernorm<CHUNKS, ROWS, STREAM>), dim3((unsigned)((N + 4 * ROWS - 1) / (4 * ROWS))),
-                     dim3(256), lds, s, x, tab, c6, which, N, tps, D, eps, o);
+template <int CHUNKS, int ROWS, bool STREAM, bool SUM>
+void launch_ln(float *x, const float *tab, const float *c6, int which, int64_t N, int64_t tps, int D, float eps,
+               bf16_t *o, const PendingSum &pend, hipStream_t s) {
+  const unsigned lds = (SUM ? 3u : 2u) * (unsigned)D * 4u;   // at most 48 KB
+  hipLaunchKernelGGL((k_modulated_layernorm<CHUNKS, ROWS, STREAM, SUM>), dim3((unsigned)((N + 4 * ROWS - 1) / (4 * ROWS))),
+                     dim3(256), lds, s, x, tab, c6, which, N, tps, D, eps, o, pend);
 }
 template <int CHUNKS>
-void launch_ln(const float *x, const float *tab, const float *c6, int which, int64_t N, int64_t tps, int D, float eps,
-               bf16_t *o, hipStream_t s) {
+void launch_ln(float *x, const float *tab, const float *c6, int which, int64_t N, int64_t tps, int D, float eps,
+               bf16_t *o, const PendingSum *pend, hipStream_t s) {
   // A wavefront with a second row hides its latency behind the first one's reductions; below 8192 rows there are
   // not four wavefronts per SIMD and the second row only makes the launch longer.  D = 1152, 1 / 2 rows: 256 rows
   // 3.5 / 4.8 us, 2304 rows 5.6 / 6.2 us, 12960 rows 19.6 / 19.8 us, 48600 rows 53.1 / 50.1 us (6.7 TB/s).
   // A stream too large for the memory-side cache is read past the L2, which keeps other launches' weights.
-  if (N < 8192) launch_ln<CHUNKS, 1, false>(x, tab, c6, which, N, tps, D, eps, o, s);
-  else if (N * (int64_t)D <= (int64_t)24 << 20) launch_ln<CHUNKS, 2, false>(x, tab, c6, which, N, tps, D, eps, o, s);
-  else launch_ln<CHUNKS, 2, true>(x, tab, c6, which, N, tps, D, eps, o, s);
+  const PendingSum none = {0, nullptr, 0, nullptr, nullptr, 0};
+  if (pend && pend->parts > 0) launch_ln<CHUNKS, 1, false, true>(x, tab, c6, which, N, tps, D, eps, o, *pend, s);
+  else if (N < 8192) launch_ln<CHUNKS, 1, false, false>(x, tab, c6, which, N, tps, D, eps, o, none, s);
+  else if (N * (int64_t)D <= (int64_t)24 << 20) launch_ln<CHUNKS, 2, false, false>(x, tab, c6, which, N, tps, D, eps, o, none, s);
+  else launch_ln<CHUNKS, 2, true, false>(x, tab, c6, which, N, tps, D, eps, o, none, s);
 }
 
-int launch_modulated_layernorm(const float *x, const float *ada_table, const float *c6, int which, int64_t N,
-                               int64_t tokens_per_sample, int D, float eps, void *out, hipStream_t s) {
+int launch_modulated_layernorm(float *x, const float *ada_table, const float *c6, int which, int64_t N,
+                               int64_t tokens_per_sample, int D, float eps, void *out, hipStream_t s,
+                               const PendingSum *pending) {
   if (N == 0) return 0;
   bf16_t *o = reinterpret_cast<bf16_t *>(out);
-  if (D <= 256 * 2) launch_ln<2>(x, ada_table, c6, which, N, tokens_per_sample, D, eps, o, s);
-  else if (D <= 256 * 5) launch_ln<5>(x, ada_table, c6, which, N, tokens_per_sample, D, eps, o, s);
-  else if (D <= 256 * 16) launch_ln<16>(x, ada_table, c6, which, N, tokens_per_sample, D, eps, o, s);
+  if (D <= 256 * 2) launch_ln<2>(x, ada_table, c6, which, N, tokens_per_sample, D, eps, o, pending, s);
+  else if (D <= 256 * 5) launch_ln<5>(x, ada_table, c6, which, N, tokens_per_sample, D, eps, o, pending, s);
+  else if (D <= 256 * 16) launch_ln<16>(x, ada_table, c6, which, N, tokens_per_sample, D, eps, o, pending, s);
   else {
     set_error("D=%d: hidden size above 4096 is not supported by the LayerNorm kernel", D);
     return -2;

@@ -35,8 +35,16 @@ int hip_fail(hipError_t e, const char *what);
 int device_cus();   // compute units of the current device (cached per process; 256 if there is no device)
 
 // kernel launchers (each validates nothing: callers have validated shapes)
-int launch_modulated_layernorm(const float *x, const float *ada_table, const float *c6, int which, int64_t N,
-                               int64_t tokens_per_sample, int D, float eps, void *out, hipStream_t s);
+// A residual update that has been computed but not yet added: x += gate_b * sum of `parts` fp32 [N, D] arrays,
+// part_stride floats apart (the bias is in the first); gate_tab / gate_c6 as in GemmArgs.
+struct PendingSum {
+  int parts; const float *part; int64_t part_stride;   // parts == 0: nothing pending
+  const float *gate_tab, *gate_c6; int64_t gate_c6_stride;
+};
+// pending (may be null): added to x, which is written back, before the LayerNorm
+int launch_modulated_layernorm(float *x, const float *ada_table, const float *c6, int which, int64_t N,
+                               int64_t tokens_per_sample, int D, float eps, void *out, hipStream_t s,
+                               const PendingSum *pending = nullptr);
 
 struct GemmArgs {
   const void *u; int64_t ld_u;      // bf16 [N,k]
@@ -52,6 +60,10 @@ struct GemmArgs {
   int tile;                         // index into the tile list, or negative: the launcher's own choice
 };
 int launch_gemm(int epilogue, const GemmArgs &a, hipStream_t s);
+// The residual update as partial sums over parts of k, fp32 [N, n] each, for a later launch to add up.
+// In how many, at most max_parts (0: in one launch is cheaper), and with which tile; the launch.
+int gemm_partial_choice(int64_t N, int n, int k, int max_parts, int *tile_out);
+int launch_gemm_partial(const GemmArgs &a, int parts, int tile, float *out, int64_t part_stride, hipStream_t s);
 // G problems that share u (a.W, a.bias, a.out are ignored; a.n is one problem's out-features): 0 = launched,
 // 1 = this shape cannot be grouped (nothing launched: launch them one by one), negative = error
 int launch_gemm_grouped(const GemmArgs &a, int G, const void *const *W, const void *const *bias, void *const *out,
@@ -96,6 +108,9 @@ int launch_qk_norm_rope(void *qk, int64_t ld, int64_t N, int slots, int q_slots,
 
 int launch_cast_bf16_to_f32(const void *in, float *out, int64_t n, hipStream_t s);
 int launch_cast_f32_to_bf16(const float *in, void *out, int64_t n, hipStream_t s);
+// out = bf16(x + pending), x left as it is
+int launch_cast_sum_to_bf16(const float *x, const PendingSum &pending, void *out, int64_t N, int64_t tokens_per_sample, int D,
+                            hipStream_t s);
 struct CondArgs {
   int B, D;
   float t[64];

@@ -78,6 +78,7 @@ struct Dims {
 
 struct Layout {
   size_t x, xh, qkv, o, kvc, h, c6, cond, rope, taps, total;
+  int fc2_parts, fc2_tile;   // partial sums fc2 comes in (0: it adds to x itself) and their tile
   size_t tap_off[2][DDIT_TAP_COUNT], tap_bytes[DDIT_TAP_COUNT];
 };
 
@@ -130,6 +131,20 @@ void make_layout(const Dims &d, uint32_t flags, Layout *lo) {
   lo->c6 = take((size_t)d.B * 6 * d.D * 4);
   lo->cond = take((size_t)d.B * (256 + 2 * d.D) * 4);
   lo->rope = (flags & DDIT_FLAG_ROPE_TEMPORAL) ? take((size_t)d.T * d.dh * 4) : 0;
+  // fc2 in partial sums: they lie from qkv on, room for two where A == D.  Where a third one is worth having (small
+  // N only, 8 MB at most) the regions behind make way, unless the shape then outgrew the built-in scratch.
+  const size_t part = (size_t)d.N * d.D * 4, room = lo->kvc - lo->qkv;
+  lo->fc2_parts = (flags & DDIT_FLAG_TAPS) ? 0 : gemm_partial_choice(d.N, (int)d.D, (int)d.M, 3, &lo->fc2_tile);
+  if (lo->fc2_parts * part > room) {
+    const size_t more = align_up(lo->fc2_parts * part - room);
+    if (off <= STATIC_SCRATCH_BYTES && off + more > STATIC_SCRATCH_BYTES) {
+      lo->fc2_parts = gemm_partial_choice(d.N, (int)d.D, (int)d.M, (int)(room / part), &lo->fc2_tile);
+    } else {
+      for (size_t *region : {&lo->kvc, &lo->h, &lo->c6, &lo->cond}) *region += more;
+      if (lo->rope) lo->rope += more;
+      off += more;
+    }
+  }
   lo->taps = off;
   const size_t ND = (size_t)d.N * d.D, NA = (size_t)d.N * d.A;
   const size_t tb[DDIT_TAP_COUNT] = {ND * 2, 3 * NA * 2, NA * 2, ND * 4, NA * 2, (size_t)d.B * d.Ly * 2 * d.A * 2,
@@ -258,10 +273,12 @@ struct Taps {
 #define DDIT_TRY(expr) do { int rc_ = (expr); if (rc_ != DDIT_OK) return rc_; } while (0)
 
 // One layer on the fp32 stream x (in the workspace).
+// pending: a residual update of the layer before that has not been added to x yet (parts == 0: none); the layer
+// adds it and may leave its own last one
 // kvc_cached: this layer's cross-attention k|v [B*Ly, 2A] formed earlier, or null (then y is projected here)
 int run_layer(ddit_attn_kind kind, const Dims &d, const ddit_layer_weights &w, const void *y, const void *kvc_cached,
               const int32_t *valid_len, const float *c6, float eps, uint32_t flags, unsigned char *ws,
-              const Layout &lo, const Taps &tp, hipStream_t s) {
+              const Layout &lo, const Taps &tp, hipStream_t s, PendingSum *pending) {
   float *x = reinterpret_cast<float *>(ws + lo.x);
   void *xh = ws + lo.xh;
   unsigned char *qkv = ws + lo.qkv;
@@ -281,7 +298,8 @@ int run_layer(ddit_attn_kind kind, const Dims &d, const ddit_layer_weights &w, c
   };
 
   // self-attention branch
-  DDIT_TRY(launch_modulated_layernorm(x, w.ada_table, c6, 0, N, d.L, (int)D, eps, xh, s));
+  DDIT_TRY(launch_modulated_layernorm(x, w.ada_table, c6, 0, N, d.L, (int)D, eps, xh, s, pending));
+  pending->parts = 0;
   DDIT_TRY(tp.keep(DDIT_TAP_XH_MSA, xh));
   base(xh, D, w.w_qkv, w.b_qkv, N, (int)(3 * A), (int)D); g.out = qkv; g.ld_out = 3 * A;
   DDIT_TRY(launch_gemm(DDIT_EPI_BF16, g, s));
@@ -331,9 +349,22 @@ int run_layer(ddit_attn_kind kind, const Dims &d, const ddit_layer_weights &w, c
   DDIT_TRY(launch_gemm(DDIT_EPI_GELU_BF16, g, s));
   DDIT_TRY(tp.keep(DDIT_TAP_H, h));
   base(h, M, w.w_fc2, w.b_fc2, N, (int)D, (int)M); gated(5);
-  DDIT_TRY(launch_gemm(DDIT_EPI_RESIDUAL_F32, g, s));
+  // Where it is cheaper in parts the next layer's first LayerNorm adds them up; until then they lie where q|k|v
+  // and o were.
+  if (lo.fc2_parts > 0) {
+    *pending = PendingSum{lo.fc2_parts, reinterpret_cast<const float *>(qkv), N * D, g.gate_tab, g.gate_c6, g.gate_c6_stride};
+    DDIT_TRY(launch_gemm_partial(g, lo.fc2_parts, lo.fc2_tile, reinterpret_cast<float *>(qkv), N * D, s));
+  } else {
+    DDIT_TRY(launch_gemm(DDIT_EPI_RESIDUAL_F32, g, s));
+  }
   DDIT_TRY(tp.keep(DDIT_TAP_X_OUT, x));
   return DDIT_OK;
+}
+
+// The stream after the last layer, rounded to bf16
+int finish_stream(const Dims &d, const float *x, const PendingSum &pending, void *x_out, hipStream_t s) {
+  if (pending.parts > 0) return launch_cast_sum_to_bf16(x, pending, x_out, d.N, d.L, (int)d.D, s);
+  return launch_cast_f32_to_bf16(x, x_out, d.N * d.D, s);
 }
 
 // Text k|v projections of all 2 * n_blocks layers: y [B*Ly, D] against every layer's w_ckv, layer l's result at
@@ -520,13 +551,14 @@ int ddit_stdit_block_fwd(const ddit_shape *shape, const ddit_block_weights *weig
   unsigned char *ws = reinterpret_cast<unsigned char *>(workspace);
   float *x = reinterpret_cast<float *>(ws + lo.x);
   Taps tp{(shape->flags & DDIT_FLAG_TAPS) != 0, ws, &lo, 0, s};
+  PendingSum pending = {0, nullptr, 0, nullptr, nullptr, 0};
   DDIT_TRY(launch_cast_bf16_to_f32(x_in, x, d.N * d.D, s));
   if (shape->flags & DDIT_FLAG_ROPE_TEMPORAL)
     DDIT_TRY(launch_rope_table(reinterpret_cast<float *>(ws + lo.rope), (int)d.T, (int)d.dh, s));
-  DDIT_TRY(run_layer(DDIT_ATTN_SPATIAL, d, weights->spatial, y, nullptr, y_valid_len_host, c6, shape->ln_eps, shape->flags, ws, lo, tp, s));
+  DDIT_TRY(run_layer(DDIT_ATTN_SPATIAL, d, weights->spatial, y, nullptr, y_valid_len_host, c6, shape->ln_eps, shape->flags, ws, lo, tp, s, &pending));
   tp.layer = 1;
-  DDIT_TRY(run_layer(DDIT_ATTN_TEMPORAL, d, weights->temporal, y, nullptr, y_valid_len_host, c6, shape->ln_eps, shape->flags, ws, lo, tp, s));
-  return launch_cast_f32_to_bf16(x, x_out, d.N * d.D, s);
+  DDIT_TRY(run_layer(DDIT_ATTN_TEMPORAL, d, weights->temporal, y, nullptr, y_valid_len_host, c6, shape->ln_eps, shape->flags, ws, lo, tp, s, &pending));
+  return finish_stream(d, x, pending, x_out, s);
 }
 
 int ddit_stdit_block_fwd_static(const ddit_shape *shape, const ddit_block_weights *weights, const void *x_in,
@@ -632,6 +664,7 @@ int ddit_denoise_step_cached(const ddit_shape *shape, const ddit_step_weights *w
   DDIT_TRY(ddit_timestep_conditioning(shape, weights, timesteps_host, temb_or_null, c6,
                                       reinterpret_cast<float *>(ws + lo.cond), hip_stream));
   Taps tp{(shape->flags & DDIT_FLAG_TAPS) != 0, ws, &lo, 0, s};
+  PendingSum pending = {0, nullptr, 0, nullptr, nullptr, 0};
   DDIT_TRY(launch_cast_bf16_to_f32(x_in, x, d.N * d.D, s));
   if (shape->flags & DDIT_FLAG_ROPE_TEMPORAL)
     DDIT_TRY(launch_rope_table(reinterpret_cast<float *>(ws + lo.rope), (int)d.T, (int)d.dh, s));
@@ -648,12 +681,12 @@ int ddit_denoise_step_cached(const ddit_shape *shape, const ddit_step_weights *w
   for (int i = 0; i < shape->n_blocks; ++i) {
     tp.layer = 0;
     DDIT_TRY(run_layer(DDIT_ATTN_SPATIAL, d, weights->blocks[i].spatial, y, kv ? kv + (size_t)(2 * i) * kv_layer : nullptr,
-                       y_valid_len_host, c6, shape->ln_eps, shape->flags, ws, lo, tp, s));
+                       y_valid_len_host, c6, shape->ln_eps, shape->flags, ws, lo, tp, s, &pending));
     tp.layer = 1;
     DDIT_TRY(run_layer(DDIT_ATTN_TEMPORAL, d, weights->blocks[i].temporal, y,
-                       kv ? kv + (size_t)(2 * i + 1) * kv_layer : nullptr, y_valid_len_host, c6, shape->ln_eps, shape->flags, ws, lo, tp, s));
+                       kv ? kv + (size_t)(2 * i + 1) * kv_layer : nullptr, y_valid_len_host, c6, shape->ln_eps, shape->flags, ws, lo, tp, s, &pending));
   }
-  return launch_cast_f32_to_bf16(x, x_out, d.N * d.D, s);
+  return finish_stream(d, x, pending, x_out, s);
 }
 
 int ddit_modulated_layernorm_fwd(const float *x, const float *ada_table, const float *c6, int which,
@@ -669,7 +702,7 @@ int ddit_modulated_layernorm_fwd(const float *x, const float *ada_table, const f
   if (!aligned16(x) || !aligned16(ada_table) || !aligned16(c6) || !aligned16(out)) {
     set_error("pointers must be 16-byte aligned"); return DDIT_ERR_ALIGNMENT;
   }
-  return launch_modulated_layernorm(x, ada_table, c6, which, N, tokens_per_sample, D, eps, out,
+  return launch_modulated_layernorm(const_cast<float *>(x), ada_table, c6, which, N, tokens_per_sample, D, eps, out,
                                     reinterpret_cast<hipStream_t>(hip_stream));
 }
 

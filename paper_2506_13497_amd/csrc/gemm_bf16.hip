@@ -44,6 +44,7 @@
 // also storing bf16(x).
 #include "ddit_common.hpp"
 
+#include <string.h>
 #include <cmath>
 #include <type_traits>
 
@@ -64,6 +65,7 @@ struct GemmParams {
   const float *gate_c6; int64_t gate_c6_stride;
   int64_t tokens_per_sample;
   int tiles_m; int tiles_n; int group_w; int total_tiles; int rounds;
+  int split_steps; int split_tiles; int64_t split_stride;   // partial sums (EPI 3): k-steps and output tiles of one part, floats between parts
   int x_stays; // the residual stream fits the memory-side cache beside what else the step touches
   int plain;   // row strides below 2^26 elements: a row group's offsets fit 32 bits
 };
@@ -231,6 +233,7 @@ __device__ __forceinline__ void *uniform_ptr(const void *q) {
 struct TileOut {
   int64_t row0; int col0;      // first token, first out-feature
   bf16_t *out; int shift;      // output of the tile's problem; its first out-feature
+  float *part;                 // partial sums: where this part's fp32 rows go
   unsigned smp0;               // sample of the first token ...
   bool one_sample;             // ... and of all of them
 };
@@ -274,7 +277,7 @@ __device__ __forceinline__ void gemm_epilogue_as(floatx16 (&acc)[TN][TM], unsign
   const int l32 = lane & 31, lh = lane >> 5;
   const int64_t row_w = to.row0 + wm * (TM * 32);   // the wavefront's first token and out-feature
   const int col_w = to.col0 + wn * (TN * 32);
-  if constexpr (EPI != 2) {
+  if constexpr (EPI < 2) {
     // rows of AG * 64 bytes: the whole width of the wavefront where it owns all of it, else one MFMA tile
     constexpr int AG = (T0 == 0 && T1 == TM * TN) ? TN : 1;
     constexpr int PITCH = C::bf16_pitch(AG), CPR = AG * 4, ITERS = AG * 2;
@@ -331,11 +334,12 @@ __device__ __forceinline__ void gemm_epilogue_as(floatx16 (&acc)[TN][TM], unsign
     // stream is read and written in whole lines.  The reads of x run DEPTH tiles ahead of their use: memory
     // requests complete in order, loads and stores alike, so a tile's loads are issued BEFORE the stores of
     // the tiles processed while they are in flight, and waiting for them never waits for a store.
-    constexpr bool EARLY = C::X_EARLY;
-    constexpr int DEPTH = EARLY ? T1 - T0 : !FULL ? 1 : (T1 - T0 < 3 ? T1 - T0 : 3);
+    // Partial sums (EPI 3) leave the same way, fp32 rows as they are, with no stream to read.
+    constexpr bool EARLY = EPI == 2 && C::X_EARLY;
+    constexpr int DEPTH = EPI == 3 ? 1 : EARLY ? T1 - T0 : !FULL ? 1 : (T1 - T0 < 3 ? T1 - T0 : 3);
     int r8 = lane >> 3, f4 = (lane & 7) * 4;
     // this wavefront's corner of the stream and of its bf16 copy, and this lane's place in a group of 8 rows
-    unsigned char *const x0 = reinterpret_cast<unsigned char *>(uniform_ptr(p.resid + row_w * p.n + col_w));
+    unsigned char *const x0 = reinterpret_cast<unsigned char *>(uniform_ptr((EPI == 3 ? to.part : p.resid) + row_w * p.n + col_w));
     unsigned char *const o0 = reinterpret_cast<unsigned char *>(uniform_ptr(p.out + (p.out ? row_w * p.ld_out + col_w : 0)));
     const unsigned lane_x = (unsigned)(r8 * p.n + f4) * 4u, lane_o = ((unsigned)r8 * (unsigned)p.ld_out + f4) * 2u;
     float4 xr[DEPTH][4];
@@ -366,7 +370,7 @@ __device__ __forceinline__ void gemm_epilogue_as(floatx16 (&acc)[TN][TM], unsign
         for (int i = 0; i < 4; ++i) xr[d][i] = early.x[d][i];
 #pragma unroll
       for (int a = 0; a < TN; ++a) gate[a] = early.gate[a];
-    } else if constexpr (FULL) {
+    } else if constexpr (FULL && EPI == 2) {
 #pragma unroll
       for (int d = 0; d < DEPTH; ++d) issue_x(T0 + d, d);
 #pragma unroll
@@ -375,7 +379,7 @@ __device__ __forceinline__ void gemm_epilogue_as(floatx16 (&acc)[TN][TM], unsign
 #pragma unroll
     for (int t = T0; t < T1; ++t) {
       const int b = t / TN, a = t - b * TN, slot = (t - T0) % DEPTH;
-      if constexpr (!FULL && !EARLY) issue_x(t, slot);
+      if constexpr (!FULL && !EARLY && EPI == 2) issue_x(t, slot);
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         floatx4 v;
@@ -400,7 +404,19 @@ __device__ __forceinline__ void gemm_epilogue_as(floatx16 (&acc)[TN][TM], unsign
         for (int e = 0; e < 4; ++e) o[e] = (bf16_t)r[e];
         return o;
       };
-      if constexpr (FULL) {
+      if constexpr (EPI == 3) {
+        // the next launch reads them: plain stores
+        if constexpr (!FULL) asm volatile("" : "+v"(r8), "+v"(f4));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int64_t tok = row_w + b * 32 + 8 * i + r8;
+          const int f = col_w + a * 32 + f4;
+          if constexpr (FULL)
+            *reinterpret_cast<uintx4 *>(x0 + ((int64_t)(b * 32 + 8 * i) * p.n + a * 32) * 4 + lane_x) = piece[i];
+          else if (tok < p.N && f < p.n)
+            *reinterpret_cast<uintx4 *>(to.part + tok * p.n + f) = piece[i];
+        }
+      } else if constexpr (FULL) {
         floatx4 r[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -429,7 +445,7 @@ __device__ __forceinline__ void gemm_epilogue_as(floatx16 (&acc)[TN][TM], unsign
         }
       }
       __builtin_amdgcn_sched_barrier(0);
-      if constexpr (FULL && !EARLY) {
+      if constexpr (FULL && !EARLY && EPI == 2) {
         if (t + DEPTH < T1) issue_x(t + DEPTH, slot);
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -457,7 +473,7 @@ template <int WGM, int WGN, int WGK, int TM, int TN, int NS, int EPI, class GT>
 __global__ __launch_bounds__(WGM *WGN *WGK * 64, 2) void k_gemm_bf16(GemmParams p, GT gt) {
   using C = GemmCfg<WGM, WGN, WGK, TM, TN, NS>;
   constexpr bool GROUPED = !std::is_same<GT, NoGroups>::value;
-  static_assert(!GROUPED || EPI != 2, "grouped launches write bf16 outputs");
+  static_assert(!GROUPED || EPI < 2, "grouped launches write bf16 outputs");
   constexpr int BM = C::BM, BN = C::BN, STAGE = C::STAGE, NW = C::NW, NJ = C::NJ, NJU = C::NJU, SUBS = C::SUBS;
   constexpr int NFRAG = TM + TN, NMFMA = TM * TN, DEFER = C::DEFER;
   // a k-step's loads are issued in two parts: after the barrier that frees their stage, and under the
@@ -472,7 +488,9 @@ __global__ __launch_bounds__(WGM *WGN *WGK * 64, 2) void k_gemm_bf16(GemmParams 
   const int wt = wave - wk * (WGM * WGN);
   const int wm = wt / WGN, wn = wt - wm * WGN;
   const int l32 = lane & 31, lh = lane >> 5;
-  const int nk = (p.k + BK - 1) / BK > C::MIN_STEPS ? (p.k + BK - 1) / BK : C::MIN_STEPS;
+  // k-steps of a tile: all of k, or (partial sums) one part of it
+  const int nk_all = EPI == 3 ? p.split_steps : (p.k + BK - 1) / BK;
+  const int nk = nk_all > C::MIN_STEPS ? nk_all : C::MIN_STEPS;
 
   // fragment reads: row (tile*32 + l32) of 128 B, chunk 2 sub + lh at slot chunk ^ ((row >> 1) & 7)
   const int frag_u = (wm * (TM * 32) + l32) * ROW;
@@ -493,6 +511,7 @@ __global__ __launch_bounds__(WGM *WGN *WGK * 64, 2) void k_gemm_bf16(GemmParams 
   // and the counts of outstanding loads stay the same.
   int ld_round = 0, ld_k = 0;           // the next k-step to fetch
   const bf16_t *ld_u = p.u, *ld_W = p.W;   // operands of its tile: first row ...
+  int ld_k0 = 0, ld_kend = p.k;         // partial sums: first k-step and end of its part of k
   int64_t tot_u = 0, tot_w = 0;         // ... and bytes from there to the matrix's last element (below 2^32)
   const int64_t du = (int64_t)p.ld_u * (NW * 16), dw = (int64_t)p.k * (NW * 16);   // bytes between a wave's loads
 
@@ -500,6 +519,13 @@ __global__ __launch_bounds__(WGM *WGN *WGK * 64, 2) void k_gemm_bf16(GemmParams 
   // else, so it has landed when k-step 0 has).
   auto ld_tile = [&](int tile) {
     if (tile < 0) { tot_u = tot_w = 0; return; }
+    int part = 0;
+    if constexpr (EPI == 3) {
+      part = tile / p.split_tiles;
+      tile -= part * p.split_tiles;
+      ld_k0 = part * p.split_steps;
+      ld_kend = ld_k0 * BK + p.split_steps * BK < p.k ? ld_k0 * BK + p.split_steps * BK : p.k;
+    }
     int tm, tn;
     decode_tile(p, tile, tm, tn);
     const int64_t row0 = (int64_t)tm * BM;
@@ -525,8 +551,8 @@ __global__ __launch_bounds__(WGM *WGN *WGK * 64, 2) void k_gemm_bf16(GemmParams 
   // starts at its eight rows
   auto ld_issue = [&](auto j0_tag, auto j1_tag, int st) {
     constexpr int J0 = decltype(j0_tag)::value, J1 = decltype(j1_tag)::value;
-    const int k0 = __builtin_amdgcn_readfirstlane(ld_k * (BK * 2));     // bytes
-    const bool in = ld_k * BK + ld_chunk * 8 < p.k;   // past the row's end: fetch nothing, write zeros
+    const int k0 = __builtin_amdgcn_readfirstlane((ld_k0 + ld_k) * (BK * 2));     // bytes
+    const bool in = (ld_k0 + ld_k) * BK + ld_chunk * 8 < ld_kend;   // past the row's end: fetch nothing, write zeros
     const unsigned vu = in ? voff_u : 0xfffffff0u, vw = in ? voff_w : 0xfffffff0u;
 #pragma unroll
     for (int j = J0; j < J1; ++j) {
@@ -582,9 +608,11 @@ __global__ __launch_bounds__(WGM *WGN *WGK * 64, 2) void k_gemm_bf16(GemmParams 
 
   int st = 0;                 // stage of the k-step being multiplied
   for (int round = 0;; ++round) {
-    int tile_m, tile_n;
+    int tile_m, tile_n, part = 0;
+    if constexpr (EPI == 3) { part = tile / p.split_tiles; tile -= part * p.split_tiles; }
     decode_tile(p, tile, tile_m, tile_n);
     TileOut to;
+    to.part = EPI == 3 ? p.resid + part * p.split_stride : nullptr;
     to.row0 = (int64_t)tile_m * BM; to.col0 = tile_n * BN; to.out = p.out; to.shift = 0;
     to.smp0 = 0; to.one_sample = true;
     XRows<C::OWN, TN> early;
@@ -629,7 +657,7 @@ __global__ __launch_bounds__(WGM *WGN *WGK * 64, 2) void k_gemm_bf16(GemmParams 
         uint2 bq[4];
 #pragma unroll
         for (int g = 0; g < 4; ++g) bq[g] = make_uint2(0u, 0u);
-        if (bias && wk == 0) lds_read4_b64(bq, bias_lds + (round % BIAS_SLOTS) * (BN * 2) + a * 64);
+        if (bias && wk == 0 && part == 0) lds_read4_b64(bq, bias_lds + (round % BIAS_SLOTS) * (BN * 2) + a * 64);
 #pragma unroll
         for (int b = 0; b < TM; ++b)
 #pragma unroll
@@ -775,6 +803,11 @@ int launch_one(const GemmParams &p0, hipStream_t s, const GT &gt = GT()) {
     return -2;
   }
   p.total_tiles = (int)total;
+  const int nk = (p.k + BK - 1) / BK;
+  if (EPI == 3) {
+    p.split_tiles = p.total_tiles;
+    p.total_tiles *= (nk + p.split_steps - 1) / p.split_steps;
+  }
   // The next launches read x again: written plainly it is found in the 256 MB memory-side cache (6851 tokens:
   // step 1.6 % shorter, 12960 tokens: 2.4 %); where it does not fit there, a plain store only pushes operands
   // out of the L2 (48600 tokens: 1 % longer), and where it is small the launch ends with writing the L2 back.
@@ -784,8 +817,8 @@ int launch_one(const GemmParams &p0, hipStream_t s, const GT &gt = GT()) {
   // each XCD a contiguous run of tiles
   int grid = ddit::device_cus() & ~7;
   if (grid < 8) grid = 8;
-  if (total <= grid) grid = (int)((total + 7) & ~(int64_t)7);
-  p.rounds = (int)(((total + 7) / 8 + grid / 8 - 1) / (grid / 8));
+  if (p.total_tiles <= grid) grid = (p.total_tiles + 7) & ~7;
+  p.rounds = ((p.total_tiles + 7) / 8 + grid / 8 - 1) / (grid / 8);
   static bool attr_set = false;  // benign race: the attribute is idempotent
   if (!attr_set) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_bf16<WGM, WGN, WGK, TM, TN, NS, EPI, GT>),
@@ -833,6 +866,8 @@ constexpr TileModel TILES[N_TILES] = {
     {64, 64, 8, 8, 0.219f, {0.89f, 1.35f, 2.54f}, 0.069f, 0.39f},
 };
 constexpr float LAUNCH_US = 2.71f;
+constexpr int FIRST_PARTIAL_TILE = 3;   // tiles compiled for partial sums: this one and the smaller ones
+constexpr float PARTIAL_SUM_US = 6.4f, PARTIAL_SUM_US_PER_PART = 1.0f;   // what adding them up later costs
 
 float predicted_us(int tile, int epilogue, int64_t N, int n, int k, int cus) {
   const TileModel &t = TILES[tile];
@@ -940,6 +975,7 @@ int launch_gemm_grouped(const GemmArgs &a, int G, const void *const *W, const vo
   p.resid = nullptr; p.gate_tab = nullptr; p.gate_c6 = nullptr; p.gate_c6_stride = 0;
   p.tokens_per_sample = a.tokens_per_sample > 0 ? a.tokens_per_sample : 1;
   p.tiles_m = 0; p.tiles_n = 0; p.group_w = 1; p.total_tiles = 0; p.rounds = 0; p.x_stays = 0; p.plain = 0;
+  p.split_steps = p.split_tiles = 0; p.split_stride = 0;
   switch (tile) {
     case 0: return launch_grouped_tile<2, 4, 1, 3, 3, 2>(p, gt, s);
     case 1: return launch_grouped_tile<2, 4, 1, 4, 2, 2>(p, gt, s);
@@ -951,6 +987,62 @@ int launch_gemm_grouped(const GemmArgs &a, int G, const void *const *W, const vo
     case 7: return launch_grouped_tile<2, 2, 2, 1, 2, 6>(p, gt, s);
     default: return launch_grouped_tile<2, 2, 2, 1, 1, 8>(p, gt, s);
   }
+}
+
+// The residual update in two launches: `parts` partial products over equal parts of k, fp32 [N, n] each, which the
+// launch that reads the stream next sums up (launch_modulated_layernorm).  It pays where so few tokens make
+// small tiles or idle CUs: the parts are that many more tiles, larger ones with a shorter chain of k-steps each.
+// fc2 (1152 x 4608) of 2304 tokens: 216 tiles of 64 x 192 and 72 steps 46 us, two parts of 108 tiles of
+// 128 x 192 and 36 steps 33 us, and 7 us more in the LayerNorm; a layer in all, one launch / parts:
+// 200 tokens 103.4 / 97.2 us (3 parts), 288 111.0 / 107.0 (2), 1152 145.6 / 141.0 (3), 2048 189.3 / 182.8 (2),
+// 2304 200.1 / 194.3 (2); from 2720 on nothing.
+// Tiles and parts are priced with the linears' model, the parts side by side being so many more columns; what the
+// sum costs elsewhere fits 6.4 us + 1 us a part at 48 .. 3072 tokens x 1152 (standard error 1.9 us).  Beyond that
+// range its traffic counts and it is not tried.
+// A third part gains most below 2 M elements, and only there is the room for it small.
+int gemm_partial_choice(int64_t N, int n, int k, int max_parts, int *tile_out) {
+  const int cus = device_cus(), steps = (k + BK - 1) / BK;
+  const int most = N * (int64_t)n <= (int64_t)2 << 20 ? max_parts : N * (int64_t)n <= (int64_t)4 << 20 ? std::min(max_parts, 2) : 0;
+  float best = predicted_us(cheapest_tile(2, N, n, k, cus), 2, N, n, k, cus);
+  int chosen = 0;
+  for (int parts = 2; parts <= most && parts <= steps; ++parts) {
+    const int per = (steps + parts - 1) / parts;
+    for (int t = FIRST_PARTIAL_TILE; t < N_TILES; ++t) {
+      const int cols = (n + TILES[t].cols - 1) / TILES[t].cols * TILES[t].cols;
+      const float us = predicted_us(t, 0, N, parts * cols, per * BK, cus) + PARTIAL_SUM_US + PARTIAL_SUM_US_PER_PART * parts;
+      if (us < best) { best = us; chosen = parts; *tile_out = t; }
+    }
+  }
+  return chosen;
+}
+
+int launch_partial_tile(int tile, const GemmParams &p, hipStream_t s) {
+  switch (tile) {
+    case 3: return launch_checked<4, 2, 1, 2, 2, 3, 3>(tile, p, s);
+    case 4: return launch_checked<4, 2, 1, 1, 3, 3, 3>(tile, p, s);
+    case 5: return launch_checked<2, 2, 2, 2, 2, 4, 3>(tile, p, s);
+    case 6: return launch_checked<2, 2, 2, 1, 3, 4, 3>(tile, p, s);
+    case 7: return launch_checked<2, 2, 2, 1, 2, 6, 3>(tile, p, s);
+    case 8: return launch_checked<2, 2, 2, 1, 1, 8, 3>(tile, p, s);
+  }
+  set_error("linear: no partial sums with tile %d", tile);
+  return -1;
+}
+
+int launch_gemm_partial(const GemmArgs &a, int parts, int tile, float *out, int64_t part_stride, hipStream_t s) {
+  if (a.N == 0 || a.n == 0) return 0;
+  GemmParams p;
+  memset(&p, 0, sizeof(p));
+  p.u = reinterpret_cast<const bf16_t *>(a.u); p.ld_u = a.ld_u;
+  p.W = reinterpret_cast<const bf16_t *>(a.W);
+  p.bias = reinterpret_cast<const bf16_t *>(a.bias);
+  p.N = a.N; p.n = a.n; p.k = a.k;
+  p.resid = out;
+  p.tokens_per_sample = 1;
+  const int steps = (a.k + BK - 1) / BK;
+  p.split_steps = (steps + parts - 1) / parts;
+  p.split_stride = part_stride;
+  return launch_partial_tile(tile, p, s);
 }
 
 int launch_gemm(int epilogue, const GemmArgs &a, hipStream_t s) {
@@ -977,6 +1069,7 @@ int launch_gemm(int epilogue, const GemmArgs &a, hipStream_t s) {
   p.gate_tab = a.gate_tab; p.gate_c6 = a.gate_c6; p.gate_c6_stride = a.gate_c6_stride;
   p.tokens_per_sample = a.tokens_per_sample > 0 ? a.tokens_per_sample : 1;
   p.tiles_m = 0; p.tiles_n = 0; p.group_w = 1; p.total_tiles = 0; p.rounds = 0; p.x_stays = 0; p.plain = 0;
+  p.split_steps = p.split_tiles = 0; p.split_stride = 0;
   switch (epilogue) {
     case 0: return launch_epi<0>(a.tile, p, s);
     case 1: return launch_epi<1>(a.tile, p, s);

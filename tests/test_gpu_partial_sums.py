@@ -1,0 +1,40 @@
+"""fc2 in partial sums that the next LayerNorm, or the final cast, adds to the stream: a step of two blocks
+against the CPU oracle at token counts where it comes in three and in two parts, with rows that end inside a
+tile and samples that change inside a workgroup's rows, the gates of the update per sample, and a k whose
+last part is ragged.  (A step that keeps its taps adds in one launch: the other tests.)"""
+import numpy as np
+import pytest
+import torch
+
+import ddit_synth as syn
+from helpers import assert_parity, dev_to_f64, dict_dev, dict_f64, to_dev, to_f64
+from oracle import stdit_oracle as ora
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,T,Hp,Wp,D,H,dh,M", [
+    (1, 2, 3, 5, 1152, 16, 72, 4608),
+    (2, 3, 5, 11, 1152, 16, 72, 4616),    # 330 rows, 165 a sample
+    (3, 3, 7, 9, 1152, 4, 72, 4608),      # 567 rows; attention narrower than the stream
+    (2, 1, 23, 25, 1152, 16, 72, 4608),   # 1150 rows
+    (1, 1, 45, 46, 1152, 16, 72, 4608),   # 2070 rows
+    (1, 1, 5, 7, 1344, 21, 64, 5376),      # LayerNorm with more than five chunks a lane
+])
+def test_step_with_partial_sums(B, T, Hp, Wp, D, H, dh, M):
+    import paper_2506_13497_amd as m
+    sh = syn.Shape(B, T, Hp, Wp, D, H, dh, M, 20, 2)
+    sw = syn.make_step_weights(sh, 51)
+    blocks = [syn.make_block_weights(sh, 51, i, table_std=0.1) for i in range(2)]
+    act = syn.make_activations(sh, 51)
+    temb = syn.make_temb(sh, 51)
+    shape = m.make_shape(B, T, Hp, Wp, D, H, dh, M, 20, 2, 0)
+    ws = m.alloc_workspace(shape)
+    ws.fill_(0xFF)
+    dsw, dblocks = {k: to_dev(v) for k, v in sw.items()}, [dict_dev(b) for b in blocks]
+    x_out = torch.full((B, T, sh.S, D), float("nan"), dtype=torch.bfloat16, device="cuda")
+    m.ddit_denoise_step(shape, m.step_struct(dsw, dblocks), to_dev(act["x"]), to_dev(act["y"]), None, None, to_dev(temb), x_out, ws)
+    torch.cuda.synchronize()
+    ref = ora.denoise_step(to_f64(act["x"]), to_f64(act["y"]), None, None, dict_f64(sw), [dict_f64(b) for b in blocks],
+                           H, dh, temb=temb.astype(np.float64))
+    assert_parity(dev_to_f64(x_out), ref, "step with fc2 in partial sums")
