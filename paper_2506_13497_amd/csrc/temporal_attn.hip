@@ -8,13 +8,19 @@
 // of a location (16 heads) are dealt to the same XCD so that cache lines straddling two head
 // groups are served from its L2.
 //
-// Each wavefront then owns one head.  T <= 32 fits a single 32x32 matrix-core tile:
+// Short sequences are packed: a workgroup takes P neighbouring locations, R = P * T <= 32 rows (location-major), and
+// the scores between different locations are masked.  LDS holds the R rows and no padding, so three workgroups of
+// T = 30 fit a CU (1620 locations, 16 heads: 101 -> 95 us = 4.7 TB/s of q, k, v and O, bound by memory with rows
+// in pieces of 576 bytes; 3600 locations, 4 heads: 62 -> 52 us).
+//
+// Each wavefront then owns one head.  R <= 32 fits a single 32x32 matrix-core tile:
 // S^T = K Q^T (keys x queries; a lane owns one query, so the softmax is a register reduction
 // plus one lane exchange), P^T rounded to bf16 is the second operand of O^T = V^T P^T as it
 // stands, with V^T gathered from LDS in the key order the accumulator registers enumerate.
 // The head dim is padded with zeros in registers only.  O is staged in LDS (over Q, which is
 // dead by then) and written out as 16-byte chunks of whole rows.
 #include "ddit_common.hpp"
+#include <algorithm>
 
 namespace {
 
@@ -28,6 +34,9 @@ struct TemporalParams {
   int64_t ld_q, ld_kv, ld_o;
   int B, T, S, H;
   int n_hg;            // head groups per location
+  int P, R;            // locations per workgroup; rows R = P * T
+  int n_packs;         // workgroups a sample's locations take (a pack never holds two samples' locations)
+  float inv_T;         // r / T = (int)((r + 0.5) * inv_T) for r < 32
   float scale_log2;    // log2(e) / sqrt(dh)
   float scale;         // 1 / sqrt(dh)
   // optional treatment of q and k on their way in (OPTS form of the kernel):
@@ -41,7 +50,7 @@ struct TCfg {
   static constexpr int DCH = DH / 8;                 // 16-byte chunks per head row
   static constexpr int RCH = HG * DCH;               // chunks per LDS row (four heads)
   static constexpr int PITCH = RCH * 16 + 16;        // +16 B: 16 consecutive rows hit 16 different bank groups
-  static constexpr int MAT = TP * PITCH;             // one operand
+  static constexpr int OPT_BYTES = TP * (DH / 2) * 8 + 2 * DH * 4;   // OPTS: angles and scales
   static constexpr int KS = (DH + 15) / 16;          // k-steps of Q K^T
   static constexpr int DT = (DH + 31) / 32;          // 32-row tiles of V^T
   static_assert((PITCH / 16) % 2 == 1, "odd pitch in 16-byte units keeps the reads conflict-free");
@@ -51,13 +60,13 @@ __device__ __forceinline__ void wg_barrier() { asm volatile("s_waitcnt vmcnt(0) 
 
 // OPTS: q and k are RMS-normalised per head and rotated by their frame's angles after they have
 // landed in LDS (every sequence is loaded exactly once here, so this costs no memory traffic):
-// one thread per (operand, frame, head) row, two passes over its d_h elements, fp32 arithmetic,
+// one thread per (operand, row, head), two passes over its d_h elements, fp32 arithmetic,
 // one rounding back to bf16; scales and the (cos, sin) rows of the T frames sit in LDS beside the operands.
 template <int DH, bool OPTS>
-__global__ __launch_bounds__(256) void k_temporal_attn(TemporalParams p) {
+__global__ __launch_bounds__(256, 3) void k_temporal_attn(TemporalParams p) {
   using C = TCfg<DH>;
-  constexpr int OPT_BYTES = OPTS ? TP * (DH / 2) * 8 + 2 * DH * 4 : 0;
-  __shared__ __attribute__((aligned(16))) unsigned char smem[3 * C::MAT + OPT_BYTES];
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // Q, K, V: R rows each; OPTS: angles, scales
+  const int R = p.R, MAT = R * C::PITCH;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l32 = lane & 31, lh = lane >> 5;
 
@@ -65,14 +74,21 @@ __global__ __launch_bounds__(256) void k_temporal_attn(TemporalParams p) {
   const int xcd = blockIdx.x & 7;
   const int rest = blockIdx.x >> 3;
   const int hg = rest % p.n_hg;
-  const int64_t loc = (int64_t)(rest / p.n_hg) * 8 + xcd;     // b * S + s
-  if (loc >= (int64_t)p.B * p.S) return;
-  const int b = (int)(loc / p.S), s = (int)(loc - (int64_t)b * p.S);
+  const int64_t pack = (int64_t)(rest / p.n_hg) * 8 + xcd;
+  if (pack >= (int64_t)p.B * p.n_packs) return;
+  const int b = (int)(pack / p.n_packs), s0 = (int)(pack - (int64_t)b * p.n_packs) * p.P;   // first location
   const int h0 = hg * HG;
   const int nh = p.H - h0 < HG ? p.H - h0 : HG;               // heads of this group that exist
-  const int64_t tok0 = (int64_t)b * p.T * p.S + s;            // token of frame 0; frame t is t*S further
+  const int64_t tok0 = (int64_t)b * p.T * p.S + s0;           // token of row 0
+  const int n_loc = p.S - s0 < p.P ? p.S - s0 : p.P;          // locations of this pack that exist
+  const int rows = n_loc * p.T;
+  auto loc_of = [&](int r) { return (int)(((float)r + 0.5f) * p.inv_T); };
+  auto row_token = [&](int r) {                               // row r = (location r / T, frame r % T)
+    const int j = loc_of(r);
+    return tok0 + j + (int64_t)(r - j * p.T) * p.S;
+  };
 
-  // ---- operands -> LDS: rows t < T, the chunks of the existing heads; V rows T..31 are zeroed.
+  // ---- operands -> LDS: the chunks of the existing locations and heads, zeros in the other rows.
   // All of a thread's loads are issued before the first one is used.
   {
     constexpr int NCH = (3 * TP * C::RCH + 255) / 256;
@@ -80,14 +96,16 @@ __global__ __launch_bounds__(256) void k_temporal_attn(TemporalParams p) {
     int dst[NCH];
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
+      dst[i] = -1;
+      if (256 * i >= 3 * R * C::RCH) continue;
       const int m = tid + 256 * i;
-      const int rr = m / C::RCH, ch = m - rr * C::RCH;           // rr = operand * T + frame
-      const int mat = (rr >= p.T) + (rr >= 2 * p.T);
-      const int r = rr - mat * p.T;
-      dst[i] = rr < 3 * p.T ? mat * C::MAT + r * C::PITCH + ch * 16 : -1;
+      const int rr = m / C::RCH, ch = m - rr * C::RCH;           // rr = operand * R + row
+      const int mat = (rr >= R) + (rr >= 2 * R);
+      const int r = rr - mat * R;
+      if (rr < 3 * R) dst[i] = rr * C::PITCH + ch * 16;
       val[i] = make_uint4(0u, 0u, 0u, 0u);
-      if (rr < 3 * p.T && ch < nh * C::DCH) {
-        const int64_t tok = tok0 + (int64_t)r * p.S;
+      if (rr < 3 * R && r < rows && ch < nh * C::DCH) {
+        const int64_t tok = row_token(r);
         const bf16_t *src = mat == 0 ? p.q + tok * p.ld_q : (mat == 1 ? p.k + tok * p.ld_kv : p.v + tok * p.ld_kv);
         val[i] = *reinterpret_cast<const uint4 *>(src + h0 * DH + ch * 8);
       }
@@ -95,23 +113,18 @@ __global__ __launch_bounds__(256) void k_temporal_attn(TemporalParams p) {
 #pragma unroll
     for (int i = 0; i < NCH; ++i)
       if (dst[i] >= 0) *reinterpret_cast<uint4 *>(smem + dst[i]) = val[i];
-    const int pad_rows = TP - p.T;
-    for (int m = tid; m < pad_rows * C::RCH; m += 256) {
-      const int r = p.T + m / C::RCH, ch = m % C::RCH;
-      *reinterpret_cast<uint4 *>(smem + 2 * C::MAT + r * C::PITCH + ch * 16) = make_uint4(0u, 0u, 0u, 0u);
-    }
   }
   if constexpr (OPTS) {
-    float2 *tab = reinterpret_cast<float2 *>(smem + 3 * C::MAT);
-    float *gs = reinterpret_cast<float *>(smem + 3 * C::MAT + TP * (DH / 2) * 8);
+    float2 *tab = reinterpret_cast<float2 *>(smem + 3 * MAT);
+    float *gs = reinterpret_cast<float *>(smem + 3 * MAT + TP * (DH / 2) * 8);
     if (p.rope)
       for (int m = tid; m < p.T * (DH / 2); m += 256) tab[m] = p.rope[m];
     if (tid < 2 * DH) gs[tid] = p.g_q ? (float)(tid < DH ? p.g_q[tid] : p.g_k[tid - DH]) : 1.0f;
     wg_barrier();
-    // row (operand, frame, head) -> thread; T <= 32 and four heads: at most 256 rows
+    // (operand, row, head) -> thread; R <= 32 and four heads: at most 256
     const int hh = tid & 3, r = (tid >> 2) % TP, mat = tid / (4 * TP);
-    if (mat < 2 && r < p.T && hh < nh) {
-      unsigned char *row = smem + mat * C::MAT + r * C::PITCH + hh * (DH * 2);
+    if (mat < 2 && r < rows && hh < nh) {
+      unsigned char *row = smem + mat * MAT + r * C::PITCH + hh * (DH * 2);
       float rinv = 1.0f;
       if (p.g_q) {
         float ss = 0.f;
@@ -124,7 +137,7 @@ __global__ __launch_bounds__(256) void k_temporal_attn(TemporalParams p) {
         rinv = rsqrtf(ss * (1.0f / DH) + p.norm_eps);
       }
       const float *g = gs + mat * DH;
-      const float2 *cs = tab + r * (DH / 2);
+      const float2 *cs = tab + (r - loc_of(r) * p.T) * (DH / 2);
 #pragma unroll
       for (int c = 0; c < C::DCH; ++c) {
         bf16x8 v = *reinterpret_cast<const bf16x8 *>(row + c * 16);
@@ -152,10 +165,11 @@ __global__ __launch_bounds__(256) void k_temporal_attn(TemporalParams p) {
   floatx16 oacc[C::DT];
   float m_q = 0.f, l_q = 1.f;
   if (wave < nh) {
-    // ---- S^T = K Q^T: lane holds key/query l32, d = 16 ks + 8 lh .. +7 (zeros past DH; rows >= T clamp)
-    const int row = l32 < p.T ? l32 : p.T - 1;
+    // ---- S^T = K Q^T: lane holds key/query l32, d = 16 ks + 8 lh .. +7 (zeros past DH; rows >= R clamp)
+    const int row = l32 < R ? l32 : R - 1;
     const unsigned char *qrow = smem + row * C::PITCH + wave * (DH * 2);
-    const unsigned char *krow = qrow + C::MAT;
+    const unsigned char *krow = qrow + MAT;
+    const int first = loc_of(row) * p.T;      // the keys of this lane's query: first .. first + T - 1
     floatx16 sc;
 #pragma unroll
     for (int e = 0; e < 16; ++e) sc[e] = 0.f;
@@ -176,7 +190,7 @@ __global__ __launch_bounds__(256) void k_temporal_attn(TemporalParams p) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int key = 8 * (r >> 2) + 4 * lh + (r & 3);
-      if (key >= p.T) sc[r] = -INFINITY;
+      if ((unsigned)(key - first) >= (unsigned)p.T) sc[r] = -INFINITY;
       mx = fmaxf(mx, sc[r]);
     }
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
@@ -195,29 +209,52 @@ __global__ __launch_bounds__(256) void k_temporal_attn(TemporalParams p) {
 
     // ---- O^T = V^T P^T: first operand V^T[d = 32 dt + l32][key]; contraction index (kc, lh, j)
     // stands for key 16 kc + 8 (j >> 2) + 4 lh + (j & 3), the order of the accumulator registers
-    const unsigned char *vcol = smem + 2 * C::MAT + wave * (DH * 2);
+    const unsigned char *vcol = smem + 2 * MAT + wave * (DH * 2);
+    auto pv = [&](floatx16 (&acc)[C::DT], int key0, int key1) {   // keys key0 .. key1 - 1
 #pragma unroll
-    for (int dt = 0; dt < C::DT; ++dt) {
+      for (int dt = 0; dt < C::DT; ++dt) {
 #pragma unroll
-      for (int e = 0; e < 16; ++e) oacc[dt][e] = 0.f;
-      const int d = 32 * dt + l32;
+        for (int e = 0; e < 16; ++e) acc[dt][e] = 0.f;
+        const int d = 32 * dt + l32;
 #pragma unroll
-      for (int kc = 0; kc < 2; ++kc) {
-        bf16x8 vf;
+        for (int kc = 0; kc < 2; ++kc) {
+          bf16x8 vf;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const int key = 16 * kc + 8 * (j >> 2) + 4 * lh + (j & 3);
-          uint16_t bits = 0;
-          if (d < DH) bits = *reinterpret_cast<const uint16_t *>(vcol + key * C::PITCH + d * 2);
-          vf[j] = __builtin_bit_cast(bf16_t, bits);
+          for (int j = 0; j < 8; ++j) {
+            const int key = 16 * kc + 8 * (j >> 2) + 4 * lh + (j & 3);
+            uint16_t bits = 0;
+            if (d < DH && key >= key0 && key < key1) bits = *reinterpret_cast<const uint16_t *>(vcol + key * C::PITCH + d * 2);
+            vf[j] = __builtin_bit_cast(bf16_t, bits);
+          }
+          acc[dt] = mfma32(vf, pf[kc], acc[dt]);
         }
-        oacc[dt] = mfma32(vf, pf[kc], oacc[dt]);
+      }
+    };
+    pv(oacc, 0, R);
+    if (p.P > 1) {
+      // A probability of zero times another location's infinity or NaN is a NaN that does not belong here: where a
+      // result is not finite, the locations are multiplied one by one.
+      bool finite = true;
+#pragma unroll
+      for (int dt = 0; dt < C::DT; ++dt)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) finite = finite && __builtin_fabsf(oacc[dt][e]) < INFINITY;
+      if (__builtin_amdgcn_ballot_w64(!finite) != 0) {
+#pragma unroll 1
+        for (int j = 0; j < p.P; ++j) {
+          floatx16 one[C::DT];
+          pv(one, j * p.T, (j + 1) * p.T);
+          if (first == j * p.T) {
+#pragma unroll
+            for (int dt = 0; dt < C::DT; ++dt) oacc[dt] = one[dt];
+          }
+        }
       }
     }
   }
   wg_barrier();   // every wavefront is done with Q: its place takes O
 
-  if (wave < nh) {
+  if (wave < nh && l32 < rows) {
     // register r of tile dt: d = 32 dt + 8 (r >> 2) + 4 lh + (r & 3), query l32
     const float inv = 1.0f / l_q;
     unsigned char *orow = smem + l32 * C::PITCH + wave * (DH * 2);
@@ -233,17 +270,16 @@ __global__ __launch_bounds__(256) void k_temporal_attn(TemporalParams p) {
           *reinterpret_cast<bf16x4 *>(orow + d0 * 2) = ov;
         }
       }
-    if (p.lse && lh == 0 && l32 < p.T)
-      p.lse[(tok0 + (int64_t)l32 * p.S) * p.H + h] = m_q * p.scale + __logf(l_q);
+    if (p.lse && lh == 0) p.lse[row_token(l32) * p.H + h] = m_q * p.scale + __logf(l_q);
   }
   wg_barrier();
   {
     const int row_ch = nh * C::DCH;   // chunks of a row that hold existing heads
 #pragma unroll 4
-    for (int m = tid; m < p.T * row_ch; m += 256) {
+    for (int m = tid; m < rows * row_ch; m += 256) {
       const int r = m / row_ch, ch = m - r * row_ch;
       const uint4 val = *reinterpret_cast<const uint4 *>(smem + r * C::PITCH + ch * 16);
-      *reinterpret_cast<uint4 *>(p.o + (tok0 + (int64_t)r * p.S) * p.ld_o + h0 * DH + ch * 8) = val;
+      *reinterpret_cast<uint4 *>(p.o + row_token(r) * p.ld_o + h0 * DH + ch * 8) = val;
     }
   }
 }
@@ -251,11 +287,19 @@ __global__ __launch_bounds__(256) void k_temporal_attn(TemporalParams p) {
 template <int DH>
 int launch_t(const TemporalParams &p, hipStream_t s) {
   const bool opts = p.g_q != nullptr || p.rope != nullptr;
-  const int64_t locs = (int64_t)p.B * p.S;
-  const int64_t blocks = ((locs + 7) / 8) * p.n_hg * 8;
+  const int64_t packs = (int64_t)p.B * p.n_packs;
+  const int64_t blocks = ((packs + 7) / 8) * p.n_hg * 8;
   if (blocks > 0x7fffffff) { ddit::set_error("temporal attention: too many workgroups"); return -2; }
-  if (opts) hipLaunchKernelGGL((k_temporal_attn<DH, true>), dim3((unsigned)blocks), dim3(256), 0, s, p);
-  else hipLaunchKernelGGL((k_temporal_attn<DH, false>), dim3((unsigned)blocks), dim3(256), 0, s, p);
+  const unsigned lds = 3u * p.R * TCfg<DH>::PITCH;
+  static bool attr_set = false;   // benign race: the attribute is idempotent
+  if (!attr_set) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_temporal_attn<DH, true>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, 3 * TP * TCfg<DH>::PITCH + TCfg<DH>::OPT_BYTES);
+    if (e != hipSuccess) return ddit::hip_fail(e, "temporal attention hipFuncSetAttribute");
+    attr_set = true;
+  }
+  if (opts) hipLaunchKernelGGL((k_temporal_attn<DH, true>), dim3((unsigned)blocks), dim3(256), lds + TCfg<DH>::OPT_BYTES, s, p);
+  else hipLaunchKernelGGL((k_temporal_attn<DH, false>), dim3((unsigned)blocks), dim3(256), lds, s, p);
   return ddit::hip_fail(hipGetLastError(), "temporal attention launch");
 }
 
@@ -279,6 +323,15 @@ int launch_temporal_attn(const void *q, const void *k, const void *v, void *o, f
   p.ld_q = ld_q; p.ld_kv = ld_kv; p.ld_o = ld_o;
   p.B = B; p.T = T; p.S = S; p.H = H;
   p.n_hg = (H + HG - 1) / HG;
+  // Up to ten frames: as many locations as the tile holds.  One location per workgroup leaves most of the tile, of the
+  // threads and (options) of the rows treated idle, and four times the workgroups; microseconds, one / packed:
+  // 3680 tokens, T = 4: 24.8 / 12.9 (q/k treated: 34.1 / 13.6), 7360, T = 8: 29.4 / 20.7, 4050, T = 10: 16.4 / 15.0.
+  // Above that a single location already keeps the loads coming, and more workgroups fit a CU: 2304, T = 16:
+  // 10.2 / 11.9, 12960, T = 16: 33.3 / 35.4; T = 13: 21.9 / 20.0, treated 27.3 / 30.7.
+  p.P = T <= 10 ? std::min(TP / T, S) : 1;
+  p.R = p.P * T;
+  p.n_packs = (S + p.P - 1) / p.P;
+  p.inv_T = 1.0f / (float)T;
   p.scale = 1.0f / sqrtf((float)dh);
   p.scale_log2 = p.scale * 1.4426950408889634f;
   p.g_q = reinterpret_cast<const bf16_t *>(g_q);
