@@ -11,7 +11,7 @@
 //
 // Work split.  Streaming form: grid = (query tiles of 128, heads, groups); 4 wavefronts per
 // workgroup, each owning 32 queries against all keys of the group, K/V tiles through a two-stage
-// LDS ring.  Resident form (key sequences of at most 320 shared by thousands of queries: the text
+// LDS ring (2 wavefronts for sequences of at most 64 queries).  Resident form (key sequences of at most 320 shared by thousands of queries: the text
 // tokens of cross-attention): 8 wavefronts, one workgroup per CU; the unit's whole K and V are
 // fetched into LDS once and the workgroup walks over a run of 256-query tiles with no further tile
 // load and no barrier (480p cross-attention: 0.149 -> 0.109 ms; each further key tile then costs
@@ -55,6 +55,7 @@
 namespace {
 
 constexpr int STREAM_NW = 4;   // wavefronts per workgroup of the streaming form (two workgroups per CU)
+constexpr int SHORT_NW = 2;    // ... for at most 64 queries (three workgroups per CU)
 constexpr int RES_NW = 8;      // ... of the resident form (one workgroup per CU)
 constexpr int RES_TILES = 5;   // key tiles the resident form keeps in LDS: sequences of up to 320 keys
 constexpr int KT = 64;         // keys per LDS tile
@@ -684,9 +685,17 @@ int launch_flash_attn(const AttnArgs &a, hipStream_t s) {
     if (a.dh == 72) return launch_dh<72, RES_NW, true>(p, blocks, s);
     if (a.dh == 64) return launch_dh<64, RES_NW, true>(p, blocks, s);
   }
-  p.n_qtiles = (a.Lq + 32 * STREAM_NW - 1) / (32 * STREAM_NW);
+  // Up to 64 queries (one tile of keys: temporal attention of 33 to 64 frames) half of a workgroup of 128 would
+  // be idle and take a CU's slots: 64 queries per workgroup, three workgroups per CU instead of two.  128 / 64
+  // queries, d_h = 72: 405 locations x 16 heads, T = 51 71.9 / 57.6 us, T = 64 69.5 / 64.1; 920 x 4, T = 33
+  // 36.0 / 27.5; 129 to 192 queries, where the last 128 are half empty too: no difference (144 queries, 256 units
+  // 12.8 / 12.7 us; 192, 480 units 22.6 / 22.8).
+  const int nw = a.Lq <= 32 * SHORT_NW ? SHORT_NW : STREAM_NW;
+  p.n_qtiles = (a.Lq + 32 * nw - 1) / (32 * nw);
   p.spread = p.n_units < 64;
   const int64_t blocks = (p.spread ? (int64_t)p.n_units : (int64_t)((p.n_units + 7) / 8) * 8) * p.n_qtiles;
+  if (nw == SHORT_NW && a.dh == 72) return launch_dh<72, SHORT_NW, false>(p, blocks, s);
+  if (nw == SHORT_NW && a.dh == 64) return launch_dh<64, SHORT_NW, false>(p, blocks, s);
   if (a.dh == 72) return launch_dh<72, STREAM_NW, false>(p, blocks, s);
   if (a.dh == 64) return launch_dh<64, STREAM_NW, false>(p, blocks, s);
   set_error("dh=%d: supported head dims are 64 and 72", a.dh);
