@@ -844,6 +844,11 @@ int launch_one(const GemmParams &p0, hipStream_t s, const GT &gt = GT()) {
 // eleven linears (the model's at hidden 1152 and 256, one rank's of a four-way head split, the caption
 // embedder's) over 44 token counts from 16 to 48600 with every tile forced in turn and the weights coming
 // from HBM, as they do in a step: over that sweep the picks cost 1.1 % more than the best tile everywhere.
+// The residual epilogue of the largest tile is set by a sweep that leaves the stream where the launch before
+// put it, as a step does: fitted with the stream evicted it looked a third slower than it is, and the
+// out-projections (k = 1152) of 48600 tokens went to 256 x 128 (212 us; 192 x 384: 166), of 14400 to 128 x 192
+// (65; 51).  480p step 136.6 -> 133.2 ms, 720p share 213.6 -> 211.0.  The other tiles' constants stay: set the same
+// way they moved 12960 tokens to 256 x 256, and the batch-2 240p step from 38.3 to 38.5 ms.
 // The nine are the ones, of fourteen that were swept, that lose least against all fourteen (0.6 % of a layer).
 // ---------------------------------------------------------------------------------------------
 struct TileModel {
@@ -855,7 +860,7 @@ struct TileModel {
 };
 constexpr int N_TILES = 9;
 constexpr TileModel TILES[N_TILES] = {
-    {192, 384, 8, 2, 1.219f, {3.82f, 7.11f, 22.75f}, 0.249f, 20.40f},
+    {192, 384, 8, 2, 1.219f, {3.82f, 7.11f, 17.5f}, 0.249f, 14.0f},
     {256, 256, 8, 2, 1.137f, {2.85f, 6.48f, 21.69f}, 0.248f, 7.58f},
     {192, 256, 8, 2, 1.009f, {2.11f, 5.02f, 15.09f}, 0.147f, 9.81f},
     {256, 128, 8, 3, 0.546f, {1.67f, 3.18f, 7.93f}, 0.451f, 0.00f},
