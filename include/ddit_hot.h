@@ -283,6 +283,16 @@ int ddit_linear_fwd_tile(int tile, int epilogue, const void *u, int64_t ld_u, co
                          const float *ada_table, const float *c6, int gate_row, int64_t tokens_per_sample,
                          void *hip_stream);
 
+/* fc2 of few tokens leaves its result as fp32 partial products over parts of k, which the next launch that reads
+ * the stream adds up.  ddit_linear_partial_choice: in how many parts, at most max_parts, a layer whose fc2 is this
+ * linear leaves it (0: in one launch that adds to the stream itself) and with which tile (-1 with 0 parts).  Host
+ * only; needs no GPU.  ddit_linear_partial_fwd: that launch with tile and parts fixed; out is fp32 [parts, N, n],
+ * the sum over parts is u W^T + bias.  DDIT_ERR_UNSUPPORTED if k has no `parts` parts of whole k-steps of 64, none
+ * of them empty; DDIT_ERR_INVALID_ARG for a tile that is not compiled for it (the largest are not). */
+int ddit_linear_partial_choice(int64_t N, int32_t n, int32_t k, int32_t max_parts, int32_t *parts_out, int32_t *tile_out);
+int ddit_linear_partial_fwd(int tile, int32_t parts, const void *u, int64_t ld_u, const void *W, const void *bias, int64_t N,
+                            int32_t n, int32_t k, float *out, void *hip_stream);
+
 /* c6 fp32 [B,6D] from timesteps (HOST fp32[B]) or from a given temb (device fp32 [B,D]).
  * scratch: device fp32, at least B*(256 + 2*D) floats. */
 int ddit_timestep_conditioning(const ddit_shape *shape, const ddit_step_weights *weights,

@@ -28,7 +28,8 @@ EXPORTS = ["ddit_abi_version", "ddit_status_string", "ddit_last_error", "ddit_wo
            "ddit_linear_fwd", "ddit_timestep_conditioning", "ddit_io_workspace_bytes", "ddit_embed_latent",
            "ddit_embed_caption", "ddit_output_head", "ddit_eps_theta", "ddit_solver_step", "ddit_sample",
            "ddit_cross_kv_bytes", "ddit_cross_kv_precompute", "ddit_denoise_step_cached", "ddit_linear_tile_count",
-           "ddit_linear_tile_info", "ddit_linear_tile_choice", "ddit_linear_fwd_tile", "ddit_qk_norm_rope_fwd", "ddit_self_attn_fwd", "ddit_optimal_dop",
+           "ddit_linear_tile_info", "ddit_linear_tile_choice", "ddit_linear_fwd_tile",
+           "ddit_linear_partial_choice", "ddit_linear_partial_fwd", "ddit_qk_norm_rope_fwd", "ddit_self_attn_fwd", "ddit_optimal_dop",
            "ddit_buddy_create", "ddit_buddy_alloc", "ddit_buddy_release", "ddit_buddy_free_gpus", "ddit_buddy_destroy",
            "ddit_sched_simulate", "ddit_probe_mfma_bf16", "ddit_probe_stream_copy", "ddit_probe_stream_read", "ddit_probe_residual_stream"]
 
@@ -144,6 +145,9 @@ def _load() -> C.CDLL:
     lib.ddit_linear_tile_info.argtypes = [C.c_int] + [C.POINTER(C.c_int32)] * 4
     lib.ddit_linear_tile_choice.argtypes = [C.c_int, C.c_int64, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32),
                                             C.POINTER(C.c_float)]
+    lib.ddit_linear_partial_choice.argtypes = [C.c_int64, C.c_int32, C.c_int32, C.c_int32] + [C.POINTER(C.c_int32)] * 2
+    lib.ddit_linear_partial_fwd.argtypes = [C.c_int, C.c_int32, C.c_void_p, C.c_int64, C.c_void_p, C.c_void_p, C.c_int64,
+                                            C.c_int32, C.c_int32, C.c_void_p, C.c_void_p]
     lib.ddit_timestep_conditioning.argtypes = [C.POINTER(ddit_shape), C.POINTER(ddit_step_weights),
                                                C.POINTER(C.c_float), C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]
     SP, WP, IP, VP, FP = C.POINTER(ddit_shape), C.POINTER(ddit_step_weights), C.POINTER(ddit_io_weights), C.c_void_p, \
@@ -385,6 +389,17 @@ def ddit_linear_fwd_tile(tile: int, epilogue: int, u, ld_u: int, W, bias, N: int
                          resid=None, ada_table=None, c6=None, gate_row: int = -1, tokens_per_sample: int = 1) -> None:
     _check(_lib.ddit_linear_fwd_tile(tile, epilogue, _ptr(u), ld_u, _ptr(W), _ptr(bias), N, n, k, _ptr(out), ld_out,
                                      _ptr(resid), _ptr(ada_table), _ptr(c6), gate_row, tokens_per_sample, _stream()))
+
+
+def ddit_linear_partial_choice(N: int, n: int, k: int, max_parts: int = 3):
+    """-> (parts, tile); (0, -1) where one launch is cheaper."""
+    parts, tile = C.c_int32(), C.c_int32()
+    _check(_lib.ddit_linear_partial_choice(N, n, k, max_parts, C.byref(parts), C.byref(tile)))
+    return parts.value, tile.value
+
+
+def ddit_linear_partial_fwd(tile: int, parts: int, u, ld_u: int, W, bias, N: int, n: int, k: int, out) -> None:
+    _check(_lib.ddit_linear_partial_fwd(tile, parts, _ptr(u), ld_u, _ptr(W), _ptr(bias), N, n, k, _ptr(out), _stream()))
 
 
 def ddit_timestep_conditioning(shape: ddit_shape, weights: ddit_step_weights, timesteps, temb, c6_out, scratch) -> None:

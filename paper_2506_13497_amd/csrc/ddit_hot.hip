@@ -815,6 +815,33 @@ int ddit_linear_fwd_tile(int tile, int epilogue, const void *u, int64_t ld_u, co
   return launch_gemm(epilogue, g, reinterpret_cast<hipStream_t>(hip_stream));
 }
 
+int ddit_linear_partial_choice(int64_t N, int32_t n, int32_t k, int32_t max_parts, int32_t *parts_out, int32_t *tile_out) {
+  if (N < 0 || n < 1 || k < 1 || max_parts < 0) {
+    set_error("linear: N=%lld n=%d k=%d max_parts=%d", (long long)N, n, k, max_parts); return DDIT_ERR_INVALID_ARG;
+  }
+  if (!parts_out || !tile_out) { set_error("parts_out and tile_out must not be NULL"); return DDIT_ERR_INVALID_ARG; }
+  int tile = -1;
+  *parts_out = gemm_partial_choice(N, n, k, max_parts, &tile);
+  *tile_out = tile;
+  return DDIT_OK;
+}
+
+int ddit_linear_partial_fwd(int tile, int32_t parts, const void *u, int64_t ld_u, const void *W, const void *bias, int64_t N,
+                            int32_t n, int32_t k, float *out, void *hip_stream) {
+  if (!u || !W || !out) { set_error("u, W and out must not be NULL"); return DDIT_ERR_INVALID_ARG; }
+  if (N < 0 || n < 1 || k < 1 || ld_u < k || parts < 1) {
+    set_error("linear: N=%lld n=%d k=%d ld_u=%lld parts=%d", (long long)N, n, k, (long long)ld_u, parts); return DDIT_ERR_INVALID_ARG;
+  }
+  if (n % 8 || k % 8 || ld_u % 8) { set_error("n, k and ld_u must be multiples of 8"); return DDIT_ERR_UNSUPPORTED; }
+  if (!aligned16(u) || !aligned16(W) || (bias && !aligned16(bias)) || !aligned16(out)) {
+    set_error("pointers must be 16-byte aligned"); return DDIT_ERR_ALIGNMENT;
+  }
+  GemmArgs g;
+  memset(&g, 0, sizeof(g));
+  g.u = u; g.ld_u = ld_u; g.W = W; g.bias = bias; g.N = N; g.n = n; g.k = k;
+  return launch_gemm_partial(g, parts, tile, out, N * (int64_t)n, reinterpret_cast<hipStream_t>(hip_stream));
+}
+
 int ddit_io_workspace_bytes(const ddit_shape *shape, const ddit_io_weights *io, size_t *bytes_out) {
   Dims d;
   DDIT_TRY(check_shape(shape, &d));

@@ -1012,6 +1012,7 @@ int gemm_partial_choice(int64_t N, int n, int k, int max_parts, int *tile_out) {
   int chosen = 0;
   for (int parts = 2; parts <= most && parts <= steps; ++parts) {
     const int per = (steps + parts - 1) / parts;
+    if ((parts - 1) * per >= steps) continue;   // the last part would be empty (4 k-steps in three parts of two)
     for (int t = FIRST_PARTIAL_TILE; t < N_TILES; ++t) {
       const int cols = (n + TILES[t].cols - 1) / TILES[t].cols * TILES[t].cols;
       const float us = predicted_us(t, 0, N, parts * cols, per * BK, cus) + PARTIAL_SUM_US + PARTIAL_SUM_US_PER_PART * parts;
@@ -1036,6 +1037,10 @@ int launch_partial_tile(int tile, const GemmParams &p, hipStream_t s) {
 
 int launch_gemm_partial(const GemmArgs &a, int parts, int tile, float *out, int64_t part_stride, hipStream_t s) {
   if (a.N == 0 || a.n == 0) return 0;
+  if ((int64_t)a.n * a.k >= (int64_t)1 << 31 || a.N * a.ld_u >= (int64_t)1 << 31) {
+    set_error("linear: n*k = %lld or N*ld_u = %lld exceeds the 31-bit index range", (long long)a.n * a.k, (long long)(a.N * a.ld_u));
+    return -2;
+  }
   GemmParams p;
   memset(&p, 0, sizeof(p));
   p.u = reinterpret_cast<const bf16_t *>(a.u); p.ld_u = a.ld_u;
@@ -1046,6 +1051,11 @@ int launch_gemm_partial(const GemmArgs &a, int parts, int tile, float *out, int6
   p.tokens_per_sample = 1;
   const int steps = (a.k + BK - 1) / BK;
   p.split_steps = (steps + parts - 1) / parts;
+  // the launch writes ceil(steps / split_steps) parts, and whoever adds them up reads `parts`
+  if (parts < 1 || (parts - 1) * p.split_steps >= steps) {
+    set_error("linear: k=%d cannot be split into %d parts of whole k-steps of %d", a.k, parts, BK);
+    return -2;
+  }
   p.split_stride = part_stride;
   return launch_partial_tile(tile, p, s);
 }

@@ -317,3 +317,26 @@ def test_bench_refuses_more_than_one_gpu():
     import sys
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True)
     assert r.returncode != 0 and "ONE GPU" in r.stderr
+
+
+def test_partial_sums_leave_no_part_empty(m):
+    """Whoever adds the parts up reads as many as were asked for, so a split whose last part would hold no k-step is
+    refused before any launch, and never chosen."""
+    lib = m.binding._lib
+    P = C.c_void_p
+    fwd = lambda tile, parts, k, N=16: lib.ddit_linear_partial_fwd(tile, parts, P(0x1000), k, P(0x2000), None, N, 64, k, P(0x3000), None)
+    tile = m.ddit_linear_tile_count() - 1
+    for k, parts in ((64, 2), (64, 3), (128, 3), (200, 3), (256, 3), (8, 2), (320, 4), (576, 7)):
+        assert fwd(tile, parts, k) == -2, (k, parts)
+        assert "parts" in m.ddit_last_error()
+    assert fwd(0, 2, 256) == -1 and "partial sums" in m.ddit_last_error()      # a tile that is not compiled for it
+    assert fwd(tile, 0, 256) == -1 and fwd(tile, 2, 250) == -2
+    assert fwd(tile, 3, 256, N=0) == 0
+    for n in (8, 256, 1152, 2048, 4096):
+        for k in list(range(8, 1200, 56)) + [4608, 16384]:
+            for N in (1, 40, 300, 1152, 2304, 3500):
+                for most in (0, 1, 2, 3, 5):
+                    parts, t = m.ddit_linear_partial_choice(N, n, k, most)
+                    steps = (k + 63) // 64
+                    assert (parts == 0 and t == -1) or (2 <= parts <= most and 0 <= t < m.ddit_linear_tile_count())
+                    assert parts == 0 or (parts - 1) * -(-steps // parts) < steps, (N, n, k, most, parts)
