@@ -36,15 +36,6 @@ __global__ __launch_bounds__(256) void k_modulated_layernorm(float *__restrict__
     sh = make_float4(ts.x + cs.x, ts.y + cs.y, ts.z + cs.z, ts.w + cs.w);
     sc1 = make_float4(1.f + (tc.x + cc.x), 1.f + (tc.y + cc.y), 1.f + (tc.z + cc.z), 1.f + (tc.w + cc.w));
   };
-  auto pending_gate = [&](int64_t b, int c) {
-    float4 g = make_float4(1.f, 1.f, 1.f, 1.f);
-    if (pend.gate_tab) {
-      g = reinterpret_cast<const float4 *>(pend.gate_tab)[c];
-      const float4 h = reinterpret_cast<const float4 *>(pend.gate_c6 + b * pend.gate_c6_stride)[c];
-      g.x += h.x; g.y += h.y; g.z += h.z; g.w += h.w;
-    }
-    return g;
-  };
   // the first row's loads are issued before the modulation vectors are fetched
   float4 v[CHUNKS];
   auto load_row = [&](int64_t row) {
@@ -78,7 +69,7 @@ __global__ __launch_bounds__(256) void k_modulated_layernorm(float *__restrict__
   const int64_t b_wg = wg_row0 / tokens_per_sample;
   for (int c = threadIdx.x; c < nchunk; c += 256) {
     modulation(b_wg, c, mod[c], mod[nchunk + c]);
-    if constexpr (SUM) mod[2 * nchunk + c] = pending_gate(b_wg, c);
+    if constexpr (SUM) mod[2 * nchunk + c] = ddit::pending_gate(pend, b_wg, c);
   }
   __syncthreads();
   if (row0 >= N) return;
@@ -93,8 +84,8 @@ __global__ __launch_bounds__(256) void k_modulated_layernorm(float *__restrict__
       for (int j = 0; j < CHUNKS; ++j) {
         const int c = lane + 64 * j;
         if (c < nchunk) {
-          const float4 g = here ? mod[2 * nchunk + c] : pending_gate(row / tokens_per_sample, c);
-          v[j] = make_float4(v[j].x + g.x * add[j].x, v[j].y + g.y * add[j].y, v[j].z + g.z * add[j].z, v[j].w + g.w * add[j].w);
+          const float4 g = here ? mod[2 * nchunk + c] : ddit::pending_gate(pend, row / tokens_per_sample, c);
+          v[j] = ddit::add_gated(v[j], g, add[j]);
           xw[c] = floatx4{v[j].x, v[j].y, v[j].z, v[j].w};
         }
       }

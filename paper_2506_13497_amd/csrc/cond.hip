@@ -66,28 +66,27 @@ __global__ void k_f32_to_bf16(const float *__restrict__ in, bf16_t *__restrict__
   reinterpret_cast<bf16x8 *>(out)[i] = v;
 }
 
-// out[n, :] = bf16(x[n, :] + gate_b * sum of the pending parts' row n)
-__global__ void k_sum_to_bf16(const float *__restrict__ x, ddit::PendingSum pend, bf16_t *__restrict__ out, int64_t n4,
+// x[n, :] + gate_b * sum of the pending parts' row n: rounded to bf16 into out (TO_BF16), or back into x
+template <bool TO_BF16>
+__global__ void k_add_pending(float *__restrict__ x, ddit::PendingSum pend, bf16_t *__restrict__ out, int64_t n4,
                               int d4, int64_t tokens_per_sample) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n4) return;
   const int64_t row = i / d4;
-  const int c = (int)(i - row * d4);
-  float4 a = make_float4(0.f, 0.f, 0.f, 0.f), g = make_float4(1.f, 1.f, 1.f, 1.f);
+  float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
   for (int q = 0; q < pend.parts; ++q) {
     const float4 t = reinterpret_cast<const float4 *>(pend.part + q * pend.part_stride)[i];
     a.x += t.x; a.y += t.y; a.z += t.z; a.w += t.w;
   }
-  if (pend.gate_tab) {
-    g = reinterpret_cast<const float4 *>(pend.gate_tab)[c];
-    const float4 h = reinterpret_cast<const float4 *>(pend.gate_c6 + (row / tokens_per_sample) * pend.gate_c6_stride)[c];
-    g.x += h.x; g.y += h.y; g.z += h.z; g.w += h.w;
+  const float4 g = ddit::pending_gate(pend, row / tokens_per_sample, (int)(i - row * d4));
+  const float4 v = ddit::add_gated(reinterpret_cast<const float4 *>(x)[i], g, a);
+  if constexpr (TO_BF16) {
+    bf16x4 o;
+    o[0] = (bf16_t)v.x; o[1] = (bf16_t)v.y; o[2] = (bf16_t)v.z; o[3] = (bf16_t)v.w;
+    reinterpret_cast<bf16x4 *>(out)[i] = o;
+  } else {
+    reinterpret_cast<float4 *>(x)[i] = v;
   }
-  const float4 v = reinterpret_cast<const float4 *>(x)[i];
-  bf16x4 o;
-  o[0] = (bf16_t)(v.x + g.x * a.x); o[1] = (bf16_t)(v.y + g.y * a.y);
-  o[2] = (bf16_t)(v.z + g.z * a.z); o[3] = (bf16_t)(v.w + g.w * a.w);
-  reinterpret_cast<bf16x4 *>(out)[i] = o;
 }
 
 }  // namespace
@@ -98,9 +97,17 @@ int launch_cast_sum_to_bf16(const float *x, const PendingSum &pending, void *out
                             hipStream_t s) {
   const int64_t n4 = N * (D / 4);
   if (n4 == 0) return 0;
-  hipLaunchKernelGGL(k_sum_to_bf16, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, x, pending,
+  hipLaunchKernelGGL(k_add_pending<true>, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, const_cast<float *>(x), pending,
                      reinterpret_cast<bf16_t *>(out), n4, D / 4, tokens_per_sample);
   return hip_fail(hipGetLastError(), "cast launch");
+}
+
+int launch_add_pending(float *x, const PendingSum &pending, int64_t N, int64_t tokens_per_sample, int D, hipStream_t s) {
+  const int64_t n4 = N * (D / 4);
+  if (n4 == 0) return 0;
+  hipLaunchKernelGGL(k_add_pending<false>, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, x, pending, nullptr, n4, D / 4,
+                     tokens_per_sample);
+  return hip_fail(hipGetLastError(), "pending sum launch");
 }
 
 int launch_cast_bf16_to_f32(const void *in, float *out, int64_t n, hipStream_t s) {

@@ -41,6 +41,20 @@ struct PendingSum {
   int parts; const float *part; int64_t part_stride;   // parts == 0: nothing pending
   const float *gate_tab, *gate_c6; int64_t gate_c6_stride;
 };
+// Its gate vector for sample b, and its addition to the stream, at the four features of chunk c.  Every launch that
+// adds a pending update uses these two, so the stream's bits do not depend on which one does.
+__device__ __forceinline__ float4 pending_gate(const PendingSum &p, int64_t b, int c) {
+  float4 g = make_float4(1.f, 1.f, 1.f, 1.f);
+  if (p.gate_tab) {
+    g = reinterpret_cast<const float4 *>(p.gate_tab)[c];
+    const float4 h = reinterpret_cast<const float4 *>(p.gate_c6 + b * p.gate_c6_stride)[c];
+    g.x += h.x; g.y += h.y; g.z += h.z; g.w += h.w;
+  }
+  return g;
+}
+__device__ __forceinline__ float4 add_gated(float4 v, float4 g, float4 a) {
+  return make_float4(__builtin_fmaf(g.x, a.x, v.x), __builtin_fmaf(g.y, a.y, v.y), __builtin_fmaf(g.z, a.z, v.z), __builtin_fmaf(g.w, a.w, v.w));
+}
 // pending (may be null): added to x, which is written back, before the LayerNorm
 int launch_modulated_layernorm(float *x, const float *ada_table, const float *c6, int which, int64_t N,
                                int64_t tokens_per_sample, int D, float eps, void *out, hipStream_t s,
@@ -111,6 +125,8 @@ int launch_cast_f32_to_bf16(const float *in, void *out, int64_t n, hipStream_t s
 // out = bf16(x + pending), x left as it is
 int launch_cast_sum_to_bf16(const float *x, const PendingSum &pending, void *out, int64_t N, int64_t tokens_per_sample, int D,
                             hipStream_t s);
+// x += pending
+int launch_add_pending(float *x, const PendingSum &pending, int64_t N, int64_t tokens_per_sample, int D, hipStream_t s);
 struct CondArgs {
   int B, D;
   float t[64];

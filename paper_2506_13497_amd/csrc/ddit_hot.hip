@@ -134,7 +134,7 @@ void make_layout(const Dims &d, uint32_t flags, Layout *lo) {
   // fc2 in partial sums: they lie from qkv on, room for two where A == D.  Where a third one is worth having (small
   // N only, 8 MB at most) the regions behind make way, unless the shape then outgrew the built-in scratch.
   const size_t part = (size_t)d.N * d.D * 4, room = lo->kvc - lo->qkv;
-  lo->fc2_parts = (flags & DDIT_FLAG_TAPS) ? 0 : gemm_partial_choice(d.N, (int)d.D, (int)d.M, 3, &lo->fc2_tile);
+  lo->fc2_parts = gemm_partial_choice(d.N, (int)d.D, (int)d.M, 3, &lo->fc2_tile);
   if (lo->fc2_parts * part > room) {
     const size_t more = align_up(lo->fc2_parts * part - room);
     if (off <= STATIC_SCRATCH_BYTES && off + more > STATIC_SCRATCH_BYTES) {
@@ -354,6 +354,10 @@ int run_layer(ddit_attn_kind kind, const Dims &d, const ddit_layer_weights &w, c
   if (lo.fc2_parts > 0) {
     *pending = PendingSum{lo.fc2_parts, reinterpret_cast<const float *>(qkv), N * D, g.gate_tab, g.gate_c6, g.gate_c6_stride};
     DDIT_TRY(launch_gemm_partial(g, lo.fc2_parts, lo.fc2_tile, reinterpret_cast<float *>(qkv), N * D, s));
+    if (tp.on) {   // the tap shows the stream after the layer: the same sum, formed here instead of by the next launch
+      DDIT_TRY(launch_add_pending(x, *pending, N, d.L, (int)D, s));
+      pending->parts = 0;
+    }
   } else {
     DDIT_TRY(launch_gemm(DDIT_EPI_RESIDUAL_F32, g, s));
   }

@@ -1,7 +1,7 @@
 """fc2 in partial sums that the next LayerNorm, or the final cast, adds to the stream: a step of two blocks
 against the CPU oracle at token counts where it comes in three and in two parts, with rows that end inside a
 tile and samples that change inside a workgroup's rows, the gates of the update per sample, and a k whose
-last part is ragged.  (A step that keeps its taps adds in one launch: the other tests.)"""
+last part is ragged."""
 import numpy as np
 import pytest
 import torch
@@ -38,3 +38,31 @@ def test_step_with_partial_sums(B, T, Hp, Wp, D, H, dh, M):
     ref = ora.denoise_step(to_f64(act["x"]), to_f64(act["y"]), None, None, dict_f64(sw), [dict_f64(b) for b in blocks],
                            H, dh, temb=temb.astype(np.float64))
     assert_parity(dev_to_f64(x_out), ref, "step with fc2 in partial sums")
+
+
+@pytest.mark.parametrize("B,T,Hp,Wp,D,H,dh,M,parts", [
+    (2, 2, 5, 10, 1152, 16, 72, 4608, 3),
+    (1, 4, 16, 31, 1152, 16, 72, 4608, 2),
+    (1, 2, 4, 5, 256, 4, 64, 1024, 0),
+])
+def test_taps_show_what_an_untapped_step_runs(B, T, Hp, Wp, D, H, dh, M, parts):
+    """Keeping taps changes neither how fc2 is split nor a bit of the result, and the last tap is the result."""
+    import paper_2506_13497_amd as m
+    sh = syn.Shape(B, T, Hp, Wp, D, H, dh, M, 20, 2)
+    assert m.ddit_linear_partial_choice(sh.N, D, M)[0] == parts
+    dsw = {k: to_dev(v) for k, v in syn.make_step_weights(sh, 52).items()}
+    dblocks = [dict_dev(syn.make_block_weights(sh, 52, i, table_std=0.1)) for i in range(2)]
+    act = syn.make_activations(sh, 52)
+    x_in, y, temb = to_dev(act["x"]), to_dev(act["y"]), to_dev(syn.make_temb(sh, 52))
+    out = []
+    for flags in (0, m.DDIT_FLAG_TAPS):
+        shape = m.make_shape(B, T, Hp, Wp, D, H, dh, M, 20, 2, flags)
+        ws = m.alloc_workspace(shape)
+        ws.fill_(0xFF)
+        x_out = torch.empty((B, T, sh.S, D), dtype=torch.bfloat16, device="cuda")
+        m.ddit_denoise_step(shape, m.step_struct(dsw, dblocks), x_in, y, None, None, temb, x_out, ws)
+        torch.cuda.synchronize()
+        out.append(x_out.reshape(sh.N, D))
+    assert torch.equal(out[0].view(torch.int16), out[1].view(torch.int16))
+    last = m.read_tap(shape, ws, 1, "x_out").reshape(sh.N, D)
+    assert torch.equal(last.to(torch.bfloat16).view(torch.int16), out[1].view(torch.int16))
