@@ -547,13 +547,20 @@ __global__ __launch_bounds__(WGM *WGN *WGK * 64, 2) void k_gemm_bf16(GemmParams 
       __builtin_amdgcn_global_load_lds((gbl_ptr_t)(bias + f), (lds_ptr_t)(smem_bias + (ld_round % BIAS_SLOTS) * (BN * 2)), 16, 0, 0);
     }
   };
+  // This lane's offsets of the stream's k-step; past the row's end: past every buffer, which fetches nothing and
+  // writes zeros.  k is in the lane's offset because that is what a buffer's length is checked against: whether the
+  // scalar offset counts there too is described both ways, and with a length of zero the difference would wrap.
+  unsigned ld_vu, ld_vw;
+  auto ld_offsets = [&]() {
+    const unsigned k0 = (unsigned)__builtin_amdgcn_readfirstlane((ld_k0 + ld_k) * (BK * 2));   // bytes
+    const bool in = (ld_k0 + ld_k) * BK + ld_chunk * 8 < ld_kend;
+    ld_vu = in ? voff_u + k0 : 0xfffffff0u;
+    ld_vw = in ? voff_w + k0 : 0xfffffff0u;
+  };
   // loads J0 .. J1-1 of the current k-step of the stream into stage ST; each instruction has a resource that
   // starts at its eight rows
   auto ld_issue = [&](auto j0_tag, auto j1_tag, int st) {
     constexpr int J0 = decltype(j0_tag)::value, J1 = decltype(j1_tag)::value;
-    const int k0 = __builtin_amdgcn_readfirstlane((ld_k0 + ld_k) * (BK * 2));     // bytes
-    const bool in = (ld_k0 + ld_k) * BK + ld_chunk * 8 < ld_kend;   // past the row's end: fetch nothing, write zeros
-    const unsigned vu = in ? voff_u : 0xfffffff0u, vw = in ? voff_w : 0xfffffff0u;
 #pragma unroll
     for (int j = J0; j < J1; ++j) {
       const bool is_u = j < NJU;
@@ -561,14 +568,16 @@ __global__ __launch_bounds__(WGM *WGN *WGK * 64, 2) void k_gemm_bf16(GemmParams 
       const unsigned lim = (unsigned)left & ~(unsigned)(left >> 63);
       const unsigned char *base = reinterpret_cast<const unsigned char *>(is_u ? ld_u : ld_W) + off;
       __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(base), 0, __builtin_amdgcn_readfirstlane((int)lim), 0x00020000);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr_t)(smem + st * STAGE + (wave + NW * j) * 1024), 16, is_u ? vu : vw, k0, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr_t)(smem + st * STAGE + (wave + NW * j) * 1024), 16, is_u ? ld_vu : ld_vw, 0, 0, 0);
     }
   };
   auto ld_advance = [&]() {
-    if (++ld_k < nk) return;
-    ld_k = 0;
-    ++ld_round;
-    ld_tile(ld_round < p.rounds ? tile_sequence_index(p, ld_round) : -1);
+    if (++ld_k == nk) {
+      ld_k = 0;
+      ++ld_round;
+      ld_tile(ld_round < p.rounds ? tile_sequence_index(p, ld_round) : -1);
+    }
+    ld_offsets();
   };
   using J_0 = std::integral_constant<int, 0>;
   using J_A = std::integral_constant<int, LA>;
@@ -593,6 +602,7 @@ __global__ __launch_bounds__(WGM *WGN *WGK * 64, 2) void k_gemm_bf16(GemmParams 
   int tile = tile_sequence_index(p, 0);
   if (tile < 0) return;
   ld_tile(tile);
+  ld_offsets();
   // the first NS k-steps, less the second part of the last one (the first k-step of the loop issues that)
 #pragma unroll
   for (int s = 0; s < NS; ++s) {
