@@ -841,7 +841,7 @@ int launch_one(const GemmParams &p0, hipStream_t s, const GT &gt = GT()) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Tile choice.  Nine output tiles are compiled.  Which is fastest depends on how the tile grid divides over
+// Tile choice.  Ten output tiles are compiled.  Which is fastest depends on how the tile grid divides over
 // the CUs far more than on the tile's own efficiency (a 192 x 384 tile does twice the work per byte
 // fetched of a 128 x 192 one, but 60 of them leave 196 CUs idle).  The launcher therefore prices every tile
 // with a small model of the kernel and takes the cheapest.  With  tiles = ceil(N / rows) * ceil(n / cols),
@@ -859,7 +859,9 @@ int launch_one(const GemmParams &p0, hipStream_t s, const GT &gt = GT()) {
 // out-projections (k = 1152) of 48600 tokens went to 256 x 128 (212 us; 192 x 384: 166), of 14400 to 128 x 192
 // (65; 51).  480p step 136.6 -> 133.2 ms, 720p share 213.6 -> 211.0.  The other tiles' constants stay: set the same
 // way they moved 12960 tokens to 256 x 256, and the batch-2 240p step from 38.3 to 38.5 ms.
-// The nine are the ones, of fourteen that were swept, that lose least against all fourteen (0.6 % of a layer).
+// Nine are the ones, of fourteen that were swept, that lose least against all fourteen (0.6 % of a layer); 192 x 288 is
+// for widths that are multiples of 288 and of nothing wider, the projections of head splits with 2, 6, 10 or 14 heads of
+// 72: the grouped text projections need a tile that divides a problem's columns (launch_gemm_grouped).
 // ---------------------------------------------------------------------------------------------
 struct TileModel {
   int rows, cols, wavefronts, stages;   // stages: depth of the operand ring in LDS
@@ -868,10 +870,11 @@ struct TileModel {
   float s;        // slow-down of a full chip
   float f;        // once per launch, residual update
 };
-constexpr int N_TILES = 9;
+constexpr int N_TILES = 10;
 constexpr TileModel TILES[N_TILES] = {
     {192, 384, 8, 2, 1.219f, {3.82f, 7.11f, 17.5f}, 0.249f, 14.0f},
     {256, 256, 8, 2, 1.137f, {2.85f, 6.48f, 21.69f}, 0.248f, 7.58f},
+    {192, 288, 6, 2, 1.06f, {3.2f, 6.0f, 14.0f}, 0.2f, 11.0f},
     {192, 256, 8, 2, 1.009f, {2.11f, 5.02f, 15.09f}, 0.147f, 9.81f},
     {256, 128, 8, 3, 0.546f, {1.67f, 3.18f, 7.93f}, 0.451f, 0.00f},
     {128, 192, 8, 3, 0.506f, {1.43f, 2.44f, 6.26f}, 0.357f, 0.00f},
@@ -881,7 +884,7 @@ constexpr TileModel TILES[N_TILES] = {
     {64, 64, 8, 8, 0.219f, {0.89f, 1.35f, 2.54f}, 0.069f, 0.39f},
 };
 constexpr float LAUNCH_US = 2.71f;
-constexpr int FIRST_PARTIAL_TILE = 3;   // tiles compiled for partial sums: this one and the smaller ones
+constexpr int FIRST_PARTIAL_TILE = 4;   // tiles compiled for partial sums: this one and the smaller ones
 constexpr float PARTIAL_SUM_US = 6.4f, PARTIAL_SUM_US_PER_PART = 1.0f;   // what adding them up later costs
 
 float predicted_us(int tile, int epilogue, int64_t N, int n, int k, int cus) {
@@ -921,13 +924,14 @@ int launch_epi(int tile, const GemmParams &p, hipStream_t s) {
   switch (tile) {
     case 0: return launch_checked<2, 4, 1, 3, 3, 2, EPI>(tile, p, s);
     case 1: return launch_checked<2, 4, 1, 4, 2, 2, EPI>(tile, p, s);
-    case 2: return launch_checked<2, 4, 1, 3, 2, 2, EPI>(tile, p, s);
-    case 3: return launch_checked<4, 2, 1, 2, 2, 3, EPI>(tile, p, s);
-    case 4: return launch_checked<4, 2, 1, 1, 3, 3, EPI>(tile, p, s);
-    case 5: return launch_checked<2, 2, 2, 2, 2, 4, EPI>(tile, p, s);
-    case 6: return launch_checked<2, 2, 2, 1, 3, 4, EPI>(tile, p, s);
-    case 7: return launch_checked<2, 2, 2, 1, 2, 6, EPI>(tile, p, s);
-    case 8: return launch_checked<2, 2, 2, 1, 1, 8, EPI>(tile, p, s);
+    case 2: return launch_checked<2, 3, 1, 3, 3, 2, EPI>(tile, p, s);
+    case 3: return launch_checked<2, 4, 1, 3, 2, 2, EPI>(tile, p, s);
+    case 4: return launch_checked<4, 2, 1, 2, 2, 3, EPI>(tile, p, s);
+    case 5: return launch_checked<4, 2, 1, 1, 3, 3, EPI>(tile, p, s);
+    case 6: return launch_checked<2, 2, 2, 2, 2, 4, EPI>(tile, p, s);
+    case 7: return launch_checked<2, 2, 2, 1, 3, 4, EPI>(tile, p, s);
+    case 8: return launch_checked<2, 2, 2, 1, 2, 6, EPI>(tile, p, s);
+    case 9: return launch_checked<2, 2, 2, 1, 1, 8, EPI>(tile, p, s);
   }
   ddit::set_error("linear: no tile %d (there are %d)", tile, N_TILES);
   return -1;
@@ -994,12 +998,13 @@ int launch_gemm_grouped(const GemmArgs &a, int G, const void *const *W, const vo
   switch (tile) {
     case 0: return launch_grouped_tile<2, 4, 1, 3, 3, 2>(p, gt, s);
     case 1: return launch_grouped_tile<2, 4, 1, 4, 2, 2>(p, gt, s);
-    case 2: return launch_grouped_tile<2, 4, 1, 3, 2, 2>(p, gt, s);
-    case 3: return launch_grouped_tile<4, 2, 1, 2, 2, 3>(p, gt, s);
-    case 4: return launch_grouped_tile<4, 2, 1, 1, 3, 3>(p, gt, s);
-    case 5: return launch_grouped_tile<2, 2, 2, 2, 2, 4>(p, gt, s);
-    case 6: return launch_grouped_tile<2, 2, 2, 1, 3, 4>(p, gt, s);
-    case 7: return launch_grouped_tile<2, 2, 2, 1, 2, 6>(p, gt, s);
+    case 2: return launch_grouped_tile<2, 3, 1, 3, 3, 2>(p, gt, s);
+    case 3: return launch_grouped_tile<2, 4, 1, 3, 2, 2>(p, gt, s);
+    case 4: return launch_grouped_tile<4, 2, 1, 2, 2, 3>(p, gt, s);
+    case 5: return launch_grouped_tile<4, 2, 1, 1, 3, 3>(p, gt, s);
+    case 6: return launch_grouped_tile<2, 2, 2, 2, 2, 4>(p, gt, s);
+    case 7: return launch_grouped_tile<2, 2, 2, 1, 3, 4>(p, gt, s);
+    case 8: return launch_grouped_tile<2, 2, 2, 1, 2, 6>(p, gt, s);
     default: return launch_grouped_tile<2, 2, 2, 1, 1, 8>(p, gt, s);
   }
 }
@@ -1034,12 +1039,12 @@ int gemm_partial_choice(int64_t N, int n, int k, int max_parts, int *tile_out) {
 
 int launch_partial_tile(int tile, const GemmParams &p, hipStream_t s) {
   switch (tile) {
-    case 3: return launch_checked<4, 2, 1, 2, 2, 3, 3>(tile, p, s);
-    case 4: return launch_checked<4, 2, 1, 1, 3, 3, 3>(tile, p, s);
-    case 5: return launch_checked<2, 2, 2, 2, 2, 4, 3>(tile, p, s);
-    case 6: return launch_checked<2, 2, 2, 1, 3, 4, 3>(tile, p, s);
-    case 7: return launch_checked<2, 2, 2, 1, 2, 6, 3>(tile, p, s);
-    case 8: return launch_checked<2, 2, 2, 1, 1, 8, 3>(tile, p, s);
+    case 4: return launch_checked<4, 2, 1, 2, 2, 3, 3>(tile, p, s);
+    case 5: return launch_checked<4, 2, 1, 1, 3, 3, 3>(tile, p, s);
+    case 6: return launch_checked<2, 2, 2, 2, 2, 4, 3>(tile, p, s);
+    case 7: return launch_checked<2, 2, 2, 1, 3, 4, 3>(tile, p, s);
+    case 8: return launch_checked<2, 2, 2, 1, 2, 6, 3>(tile, p, s);
+    case 9: return launch_checked<2, 2, 2, 1, 1, 8, 3>(tile, p, s);
   }
   set_error("linear: no partial sums with tile %d", tile);
   return -1;

@@ -340,3 +340,12 @@ def test_partial_sums_leave_no_part_empty(m):
                     steps = (k + 63) // 64
                     assert (parts == 0 and t == -1) or (2 <= parts <= most and 0 <= t < m.ddit_linear_tile_count())
                     assert parts == 0 or (parts - 1) * -(-steps // parts) < steps, (N, n, k, most, parts)
+
+
+def test_text_projections_of_every_even_head_split_are_grouped(m):
+    """One launch for the text k|v projections of all layers needs a tile whose columns divide a layer's 2 * H * d_h
+    out-features: without it 56 launches go one by one."""
+    cols = [m.ddit_linear_tile_info(t)["cols"] for t in range(m.ddit_linear_tile_count())]
+    for H in range(2, 33, 2):
+        for dh in (64, 72):
+            assert any(2 * H * dh % c == 0 for c in cols), (H, dh)
