@@ -124,7 +124,8 @@ const char *ddit_status_string(int status);
 const char *ddit_last_error(void); /* thread-local, never NULL */
 
 /* Bytes of workspace ddit_stdit_block_fwd / ddit_denoise_step / ddit_attn_fwd need for
- * this shape (with DDIT_FLAG_TAPS: including the tap area). */
+ * this shape (with DDIT_FLAG_TAPS: including the tap area).  Host arithmetic on the shape:
+ * touches no device, and is the same on every machine. */
 int ddit_workspace_bytes(const ddit_shape *shape, size_t *bytes_out);
 
 /* Where a tap lives, when DDIT_FLAG_TAPS is set: offset from the start of the workspace
@@ -174,7 +175,8 @@ int ddit_stdit_block_fwd(const ddit_shape *shape, const ddit_block_weights *weig
  * block's workspace is a device array built into the library, DDIT_STATIC_SCRATCH_BYTES per GPU,
  * held from the library's load until the process ends.  The call allocates and frees nothing.
  * Same arguments and results as ddit_stdit_block_fwd, less the workspace.  Shapes whose
- * ddit_workspace_bytes() exceeds DDIT_STATIC_SCRATCH_BYTES are refused with DDIT_ERR_WORKSPACE
+ * ddit_workspace_bytes() exceeds DDIT_STATIC_SCRATCH_BYTES are refused with DDIT_ERR_WORKSPACE, unless only the
+ * partial sums of fc2 do not fit (ddit_linear_partial_choice): it then comes in as many as fit, or in one launch
  * (64 MiB holds a block of the 144p latent: T=16, 9x16 tokens per frame, hidden 1152);
  * DDIT_FLAG_TAPS is refused with DDIT_ERR_UNSUPPORTED.  Every call on one GPU uses that GPU's one
  * array: calls that overlap in time on the same GPU (different streams or threads) race on it;

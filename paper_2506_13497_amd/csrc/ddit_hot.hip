@@ -118,7 +118,8 @@ int check_shape(const ddit_shape *sh, Dims *d) {
   return DDIT_OK;
 }
 
-void make_layout(const Dims &d, uint32_t flags, Layout *lo) {
+// limit: a workspace that cannot grow (the built-in scratch); a shape that fits it with fewer parts of fc2 takes those
+void make_layout(const Dims &d, uint32_t flags, Layout *lo, size_t limit = SIZE_MAX) {
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += align_up(bytes); return o; };
   lo->x = take((size_t)d.N * d.D * 4);
@@ -131,13 +132,14 @@ void make_layout(const Dims &d, uint32_t flags, Layout *lo) {
   lo->c6 = take((size_t)d.B * 6 * d.D * 4);
   lo->cond = take((size_t)d.B * (256 + 2 * d.D) * 4);
   lo->rope = (flags & DDIT_FLAG_ROPE_TEMPORAL) ? take((size_t)d.T * d.dh * 4) : 0;
-  // fc2 in partial sums: they lie from qkv on, room for two where A == D.  Where a third one is worth having (small
-  // N only, 8 MB at most) the regions behind make way, unless the shape then outgrew the built-in scratch.
+  // fc2 in partial sums, in as many as the shape alone says: they lie from qkv on, room for two where A == D.  A third
+  // one, or two where A is far below D, push the regions behind further back: at most 4 N D and 8 N (D - A) bytes, 25 MB
+  // at the largest N * D that is split.
   const size_t part = (size_t)d.N * d.D * 4, room = lo->kvc - lo->qkv;
   lo->fc2_parts = gemm_partial_choice(d.N, (int)d.D, (int)d.M, 3, &lo->fc2_tile);
   if (lo->fc2_parts * part > room) {
     const size_t more = align_up(lo->fc2_parts * part - room);
-    if (off <= STATIC_SCRATCH_BYTES && off + more > STATIC_SCRATCH_BYTES) {
+    if (off <= limit && off + more > limit) {
       lo->fc2_parts = gemm_partial_choice(d.N, (int)d.D, (int)d.M, (int)(room / part), &lo->fc2_tile);
     } else {
       for (size_t *region : {&lo->kvc, &lo->h, &lo->c6, &lo->cond}) *region += more;
@@ -538,13 +540,10 @@ int ddit_attn_fwd(ddit_attn_kind kind, const ddit_shape *shape, const void *q, c
                        lse_or_null, reinterpret_cast<hipStream_t>(hip_stream));
 }
 
-int ddit_stdit_block_fwd(const ddit_shape *shape, const ddit_block_weights *weights, const void *x_in,
-                         const void *y, const int32_t *y_valid_len_host, const float *c6, void *x_out,
-                         void *workspace, size_t workspace_bytes, void *hip_stream) {
-  Dims d;
-  DDIT_TRY(check_shape(shape, &d));
-  Layout lo;
-  make_layout(d, shape->flags, &lo);
+// One block in a workspace laid out as `lo`
+static int block_fwd(const ddit_shape *shape, const Dims &d, const Layout &lo, const ddit_block_weights *weights, const void *x_in,
+                     const void *y, const int32_t *y_valid_len_host, const float *c6, void *x_out, void *workspace,
+                     size_t workspace_bytes, void *hip_stream) {
   if (!weights || !c6) { set_error("weights and c6 must not be NULL"); return DDIT_ERR_INVALID_ARG; }
   if (!aligned16(c6)) { set_error("c6 must be 16-byte aligned"); return DDIT_ERR_ALIGNMENT; }
   DDIT_TRY(check_common(d, lo, x_in, y, x_out, workspace, workspace_bytes));
@@ -565,6 +564,16 @@ int ddit_stdit_block_fwd(const ddit_shape *shape, const ddit_block_weights *weig
   return finish_stream(d, x, pending, x_out, s);
 }
 
+int ddit_stdit_block_fwd(const ddit_shape *shape, const ddit_block_weights *weights, const void *x_in,
+                         const void *y, const int32_t *y_valid_len_host, const float *c6, void *x_out,
+                         void *workspace, size_t workspace_bytes, void *hip_stream) {
+  Dims d;
+  DDIT_TRY(check_shape(shape, &d));
+  Layout lo;
+  make_layout(d, shape->flags, &lo);
+  return block_fwd(shape, d, lo, weights, x_in, y, y_valid_len_host, c6, x_out, workspace, workspace_bytes, hip_stream);
+}
+
 int ddit_stdit_block_fwd_static(const ddit_shape *shape, const ddit_block_weights *weights, const void *x_in,
                                 const void *y, const int32_t *y_valid_len_host, const float *c6, void *x_out,
                                 void *hip_stream) {
@@ -574,7 +583,7 @@ int ddit_stdit_block_fwd_static(const ddit_shape *shape, const ddit_block_weight
     set_error("ddit_stdit_block_fwd_static keeps no taps: clear DDIT_FLAG_TAPS"); return DDIT_ERR_UNSUPPORTED;
   }
   Layout lo;
-  make_layout(d, shape->flags, &lo);
+  make_layout(d, shape->flags, &lo, STATIC_SCRATCH_BYTES);
   if (lo.total > STATIC_SCRATCH_BYTES) {
     set_error("this shape needs %zu bytes of workspace; the built-in scratch of ddit_stdit_block_fwd_static holds %zu "
               "(use ddit_stdit_block_fwd with a caller-owned workspace)", lo.total, STATIC_SCRATCH_BYTES);
@@ -583,7 +592,7 @@ int ddit_stdit_block_fwd_static(const ddit_shape *shape, const ddit_block_weight
   void *ws = nullptr;
   DDIT_TRY(static_scratch(&ws));
   // nothing in the block's workspace has to start at zero: every region is written before it is read
-  return ddit_stdit_block_fwd(shape, weights, x_in, y, y_valid_len_host, c6, x_out, ws, STATIC_SCRATCH_BYTES, hip_stream);
+  return block_fwd(shape, d, lo, weights, x_in, y, y_valid_len_host, c6, x_out, ws, STATIC_SCRATCH_BYTES, hip_stream);
 }
 
 int ddit_timestep_conditioning(const ddit_shape *shape, const ddit_step_weights *weights,

@@ -884,6 +884,7 @@ constexpr TileModel TILES[N_TILES] = {
     {64, 64, 8, 8, 0.219f, {0.89f, 1.35f, 2.54f}, 0.069f, 0.39f},
 };
 constexpr float LAUNCH_US = 2.71f;
+constexpr int CHIP_CUS = 256;
 constexpr int FIRST_PARTIAL_TILE = 4;   // tiles compiled for partial sums: this one and the smaller ones
 constexpr float PARTIAL_SUM_US = 6.4f, PARTIAL_SUM_US_PER_PART = 1.0f;   // what adding them up later costs
 
@@ -1020,8 +1021,9 @@ int launch_gemm_grouped(const GemmArgs &a, int G, const void *const *W, const vo
 // sum costs elsewhere fits 6.4 us + 1 us a part at 48 .. 3072 tokens x 1152 (standard error 1.9 us).  Beyond that
 // range its traffic counts and it is not tried.
 // A third part gains most below 2 M elements, and only there is the room for it small.
+// The answer sizes workspaces, so it depends on the shape alone: priced for the whole chip whatever device is current.
 int gemm_partial_choice(int64_t N, int n, int k, int max_parts, int *tile_out) {
-  const int cus = device_cus(), steps = (k + BK - 1) / BK;
+  const int cus = CHIP_CUS, steps = (k + BK - 1) / BK;
   const int most = N * (int64_t)n <= (int64_t)2 << 20 ? max_parts : N * (int64_t)n <= (int64_t)4 << 20 ? std::min(max_parts, 2) : 0;
   float best = predicted_us(cheapest_tile(2, N, n, k, cus), 2, N, n, k, cus);
   int chosen = 0;

@@ -349,3 +349,18 @@ def test_text_projections_of_every_even_head_split_are_grouped(m):
     for H in range(2, 33, 2):
         for dh in (64, 72):
             assert any(2 * H * dh % c == 0 for c in cols), (H, dh)
+
+
+def test_workspace_depends_on_the_shape_alone(m):
+    """A layer's fc2 is split the same way whatever else the workspace holds: a step of 28 blocks differs from one block by
+    the text k|v of its layers and nothing else (one rank's share of a head split, where the parts need room)."""
+    for H, T, S in ((4, 4, 650), (4, 2, 1240), (2, 4, 600), (4, 1, 1000), (16, 2, 900)):
+        D, Ly = 1152, 300
+        ws = lambda blocks: m.ddit_workspace_bytes(m.make_shape(1, T, 1, S, D, H, 72, 4608, Ly, blocks))
+        layer = Ly * 2 * H * 72 * 2
+        up = lambda b: (b + 255) & ~255
+        assert ws(28) - ws(1) == up(56 * layer) - up(2 * layer), (H, T, S)
+        # what the parts add is bounded
+        N = T * S
+        plain = sum(up(b) for b in (N * D * 4, N * D * 2, N * 3 * H * 72 * 2, N * H * 72 * 2, 2 * layer, N * 4608 * 2, 6 * D * 4, (256 + 2 * D) * 4))
+        assert 0 <= ws(1) - plain <= 25 << 20

@@ -66,3 +66,43 @@ def test_taps_show_what_an_untapped_step_runs(B, T, Hp, Wp, D, H, dh, M, parts):
     assert torch.equal(out[0].view(torch.int16), out[1].view(torch.int16))
     last = m.read_tap(shape, ws, 1, "x_out").reshape(sh.N, D)
     assert torch.equal(last.to(torch.bfloat16).view(torch.int16), out[1].view(torch.int16))
+
+
+def test_workspace_query_touches_no_device():
+    """The query in a process of its own opens no GPU: a parent that forks its workers may ask first."""
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    code = ("import os, paper_2506_13497_amd as m\n"
+            "fds = lambda: sum('kfd' in os.readlink('/proc/self/fd/' + f) for f in os.listdir('/proc/self/fd') if os.path.exists('/proc/self/fd/' + f))\n"
+            "before = fds()\n"
+            "m.ddit_workspace_bytes(m.make_shape(1, 16, 9, 16, 1152, 16, 72, 4608, 300, 28))\n"
+            "print('opened', fds() - before)\n")
+    r = subprocess.run([sys.executable, "-c", code], cwd=root, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and "opened 0" in r.stdout, r.stdout + r.stderr
+
+
+@pytest.mark.parametrize("n_blocks", [1, 28])
+def test_static_scratch_takes_the_parts_that_fit(n_blocks):
+    """One rank's share at 2500 tokens: with one block's text the two parts of fc2 fit the built-in scratch, with 28
+    blocks' they do not and fc2 adds in one launch; both match the oracle, as the caller-owned workspace does."""
+    import paper_2506_13497_amd as m
+    B, T, Hp, Wp, D, H, dh, M, Ly = 1, 4, 25, 25, 1152, 4, 72, 4608, 300
+    sh = syn.Shape(B, T, Hp, Wp, D, H, dh, M, Ly, n_blocks)
+    shape = m.make_shape(B, T, Hp, Wp, D, H, dh, M, Ly, n_blocks)
+    assert (m.ddit_workspace_bytes(shape) > 64 << 20) == (n_blocks == 28)
+    w = syn.make_block_weights(sh, 57, 0, table_std=0.1)
+    act, c6 = syn.make_activations(sh, 57), syn.make_c6(sh, 57, 0.5)
+    dw = dict_dev(w)
+    bw = m.block_struct(dw)
+    x, y, dc6 = to_dev(act["x"]), to_dev(act["y"]), to_dev(c6)
+    ref = ora.block_fwd(to_f64(act["x"]), to_f64(act["y"]), None, to_f64(c6), dict_f64(w), H, dh)
+    ws = m.alloc_workspace(shape)
+    ws.fill_(0xFF)
+    for call in (lambda o: m.ddit_stdit_block_fwd(shape, bw, x, y, None, dc6, o, ws),
+                 lambda o: m.ddit_stdit_block_fwd_static(shape, bw, x, y, None, dc6, o)):
+        out = torch.empty((B, T, sh.S, D), dtype=torch.bfloat16, device="cuda")
+        call(out)
+        torch.cuda.synchronize()
+        assert_parity(dev_to_f64(out), ref, "block, %d blocks' text" % n_blocks)
