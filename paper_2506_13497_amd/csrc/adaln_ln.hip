@@ -140,12 +140,17 @@ void launch_ln(float *x, const float *tab, const float *c6, int which, int64_t N
   // A wavefront with a second row hides its latency behind the first one's reductions; below 8192 rows there are
   // not four wavefronts per SIMD and the second row only makes the launch longer.  D = 1152, 1 / 2 rows: 256 rows
   // 3.5 / 4.8 us, 2304 rows 5.6 / 6.2 us, 12960 rows 19.6 / 19.8 us, 48600 rows 53.1 / 50.1 us (6.7 TB/s).
-  // A stream too large for the memory-side cache is read past the L2, which keeps other launches' weights.
+  // Wider rows fill the registers by themselves, and a second one takes away wavefronts (D = 2048, 1 / 2 rows: 12960 rows
+  // 28.5 / 29.8 us, 48600 92.3 / 94.4; D = 4096: 12960 55.8 / 71.9, 48600 196 / 231).
+  // A stream too large for the memory-side cache is read past the L2, which keeps other launches' weights, and past
+  // that cache, which keeps what is read again (plain / streaming: 20000 rows of 1280, 26 M elements, 31.6 / 26.6 us;
+  // 12960 of 2048, 27 M, 33.9 / 28.5; 108000 of 256, 28 M, 40.8 / 36.2; 20000 of 1152, 23 M, 25.1 / 24.5).
+  constexpr int ROWS = CHUNKS <= 5 ? 2 : 1;
   const PendingSum none = {0, nullptr, 0, nullptr, nullptr, 0};
   if (pend && pend->parts > 0) launch_ln<CHUNKS, 1, false, true>(x, tab, c6, which, N, tps, D, eps, o, *pend, s);
   else if (N < 8192) launch_ln<CHUNKS, 1, false, false>(x, tab, c6, which, N, tps, D, eps, o, none, s);
-  else if (N * (int64_t)D <= (int64_t)24 << 20) launch_ln<CHUNKS, 2, false, false>(x, tab, c6, which, N, tps, D, eps, o, none, s);
-  else launch_ln<CHUNKS, 2, true, false>(x, tab, c6, which, N, tps, D, eps, o, none, s);
+  else if (N * (int64_t)D <= (int64_t)24 << 20) launch_ln<CHUNKS, ROWS, false, false>(x, tab, c6, which, N, tps, D, eps, o, none, s);
+  else launch_ln<CHUNKS, ROWS, true, false>(x, tab, c6, which, N, tps, D, eps, o, none, s);
 }
 
 int launch_modulated_layernorm(float *x, const float *ada_table, const float *c6, int which, int64_t N,
@@ -155,6 +160,7 @@ int launch_modulated_layernorm(float *x, const float *ada_table, const float *c6
   bf16_t *o = reinterpret_cast<bf16_t *>(out);
   if (D <= 256 * 2) launch_ln<2>(x, ada_table, c6, which, N, tokens_per_sample, D, eps, o, pending, s);
   else if (D <= 256 * 5) launch_ln<5>(x, ada_table, c6, which, N, tokens_per_sample, D, eps, o, pending, s);
+  else if (D <= 256 * 8) launch_ln<8>(x, ada_table, c6, which, N, tokens_per_sample, D, eps, o, pending, s);
   else if (D <= 256 * 16) launch_ln<16>(x, ada_table, c6, which, N, tokens_per_sample, D, eps, o, pending, s);
   else {
     set_error("D=%d: hidden size above 4096 is not supported by the LayerNorm kernel", D);
