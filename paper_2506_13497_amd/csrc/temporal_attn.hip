@@ -50,7 +50,6 @@ struct TCfg {
   static constexpr int DCH = DH / 8;                 // 16-byte chunks per head row
   static constexpr int RCH = HG * DCH;               // chunks per LDS row (four heads)
   static constexpr int PITCH = RCH * 16 + 16;        // +16 B: 16 consecutive rows hit 16 different bank groups
-  static constexpr int OPT_BYTES = TP * (DH / 2) * 8 + 2 * DH * 4;   // OPTS: angles and scales
   static constexpr int KS = (DH + 15) / 16;          // k-steps of Q K^T
   static constexpr int DT = (DH + 31) / 32;          // 32-row tiles of V^T
   static_assert((PITCH / 16) % 2 == 1, "odd pitch in 16-byte units keeps the reads conflict-free");
@@ -61,11 +60,15 @@ __device__ __forceinline__ void wg_barrier() { asm volatile("s_waitcnt vmcnt(0) 
 // OPTS: q and k are RMS-normalised per head and rotated by their frame's angles after they have
 // landed in LDS (every sequence is loaded exactly once here, so this costs no memory traffic):
 // one thread per (operand, row, head), two passes over its d_h elements, fp32 arithmetic,
-// one rounding back to bf16; scales and the (cos, sin) rows of the T frames sit in LDS beside the operands.
-template <int DH, bool OPTS>
+// one rounding back to bf16.  Scales and the (cos, sin) rows of the T frames, 9 KB that all workgroups share, are read
+// from cache into registers ahead of their use: a copy in LDS beside the operands let only two workgroups of T = 30
+// onto a CU (T = 30, LDS / registers: 1620 locations, 16 heads 166 / 122 us; 3600, 4 heads 99 / 73; read where they are
+// used, without the lead: 149 and 82, and short clips 5 % longer).
+// PACK: more than one location per workgroup.
+template <int DH, bool OPTS, bool PACK>
 __global__ __launch_bounds__(256, 3) void k_temporal_attn(TemporalParams p) {
   using C = TCfg<DH>;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // Q, K, V: R rows each; OPTS: angles, scales
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // Q, K, V: R rows each
   const int R = p.R, MAT = R * C::PITCH;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l32 = lane & 31, lh = lane >> 5;
@@ -82,11 +85,24 @@ __global__ __launch_bounds__(256, 3) void k_temporal_attn(TemporalParams p) {
   const int64_t tok0 = (int64_t)b * p.T * p.S + s0;           // token of row 0
   const int n_loc = p.S - s0 < p.P ? p.S - s0 : p.P;          // locations of this pack that exist
   const int rows = n_loc * p.T;
-  auto loc_of = [&](int r) { return (int)(((float)r + 0.5f) * p.inv_T); };
+  auto loc_of = [&](int r) { return PACK ? (int)(((float)r + 0.5f) * p.inv_T) : 0; };
   auto row_token = [&](int r) {                               // row r = (location r / T, frame r % T)
     const int j = loc_of(r);
     return tok0 + j + (int64_t)(r - j * p.T) * p.S;
   };
+
+  // OPTS: (operand, row, head) of this thread's treatment (R <= 32 and four heads: at most 256); its angles are on
+  // their way before the operands
+  const int t_hh = tid & 3, t_r = (tid >> 2) % TP, t_mat = tid / (4 * TP);
+  const bool treats = OPTS && t_mat < 2 && t_r < rows && t_hh < nh;
+  float4 ang[OPTS ? DH / 4 : 1];    // two (cos, sin) pairs each
+  if constexpr (OPTS) {
+    if (treats && p.rope) {
+      const float4 *cs = reinterpret_cast<const float4 *>(p.rope) + (t_r - loc_of(t_r) * p.T) * (DH / 4);
+#pragma unroll
+      for (int c = 0; c < DH / 4; ++c) ang[c] = cs[c];
+    }
+  }
 
   // ---- operands -> LDS: the chunks of the existing locations and heads, zeros in the other rows.
   // All of a thread's loads are issued before the first one is used.
@@ -115,16 +131,15 @@ __global__ __launch_bounds__(256, 3) void k_temporal_attn(TemporalParams p) {
       if (dst[i] >= 0) *reinterpret_cast<uint4 *>(smem + dst[i]) = val[i];
   }
   if constexpr (OPTS) {
-    float2 *tab = reinterpret_cast<float2 *>(smem + 3 * MAT);
-    float *gs = reinterpret_cast<float *>(smem + 3 * MAT + TP * (DH / 2) * 8);
-    if (p.rope)
-      for (int m = tid; m < p.T * (DH / 2); m += 256) tab[m] = p.rope[m];
-    if (tid < 2 * DH) gs[tid] = p.g_q ? (float)(tid < DH ? p.g_q[tid] : p.g_k[tid - DH]) : 1.0f;
+    bf16x8 gain[C::DCH];   // in the registers that the operands have left
+    if (treats && p.g_q) {
+      const bf16x8 *g = reinterpret_cast<const bf16x8 *>(t_mat == 0 ? p.g_q : p.g_k);
+#pragma unroll
+      for (int c = 0; c < C::DCH; ++c) gain[c] = g[c];
+    }
     wg_barrier();
-    // (operand, row, head) -> thread; R <= 32 and four heads: at most 256
-    const int hh = tid & 3, r = (tid >> 2) % TP, mat = tid / (4 * TP);
-    if (mat < 2 && r < rows && hh < nh) {
-      unsigned char *row = smem + mat * MAT + r * C::PITCH + hh * (DH * 2);
+    if (treats) {
+      unsigned char *row = smem + t_mat * MAT + t_r * C::PITCH + t_hh * (DH * 2);
       float rinv = 1.0f;
       if (p.g_q) {
         float ss = 0.f;
@@ -136,21 +151,25 @@ __global__ __launch_bounds__(256, 3) void k_temporal_attn(TemporalParams p) {
         }
         rinv = rsqrtf(ss * (1.0f / DH) + p.norm_eps);
       }
-      const float *g = gs + mat * DH;
-      const float2 *cs = tab + (r - loc_of(r) * p.T) * (DH / 2);
 #pragma unroll
       for (int c = 0; c < C::DCH; ++c) {
         bf16x8 v = *reinterpret_cast<const bf16x8 *>(row + c * 16);
         float f[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) f[e] = (float)v[e] * rinv * g[c * 8 + e];
+        for (int e = 0; e < 8; ++e) f[e] = (float)v[e] * rinv;
+        if (p.g_q) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) f[e] *= (float)gain[c][e];
+        }
         if (p.rope) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const float2 a = cs[c * 4 + j];
-            const float x0 = f[2 * j], x1 = f[2 * j + 1];
-            f[2 * j] = x0 * a.x - x1 * a.y;
-            f[2 * j + 1] = x1 * a.x + x0 * a.y;
+          for (int j = 0; j < 2; ++j) {
+            const float4 a = ang[c * 2 + j];
+            const float x0 = f[4 * j], x1 = f[4 * j + 1], x2 = f[4 * j + 2], x3 = f[4 * j + 3];
+            f[4 * j] = x0 * a.x - x1 * a.y;
+            f[4 * j + 1] = x1 * a.x + x0 * a.y;
+            f[4 * j + 2] = x2 * a.z - x3 * a.w;
+            f[4 * j + 3] = x3 * a.z + x2 * a.w;
           }
         }
 #pragma unroll
@@ -190,7 +209,7 @@ __global__ __launch_bounds__(256, 3) void k_temporal_attn(TemporalParams p) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int key = 8 * (r >> 2) + 4 * lh + (r & 3);
-      if ((unsigned)(key - first) >= (unsigned)p.T) sc[r] = -INFINITY;
+      if (PACK ? (unsigned)(key - first) >= (unsigned)p.T : key >= p.T) sc[r] = -INFINITY;
       mx = fmaxf(mx, sc[r]);
     }
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
@@ -231,7 +250,7 @@ __global__ __launch_bounds__(256, 3) void k_temporal_attn(TemporalParams p) {
       }
     };
     pv(oacc, 0, R);
-    if (p.P > 1) {
+    if constexpr (PACK) {
       // A probability of zero times another location's infinity or NaN is a NaN that does not belong here: where a
       // result is not finite, the locations are multiplied one by one.
       bool finite = true;
@@ -291,15 +310,13 @@ int launch_t(const TemporalParams &p, hipStream_t s) {
   const int64_t blocks = ((packs + 7) / 8) * p.n_hg * 8;
   if (blocks > 0x7fffffff) { ddit::set_error("temporal attention: too many workgroups"); return -2; }
   const unsigned lds = 3u * p.R * TCfg<DH>::PITCH;
-  static bool attr_set = false;   // benign race: the attribute is idempotent
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_temporal_attn<DH, true>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 3 * TP * TCfg<DH>::PITCH + TCfg<DH>::OPT_BYTES);
-    if (e != hipSuccess) return ddit::hip_fail(e, "temporal attention hipFuncSetAttribute");
-    attr_set = true;
+  if (opts) {
+    if (p.P > 1) hipLaunchKernelGGL((k_temporal_attn<DH, true, true>), dim3((unsigned)blocks), dim3(256), lds, s, p);
+    else hipLaunchKernelGGL((k_temporal_attn<DH, true, false>), dim3((unsigned)blocks), dim3(256), lds, s, p);
+  } else {
+    if (p.P > 1) hipLaunchKernelGGL((k_temporal_attn<DH, false, true>), dim3((unsigned)blocks), dim3(256), lds, s, p);
+    else hipLaunchKernelGGL((k_temporal_attn<DH, false, false>), dim3((unsigned)blocks), dim3(256), lds, s, p);
   }
-  if (opts) hipLaunchKernelGGL((k_temporal_attn<DH, true>), dim3((unsigned)blocks), dim3(256), lds + TCfg<DH>::OPT_BYTES, s, p);
-  else hipLaunchKernelGGL((k_temporal_attn<DH, false>), dim3((unsigned)blocks), dim3(256), lds, s, p);
   return ddit::hip_fail(hipGetLastError(), "temporal attention launch");
 }
 
@@ -328,7 +345,17 @@ int launch_temporal_attn(const void *q, const void *k, const void *v, void *o, f
   // 3680 tokens, T = 4: 24.8 / 12.9 (q/k treated: 34.1 / 13.6), 7360, T = 8: 29.4 / 20.7, 4050, T = 10: 16.4 / 15.0.
   // Above that a single location already keeps the loads coming, and more workgroups fit a CU: 2304, T = 16:
   // 10.2 / 11.9, 12960, T = 16: 33.3 / 35.4; T = 13: 21.9 / 20.0, treated 27.3 / 30.7.
-  p.P = T <= 10 ? std::min(TP / T, S) : 1;
+  // But never fewer workgroups than CUs for it: where that many packs are not to be had, the power of two below (1, what
+  // is taken / as many as the tile holds): 16 heads, T = 2, 144 locations 9.1, 9.1 / 10.6, 405 locations 15.0, 9.4 / 10.7;
+  // 4 heads, T = 2, 144 locations 8.6, 8.6 / 10.5, 405 8.4, 8.4 / 10.6, T = 4, 920 11.9, 9.6 / 10.9, T = 8, 144 9.4,
+  // 9.4 / 10.6.
+  p.P = 1;
+  if (T <= 10) {
+    const int most = std::min(TP / T, S);
+    const int64_t per_cu = (int64_t)B * S * p.n_hg / device_cus();
+    if (per_cu >= most) p.P = most;
+    else while (2 * p.P <= per_cu) p.P *= 2;
+  }
   p.R = p.P * T;
   p.n_packs = (S + p.P - 1) / p.P;
   p.inv_T = 1.0f / (float)T;
