@@ -123,49 +123,148 @@ def dop_table(m, syn, torch, steps):
     return rows
 
 
-# the model's linears (hidden 1152, MLP 4608): name, epilogue, out-features, in-features
-SWEEP_LINEARS = [("qkv", 0, 3456, 1152), ("attn_out", 2, 1152, 1152), ("fc1", 1, 4608, 1152), ("fc2", 2, 1152, 4608),
-                 ("cross_q", 0, 1152, 1152), ("cross_kv", 0, 2304, 1152)]
-SWEEP_TOKENS = [288, 576, 920, 1215, 1840, 2304, 2880, 3240, 3680, 4320, 4860, 5760, 6480, 7360, 8640, 9720, 11520, 12960,
-                14400, 19440, 24300, 36000, 48600]
+# Layers of the sweep: hidden width, heads of this rank, head width, MLP width.  The model's, one rank's of a two-, four-
+# and eight-way head split, and a narrow and a wide one.
+SWEEP_LAYERS = [(1152, 16, 72, 4608), (1152, 8, 72, 4608), (1152, 4, 72, 4608), (1152, 2, 72, 4608), (256, 4, 64, 1024),
+                (2048, 32, 64, 8192)]
+SWEEP_FRAMES = 4
+# locations per frame: three token counts an octave from 96 to 100 thousand, none of them a latent's
+SWEEP_LOCATIONS = [int(round(24 * 2 ** (i / 3.0))) + (5 * i) % 7 for i in range(31)]
 
 
-def tile_sweep(m, torch, tokens):
-    """Every compiled output tile of the linear forced in turn (ddit_linear_fwd_tile) on the model's linears over a
-    range of token counts, beside the launcher's own pick: the table the launcher's cost model was fitted to."""
+def tile_sweep(m, torch):
+    """Every compiled output tile of the linear forced in turn (ddit_linear_fwd_tile), beside the launcher's own pick: what the
+    launcher's cost model is fitted to (--tile-fit).  Each pass issues a whole layer in a step's order, every linear with the
+    pass's tile and with weights that no earlier pass left in a cache, so operands and the residual stream are where the
+    launches before leave them; one event pair per linear, passes of all tiles in turn, median of nine."""
     count = m.ddit_linear_tile_count()
     tiles = [m.ddit_linear_tile_info(t) for t in range(count)]
     print("tiles: " + "  ".join("%d=%dx%d" % (i, t["rows"], t["cols"]) for i, t in enumerate(tiles)))
-    print("%-9s %6s %5s %8s | " % ("linear", "N", "pick", "pick_us") + " ".join("%7s" % ("t%d_us" % i) for i in range(count))
-          + " | pick/best")
+    print("linear epi n k N pick pick_us | " + " ".join("t%d_us" % i for i in range(count)) + " | pick/best")
     torch.manual_seed(0)
-    tab, c6 = torch.randn(6, 1152, device="cuda"), torch.randn(1, 6 * 1152, device="cuda")
+    pool = torch.empty(1 << 28, device="cuda", dtype=torch.bfloat16).normal_(0.0, 0.03)   # twice the memory-side cache
+    ahead = torch.zeros(1 << 28, device="cuda")
     ratios = []
-    for N in tokens:
-        for name, epi, n, k in SWEEP_LINEARS:
-            u, W = (torch.randn(N, k, device="cuda") * 0.5).bfloat16(), (torch.randn(n, k, device="cuda") * 0.03).bfloat16()
-            bias, out = torch.randn(n, device="cuda").bfloat16(), torch.empty(N, n, device="cuda", dtype=torch.bfloat16)
-            resid = torch.zeros(N, n, device="cuda") if epi == 2 else None
+    for D, H, dh, M in SWEEP_LAYERS:
+        A, at = H * dh, [0]
 
-            def timed(tile):
-                call = lambda: m.ddit_linear_fwd_tile(tile, epi, u, k, W, bias, N, n, k, None if epi == 2 else out, n, resid=resid,
-                                                      ada_table=tab if epi == 2 else None, c6=c6 if epi == 2 else None,
-                                                      gate_row=2 if epi == 2 else -1, tokens_per_sample=N)
-                for _ in range(3):
-                    call()
-                e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-                e0.record()
-                for _ in range(20):
-                    call()
-                e1.record()
-                e1.synchronize()
-                return e0.elapsed_time(e1) / 20 * 1000.0
-            us = [timed(t) for t in range(count)]
-            pick, pick_us = m.ddit_linear_tile_choice(epi, N, n, k)[0], timed(-1)
-            ratios.append(pick_us / min(us))
-            print("%-9s %6d %5d %8.1f | " % (name, N, pick, pick_us) + " ".join("%7.1f" % x for x in us)
-                  + " | %.2f" % ratios[-1], flush=True)
+        def fresh(n, k):
+            if at[0] + n * k > pool.numel():
+                at[0] = 0
+            at[0] += n * k
+            return pool[at[0] - n * k:at[0]].view(n, k)
+        bias = torch.randn(max(3 * A, M, D), device="cuda").bfloat16()
+        tab, c6 = torch.randn(6, D, device="cuda") * 0.1, torch.randn(1, 6 * D, device="cuda") * 0.1
+        kvc = torch.randn(300, 2 * A, device="cuda").bfloat16()
+        for S in SWEEP_LOCATIONS:
+            N = SWEEP_FRAMES * S
+            if N * max(3 * A, M) * 2 > 1 << 30:
+                continue
+            shape = m.make_shape(1, SWEEP_FRAMES, 1, S, D, H, dh, M, 300, 1)
+            x32 = torch.randn(N, D, device="cuda")
+            xh, h = torch.empty(N, D, dtype=torch.bfloat16, device="cuda"), torch.empty(N, M, dtype=torch.bfloat16, device="cuda")
+            qkv, o = torch.empty(N, 3 * A, dtype=torch.bfloat16, device="cuda"), torch.empty(N, A, dtype=torch.bfloat16, device="cuda")
+            linears = (("qkv", 0, 3 * A, D), ("attn_out", 2 | m.DDIT_EPI_COPY, D, A), ("cross_q", 0, A, D), ("cross_out", 2, D, A), ("fc1", 1, M, D), ("fc2", 2, D, M))
+
+            def layer(tile, events):
+                def lin(i, u, out, ld_out, gate):
+                    name, epi, n, k = linears[i]
+                    epi &= 3
+                    W = fresh(n, k)
+                    events[i][0].record()
+                    m.ddit_linear_fwd_tile(tile, epi, u, k, W, bias[:n], N, n, k, out, ld_out, resid=x32 if epi == 2 else None,
+                                           ada_table=tab if gate >= 0 else None, c6=c6 if gate >= 0 else None, gate_row=gate,
+                                           tokens_per_sample=N)
+                    events[i][1].record()
+                attn = lambda kind, k_, v_, ld: m.ddit_attn_fwd(kind, shape, qkv[:, :A], k_, v_, 3 * A, ld, None, o, A)
+                m.ddit_modulated_layernorm_fwd(x32, tab, c6, 0, N, 1e-6, xh)
+                lin(0, xh, qkv, 3 * A, -1)
+                attn(m.DDIT_ATTN_TEMPORAL, qkv[:, A:2 * A], qkv[:, 2 * A:], 3 * A)
+                lin(1, o, xh, D, 2)
+                lin(2, xh, qkv, 3 * A, -1)
+                attn(m.DDIT_ATTN_CROSS, kvc[:, :A], kvc[:, A:], 2 * A)
+                lin(3, o, None, 0, -1)
+                m.ddit_modulated_layernorm_fwd(x32, tab, c6, 1, N, 1e-6, xh)
+                lin(4, xh, h, M, -1)
+                lin(5, h, None, 0, 5)
+            passes = list(range(count)) + [-1]
+            pair = lambda: (torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True))
+            events = [[[pair() for _ in linears] for _ in passes] for _ in range(10)]
+            for r in range(10):
+                x32.normal_()
+                for p, tile in enumerate(passes):
+                    if N < 16000:
+                        ahead.add_(1.0)   # half a millisecond in which the host gets ahead: the launches then follow each other
+                    layer(tile, events[r][p])
+            torch.cuda.synchronize()
+            for i, (name, epi, n, k) in enumerate(linears):
+                if A < D and i > 3:
+                    continue                    # the whole layer's rows have them
+                us = [sorted(events[r][p][i][0].elapsed_time(events[r][p][i][1]) * 1000.0 for r in range(1, 10))[4] for p in range(len(passes))]
+                pick = m.ddit_linear_tile_choice(epi, N, n, k)[0]
+                ratios.append(us[pick] / min(us[:count]))
+                print("%s %d %d %d %d %d %.1f | " % (name, epi, n, k, N, pick, us[-1]) + " ".join("%.1f" % x for x in us[:count])
+                      + " | %.2f" % ratios[-1], flush=True)
+            del x32, xh, h, qkv, o
     print("rows %d; pick / best: mean %.3f, worst %.2f" % (len(ratios), sum(ratios) / len(ratios), max(ratios)))
+
+
+def read_tile_sweep(path):
+    """Rows (epilogue, out-features, in-features, tokens, [microseconds of each tile]) of a table that --tile-sweep printed,
+    and its tiles' (rows, cols)."""
+    rows, tiles = [], []
+    for line in open(path):
+        if line.startswith("tiles:"):
+            tiles = [tuple(int(x) for x in t.split("=")[1].split("x")) for t in line.split()[1:]]
+        part = line.split("|")
+        if len(part) == 3 and not line.startswith("linear"):
+            head = part[0].split()
+            rows.append((*(int(x) for x in head[1:5]), [float(x) for x in part[1].split()]))
+    return rows, tiles
+
+
+SWEEP_EVENT_US = 3.5    # what an event pair adds to a launch
+SWEEP_LAUNCH_US = 2.71  # the model's constant for a launch
+
+
+def tile_fit(path):
+    """The launcher's cost model fitted to a sweep: per tile a, e[4], s, f[2] by least squares in log time, where a row counts
+    with the square of how near the tile comes to the row's best one (a price far from being taken need not be right).
+    Fitted to every other token count and judged on the rest, then to all."""
+    import numpy as np
+    from scipy.optimize import least_squares
+    rows, tiles = read_tile_sweep(path)
+    epi, n, k, N = (np.array([r[i] for r in rows]) for i in range(4))
+    epi = np.where(epi & 16, 3, epi)          # DDIT_EPI_COPY
+    us = np.array([r[4] for r in rows])
+    best, steps = us.min(1), np.ceil(k / 64)
+    odd = np.searchsorted(np.unique(N), N) % 2 == 1
+
+    def price(c, t):
+        count = np.ceil(N / tiles[t][0]) * np.ceil(n / tiles[t][1])
+        full = np.minimum(1.0, count / 256)
+        one = c[0] * steps + np.choose(epi, c[1:5])
+        return one * np.ceil(count / 256) * (1.0 + c[5] * full) + np.where(epi >= 2, c[6 + (epi == 3)] * full, 0.0) + SWEEP_LAUNCH_US + SWEEP_EVENT_US
+
+    def fit(use):
+        out = []
+        for t in range(len(tiles)):
+            w = (best / us[:, t]) ** 2
+            start = [tiles[t][0] * tiles[t][1] / 73728 * 1.2, 2, 4, 10, 10, 0.2, 3, 3]
+            out.append(least_squares(lambda c: ((np.log(price(c, t)) - np.log(us[:, t])) * w)[use], start,
+                                     bounds=([0.01] + 7 * [0], [9] + 7 * [60]), loss="soft_l1", f_scale=0.05).x)
+        return out
+
+    def judge(c, use):
+        pick = np.stack([price(c[t], t) for t in range(len(tiles))], 1).argmin(1)
+        r = (us[np.arange(len(us)), pick] / best)[use]
+        return "pick / best: mean %.4f, worst %.2f" % (r.mean(), r.max())
+    half = fit(~odd)
+    print("fitted to every other token count, judged on the rest: " + judge(half, odd))
+    c = fit(odd | ~odd)
+    print("fitted to all: " + judge(c, odd | ~odd))
+    for t, (a, e0, e1, e2, e3, s, f2, f3) in enumerate(c):
+        print("{%d, %d, ..., %.3ff, {%.2ff, %.2ff, %.2ff, %.2ff}, %.3ff, {%.2ff, %.2ff}}" % (*tiles[t], a, e0, e1, e2, e3, s, f2, f3))
 
 
 class Workload:
@@ -340,7 +439,7 @@ class Workload:
         """The output tile the launcher's model takes for each linear of this workload (rows x cols)."""
         m, sh = self.m, self.sh
         out = {}
-        for name, epi, n, k in (("qkv", m.DDIT_EPI_BF16, 3 * sh.A, sh.D), ("attn_out", m.DDIT_EPI_RESIDUAL_F32, sh.D, sh.A),
+        for name, epi, n, k in (("qkv", m.DDIT_EPI_BF16, 3 * sh.A, sh.D), ("attn_out", m.DDIT_EPI_RESIDUAL_F32 | m.DDIT_EPI_COPY, sh.D, sh.A),
                                 ("cross_q", m.DDIT_EPI_BF16, sh.A, sh.D), ("fc1", m.DDIT_EPI_GELU_BF16, sh.M, sh.D),
                                 ("fc2", m.DDIT_EPI_RESIDUAL_F32, sh.D, sh.M)):
             tile, _ = m.ddit_linear_tile_choice(epi, sh.N, n, k)
@@ -421,6 +520,7 @@ def main():
                     help="time only this entry of 'stages' (for counter runs of one kernel), e.g. spatial_attention")
     ap.add_argument("--tile-sweep", action="store_true",
                     help="instead of the benchmark line: every compiled tile of the linear forced in turn, beside the launcher's pick")
+    ap.add_argument("--tile-fit", default=None, metavar="TABLE", help="fit the launcher's cost model to a table of --tile-sweep (needs no GPU)")
     ap.add_argument("--dop-table", action="store_true",
                     help="instead of the benchmark line: per-rank step time by resolution and degree of parallelism")
     args = ap.parse_args()
@@ -428,6 +528,10 @@ def main():
         print("bench.py: this build runs on ONE GPU (one rank's share of the step); --gpus %d is not supported"
               % args.gpus, file=sys.stderr)
         sys.exit(2)
+
+    if args.tile_fit:
+        tile_fit(args.tile_fit)
+        return
 
     import numpy as np
     import torch
@@ -438,7 +542,7 @@ def main():
     assert torch.cuda.is_available(), "bench.py needs a GPU"
     torch.cuda.set_device(0)
     if args.tile_sweep:
-        tile_sweep(m, torch, SWEEP_TOKENS)
+        tile_sweep(m, torch)
         return
     if args.dop_table:
         rows = dop_table(m, syn, torch, max(args.steps // 3, 2))

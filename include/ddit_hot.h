@@ -273,8 +273,10 @@ int ddit_linear_tile_info(int tile, int32_t *rows, int32_t *cols, int32_t *wavef
 
 /* The tile ddit_linear_fwd would take for this problem on a device of compute_units CUs
  * (compute_units <= 0: the current device's count, 256 if there is no device) -> *tile_out.
+ * epilogue: DDIT_EPI_RESIDUAL_F32 | DDIT_EPI_COPY for a residual update whose out is given.
  * predicted_us_host, if not NULL, is a HOST array of ddit_linear_tile_count() floats that
  * receives the model's time for every tile, in microseconds.  Host only; needs no GPU. */
+#define DDIT_EPI_COPY 16
 int ddit_linear_tile_choice(int epilogue, int64_t N, int32_t n, int32_t k, int32_t compute_units,
                             int32_t *tile_out, float *predicted_us_host);
 

@@ -19,6 +19,7 @@ DDIT_OK = 0
 DDIT_ERR_INVALID_ARG, DDIT_ERR_UNSUPPORTED, DDIT_ERR_WORKSPACE, DDIT_ERR_ALIGNMENT, DDIT_ERR_HIP = -1, -2, -3, -4, -5
 DDIT_ATTN_SPATIAL, DDIT_ATTN_TEMPORAL, DDIT_ATTN_CROSS = 0, 1, 2
 DDIT_EPI_BF16, DDIT_EPI_GELU_BF16, DDIT_EPI_RESIDUAL_F32 = 0, 1, 2
+DDIT_EPI_COPY = 16   # ddit_linear_tile_choice: a residual update that also writes bf16(x)
 DDIT_FLAG_TAPS, DDIT_FLAG_QK_NORM, DDIT_FLAG_ROPE_TEMPORAL = 1, 2, 4
 TAP_NAMES = ["xh_msa", "qkv", "o", "x_after_attn", "qc", "kvc", "oc", "x_after_cross", "xh_mlp", "h", "x_out"]
 _TAP_DTYPE = {"x_after_attn": torch.float32, "x_after_cross": torch.float32, "x_out": torch.float32}

@@ -86,7 +86,7 @@ int gemm_tile_count();
 int gemm_tile_info(int tile, int *rows, int *cols, int *wavefronts, int *wg_per_cu);
 // the tile the launcher would take (cus <= 0: the current device's CU count); us_per_tile, if not
 // null, receives the model's time for each of the gemm_tile_count() tiles
-int gemm_tile_choice(int epilogue, int64_t N, int n, int k, int cus, float *us_per_tile);
+int gemm_tile_choice(int epilogue, bool copy, int64_t N, int n, int k, int cus, float *us_per_tile);
 
 struct AttnArgs {
   const void *q, *k, *v; void *o; float *lse;

@@ -777,10 +777,12 @@ int ddit_linear_tile_info(int tile, int32_t *rows, int32_t *cols, int32_t *wavef
 
 int ddit_linear_tile_choice(int epilogue, int64_t N, int32_t n, int32_t k, int32_t compute_units, int32_t *tile_out,
                             float *predicted_us_host) {
+  const bool copy = epilogue == (DDIT_EPI_RESIDUAL_F32 | DDIT_EPI_COPY);
+  if (copy) epilogue = DDIT_EPI_RESIDUAL_F32;
   if (epilogue < 0 || epilogue > 2) { set_error("unknown epilogue %d", epilogue); return DDIT_ERR_INVALID_ARG; }
   if (N < 0 || n < 1 || k < 1) { set_error("linear: N=%lld n=%d k=%d", (long long)N, n, k); return DDIT_ERR_INVALID_ARG; }
   if (!tile_out) { set_error("tile_out is NULL"); return DDIT_ERR_INVALID_ARG; }
-  *tile_out = gemm_tile_choice(epilogue, N, n, k, compute_units, predicted_us_host);
+  *tile_out = gemm_tile_choice(epilogue, copy, N, n, k, compute_units, predicted_us_host);
   return DDIT_OK;
 }
 

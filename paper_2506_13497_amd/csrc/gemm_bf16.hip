@@ -847,18 +847,17 @@ int launch_one(const GemmParams &p0, hipStream_t s, const GT &gt = GT()) {
 // with a small model of the kernel and takes the cheapest.  With  tiles = ceil(N / rows) * ceil(n / cols),
 // q = ceil(tiles / CUs)  tiles on the busiest CU and  steps = ceil(k / 64),
 //     t = (a * steps + e[epilogue]) * q * (1 + s * min(1, tiles / CUs)) + 2.71      [microseconds]
-//         (+ f * min(1, tiles / CUs) for the residual update)
+//         (+ f[copy] * min(1, tiles / CUs) for the residual update)
 // a: one k-step; e: a tile's epilogue and set-up; s: the clock and memory slow-down of a full chip against a
 // single busy CU; f: what the first round's epilogues cost more, when all CUs reach the memory-bound phase
-// together; the rest is the launch.  The constants are a least-squares fit (in log time) to a sweep of
-// eleven linears (the model's at hidden 1152 and 256, one rank's of a four-way head split, the caption
-// embedder's) over 44 token counts from 16 to 48600 with every tile forced in turn and the weights coming
-// from HBM, as they do in a step: over that sweep the picks cost 1.1 % more than the best tile everywhere.
-// The residual epilogue of the largest tile is set by a sweep that leaves the stream where the launch before
-// put it, as a step does: fitted with the stream evicted it looked a third slower than it is, and the
-// out-projections (k = 1152) of 48600 tokens went to 256 x 128 (212 us; 192 x 384: 166), of 14400 to 128 x 192
-// (65; 51).  480p step 136.6 -> 133.2 ms, 720p share 213.6 -> 211.0.  The other tiles' constants stay: set the same
-// way they moved 12960 tokens to 256 x 256, and the batch-2 240p step from 38.3 to 38.5 ms.
+// together; the rest is the launch.  The constants are a least-squares fit (in log time; bench.py --tile-fit) to a sweep
+// (bench.py --tile-sweep, kept in profiles/gemm_tile_sweep.txt) of whole layers with every tile forced in turn, so that
+// operands, weights and the residual stream are where a step leaves them: hidden 1152 with 16, 8, 4 and 2 heads of 72, 256
+// and 2048, 31 token counts from 96 to 98316, twice.  Over that sweep the picks cost 0.5 % more than the best tile
+// everywhere, 1.15 times at worst (1.1 % and 1.29 with constants that had been fitted to launches with everything evicted),
+// and as much on the token counts that a fit to every other one has not seen.  The residual update that also writes
+// bf16(x) has constants of its own: at 12288 tokens, 1152 x 288, the largest tile takes 52.2 us with the copy and 31.6
+// without, 256 x 128 39.6 and 35.1.
 // Nine are the ones, of fourteen that were swept, that lose least against all fourteen (0.6 % of a layer); 192 x 288 is
 // for widths that are multiples of 288 and of nothing wider, the projections of head splits with 2, 6, 10 or 14 heads of
 // 72: the grouped text projections need a tile that divides a problem's columns (launch_gemm_grouped).
@@ -866,27 +865,29 @@ int launch_one(const GemmParams &p0, hipStream_t s, const GT &gt = GT()) {
 struct TileModel {
   int rows, cols, wavefronts, stages;   // stages: depth of the operand ring in LDS
   float a;        // microseconds per k-step of 64
-  float e[3];     // epilogue + set-up microseconds: bf16 / GELU / gated residual
+  float e[4];     // epilogue + set-up microseconds: bf16 / GELU / gated residual / gated residual with the bf16 copy
   float s;        // slow-down of a full chip
-  float f;        // once per launch, residual update
+  float f[2];     // once per launch, residual update without / with the copy
 };
 constexpr int N_TILES = 10;
 constexpr TileModel TILES[N_TILES] = {
-    {192, 384, 8, 2, 1.219f, {3.82f, 7.11f, 17.5f}, 0.249f, 14.0f},
-    {256, 256, 8, 2, 1.137f, {2.85f, 6.48f, 21.69f}, 0.248f, 7.58f},
-    {192, 288, 6, 2, 1.06f, {3.2f, 6.0f, 14.0f}, 0.2f, 11.0f},
-    {192, 256, 8, 2, 1.009f, {2.11f, 5.02f, 15.09f}, 0.147f, 9.81f},
-    {256, 128, 8, 3, 0.546f, {1.67f, 3.18f, 7.93f}, 0.451f, 0.00f},
-    {128, 192, 8, 3, 0.506f, {1.43f, 2.44f, 6.26f}, 0.357f, 0.00f},
-    {128, 128, 8, 4, 0.364f, {1.65f, 2.66f, 5.52f}, 0.298f, 0.19f},
-    {64, 192, 8, 4, 0.368f, {1.37f, 2.97f, 5.28f}, 0.129f, 0.00f},
-    {64, 128, 8, 6, 0.283f, {1.30f, 2.17f, 3.72f}, 0.115f, 0.23f},
-    {64, 64, 8, 8, 0.219f, {0.89f, 1.35f, 2.54f}, 0.069f, 0.39f},
+    {192, 384, 8, 2, 1.277f, {4.46f, 6.06f, 13.92f, 17.05f}, 0.310f, {1.30f, 17.05f}},
+    {256, 256, 8, 2, 1.114f, {4.21f, 5.43f, 12.17f, 15.78f}, 0.340f, {1.94f, 11.88f}},
+    {192, 288, 6, 2, 1.192f, {4.27f, 5.97f, 11.16f, 15.29f}, 0.213f, {3.66f, 12.91f}},
+    {192, 256, 8, 2, 1.023f, {3.38f, 4.12f, 9.02f, 12.22f}, 0.220f, {2.78f, 8.91f}},
+    {256, 128, 8, 3, 0.622f, {2.24f, 2.72f, 6.98f, 8.83f}, 0.370f, {0.13f, 0.00f}},
+    {128, 192, 8, 3, 0.542f, {2.04f, 2.56f, 5.51f, 7.77f}, 0.294f, {0.00f, 0.00f}},
+    {128, 128, 8, 4, 0.442f, {2.11f, 2.66f, 4.77f, 6.63f}, 0.187f, {0.03f, 0.72f}},
+    {64, 192, 8, 4, 0.483f, {1.66f, 1.93f, 3.68f, 5.46f}, 0.056f, {0.82f, 2.20f}},
+    {64, 128, 8, 6, 0.364f, {1.42f, 1.92f, 2.78f, 4.25f}, 0.000f, {0.85f, 2.25f}},
+    {64, 64, 8, 8, 0.232f, {0.82f, 1.30f, 1.80f, 2.32f}, 0.087f, {0.00f, 2.16f}},
 };
+constexpr int RESIDUAL_COPY = 3;   // the model's index of the residual update that also writes bf16(x)
 constexpr float LAUNCH_US = 2.71f;
 constexpr int CHIP_CUS = 256;
 constexpr int FIRST_PARTIAL_TILE = 4;   // tiles compiled for partial sums: this one and the smaller ones
-constexpr float PARTIAL_SUM_US = 6.4f, PARTIAL_SUM_US_PER_PART = 1.0f;   // what adding them up later costs
+// what adding them up later costs: once, a part, a part and million elements; what a split has to gain to be taken
+constexpr float PARTIAL_SUM_US = 5.0f, PARTIAL_SUM_US_PER_PART = 1.0f, PARTIAL_SUM_US_PER_M = 0.6f, PARTIAL_MARGIN_US = 1.5f;
 
 float predicted_us(int tile, int epilogue, int64_t N, int n, int k, int cus) {
   const TileModel &t = TILES[tile];
@@ -894,7 +895,7 @@ float predicted_us(int tile, int epilogue, int64_t N, int n, int k, int cus) {
   const double q = std::ceil(tiles / cus);
   const double one = t.a * (double)((k + BK - 1) / BK) + t.e[epilogue];
   const double full = tiles < cus ? tiles / cus : 1.0;
-  return (float)(one * q * (1.0 + t.s * full) + (epilogue == 2 ? t.f * full : 0.0) + LAUNCH_US);
+  return (float)(one * q * (1.0 + t.s * full) + (epilogue >= 2 ? t.f[epilogue - 2] * full : 0.0) + LAUNCH_US);
 }
 
 int cheapest_tile(int epilogue, int64_t N, int n, int k, int cus) {
@@ -921,7 +922,7 @@ int launch_checked(int tile, const GemmParams &p, hipStream_t s) {
 
 template <int EPI>
 int launch_epi(int tile, const GemmParams &p, hipStream_t s) {
-  if (tile < 0) tile = cheapest_tile(EPI, p.N, p.n, p.k, ddit::device_cus());
+  if (tile < 0) tile = cheapest_tile(EPI == 2 && p.out ? RESIDUAL_COPY : EPI, p.N, p.n, p.k, ddit::device_cus());
   switch (tile) {
     case 0: return launch_checked<2, 4, 1, 3, 3, 2, EPI>(tile, p, s);
     case 1: return launch_checked<2, 4, 1, 4, 2, 2, EPI>(tile, p, s);
@@ -951,7 +952,8 @@ int gemm_tile_info(int tile, int *rows, int *cols, int *wavefronts, int *wg_per_
   return 0;
 }
 
-int gemm_tile_choice(int epilogue, int64_t N, int n, int k, int cus, float *us_per_tile) {
+int gemm_tile_choice(int epilogue, bool copy, int64_t N, int n, int k, int cus, float *us_per_tile) {
+  if (epilogue == 2 && copy) epilogue = RESIDUAL_COPY;
   if (cus <= 0) cus = ddit::device_cus();
   if (us_per_tile)
     for (int t = 0; t < N_TILES; ++t) us_per_tile[t] = predicted_us(t, epilogue, N, n, k, cus);
@@ -1014,25 +1016,27 @@ int launch_gemm_grouped(const GemmArgs &a, int G, const void *const *W, const vo
 // launch that reads the stream next sums up (launch_modulated_layernorm).  It pays where so few tokens make
 // small tiles or idle CUs: the parts are that many more tiles, larger ones with a shorter chain of k-steps each.
 // fc2 (1152 x 4608) of 2304 tokens: 216 tiles of 64 x 192 and 72 steps 46 us, two parts of 108 tiles of
-// 128 x 192 and 36 steps 33 us, and 7 us more in the LayerNorm; a layer in all, one launch / parts:
-// 200 tokens 103.4 / 97.2 us (3 parts), 288 111.0 / 107.0 (2), 1152 145.6 / 141.0 (3), 2048 189.3 / 182.8 (2),
-// 2304 200.1 / 194.3 (2); from 2720 on nothing.
-// Tiles and parts are priced with the linears' model, the parts side by side being so many more columns; what the
-// sum costs elsewhere fits 6.4 us + 1 us a part at 48 .. 3072 tokens x 1152 (standard error 1.9 us).  Beyond that
-// range its traffic counts and it is not tried.
+// 128 x 192 and 36 steps 33 us, and 7 us more in the LayerNorm; a layer of 16 heads in all, one launch / 2 / 3 parts:
+// 200 tokens 102.0 / 97.0 / 95.5 us, 400 106.5 / 103.5 / 103.6, 800 117.0 / 119.5 / 120.8, 1152 144.3 / 142.4 / 138.2,
+// 1500 149.8 / 150.8 / 150.6, 1800 180.6 / 175.5 / 177.0, 2048 187.9 / 181.3, 2304 199.8 / 192.5, 2500 202.7 / 198.2,
+// 2720 212.6 / 213.4, 2900 to 3500 the same within 0.6 (4 heads alike; 2720 167.8 / 171.2): nothing is split beyond 2.75 M
+// elements, 2503 tokens.
+// Tiles and parts are priced with the linears' model, the parts side by side being so many more columns, and what the sum
+// costs elsewhere is set to these times (standard error 1.5 us, which a split has to gain).
 // A third part gains most below 2 M elements, and only there is the room for it small.
 // The answer sizes workspaces, so it depends on the shape alone: priced for the whole chip whatever device is current.
 int gemm_partial_choice(int64_t N, int n, int k, int max_parts, int *tile_out) {
   const int cus = CHIP_CUS, steps = (k + BK - 1) / BK;
-  const int most = N * (int64_t)n <= (int64_t)2 << 20 ? max_parts : N * (int64_t)n <= (int64_t)4 << 20 ? std::min(max_parts, 2) : 0;
-  float best = predicted_us(cheapest_tile(2, N, n, k, cus), 2, N, n, k, cus);
+  const int most = N * (int64_t)n <= (int64_t)2 << 20 ? max_parts : N * (int64_t)n <= (int64_t)11 << 18 ? std::min(max_parts, 2) : 0;
+  float best = predicted_us(cheapest_tile(2, N, n, k, cus), 2, N, n, k, cus) - PARTIAL_MARGIN_US;
   int chosen = 0;
   for (int parts = 2; parts <= most && parts <= steps; ++parts) {
     const int per = (steps + parts - 1) / parts;
     if ((parts - 1) * per >= steps) continue;   // the last part would be empty (4 k-steps in three parts of two)
     for (int t = FIRST_PARTIAL_TILE; t < N_TILES; ++t) {
       const int cols = (n + TILES[t].cols - 1) / TILES[t].cols * TILES[t].cols;
-      const float us = predicted_us(t, 0, N, parts * cols, per * BK, cus) + PARTIAL_SUM_US + PARTIAL_SUM_US_PER_PART * parts;
+      const float us = predicted_us(t, 0, N, parts * cols, per * BK, cus) + PARTIAL_SUM_US +
+                       (PARTIAL_SUM_US_PER_PART + PARTIAL_SUM_US_PER_M * (float)(N * n) * 1e-6f) * parts;
       if (us < best) { best = us; chosen = parts; *tile_out = t; }
     }
   }

@@ -1,0 +1,38 @@
+"""The rules that choose a linear's output tile and fc2's split, against the times they rest on (host only)."""
+import os
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def m():
+    import paper_2506_13497_amd as mod
+    return mod
+
+
+def test_picks_against_the_recorded_sweep(m):
+    """Every tile timed on linears of six layers at 31 token counts: what the launcher picks costs little more than the best
+    tile there, on average and at worst."""
+    import bench
+    rows, tiles = bench.read_tile_sweep(os.path.join(ROOT, "profiles", "gemm_tile_sweep.txt"))
+    info = [m.ddit_linear_tile_info(t) for t in range(m.ddit_linear_tile_count())]
+    assert tiles == [(t["rows"], t["cols"]) for t in info] and len(rows) > 800
+    ratio = [us[m.ddit_linear_tile_choice(epi, N, n, k, 256)[0]] / min(us) for epi, n, k, N, us in rows]
+    assert sum(ratio) / len(ratio) <= 1.009 and max(ratio) <= 1.27
+
+
+# microseconds of a layer (hidden 1152, MLP 4608, 16 heads) with fc2 in one launch and in two and three parts
+SPLIT_TIMES = {200: (102.0, 97.0, 95.5), 400: (106.5, 103.5, 103.6), 800: (117.0, 119.5, 120.8), 1152: (144.3, 142.4, 138.2),
+               1500: (149.8, 150.8, 150.6), 1800: (180.6, 175.5, 177.0), 2048: (187.9, 181.3), 2304: (199.8, 192.5),
+               2500: (202.7, 198.2), 2720: (212.6, 213.4), 2900: (215.7, 215.6), 3200: (222.5, 221.8), 3500: (233.5, 233.4)}
+
+
+@pytest.mark.parametrize("N", sorted(SPLIT_TIMES))
+def test_split_of_fc2_against_measured_layers(m, N):
+    """The split taken is within a microsecond or two of the best one, and none is taken where none was measured to pay."""
+    us = SPLIT_TIMES[N]
+    parts = m.ddit_linear_partial_choice(N, 1152, 4608)[0]
+    assert us[max(parts - 1, 0)] <= min(us) + 2.0
+    assert parts == 0 or us[parts - 1] < us[0]
