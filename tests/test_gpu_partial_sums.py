@@ -106,3 +106,26 @@ def test_static_scratch_takes_the_parts_that_fit(n_blocks):
         call(out)
         torch.cuda.synchronize()
         assert_parity(dev_to_f64(out), ref, "block, %d blocks' text" % n_blocks)
+
+
+@pytest.mark.parametrize("tile", range(4, 10))   # the tiles compiled for partial sums
+@pytest.mark.parametrize("N,n,k", [(70, 392, 4608), (1, 8, 520), (1300, 1152, 4608), (2600, 1152, 1160)])
+def test_every_partial_sum_tile(tile, N, n, k):
+    """One ragged tile; one row; a tile grid that fills the CUs and more than one round of it; a k whose last part is
+    ragged: every part against float64 over its own k, the bias in the first.  fp32 sums of at most 4608 products:
+    2 sqrt(k) 2^-24 of the terms' size, taken four times."""
+    import paper_2506_13497_amd as m
+    info = m.ddit_linear_tile_info(tile)
+    g = torch.Generator(device="cuda").manual_seed(tile + N)
+    u = torch.randn(N, k, device="cuda", generator=g).bfloat16()
+    W, bias = torch.randn(n, k, device="cuda", generator=g).bfloat16(), torch.randn(n, device="cuda", generator=g).bfloat16()
+    for parts in (2, 3):
+        per = -(-(-(-k // 64)) // parts) * 64
+        out = torch.full((parts, N, n), float("nan"), device="cuda")
+        m.ddit_linear_partial_fwd(tile, parts, u, k, W, bias, N, n, k, out)
+        torch.cuda.synchronize()
+        for p in range(parts):
+            ref = u[:, p * per:(p + 1) * per].double() @ W[:, p * per:(p + 1) * per].double().t()
+            if p == 0:
+                ref += bias.double()
+            assert (out[p].double() - ref).abs().max() <= 8 * k ** 0.5 * 2.0 ** -24 * k ** 0.5, (info, parts, p)
