@@ -66,7 +66,6 @@ struct GemmParams {
   int64_t tokens_per_sample;
   int tiles_m; int tiles_n; int group_w; int total_tiles; int rounds;
   int split_steps; int split_tiles; int64_t split_stride;   // partial sums (EPI 3): k-steps and output tiles of one part, floats between parts
-  int x_stays; // the residual stream fits the memory-side cache beside what else the step touches
   int plain;   // row strides below 2^26 elements: a row group's offsets fit 32 bits
 };
 
@@ -270,6 +269,9 @@ __device__ __forceinline__ float4 gate_vector(const GemmParams &p, unsigned smp,
 // 8g + 4 lh + e] of it, bias inside).  `stg`: this wavefront's staging bytes (LDS offset); nothing here
 // synchronises with other wavefronts.
 // FULL: the whole tile lies inside the problem and (residual update) inside one sample: straight-line code.
+// EPI: 0 bf16, 1 GELU + bf16, 2 residual update, 3 partial sums, 4 residual update with streaming stores of the stream
+constexpr bool is_residual(int epi) { return epi == 2 || epi == 4; }
+
 template <class C, int TM, int TN, int EPI, int T0, int T1, bool FULL>
 __device__ __forceinline__ void gemm_epilogue_as(floatx16 (&acc)[TN][TM], unsigned stg, unsigned char *stg_ptr,
                                               const GemmParams &p, const TileOut &to, int lane, int wm, int wn, unsigned smp0,
@@ -335,7 +337,7 @@ __device__ __forceinline__ void gemm_epilogue_as(floatx16 (&acc)[TN][TM], unsign
     // requests complete in order, loads and stores alike, so a tile's loads are issued BEFORE the stores of
     // the tiles processed while they are in flight, and waiting for them never waits for a store.
     // Partial sums (EPI 3) leave the same way, fp32 rows as they are, with no stream to read.
-    constexpr bool EARLY = EPI == 2 && C::X_EARLY;
+    constexpr bool EARLY = is_residual(EPI) && C::X_EARLY;
     constexpr int DEPTH = EPI == 3 ? 1 : EARLY ? T1 - T0 : !FULL ? 1 : (T1 - T0 < 3 ? T1 - T0 : 3);
     int r8 = lane >> 3, f4 = (lane & 7) * 4;
     // this wavefront's corner of the stream and of its bf16 copy, and this lane's place in a group of 8 rows
@@ -370,7 +372,7 @@ __device__ __forceinline__ void gemm_epilogue_as(floatx16 (&acc)[TN][TM], unsign
         for (int i = 0; i < 4; ++i) xr[d][i] = early.x[d][i];
 #pragma unroll
       for (int a = 0; a < TN; ++a) gate[a] = early.gate[a];
-    } else if constexpr (FULL && EPI == 2) {
+    } else if constexpr (FULL && is_residual(EPI)) {
 #pragma unroll
       for (int d = 0; d < DEPTH; ++d) issue_x(T0 + d, d);
 #pragma unroll
@@ -379,7 +381,7 @@ __device__ __forceinline__ void gemm_epilogue_as(floatx16 (&acc)[TN][TM], unsign
 #pragma unroll
     for (int t = T0; t < T1; ++t) {
       const int b = t / TN, a = t - b * TN, slot = (t - T0) % DEPTH;
-      if constexpr (!FULL && !EARLY && EPI == 2) issue_x(t, slot);
+      if constexpr (!FULL && !EARLY && is_residual(EPI)) issue_x(t, slot);
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         floatx4 v;
@@ -422,8 +424,9 @@ __device__ __forceinline__ void gemm_epilogue_as(floatx16 (&acc)[TN][TM], unsign
         for (int i = 0; i < 4; ++i) {
           r[i] = update(i, gate[a]);
           floatx4 *const dst = reinterpret_cast<floatx4 *>(x0 + ((int64_t)(b * 32 + 8 * i) * p.n + a * 32) * 4 + lane_x);
-          if (p.x_stays) *dst = r[i];
-          else __builtin_nontemporal_store(r[i], dst);
+          // the two stores are two kernels: in one, as a choice at run time, the compiler makes both of them plain
+          if constexpr (EPI == 4) __builtin_nontemporal_store(r[i], dst);
+          else *dst = r[i];
         }
         if (p.out) {
 #pragma unroll
@@ -445,7 +448,7 @@ __device__ __forceinline__ void gemm_epilogue_as(floatx16 (&acc)[TN][TM], unsign
         }
       }
       __builtin_amdgcn_sched_barrier(0);
-      if constexpr (FULL && !EARLY && EPI == 2) {
+      if constexpr (FULL && !EARLY && is_residual(EPI)) {
         if (t + DEPTH < T1) issue_x(t + DEPTH, slot);
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -626,7 +629,7 @@ __global__ __launch_bounds__(WGM *WGN *WGK * 64, 2) void k_gemm_bf16(GemmParams 
     to.row0 = (int64_t)tile_m * BM; to.col0 = tile_n * BN; to.out = p.out; to.shift = 0;
     to.smp0 = 0; to.one_sample = true;
     XRows<C::OWN, TN> early;
-    if constexpr (EPI == 2) {
+    if constexpr (is_residual(EPI)) {
       if (p.gate_tab && p.gate_c6) {
         to.smp0 = sample_of(p, to.row0);
         to.one_sample = to.smp0 == sample_of(p, (to.row0 + BM < p.N ? to.row0 + BM : p.N) - 1);
@@ -818,10 +821,6 @@ int launch_one(const GemmParams &p0, hipStream_t s, const GT &gt = GT()) {
     p.split_tiles = p.total_tiles;
     p.total_tiles *= (nk + p.split_steps - 1) / p.split_steps;
   }
-  // The next launches read x again: written plainly it is found in the 256 MB memory-side cache (6851 tokens:
-  // step 1.6 % shorter, 12960 tokens: 2.4 %); where it does not fit there, a plain store only pushes operands
-  // out of the L2 (48600 tokens: 1 % longer), and where it is small the launch ends with writing the L2 back.
-  p.x_stays = p.N * (int64_t)p.n <= (int64_t)24 << 20 && p.N * (int64_t)p.n >= (int64_t)4 << 20;
   p.plain = p.n < (1 << 26) && p.ld_out < (1 << 26);
   // one workgroup per CU (its stages take most of the LDS); a multiple of 8 so that every round gives
   // each XCD a contiguous run of tiles
@@ -885,7 +884,7 @@ constexpr TileModel TILES[N_TILES] = {
 constexpr int RESIDUAL_COPY = 3;   // the model's index of the residual update that also writes bf16(x)
 constexpr float LAUNCH_US = 2.71f;
 constexpr int CHIP_CUS = 256;
-constexpr int FIRST_PARTIAL_TILE = 4;   // tiles compiled for partial sums: this one and the smaller ones
+constexpr int FIRST_SMALL_TILE = 4;   // tiles compiled for partial sums and streaming residuals: this one and the smaller ones
 // what adding them up later costs: once, a part, a part and million elements; what a split has to gain to be taken
 constexpr float PARTIAL_SUM_US = 5.0f, PARTIAL_SUM_US_PER_PART = 1.0f, PARTIAL_SUM_US_PER_M = 0.6f, PARTIAL_MARGIN_US = 1.5f;
 
@@ -920,9 +919,32 @@ int launch_checked(int tile, const GemmParams &p, hipStream_t s) {
   return launch_one<WGM, WGN, WGK, TM, TN, NS, EPI>(p, s);
 }
 
+// How the residual update writes the stream.  The next launches read x again: written plainly a large one is found in the
+// 256 MB memory-side cache; one of a few million elements stays there either way, and the launch then ends with writing
+// the L2 back; the smallest stay in the L2 itself.  Streaming / plain, microseconds a layer of a step: 600 tokens x 1152
+// (0.7 Mi elements) 113.5 / 113.6, 1200 (1.3 Mi) 145.7 / 146.6, 2304 (2.5) 193.0 / 195.1, 3680 (4.0) 253.9 / 257.1, 4600
+// (5.1) 301.0 / 301.6, 6000 (6.6) 346.1 / 344.5, 12960 (14.2) 728 / 715, 19000 (20.9) 1131 / 1121, 48600 3518 / 3522;
+// x 2048, 2.3 Mi 255.3 / 258.1, 5.5 Mi 427.8 / 427.3, 7.2 Mi 513.4 / 507.7; x 256, 0.9 Mi 76.2 / 75.6, 1.5 Mi 91.7 / 92.2,
+// 5.6 Mi 276.0 / 278.3, 14.6 Mi 971 / 962.  Compiled for the tiles that so few elements take.
+constexpr int64_t STREAM_WRITES_FROM = (int64_t)5 << 18, PLAIN_WRITES_FROM = (int64_t)6 << 20;
+
+int launch_residual_streaming(int tile, const GemmParams &p, hipStream_t s) {
+  switch (tile) {
+    case 4: return launch_checked<4, 2, 1, 2, 2, 3, 4>(tile, p, s);
+    case 5: return launch_checked<4, 2, 1, 1, 3, 3, 4>(tile, p, s);
+    case 6: return launch_checked<2, 2, 2, 2, 2, 4, 4>(tile, p, s);
+    case 7: return launch_checked<2, 2, 2, 1, 3, 4, 4>(tile, p, s);
+    case 8: return launch_checked<2, 2, 2, 1, 2, 6, 4>(tile, p, s);
+    default: return launch_checked<2, 2, 2, 1, 1, 8, 4>(tile, p, s);
+  }
+}
+
 template <int EPI>
 int launch_epi(int tile, const GemmParams &p, hipStream_t s) {
   if (tile < 0) tile = cheapest_tile(EPI == 2 && p.out ? RESIDUAL_COPY : EPI, p.N, p.n, p.k, ddit::device_cus());
+  const int64_t elements = p.N * (int64_t)p.n;
+  if (EPI == 2 && tile >= FIRST_SMALL_TILE && tile < N_TILES && elements >= STREAM_WRITES_FROM && elements < PLAIN_WRITES_FROM)
+    return launch_residual_streaming(tile, p, s);
   switch (tile) {
     case 0: return launch_checked<2, 4, 1, 3, 3, 2, EPI>(tile, p, s);
     case 1: return launch_checked<2, 4, 1, 4, 2, 2, EPI>(tile, p, s);
@@ -996,7 +1018,7 @@ int launch_gemm_grouped(const GemmArgs &a, int G, const void *const *W, const vo
   p.out = gt.out[0]; p.ld_out = a.ld_out;
   p.resid = nullptr; p.gate_tab = nullptr; p.gate_c6 = nullptr; p.gate_c6_stride = 0;
   p.tokens_per_sample = a.tokens_per_sample > 0 ? a.tokens_per_sample : 1;
-  p.tiles_m = 0; p.tiles_n = 0; p.group_w = 1; p.total_tiles = 0; p.rounds = 0; p.x_stays = 0; p.plain = 0;
+  p.tiles_m = 0; p.tiles_n = 0; p.group_w = 1; p.total_tiles = 0; p.rounds = 0; p.plain = 0;
   p.split_steps = p.split_tiles = 0; p.split_stride = 0;
   switch (tile) {
     case 0: return launch_grouped_tile<2, 4, 1, 3, 3, 2>(p, gt, s);
@@ -1033,7 +1055,7 @@ int gemm_partial_choice(int64_t N, int n, int k, int max_parts, int *tile_out) {
   for (int parts = 2; parts <= most && parts <= steps; ++parts) {
     const int per = (steps + parts - 1) / parts;
     if ((parts - 1) * per >= steps) continue;   // the last part would be empty (4 k-steps in three parts of two)
-    for (int t = FIRST_PARTIAL_TILE; t < N_TILES; ++t) {
+    for (int t = FIRST_SMALL_TILE; t < N_TILES; ++t) {
       const int cols = (n + TILES[t].cols - 1) / TILES[t].cols * TILES[t].cols;
       const float us = predicted_us(t, 0, N, parts * cols, per * BK, cus) + PARTIAL_SUM_US +
                        (PARTIAL_SUM_US_PER_PART + PARTIAL_SUM_US_PER_M * (float)(N * n) * 1e-6f) * parts;
@@ -1104,7 +1126,7 @@ int launch_gemm(int epilogue, const GemmArgs &a, hipStream_t s) {
   p.resid = a.resid;
   p.gate_tab = a.gate_tab; p.gate_c6 = a.gate_c6; p.gate_c6_stride = a.gate_c6_stride;
   p.tokens_per_sample = a.tokens_per_sample > 0 ? a.tokens_per_sample : 1;
-  p.tiles_m = 0; p.tiles_n = 0; p.group_w = 1; p.total_tiles = 0; p.rounds = 0; p.x_stays = 0; p.plain = 0;
+  p.tiles_m = 0; p.tiles_n = 0; p.group_w = 1; p.total_tiles = 0; p.rounds = 0; p.plain = 0;
   p.split_steps = p.split_tiles = 0; p.split_stride = 0;
   switch (epilogue) {
     case 0: return launch_epi<0>(a.tile, p, s);
