@@ -52,18 +52,20 @@ def step_flops(sh, valid):
             "temporal": temporal, "cross": cross, "fc1": lin(N, M, D)}
 
 
-def measured_traffic(group, workload):
+def measured_traffic(group, workload, tiles):
     """HBM bytes per launch of a kernel group as measured with rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (two
     runs, scaled by what the same counters read for a plain copy kernel of known size); the figure is kept,
-    with the commands that produced it, in profiles/.  None if not measured for this workload."""
+    with the commands that produced it, in profiles/.  None if not measured for this workload, or if the launcher now takes
+    other output tiles than the kernels that were measured."""
     path = os.path.join(ROOT, "profiles", "%s_%s_hbm_traffic.txt" % (group, WORKLOAD_NAMES[workload].split("-")[0]))
     try:
-        for line in open(path):
-            if line.startswith("traffic_bytes_per_launch:"):
-                return int(float(line.split(":", 1)[1]))
+        lines = dict(line.rstrip("\n").split(":", 1) for line in open(path) if ":" in line)
     except OSError:
-        pass
-    return None
+        return None
+    measured = dict(t.split("=") for t in lines.get("tiles", "").split())
+    if "traffic_bytes_per_launch" not in lines or any(tiles.get(name) != tile for name, tile in measured.items()):
+        return None
+    return int(float(lines["traffic_bytes_per_launch"].split()[0]))
 
 
 # per-step time of one rank at degree of parallelism p (section 4.2.3): latent shapes by resolution
@@ -440,8 +442,8 @@ class Workload:
         m, sh = self.m, self.sh
         out = {}
         for name, epi, n, k in (("qkv", m.DDIT_EPI_BF16, 3 * sh.A, sh.D), ("attn_out", m.DDIT_EPI_RESIDUAL_F32 | m.DDIT_EPI_COPY, sh.D, sh.A),
-                                ("cross_q", m.DDIT_EPI_BF16, sh.A, sh.D), ("fc1", m.DDIT_EPI_GELU_BF16, sh.M, sh.D),
-                                ("fc2", m.DDIT_EPI_RESIDUAL_F32, sh.D, sh.M)):
+                                ("cross_q", m.DDIT_EPI_BF16, sh.A, sh.D), ("cross_out", m.DDIT_EPI_RESIDUAL_F32, sh.D, sh.A),
+                                ("fc1", m.DDIT_EPI_GELU_BF16, sh.M, sh.D), ("fc2", m.DDIT_EPI_RESIDUAL_F32, sh.D, sh.M)):
             tile, _ = m.ddit_linear_tile_choice(epi, sh.N, n, k)
             info = m.ddit_linear_tile_info(tile)
             out[name] = "%dx%d" % (info["rows"], info["cols"])
@@ -453,7 +455,7 @@ def roofline_of(table, workload, tiles):
     top = table[0]
     r = {"kernel": top["kernel"], "group": top["group"], "bound": top["bound"], "achieved": top["achieved"], "peak": top["peak"],
          "unit": top["unit"], "frac": top["frac"], "ms_per_launch": top["avg_ms"], "share_of_step": top["share_of_step"],
-         "launches_per_step": top["launches_per_step"], "traffic": measured_traffic(top["group"], workload)}
+         "launches_per_step": top["launches_per_step"], "traffic": measured_traffic(top["group"], workload, tiles)}
     if top["group"].startswith("gemm"):
         r["tiles"] = tiles
     return r
