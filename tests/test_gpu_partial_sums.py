@@ -129,3 +129,26 @@ def test_every_partial_sum_tile(tile, N, n, k):
             if p == 0:
                 ref += bias.double()
             assert (out[p].double() - ref).abs().max() <= 8 * k ** 0.5 * 2.0 ** -24 * k ** 0.5, (info, parts, p)
+
+
+@pytest.mark.parametrize("B,T,Hp,Wp,H,parts", [(2, 2, 5, 10, 16, 3), (1, 5, 10, 23, 4, 3), (1, 5, 20, 23, 4, 2), (1, 4, 10, 10, 4, 2)])
+def test_parts_beside_the_treated_attention(B, T, Hp, Wp, H, parts):
+    """The split is taken (the count is asserted), the regions behind the parts move for it (a third part; attention
+    narrower than the stream), and with them the angles of the rotary embedding."""
+    import paper_2506_13497_amd as m
+    D, dh, M, Ly = 1152, 72, 4608, 20
+    sh = syn.Shape(B, T, Hp, Wp, D, H, dh, M, Ly, 2)
+    assert m.ddit_linear_partial_choice(sh.N, D, M)[0] == parts
+    sw = syn.make_step_weights(sh, 53)
+    blocks = [syn.make_block_weights(sh, 53, i, qk_norm=True, table_std=0.1) for i in range(2)]
+    act, temb = syn.make_activations(sh, 53), syn.make_temb(sh, 53)
+    shape = m.make_shape(B, T, Hp, Wp, D, H, dh, M, Ly, 2, m.DDIT_FLAG_QK_NORM | m.DDIT_FLAG_ROPE_TEMPORAL)
+    ws = m.alloc_workspace(shape)
+    ws.fill_(0xFF)
+    dsw, dblocks = {k: to_dev(v) for k, v in sw.items()}, [dict_dev(b) for b in blocks]
+    x_out = torch.full((B, T, sh.S, D), float("nan"), dtype=torch.bfloat16, device="cuda")
+    m.ddit_denoise_step(shape, m.step_struct(dsw, dblocks), to_dev(act["x"]), to_dev(act["y"]), None, None, to_dev(temb), x_out, ws)
+    torch.cuda.synchronize()
+    ref = ora.denoise_step(to_f64(act["x"]), to_f64(act["y"]), None, None, dict_f64(sw), [dict_f64(b) for b in blocks],
+                           H, dh, temb=temb.astype(np.float64), rope_temporal=True)
+    assert_parity(dev_to_f64(x_out), ref, "step with fc2 in %d parts and treated q, k" % parts)
