@@ -73,11 +73,14 @@ __global__ void k_add_pending(float *__restrict__ x, ddit::PendingSum pend, bf16
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n4) return;
   const int64_t row = i / d4;
-  float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int q = 0; q < pend.parts; ++q) {
-    const float4 t = reinterpret_cast<const float4 *>(pend.part + q * pend.part_stride)[i];
-    a.x += t.x; a.y += t.y; a.z += t.z; a.w += t.w;
-  }
+  float4 part[ddit::MAX_PENDING_PARTS];
+#pragma unroll
+  for (int q = 0; q < ddit::MAX_PENDING_PARTS; ++q)   // all loads before the first use; a part too many reads the last one again
+    part[q] = reinterpret_cast<const float4 *>(pend.part + (q < pend.parts ? q : pend.parts - 1) * pend.part_stride)[i];
+  float4 a = part[0];
+#pragma unroll
+  for (int q = 1; q < ddit::MAX_PENDING_PARTS; ++q)
+    if (q < pend.parts) { a.x += part[q].x; a.y += part[q].y; a.z += part[q].z; a.w += part[q].w; }
   const float4 g = ddit::pending_gate(pend, row / tokens_per_sample, (int)(i - row * d4));
   const float4 v = ddit::add_gated(reinterpret_cast<const float4 *>(x)[i], g, a);
   if constexpr (TO_BF16) {

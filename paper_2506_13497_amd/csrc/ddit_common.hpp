@@ -36,7 +36,8 @@ int device_cus();   // compute units of the current device (cached per process; 
 
 // kernel launchers (each validates nothing: callers have validated shapes)
 // A residual update that has been computed but not yet added: x += gate_b * sum of `parts` fp32 [N, D] arrays,
-// part_stride floats apart (the bias is in the first); gate_tab / gate_c6 as in GemmArgs.
+// part_stride floats apart (the bias is in the first); gate_tab / gate_c6 as in GemmArgs.  Two or three parts, or none.
+constexpr int MAX_PENDING_PARTS = 3;
 struct PendingSum {
   int parts; const float *part; int64_t part_stride;   // parts == 0: nothing pending
   const float *gate_tab, *gate_c6; int64_t gate_c6_stride;

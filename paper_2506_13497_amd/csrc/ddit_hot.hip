@@ -136,7 +136,7 @@ void make_layout(const Dims &d, uint32_t flags, Layout *lo, size_t limit = SIZE_
   // one, or two where A is far below D, push the regions behind further back: at most 4 N D and 8 N (D - A) bytes, 25 MB
   // at the largest N * D that is split.
   const size_t part = (size_t)d.N * d.D * 4, room = lo->kvc - lo->qkv;
-  lo->fc2_parts = gemm_partial_choice(d.N, (int)d.D, (int)d.M, 3, &lo->fc2_tile);
+  lo->fc2_parts = gemm_partial_choice(d.N, (int)d.D, (int)d.M, MAX_PENDING_PARTS, &lo->fc2_tile);
   if (lo->fc2_parts * part > room) {
     const size_t more = align_up(lo->fc2_parts * part - room);
     if (off <= limit && off + more > limit) {
