@@ -24,7 +24,11 @@ __global__ __launch_bounds__(256) void k_modulated_layernorm(float *__restrict__
                                                              const float *__restrict__ tab,
                                                              const float *__restrict__ c6, int which, int64_t N,
                                                              int64_t tokens_per_sample, int D, float eps,
-                                                             bf16_t *__restrict__ out, ddit::PendingSum pend) {
+                                                             bf16_t *__restrict__ out, ddit::PendingSum pend, ddit::Prefetch ahead) {
+  if (blockIdx.y) {
+    ddit::prefetch_share<256>(ahead);
+    return;
+  }
   extern __shared__ __attribute__((aligned(16))) float4 mod[];   // [2 (+ 1)][nchunk]: 1 + scale, shift (, gate of the pending update)
   const int lane = threadIdx.x & 63;
   const int64_t wg_row0 = (int64_t)blockIdx.x * (4 * ROWS);
@@ -133,14 +137,15 @@ namespace ddit {
 
 template <int CHUNKS, int ROWS, bool STREAM, int PARTS>
 void launch_ln(float *x, const float *tab, const float *c6, int which, int64_t N, int64_t tps, int D, float eps,
-               bf16_t *o, const PendingSum &pend, hipStream_t s) {
+               bf16_t *o, const PendingSum &pend, const Prefetch &ahead, hipStream_t s) {
   const unsigned lds = (PARTS > 0 ? 3u : 2u) * (unsigned)D * 4u;   // at most 48 KB
-  hipLaunchKernelGGL((k_modulated_layernorm<CHUNKS, ROWS, STREAM, PARTS>), dim3((unsigned)((N + 4 * ROWS - 1) / (4 * ROWS))),
-                     dim3(256), lds, s, x, tab, c6, which, N, tps, D, eps, o, pend);
+  const unsigned blocks = (unsigned)((N + 4 * ROWS - 1) / (4 * ROWS));
+  hipLaunchKernelGGL((k_modulated_layernorm<CHUNKS, ROWS, STREAM, PARTS>), dim3(blocks, prefetch_rows(ahead, blocks)), dim3(256),
+                     lds, s, x, tab, c6, which, N, tps, D, eps, o, pend, ahead);
 }
 template <int CHUNKS>
 void launch_ln(float *x, const float *tab, const float *c6, int which, int64_t N, int64_t tps, int D, float eps,
-               bf16_t *o, const PendingSum *pend, hipStream_t s) {
+               bf16_t *o, const PendingSum *pend, const Prefetch &ahead, hipStream_t s) {
   // A wavefront with a second row hides its latency behind the first one's reductions; below 8192 rows there are
   // not four wavefronts per SIMD and the second row only makes the launch longer.  D = 1152, 1 / 2 rows: 256 rows
   // 3.5 / 4.8 us, 2304 rows 5.6 / 6.2 us, 12960 rows 19.6 / 19.8 us, 48600 rows 53.1 / 50.1 us (6.7 TB/s).
@@ -151,26 +156,26 @@ void launch_ln(float *x, const float *tab, const float *c6, int which, int64_t N
   // 12960 of 2048, 27 M, 33.9 / 28.5; 108000 of 256, 28 M, 40.8 / 36.2; 20000 of 1152, 23 M, 25.1 / 24.5).
   constexpr int ROWS = CHUNKS <= 5 ? 2 : 1;
   const PendingSum none = {0, nullptr, 0, nullptr, nullptr, 0};
-  if (pend && pend->parts == 2) launch_ln<CHUNKS, 1, false, 2>(x, tab, c6, which, N, tps, D, eps, o, *pend, s);
-  else if (pend && pend->parts == 3) launch_ln<CHUNKS, 1, false, 3>(x, tab, c6, which, N, tps, D, eps, o, *pend, s);
-  else if (N < 8192) launch_ln<CHUNKS, 1, false, 0>(x, tab, c6, which, N, tps, D, eps, o, none, s);
-  else if (N * (int64_t)D <= (int64_t)24 << 20) launch_ln<CHUNKS, ROWS, false, 0>(x, tab, c6, which, N, tps, D, eps, o, none, s);
-  else launch_ln<CHUNKS, ROWS, true, 0>(x, tab, c6, which, N, tps, D, eps, o, none, s);
+  if (pend && pend->parts == 2) launch_ln<CHUNKS, 1, false, 2>(x, tab, c6, which, N, tps, D, eps, o, *pend, ahead, s);
+  else if (pend && pend->parts == 3) launch_ln<CHUNKS, 1, false, 3>(x, tab, c6, which, N, tps, D, eps, o, *pend, ahead, s);
+  else if (N < 8192) launch_ln<CHUNKS, 1, false, 0>(x, tab, c6, which, N, tps, D, eps, o, none, ahead, s);
+  else if (N * (int64_t)D <= (int64_t)24 << 20) launch_ln<CHUNKS, ROWS, false, 0>(x, tab, c6, which, N, tps, D, eps, o, none, ahead, s);
+  else launch_ln<CHUNKS, ROWS, true, 0>(x, tab, c6, which, N, tps, D, eps, o, none, ahead, s);
 }
 
 int launch_modulated_layernorm(float *x, const float *ada_table, const float *c6, int which, int64_t N,
                                int64_t tokens_per_sample, int D, float eps, void *out, hipStream_t s,
-                               const PendingSum *pending) {
+                               const PendingSum *pending, const Prefetch &ahead) {
   if (N == 0) return 0;
   if (pending && (pending->parts < 0 || pending->parts > MAX_PENDING_PARTS || pending->parts == 1)) {
     set_error("modulated_layernorm: a pending update in %d parts", pending->parts);
     return -2;
   }
   bf16_t *o = reinterpret_cast<bf16_t *>(out);
-  if (D <= 256 * 2) launch_ln<2>(x, ada_table, c6, which, N, tokens_per_sample, D, eps, o, pending, s);
-  else if (D <= 256 * 5) launch_ln<5>(x, ada_table, c6, which, N, tokens_per_sample, D, eps, o, pending, s);
-  else if (D <= 256 * 8) launch_ln<8>(x, ada_table, c6, which, N, tokens_per_sample, D, eps, o, pending, s);
-  else if (D <= 256 * 16) launch_ln<16>(x, ada_table, c6, which, N, tokens_per_sample, D, eps, o, pending, s);
+  if (D <= 256 * 2) launch_ln<2>(x, ada_table, c6, which, N, tokens_per_sample, D, eps, o, pending, ahead, s);
+  else if (D <= 256 * 5) launch_ln<5>(x, ada_table, c6, which, N, tokens_per_sample, D, eps, o, pending, ahead, s);
+  else if (D <= 256 * 8) launch_ln<8>(x, ada_table, c6, which, N, tokens_per_sample, D, eps, o, pending, ahead, s);
+  else if (D <= 256 * 16) launch_ln<16>(x, ada_table, c6, which, N, tokens_per_sample, D, eps, o, pending, ahead, s);
   else {
     set_error("D=%d: hidden size above 4096 is not supported by the LayerNorm kernel", D);
     return -2;

@@ -28,6 +28,42 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
+namespace ddit {
+// Weights that the launches after this one read.  Further rows of workgroups (blockIdx.y > 0), each as many as the launch's
+// own, read them once, in address order, so that they are in the memory-side cache by then.
+struct Prefetch {
+  const void *p[2];
+  unsigned pieces[2];   // of 16 bytes; none: no further row
+};
+// Rows of a grid of `blocks` workgroups: its own, and so many more that none reads over 48 KB.
+inline unsigned prefetch_rows(const Prefetch &f, int64_t blocks) {
+  const int64_t at_most = blocks * 3072;
+  return 1 + (unsigned)(((int64_t)f.pieces[0] + f.pieces[1] + at_most - 1) / at_most);
+}
+
+template <int THREADS>
+__device__ __forceinline__ void prefetch_share(const Prefetch &f) {
+  constexpr unsigned AHEAD = 8;   // loads in flight per thread
+#pragma unroll
+  for (int w = 0; w < 2; ++w) {
+    const uint4 *src = reinterpret_cast<const uint4 *>(f.p[w]);
+    const unsigned n = f.pieces[w], readers = gridDim.x * (gridDim.y - 1);
+    const unsigned share = (n + readers - 1) / readers, from = ((blockIdx.y - 1) * gridDim.x + blockIdx.x) * share;
+    const unsigned end = from + share < n ? from + share : n;
+    for (unsigned at = from; at < end; at += THREADS * AHEAD) {
+      uint4 v[AHEAD];
+#pragma unroll
+      for (unsigned j = 0; j < AHEAD; ++j) {
+        const unsigned i = at + j * THREADS + threadIdx.x;
+        v[j] = src[i < end ? i : end - 1];
+      }
+#pragma unroll
+      for (unsigned j = 0; j < AHEAD; ++j) asm volatile("" ::"v"(v[j].x), "v"(v[j].y), "v"(v[j].z), "v"(v[j].w));
+    }
+  }
+}
+}  // namespace ddit
+
 // host side ---------------------------------------------------------------
 namespace ddit {
 void set_error(const char *fmt, ...);
@@ -59,7 +95,7 @@ __device__ __forceinline__ float4 add_gated(float4 v, float4 g, float4 a) {
 // pending (may be null): added to x, which is written back, before the LayerNorm
 int launch_modulated_layernorm(float *x, const float *ada_table, const float *c6, int which, int64_t N,
                                int64_t tokens_per_sample, int D, float eps, void *out, hipStream_t s,
-                               const PendingSum *pending = nullptr);
+                               const PendingSum *pending = nullptr, const Prefetch &prefetch = Prefetch{});
 
 struct GemmArgs {
   const void *u; int64_t ld_u;      // bf16 [N,k]
@@ -104,6 +140,7 @@ struct AttnArgs {
   int H, dh;
   const void *q_norm_g;             // bf16 [dh] or null: RMS-normalise every query with these scales as it is loaded
   float q_norm_eps;
+  Prefetch prefetch;
 };
 int launch_flash_attn(const AttnArgs &a, hipStream_t s);
 int temporal_attn_max_T();   // longest sequence the dedicated temporal kernel takes
@@ -111,7 +148,7 @@ int temporal_attn_max_T();   // longest sequence the dedicated temporal kernel t
 // when given, q and k are normalised / rotated inside the kernel on their way in
 int launch_temporal_attn(const void *q, const void *k, const void *v, void *o, float *lse, int64_t ld_q,
                          int64_t ld_kv, int64_t ld_o, int B, int T, int S, int H, int dh, const void *g_q,
-                         const void *g_k, float norm_eps, const float *rope_table, hipStream_t s);
+                         const void *g_k, float norm_eps, const float *rope_table, const Prefetch &prefetch, hipStream_t s);
 
 // per-head RMS normalisation and rotary embedding, in place (qk_norm_rope.hip), of `slots` consecutive heads
 // per token row starting at qk: the first q_slots of them take the scales g_q, the others g_k (q | k of a

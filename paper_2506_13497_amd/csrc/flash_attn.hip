@@ -84,6 +84,7 @@ struct FlashParams {
   float rebase;      // 8 / scale_log2: a score this far above its query's reference moves the reference
   const bf16_t *q_norm_g;   // per-head RMS-norm scales of the queries [dh], or null
   float q_norm_eps;
+  ddit::Prefetch ahead;
 };
 
 template <int DH>
@@ -142,6 +143,10 @@ __global__ __launch_bounds__(64 * NW, 2) void k_flash_attn(FlashParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l32 = lane & 31, lh = lane >> 5;
+  if (blockIdx.y) {
+    ddit::prefetch_share<64 * NW>(p.ahead);
+    return;
+  }
   // The scalar arguments of the set-up are fetched in ONE batch: left to itself the compiler
   // fetches each where it is first used, one memory latency after the other.
   {
@@ -636,7 +641,7 @@ int launch_dh(const FlashParams &p, int64_t blocks, hipStream_t s) {
     attr_set = true;
   }
   if (blocks > 0x7fffffff) { ddit::set_error("attention: too many workgroups"); return -2; }
-  hipLaunchKernelGGL((k_flash_attn<DH, NW, RES>), dim3((unsigned)blocks), dim3(64 * NW), smem, s, p);
+  hipLaunchKernelGGL((k_flash_attn<DH, NW, RES>), dim3((unsigned)blocks, ddit::prefetch_rows(p.ahead, blocks)), dim3(64 * NW), smem, s, p);
   return ddit::hip_fail(hipGetLastError(), "flash attention launch");
 }
 
@@ -664,6 +669,7 @@ int launch_flash_attn(const AttnArgs &a, hipStream_t s) {
   p.rebase = 8.0f / p.scale_log2;
   p.q_norm_g = reinterpret_cast<const bf16_t *>(a.q_norm_g);
   p.q_norm_eps = a.q_norm_eps;
+  p.ahead = a.prefetch;
   if ((int64_t)a.n_groups * a.H > 0x3fffffff) {
     set_error("attention grid too large (groups=%d heads=%d)", a.n_groups, a.H);
     return -2;

@@ -43,6 +43,7 @@ struct TemporalParams {
   const bf16_t *g_q, *g_k;   // per-head RMS-norm scales [dh], or null
   const float2 *rope;        // (cos, sin) of frame t, pair i at [t * dh/2 + i], or null
   float norm_eps;
+  ddit::Prefetch ahead;
 };
 
 template <int DH>
@@ -69,6 +70,10 @@ template <int DH, bool OPTS, bool PACK>
 __global__ __launch_bounds__(256, 3) void k_temporal_attn(TemporalParams p) {
   using C = TCfg<DH>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // Q, K, V: R rows each
+  if (blockIdx.y) {
+    ddit::prefetch_share<256>(p.ahead);
+    return;
+  }
   const int R = p.R, MAT = R * C::PITCH;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l32 = lane & 31, lh = lane >> 5;
@@ -309,13 +314,14 @@ int launch_t(const TemporalParams &p, hipStream_t s) {
   const int64_t packs = (int64_t)p.B * p.n_packs;
   const int64_t blocks = ((packs + 7) / 8) * p.n_hg * 8;
   if (blocks > 0x7fffffff) { ddit::set_error("temporal attention: too many workgroups"); return -2; }
+  const dim3 grid((unsigned)blocks, ddit::prefetch_rows(p.ahead, blocks));
   const unsigned lds = 3u * p.R * TCfg<DH>::PITCH;
   if (opts) {
-    if (p.P > 1) hipLaunchKernelGGL((k_temporal_attn<DH, true, true>), dim3((unsigned)blocks), dim3(256), lds, s, p);
-    else hipLaunchKernelGGL((k_temporal_attn<DH, true, false>), dim3((unsigned)blocks), dim3(256), lds, s, p);
+    if (p.P > 1) hipLaunchKernelGGL((k_temporal_attn<DH, true, true>), grid, dim3(256), lds, s, p);
+    else hipLaunchKernelGGL((k_temporal_attn<DH, true, false>), grid, dim3(256), lds, s, p);
   } else {
-    if (p.P > 1) hipLaunchKernelGGL((k_temporal_attn<DH, false, true>), dim3((unsigned)blocks), dim3(256), lds, s, p);
-    else hipLaunchKernelGGL((k_temporal_attn<DH, false, false>), dim3((unsigned)blocks), dim3(256), lds, s, p);
+    if (p.P > 1) hipLaunchKernelGGL((k_temporal_attn<DH, false, true>), grid, dim3(256), lds, s, p);
+    else hipLaunchKernelGGL((k_temporal_attn<DH, false, false>), grid, dim3(256), lds, s, p);
   }
   return ddit::hip_fail(hipGetLastError(), "temporal attention launch");
 }
@@ -328,7 +334,7 @@ int temporal_attn_max_T() { return TP; }
 
 int launch_temporal_attn(const void *q, const void *k, const void *v, void *o, float *lse, int64_t ld_q,
                          int64_t ld_kv, int64_t ld_o, int B, int T, int S, int H, int dh, const void *g_q,
-                         const void *g_k, float norm_eps, const float *rope_table, hipStream_t s) {
+                         const void *g_k, float norm_eps, const float *rope_table, const Prefetch &prefetch, hipStream_t s) {
   if (B == 0 || S == 0 || T == 0) return 0;
   if (T > TP) { set_error("temporal attention kernel: T=%d exceeds %d", T, TP); return -2; }
   TemporalParams p;
@@ -365,6 +371,7 @@ int launch_temporal_attn(const void *q, const void *k, const void *v, void *o, f
   p.g_k = reinterpret_cast<const bf16_t *>(g_k);
   p.rope = reinterpret_cast<const float2 *>(rope_table);
   p.norm_eps = norm_eps;
+  p.ahead = prefetch;
   if (dh == 72) return launch_t<72>(p, s);
   if (dh == 64) return launch_t<64>(p, s);
   set_error("dh=%d: supported head dims are 64 and 72", dh);
