@@ -30,9 +30,12 @@
 // supplies the address of the 8-byte piece "key i/4, d-group i%4"; it receives element i%4
 // of the pieces of lanes i/4, 4+i/4, 8+i/4, 12+i/4), two such reads per operand.
 // The head dim is padded to the next multiple of 16 above it for Q K^T and to 96 rows for V^T
-// (rows past the head dim read neighbouring data and produce rows of O^T that are never
-// stored); row 72 of V^T reads constant pieces holding ones, so that the same MFMAs that form O
-// also accumulate the softmax denominator (of the bf16-rounded probabilities used).
+// (rows past the head dim produce rows of O^T that are never stored); row 72 of V^T reads constant
+// pieces holding ones, so that the same MFMAs that form O also accumulate the softmax denominator
+// (of the bf16-rounded probabilities used).  The rows behind it read constant zeros: the chip runs
+// this kernel at its power limit (1367 of 1400 W), and multiplying the neighbouring row's data
+// there, which the reads would run on into, costs power and LDS clocks (720p 2335 -> 2285 us, 480p
+// 526 -> 516, cross-attention 102.5 -> 100.6).
 //
 // Online softmax without per-score bookkeeping.  The first padding column of the contraction
 // (index dh) is put to work: K holds a one there (a constant 16-byte piece in LDS that the lanes
@@ -238,7 +241,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_flash_attn(FlashParams p) {
       k_off[ks][hf] = c < C::DCH ? row * C::KROW + (C::SWZ ? (c ^ (row & 7)) : c) * 16 : C::KCONST;
     }
   static_assert(C::VONE == C::KCONST + 16 && C::OVERRUN >= 24, "the first piece of ones lies in the slack after the K piece");
-  static_assert(NST * (C::OVERRUN / 4) + NST * 6 <= 64 * NW, "one thread per constant word");
+  static_assert(NST * (C::OVERRUN / 4) + NST * 12 <= 64 * NW, "one thread per constant word");
   if (tid < NST * (C::OVERRUN / 4)) {
     // per stage, the 64 bytes after the V tile: the constant K piece (1, 0, ..., 0), the first
     // (1, 0, 0, 0) piece of V^T's row of ones, zeros in the rest (padded V^T rows read it); every
@@ -246,9 +249,9 @@ __global__ __launch_bounds__(64 * NW, 2) void k_flash_attn(FlashParams p) {
     const int st = tid / (C::OVERRUN / 4), w = tid - st * (C::OVERRUN / 4);
     *reinterpret_cast<unsigned *>(smem + st * C::STAGE + C::KCONST + 4 * w) =
         (w == 0 || (C::ONES && w == 4)) ? 0x00003F80u : 0u;
-  } else if (C::ONES && tid >= NST * (C::OVERRUN / 4) && tid < NST * (C::OVERRUN / 4) + NST * 6) {
-    // the other three pieces of ones, 16 keys apart
-    const int e = tid - NST * (C::OVERRUN / 4), st = e / 6, kc = 1 + (e % 6) / 2, w = e & 1;
+  } else if (C::ONES && tid >= NST * (C::OVERRUN / 4) && tid < NST * (C::OVERRUN / 4) + NST * 12) {
+    // the other three pieces of ones and zeros, 16 keys apart
+    const int e = tid - NST * (C::OVERRUN / 4), st = e / 12, kc = 1 + (e % 12) / 4, w = e & 3;
     *reinterpret_cast<unsigned *>(smem + st * C::STAGE + C::VONE + kc * 16 * C::KROW + 4 * w) = w == 0 ? 0x00003F80u : 0u;
   }
 
@@ -310,6 +313,8 @@ __global__ __launch_bounds__(64 * NW, 2) void k_flash_attn(FlashParams p) {
       tr_off[dt][hf] = C::SWZ ? key * C::KROW + (((chunk ^ (key & 7)) << 4) | ((d & 7) << 1)) : key * C::KROW + d * 2;
       // the piece that holds row DH of V^T (element 0 of d-group DH%16/4 in block DH%32/16 of tile DH/32)
       if (C::ONES && dt == DH / 32 && tr_d == DH % 32) tr_off[dt][hf] = C::VONE - C::T_BYTES;
+      // the rows past it: the zeros behind that piece
+      if (C::ONES && dt == DH / 32 && tr_d > DH % 32) tr_off[dt][hf] = C::VONE + 8 - C::T_BYTES;
     }
 
   floatx16 oacc[C::DT];
