@@ -141,6 +141,8 @@ struct AttnArgs {
   const void *q_norm_g;             // bf16 [dh] or null: RMS-normalise every query with these scales as it is loaded
   float q_norm_eps;
   Prefetch prefetch;
+  // keys and values of the outer indices from `split` on, counted from there; null: k and v hold them all
+  const void *k2, *v2; int split;
 };
 int launch_flash_attn(const AttnArgs &a, hipStream_t s);
 int temporal_attn_max_T();   // longest sequence the dedicated temporal kernel takes
@@ -175,7 +177,7 @@ int launch_timestep_conditioning(const CondArgs &c, const void *w_t1, const void
 
 // layers around the token-space step, solver
 int launch_position_code(float *pos, int Hp, int Wp, int D, hipStream_t s);
-int launch_patch_embed(const float *z, const void *W, const void *bias, const float *pos, void *x, int B, int C,
+int launch_patch_embed(const float *z, const void *W, const void *bias, const float *pos, void *x, int B, int Bz, int C,
                        int T, int Hp, int Wp, int D, hipStream_t s);
 int launch_output_head(const void *x, const float *temb, const float *table, const void *W, const void *bias,
                        float *out, int B, int C_out, int T, int Hp, int Wp, int D, float eps, hipStream_t s);

@@ -88,6 +88,8 @@ struct FlashParams {
   const bf16_t *q_norm_g;   // per-head RMS-norm scales of the queries [dh], or null
   float q_norm_eps;
   ddit::Prefetch ahead;
+  const bf16_t *k2, *v2;    // keys and values of the outer groups from `split` on
+  int split;
 };
 
 template <int DH>
@@ -154,12 +156,12 @@ __global__ __launch_bounds__(64 * NW, 2) void k_flash_attn(FlashParams p) {
   // fetches each where it is first used, one memory latency after the other.
   {
     const int a0 = p.spread, a1 = p.n_qtiles, a2 = p.n_units, a3 = p.H, a4 = p.g_inner, a5 = p.use_kv_len,
-              a6 = p.Lk_max, a7 = p.Lq;
+              a6 = p.Lk_max, a7 = p.Lq, a8 = p.split;
     const int64_t b0 = p.q_outer, b1 = p.q_inner, b2 = p.kv_outer, b3 = p.kv_inner, b4 = p.q_tok_step,
                   b5 = p.kv_tok_step, b6 = p.ld_q, b7 = p.ld_kv;
-    const void *c0 = p.q, *c1 = p.k, *c2 = p.v;
-    asm volatile("" ::"s"(a0), "s"(a1), "s"(a2), "s"(a3), "s"(a4), "s"(a5), "s"(a6), "s"(a7), "s"(b0), "s"(b1),
-                 "s"(b2), "s"(b3), "s"(b4), "s"(b5), "s"(b6), "s"(b7), "s"(c0), "s"(c1), "s"(c2));
+    const void *c0 = p.q, *c1 = p.k, *c2 = p.v, *c3 = p.k2, *c4 = p.v2;
+    asm volatile("" ::"s"(a0), "s"(a1), "s"(a2), "s"(a3), "s"(a4), "s"(a5), "s"(a6), "s"(a7), "s"(a8), "s"(b0), "s"(b1),
+                 "s"(b2), "s"(b3), "s"(b4), "s"(b5), "s"(b6), "s"(b7), "s"(c0), "s"(c1), "s"(c2), "s"(c3), "s"(c4));
   }
   // Workgroups are dealt round-robin to the 8 XCDs (each with its own L2).  All query tiles of a
   // (group, head) unit read the same K/V, so a unit lives on ONE XCD: unit u on XCD u % 8, its
@@ -185,9 +187,10 @@ __global__ __launch_bounds__(64 * NW, 2) void k_flash_attn(FlashParams p) {
   const int g_out = g / p.g_inner, g_in = g - g_out * p.g_inner;
   const int Lk = p.use_kv_len ? p.kv_len[g_out] : p.Lk_max;
   const int64_t q_tok0 = p.q_outer * g_out + p.q_inner * g_in;
-  const int64_t kv_tok0 = p.kv_outer * g_out + p.kv_inner * g_in;
-  const bf16_t *kbase = p.k + kv_tok0 * p.ld_kv + h * DH;
-  const bf16_t *vbase = p.v + kv_tok0 * p.ld_kv + h * DH;
+  const bool second = g_out >= p.split;
+  const int64_t kv_tok0 = p.kv_outer * (second ? g_out - p.split : g_out) + p.kv_inner * g_in;
+  const bf16_t *kbase = (second ? p.k2 : p.k) + kv_tok0 * p.ld_kv + h * DH;
+  const bf16_t *vbase = (second ? p.v2 : p.v) + kv_tok0 * p.ld_kv + h * DH;
   const int64_t kv_row = p.kv_tok_step * p.ld_kv;   // elements between consecutive keys
 
   // ---- Q fragment: lane holds query l32, d = 16 ks + 8 lh .. +7.  Column DH (zero for now) will
@@ -675,6 +678,9 @@ int launch_flash_attn(const AttnArgs &a, hipStream_t s) {
   p.q_norm_g = reinterpret_cast<const bf16_t *>(a.q_norm_g);
   p.q_norm_eps = a.q_norm_eps;
   p.ahead = a.prefetch;
+  p.k2 = reinterpret_cast<const bf16_t *>(a.k2 ? a.k2 : a.k);
+  p.v2 = reinterpret_cast<const bf16_t *>(a.k2 ? a.v2 : a.v);
+  p.split = a.k2 ? a.split : 0x7fffffff;
   if ((int64_t)a.n_groups * a.H > 0x3fffffff) {
     set_error("attention grid too large (groups=%d heads=%d)", a.n_groups, a.H);
     return -2;

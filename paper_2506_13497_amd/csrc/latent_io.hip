@@ -30,11 +30,12 @@ __global__ void k_position_code(float *__restrict__ pos, int Hp, int Wp, int D) 
 // owns output features d = tid, tid + 256, ... and keeps that feature's weight row in registers
 // across the tokens.  PC = compile-time channel count (weight rows fetched as 16-byte pieces,
 // patches read from LDS four values at a time), or 0 for any channel count.
+// Bz: samples of z; x's samples from there on (at most as many) are z's again.
 template <int PC>
 __global__ __launch_bounds__(256) void k_patch_embed(const float *__restrict__ z, const bf16_t *__restrict__ W,
                                                      const bf16_t *__restrict__ bias, const float *__restrict__ pos,
-                                                     bf16_t *__restrict__ x, int B, int C, int T, int Hp, int Wp,
-                                                     int D) {
+                                                     bf16_t *__restrict__ x, int B, int Bz, int C, int T, int Hp,
+                                                     int Wp, int D) {
   __shared__ __attribute__((aligned(16))) float patch[TOK_PER_WG][PATCH_MAX];
   const int P = PC > 0 ? 4 * PC : 4 * C;
   const int64_t S = (int64_t)Hp * Wp, N = (int64_t)B * T * S;
@@ -45,10 +46,10 @@ __global__ __launch_bounds__(256) void k_patch_embed(const float *__restrict__ z
     float v = 0.f;
     if (tok < N) {
       const int64_t bt = tok / S, s = tok - bt * S;
-      const int b = (int)(bt / T), t = (int)(bt - (int64_t)b * T);
+      const int b = (int)(bt / T), t = (int)(bt - (int64_t)b * T), bz = b < Bz ? b : b - Bz;
       const int i = (int)(s / Wp), j = (int)(s - (int64_t)i * Wp);
       const int c = p >> 2, di = (p >> 1) & 1, dj = p & 1;
-      v = z[((((int64_t)b * C + c) * T + t) * (2 * Hp) + (2 * i + di)) * (2 * Wp) + (2 * j + dj)];
+      v = z[((((int64_t)bz * C + c) * T + t) * (2 * Hp) + (2 * i + di)) * (2 * Wp) + (2 * j + dj)];
     }
     patch[k][p] = v;
   }
@@ -183,7 +184,7 @@ int launch_position_code(float *pos, int Hp, int Wp, int D, hipStream_t s) {
   return hip_fail(hipGetLastError(), "position code launch");
 }
 
-int launch_patch_embed(const float *z, const void *W, const void *bias, const float *pos, void *x, int B, int C,
+int launch_patch_embed(const float *z, const void *W, const void *bias, const float *pos, void *x, int B, int Bz, int C,
                        int T, int Hp, int Wp, int D, hipStream_t s) {
   const int64_t N = (int64_t)B * T * Hp * Wp;
   if (N == 0) return 0;
@@ -192,10 +193,10 @@ int launch_patch_embed(const float *z, const void *W, const void *bias, const fl
   const bf16_t *w = reinterpret_cast<const bf16_t *>(W), *bb = reinterpret_cast<const bf16_t *>(bias);
   bf16_t *xo = reinterpret_cast<bf16_t *>(x);
   // weight rows of 4*C bf16 are fetched as 16-byte pieces when that keeps them aligned
-  if (C == 4) hipLaunchKernelGGL(k_patch_embed<4>, grid, dim3(256), 0, s, z, w, bb, pos, xo, B, C, T, Hp, Wp, D);
-  else if (C == 8) hipLaunchKernelGGL(k_patch_embed<8>, grid, dim3(256), 0, s, z, w, bb, pos, xo, B, C, T, Hp, Wp, D);
-  else if (C == 16) hipLaunchKernelGGL(k_patch_embed<16>, grid, dim3(256), 0, s, z, w, bb, pos, xo, B, C, T, Hp, Wp, D);
-  else hipLaunchKernelGGL(k_patch_embed<0>, grid, dim3(256), 0, s, z, w, bb, pos, xo, B, C, T, Hp, Wp, D);
+  if (C == 4) hipLaunchKernelGGL(k_patch_embed<4>, grid, dim3(256), 0, s, z, w, bb, pos, xo, B, Bz, C, T, Hp, Wp, D);
+  else if (C == 8) hipLaunchKernelGGL(k_patch_embed<8>, grid, dim3(256), 0, s, z, w, bb, pos, xo, B, Bz, C, T, Hp, Wp, D);
+  else if (C == 16) hipLaunchKernelGGL(k_patch_embed<16>, grid, dim3(256), 0, s, z, w, bb, pos, xo, B, Bz, C, T, Hp, Wp, D);
+  else hipLaunchKernelGGL(k_patch_embed<0>, grid, dim3(256), 0, s, z, w, bb, pos, xo, B, Bz, C, T, Hp, Wp, D);
   return hip_fail(hipGetLastError(), "patch embedding launch");
 }
 
