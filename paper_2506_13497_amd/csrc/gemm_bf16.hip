@@ -684,13 +684,13 @@ __global__ __launch_bounds__(WGM *WGN *WGK * 64, 2) void k_gemm_bf16(GemmParams 
     }
     bf16x8 uf[2][TM], wf[2][TN];
     DL_READ_FRAGS(0, st, 0);
-    // One k-step.  TAIL = -1: in the middle of the tile; TAIL = i: the i-th of the tile's last DEFER steps, whose
-    // stage the epilogue uses.  Each group of MFMAs issues one MFMA first, then the LDS reads of the NEXT
+    // One k-step.  TAIL = -1: in the middle of the tile; TAIL = i: the i-th of the last ones, whose stage is not filled
+    // again (see tail_steps), `last`: the very last.  Each group of MFMAs issues one MFMA first, then the LDS reads of the NEXT
     // group's fragments, then the rest: the wait that the compiler places before the first MFMA (it always
     // waits for every LDS read issued so far) then covers only reads issued a whole group earlier.
-    auto k_step = [&](auto tail_tag) {
+    auto k_step = [&](auto tail_tag, auto last_tag) {
       constexpr int TAIL = decltype(tail_tag)::value;
-      constexpr bool LAST = TAIL == DEFER - 1;
+      constexpr bool LAST = decltype(last_tag)::value;
       const int st_next = st + 1 == NS ? 0 : st + 1, st_prev = st == 0 ? NS - 1 : st - 1;
 #pragma unroll
       for (int s = 0; s < SUBS; ++s) {
@@ -707,7 +707,7 @@ __global__ __launch_bounds__(WGM *WGN *WGK * 64, 2) void k_gemm_bf16(GemmParams 
         } else {
           // every fragment of this k-step is in registers (or on its way): past the barrier its stage is free,
           // and the next k-step's stage is complete
-          wait_vmcnt<(NS - 2 - (TAIL > 0 ? TAIL : 0)) * NJ>();
+          if constexpr (NS - 2 - TAIL >= 0) wait_vmcnt<(NS - 2 - (TAIL > 0 ? TAIL : 0)) * NJ>();
           lds_barrier();
           if (!LAST) DL_READ_FRAGS((s + 1) & 1, st_next, 0);
           if (TAIL < 0) ld_issue(J_0{}, J_A{}, st);
@@ -723,12 +723,24 @@ __global__ __launch_bounds__(WGM *WGN *WGK * 64, 2) void k_gemm_bf16(GemmParams 
       }
       st = st_next;
     };
-    for (int kt = 0; kt < nk - DEFER; ++kt) k_step(std::integral_constant<int, -1>{});
-    k_step(std::integral_constant<int, 0>{});
-    if constexpr (DEFER > 1) k_step(std::integral_constant<int, 1>{});
-    if constexpr (DEFER > 2) k_step(std::integral_constant<int, 2>{});
-    if constexpr (DEFER > 3) k_step(std::integral_constant<int, 3>{});
-    static_assert(DEFER <= 4, "k_step calls");
+    // The last k-steps of a tile, which fill no stage: DEFER, whose stages the epilogue uses.  Of a workgroup's last tile they
+    // are all that the ring holds, as behind it there is nothing to fetch: loads of length zero cost as much as others to
+    // issue.  Where the ring is long, that is; with three or four stages it gave nothing, and of the large tiles the compiler
+    // would keep the accumulators twice (a layer of 16 / 64 / 128 / 256 / 512 / 1200 tokens 79.3 / 82.4 / 85.1 / 90.2 / 107.0 /
+    // 140.3 -> 78.9 / 81.8 / 84.2 / 89.2 / 106.4 / 139.5 us).
+    auto tail_steps = [&](auto n_tag) {
+      constexpr int N = decltype(n_tag)::value;
+      static_assert(N <= 8, "k_step calls");
+#define DL_TAIL(I) if constexpr (N > I) k_step(std::integral_constant<int, I>{}, std::integral_constant<bool, I == N - 1>{})
+      DL_TAIL(0); DL_TAIL(1); DL_TAIL(2); DL_TAIL(3); DL_TAIL(4); DL_TAIL(5); DL_TAIL(6); DL_TAIL(7);
+#undef DL_TAIL
+    };
+    constexpr bool DRAIN = NS >= 6;
+    const bool last_tile = DRAIN && nk >= NS && (round + 1 >= p.rounds || tile_sequence_index(p, round + 1) < 0);
+    const int full = nk - (last_tile ? NS : DEFER);
+    for (int kt = 0; kt < full; ++kt) k_step(std::integral_constant<int, -1>{}, std::false_type{});
+    if (last_tile) tail_steps(std::integral_constant<int, DRAIN ? NS : DEFER>{});
+    else tail_steps(std::integral_constant<int, DEFER>{});
 
     // the i-th slice of EACH bytes inside the stages of the last DEFER k-steps
     auto slice = [&](int i, int each) {
