@@ -64,6 +64,7 @@ struct GemmParams {
   const float *gate_tab;
   const float *gate_c6; int64_t gate_c6_stride;
   int64_t tokens_per_sample;
+  int64_t tok0;   // tokens of the linear before this launch's first (a linear in two launches)
   int tiles_m; int tiles_n; int group_w; int total_tiles; int rounds;
   int split_steps; int split_tiles; int64_t split_stride;   // partial sums (EPI 3): k-steps and output tiles of one part, floats between parts
   int plain;   // row strides below 2^26 elements: a row group's offsets fit 32 bits
@@ -239,7 +240,7 @@ struct TileOut {
 
 // The sample a token belongs to (token counts stay below 2^30).
 __device__ __forceinline__ unsigned sample_of(const GemmParams &p, int64_t tok) {
-  return p.tokens_per_sample > 0x7fffffff ? 0u : (unsigned)tok / (unsigned)p.tokens_per_sample;
+  return p.tokens_per_sample > 0x7fffffff ? 0u : (unsigned)(tok + p.tok0) / (unsigned)p.tokens_per_sample;
 }
 
 // Rows of the residual stream and gate vectors of a wavefront's tiles, fetched before they are needed: lane l of a
@@ -940,6 +941,29 @@ int launch_checked(int tile, const GemmParams &p, hipStream_t s) {
 // 5.6 Mi 276.0 / 278.3, 14.6 Mi 971 / 962.  Compiled for the tiles that so few elements take.
 constexpr int64_t STREAM_WRITES_FROM = (int64_t)5 << 18, PLAIN_WRITES_FROM = (int64_t)6 << 20;
 
+// Two launches for a long contraction (fc2).  Its tiles read the tokens from memory rather than from the L2, the smaller
+// tiles more often, but the largest tile may fill the chip a few times and then a small part of it.  Then the tokens of the
+// full rounds are one launch of it, and the rest, at most three fifths of a round, another of whichever tile suits; where the
+// model sees a twentieth in that, which it is wont to overstate.  Returns the first one's tokens, or 0.  One launch / two,
+// microseconds, 1152 x 4608: 16600 tokens 191 / 161, 18000 193 / 172, 20000 206 / 203, 22500 235 / 227, 33500 411 / 331, 36000
+// 422 / 362, 42000 429 / 417, 50200 602 / 494, 67000 701 / 639, 70000 704 / 664 (27000, where two thirds of a round are left,
+// 274 / 281); 1344 x 5376: 15000 223 / 210, 16600 230 / 232, 25500 405 / 363, 67000 975 / 906; 2048 x 8192: 9300 292 / 290,
+// 25500 801 / 754.  Contractions of 1152 gain nothing: the model sees up to a sixth, and -4 to +9 hundredths came of it.
+constexpr int64_t TWO_LAUNCHES_FROM = 4096;
+constexpr int TWO_LAUNCHES_K = 3072;
+
+int64_t tokens_in_front(int epilogue, int64_t N, int n, int k, int cus) {
+  if (N < TWO_LAUNCHES_FROM || k < TWO_LAUNCHES_K) return 0;
+  const int64_t cols = (n + TILES[0].cols - 1) / TILES[0].cols, round = cus / cols * TILES[0].rows;
+  const int64_t rows = (N + TILES[0].rows - 1) / TILES[0].rows;
+  const int64_t front = rows * cols / cus * cus / cols * TILES[0].rows;   // whole rows of tiles
+  if (front <= 0 || front >= N || (N - front) * 5 > round * 3) return 0;
+  const float one = predicted_us(cheapest_tile(epilogue, N, n, k, cus), epilogue, N, n, k, cus);
+  const float two = predicted_us(0, epilogue, front, n, k, cus) +
+                    predicted_us(cheapest_tile(epilogue, N - front, n, k, cus), epilogue, N - front, n, k, cus);
+  return two < 0.95f * one ? front : 0;
+}
+
 int launch_residual_streaming(int tile, const GemmParams &p, hipStream_t s) {
   switch (tile) {
     case 4: return launch_checked<4, 2, 1, 2, 2, 3, 4>(tile, p, s);
@@ -951,10 +975,10 @@ int launch_residual_streaming(int tile, const GemmParams &p, hipStream_t s) {
   }
 }
 
+// elements: of the whole residual stream
 template <int EPI>
-int launch_epi(int tile, const GemmParams &p, hipStream_t s) {
+int launch_epi(int tile, const GemmParams &p, int64_t elements, hipStream_t s) {
   if (tile < 0) tile = cheapest_tile(EPI == 2 && p.out ? RESIDUAL_COPY : EPI, p.N, p.n, p.k, ddit::device_cus());
-  const int64_t elements = p.N * (int64_t)p.n;
   if (EPI == 2 && tile >= FIRST_SMALL_TILE && tile < N_TILES && elements >= STREAM_WRITES_FROM && elements < PLAIN_WRITES_FROM)
     return launch_residual_streaming(tile, p, s);
   switch (tile) {
@@ -1140,13 +1164,31 @@ int launch_gemm(int epilogue, const GemmArgs &a, hipStream_t s) {
   p.tokens_per_sample = a.tokens_per_sample > 0 ? a.tokens_per_sample : 1;
   p.tiles_m = 0; p.tiles_n = 0; p.group_w = 1; p.total_tiles = 0; p.rounds = 0; p.plain = 0;
   p.split_steps = p.split_tiles = 0; p.split_stride = 0;
-  switch (epilogue) {
-    case 0: return launch_epi<0>(a.tile, p, s);
-    case 1: return launch_epi<1>(a.tile, p, s);
-    case 2: return launch_epi<2>(a.tile, p, s);
+  if (epilogue < 0 || epilogue > 2) {
+    set_error("unknown epilogue %d", epilogue);
+    return -1;
   }
-  set_error("unknown epilogue %d", epilogue);
-  return -1;
+  p.tok0 = 0;
+  const int64_t elements = p.N * (int64_t)p.n;
+  auto launch = [&](int tile, const GemmParams &q) {
+    return epilogue == 0 ? launch_epi<0>(tile, q, elements, s) : epilogue == 1 ? launch_epi<1>(tile, q, elements, s)
+                                                                                : launch_epi<2>(tile, q, elements, s);
+  };
+  if (a.tile < 0) {
+    const int64_t front = tokens_in_front(epilogue == 2 && p.out ? RESIDUAL_COPY : epilogue, p.N, p.n, p.k, device_cus());
+    if (front > 0) {
+      GemmParams first = p;
+      first.N = front;
+      const int rc = launch(0, first);
+      if (rc != 0) return rc;
+      p.u += front * p.ld_u;
+      if (p.out) p.out += front * p.ld_out;
+      if (p.resid) p.resid += front * p.n;
+      p.N -= front;
+      p.tok0 = front;
+    }
+  }
+  return launch(a.tile, p);
 }
 
 }  // namespace ddit
