@@ -1039,11 +1039,11 @@ static int eps_theta_pair(const ddit_shape &shape, const Dims &d, const PairLayo
 // 5000 33.3 / 30.4, 6851 42.5 / 39.8, 9000 57.8 / 52.4, 12150 69.8 / 67.4, 16200 92.9 / 89.0, 24300 140.8 / 131.4; 4 of the 16
 // heads: 64 9.89 / 4.68, 2304 17.0 / 12.1.
 static bool pair_of_evaluations(const ddit_shape *shape, const Dims &d, const ddit_step_weights *weights, const ddit_io_weights *io,
-                                const float *z, const void *kv, const void *kv_second, const int32_t *valid_len,
+                                const float *z, const void *y, const void *y_second, const void *kv, const void *kv_second, const int32_t *valid_len,
                                 void *workspace, size_t workspace_bytes, ddit_shape *shape2, Dims *d2, PairLayout *lo) {
   if (!kv || !kv_second || !weights || 2 * d.B > 64 || 2 * d.N > PAIR_UP_TO || (shape->flags & DDIT_FLAG_TAPS)) return false;
   if (!io->w_patch || !io->final_table || !io->w_final || (shape->n_blocks > 0 && !weights->blocks)) return false;
-  for (const void *p : {(const void *)z, kv, kv_second, io->w_patch, io->w_final})
+  for (const void *p : {(const void *)z, y, y_second, kv, kv_second, io->w_patch, io->w_final})
     if (!aligned16(p)) return false;
   *shape2 = *shape;
   shape2->B = 2 * shape->B;
@@ -1092,8 +1092,8 @@ int ddit_sample(const ddit_shape *shape, const ddit_step_weights *weights, const
   ddit_shape shape2;
   Dims d2;
   PairLayout pair;
-  const bool together = y_uncond_or_null && pair_of_evaluations(shape, d, weights, io, z, cross_kv_or_null, cross_kv_uncond_or_null,
-                                                                y_valid_len_host, workspace, workspace_bytes, &shape2, &d2, &pair);
+  const bool together = y_uncond_or_null && pair_of_evaluations(shape, d, weights, io, z, y, y_uncond_or_null, cross_kv_or_null,
+                                                                cross_kv_uncond_or_null, y_valid_len_host, workspace, workspace_bytes, &shape2, &d2, &pair);
   int32_t valid[64];
   if (together)
     for (int b = 0; b < 2 * d.B; ++b) valid[b] = b < d.B && y_valid_len_host ? y_valid_len_host[b] : (int32_t)d.Ly;

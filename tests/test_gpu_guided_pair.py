@@ -2,7 +2,7 @@
 them.  Against the oracle's loop, at shapes where fc2 comes in parts beside h, where h lies where q|k|v and o were, with two
 samples of different text lengths, with the q/k treatment, and where there is no room and they run one by one; and against
 the same steps taken call by call: the same operands, fp32 sums in another order and bf16 roundings of intermediates that
-may fall the other way (2^-9 each; 2e-3 of a latent's change, measured 1.2e-3)."""
+may fall the other way (2^-9 each; measured 1.2e-3 of a latent's change, of which the bar is four times)."""
 import numpy as np
 import pytest
 import torch
@@ -50,3 +50,18 @@ def test_guided_steps_with_caches(B, T, Hp, Wp, D, H, dh, M, Ly, blocks, options
         lib.ddit_solver_step(z1, scratch[0], scratch[1], guidance, t, tn, z1.numel() // B)
     torch.cuda.synchronize()
     assert rel_fro(dev_to_f64(z) - st.z, dev_to_f64(z1) - st.z) < 5e-3
+
+
+@pytest.mark.parametrize("which", ["y", "y_uncond"])
+def test_misaligned_text_is_refused_with_caches(which):
+    """The text itself is not read when the caches are given, but a misaligned pointer is refused as without guidance."""
+    import paper_2506_13497_amd as lib
+    st = Setup(lib, syn.Shape(1, 2, 3, 4, 256, 4, 64, 1024, 16, 1), 4, 64)
+    y = torch.zeros(16 * 256 + 1, dtype=torch.bfloat16, device="cuda")
+    kv = torch.zeros(lib.ddit_cross_kv_bytes(st.shape) // 2, dtype=torch.bfloat16, device="cuda")
+    z = to_dev(st.z)
+    scratch = torch.empty((2,) + tuple(z.shape), dtype=torch.float32, device="cuda")
+    with pytest.raises(lib.DditError) as e:
+        lib.ddit_sample(st.shape, st.step, st.io, z, y[which == "y":], None, y[which == "y_uncond":], 2.5, 4, 1, 2, scratch,
+                        st.ws, kv, kv)
+    assert "aligned" in str(e.value)
