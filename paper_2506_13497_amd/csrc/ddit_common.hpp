@@ -35,10 +35,11 @@ struct Prefetch {
   const void *p[2];
   unsigned pieces[2];   // of 16 bytes; none: no further row
 };
-// Rows of a grid of `blocks` workgroups: its own, and so many more that none reads over 48 KB.
+// Rows of a grid of `blocks` workgroups: its own, and so many more that none reads over 48 KB, within what a grid may have
+// (weights of over 3.2 GB beside a single workgroup would ask for more).
 inline unsigned prefetch_rows(const Prefetch &f, int64_t blocks) {
-  const int64_t at_most = blocks * 3072;
-  return 1 + (unsigned)(((int64_t)f.pieces[0] + f.pieces[1] + at_most - 1) / at_most);
+  const int64_t at_most = blocks * 3072, rows = 1 + ((int64_t)f.pieces[0] + f.pieces[1] + at_most - 1) / at_most;
+  return (unsigned)(rows < 65535 ? rows : 65535);
 }
 
 template <int THREADS>

@@ -35,3 +35,22 @@ def test_block_with_weights_fetched_ahead(B, T, Hp, Wp, D, H, dh, M, options):
     torch.cuda.synchronize()
     ref = ora.block_fwd(to_f64(act["x"]), to_f64(act["y"]), None, c6.astype("float64"), dict_f64(wb), H, dh, rope_temporal=options)
     assert_parity(dev_to_f64(x_out), ref, "block of %d tokens" % sh.N)
+
+
+def test_weights_beyond_a_grids_rows():
+    """fc1 and fc2 of 3.3 GB each beside launches of one workgroup: more rows of workgroups would be due than a grid may have.
+    With weights of zero the MLP adds nothing, whatever its width."""
+    import paper_2506_13497_amd as m
+    D, widths = 4096, (8, 400000)
+    sh = syn.Shape(1, 1, 1, 1, D, 1, 64, widths[0], 6, 1)
+    act, c6, wb = syn.make_activations(sh, 71), to_dev(syn.make_c6(sh, 71, 0.5)), syn.make_block_weights(sh, 71, 0, table_std=0.02)
+    dwb, x, y = dict_dev(wb), to_dev(act["x"]), to_dev(act["y"])
+    zeros, out = torch.zeros(widths[1] * D, dtype=torch.bfloat16, device="cuda"), []
+    for M in widths:
+        for layer in dwb.values():
+            layer.update(w_fc1=zeros, w_fc2=zeros, b_fc1=zeros, b_fc2=zeros)
+        shape = m.make_shape(1, 1, 1, 1, D, 1, 64, M, 6, 1, 0)
+        out.append(torch.full((1, 1, 1, D), float("nan"), dtype=torch.bfloat16, device="cuda"))
+        m.ddit_stdit_block_fwd(shape, m.block_struct(dwb), x, y, None, c6, out[-1], m.alloc_workspace(shape))
+        torch.cuda.synchronize()
+    assert not torch.isnan(out[0]).any() and torch.equal(out[0], out[1])
