@@ -64,10 +64,10 @@ struct GemmParams {
   const float *gate_tab;
   const float *gate_c6; int64_t gate_c6_stride;
   int64_t tokens_per_sample;
-  int64_t tok0;   // tokens of the linear before this launch's first (a linear in two launches)
   int tiles_m; int tiles_n; int group_w; int total_tiles; int rounds;
   int split_steps; int split_tiles; int64_t split_stride;   // partial sums (EPI 3): k-steps and output tiles of one part, floats between parts
   int plain;   // row strides below 2^26 elements: a row group's offsets fit 32 bits
+  unsigned tok0;   // tokens of the linear before this launch's first (a linear in two launches)
 };
 
 // A grouped launch: one token matrix u against G weight matrices of the same shape [group_n, k], each
@@ -240,7 +240,7 @@ struct TileOut {
 
 // The sample a token belongs to (token counts stay below 2^30).
 __device__ __forceinline__ unsigned sample_of(const GemmParams &p, int64_t tok) {
-  return p.tokens_per_sample > 0x7fffffff ? 0u : (unsigned)(tok + p.tok0) / (unsigned)p.tokens_per_sample;
+  return p.tokens_per_sample > 0x7fffffff ? 0u : ((unsigned)tok + p.tok0) / (unsigned)p.tokens_per_sample;
 }
 
 // Rows of the residual stream and gate vectors of a wavefront's tiles, fetched before they are needed: lane l of a
@@ -473,7 +473,7 @@ __device__ __forceinline__ void gemm_epilogue(floatx16 (&acc)[TN][TM], unsigned 
 typedef __attribute__((address_space(3))) void *lds_ptr_t;
 typedef __attribute__((address_space(1))) const void *gbl_ptr_t;
 
-template <int WGM, int WGN, int WGK, int TM, int TN, int NS, int EPI, class GT>
+template <int WGM, int WGN, int WGK, int TM, int TN, int NS, int EPI, bool DRAIN, class GT>
 __global__ __launch_bounds__(WGM *WGN *WGK * 64, 2) void k_gemm_bf16(GemmParams p, GT gt) {
   using C = GemmCfg<WGM, WGN, WGK, TM, TN, NS>;
   constexpr bool GROUPED = !std::is_same<GT, NoGroups>::value;
@@ -726,9 +726,9 @@ __global__ __launch_bounds__(WGM *WGN *WGK * 64, 2) void k_gemm_bf16(GemmParams 
     };
     // The last k-steps of a tile, which fill no stage: DEFER, whose stages the epilogue uses.  Of a workgroup's last tile they
     // are all that the ring holds, as behind it there is nothing to fetch: loads of length zero cost as much as others to
-    // issue.  Where the ring is long, that is; with three or four stages it gave nothing, and of the large tiles the compiler
-    // would keep the accumulators twice (a layer of 16 / 64 / 128 / 256 / 512 / 1200 tokens 79.3 / 82.4 / 85.1 / 90.2 / 107.0 /
-    // 140.3 -> 78.9 / 81.8 / 84.2 / 89.2 / 106.4 / 139.5 us).
+    // issue.  DRAIN: where the ring is long and the contraction fills it (launch_one); with three or four stages it gave
+    // nothing, and of the large tiles the compiler would keep the accumulators twice (a layer of 16 / 64 / 128 / 256 / 512 /
+    // 1200 tokens 79.3 / 82.4 / 85.1 / 90.2 / 107.0 / 140.3 -> 78.9 / 81.8 / 84.2 / 89.2 / 106.4 / 139.5 us).
     auto tail_steps = [&](auto n_tag) {
       constexpr int N = decltype(n_tag)::value;
       static_assert(N <= 8, "k_step calls");
@@ -736,7 +736,6 @@ __global__ __launch_bounds__(WGM *WGN *WGK * 64, 2) void k_gemm_bf16(GemmParams 
       DL_TAIL(0); DL_TAIL(1); DL_TAIL(2); DL_TAIL(3); DL_TAIL(4); DL_TAIL(5); DL_TAIL(6); DL_TAIL(7);
 #undef DL_TAIL
     };
-    constexpr bool DRAIN = NS >= 6;
     const bool last_tile = DRAIN && nk >= NS && (round + 1 >= p.rounds || tile_sequence_index(p, round + 1) < 0);
     const int full = nk - (last_tile ? NS : DEFER);
     for (int kt = 0; kt < full; ++kt) k_step(std::integral_constant<int, -1>{}, std::false_type{});
@@ -809,11 +808,24 @@ __global__ __launch_bounds__(WGM *WGN *WGK * 64, 2) void k_gemm_bf16(GemmParams 
 #undef DL_MFMAS
 }
 
+template <int WGM, int WGN, int WGK, int TM, int TN, int NS, int EPI, bool DRAIN, class GT>
+int launch_kernel(const GemmParams &p, int grid, hipStream_t s, const GT &gt) {
+  using C = GemmCfg<WGM, WGN, WGK, TM, TN, NS>;
+  static bool attr_set = false;  // benign race: the attribute is idempotent
+  if (!attr_set) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_bf16<WGM, WGN, WGK, TM, TN, NS, EPI, DRAIN, GT>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, C::SMEM);
+    if (e != hipSuccess) return ddit::hip_fail(e, "gemm hipFuncSetAttribute");
+    attr_set = true;
+  }
+  hipLaunchKernelGGL((k_gemm_bf16<WGM, WGN, WGK, TM, TN, NS, EPI, DRAIN, GT>), dim3((unsigned)grid), dim3(C::NT), C::SMEM, s, p, gt);
+  return ddit::hip_fail(hipGetLastError(), "gemm launch");
+}
+
 template <int WGM, int WGN, int WGK, int TM, int TN, int NS, int EPI, class GT = NoGroups>
 int launch_one(const GemmParams &p0, hipStream_t s, const GT &gt = GT()) {
   using C = GemmCfg<WGM, WGN, WGK, TM, TN, NS>;
-  constexpr int LDS_BYTES = C::SMEM;
-  static_assert(LDS_BYTES <= 160 * 1024, "the tile's stages must fit the LDS");
+  static_assert(C::SMEM <= 160 * 1024, "the tile's stages must fit the LDS");
   GemmParams p = p0;
   const int64_t tiles_m = (p.N + C::BM - 1) / C::BM;
   p.tiles_m = (int)tiles_m;
@@ -841,15 +853,14 @@ int launch_one(const GemmParams &p0, hipStream_t s, const GT &gt = GT()) {
   if (grid < 8) grid = 8;
   if (p.total_tiles <= grid) grid = (p.total_tiles + 7) & ~7;
   p.rounds = ((p.total_tiles + 7) / 8 + grid / 8 - 1) / (grid / 8);
-  static bool attr_set = false;  // benign race: the attribute is idempotent
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_bf16<WGM, WGN, WGK, TM, TN, NS, EPI, GT>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
-    if (e != hipSuccess) return ddit::hip_fail(e, "gemm hipFuncSetAttribute");
-    attr_set = true;
-  }
-  hipLaunchKernelGGL((k_gemm_bf16<WGM, WGN, WGK, TM, TN, NS, EPI, GT>), dim3((unsigned)grid), dim3(C::NT), LDS_BYTES, s, p, gt);
-  return ddit::hip_fail(hipGetLastError(), "gemm launch");
+  // A contraction shorter than the ring has no k-steps to drain, and the kernel without them is the shorter one to fetch: a
+  // block of hidden size 256, 16 / 64 / 576 tokens, one kernel for both / two, 109.4 / 105.1, 113.4 / 111.7, 124.1 / 123.7 us; 4 heads
+  // of 1152 features, 16 tokens 160.2 / 156.8 (a step of 28 blocks, 64 tokens, 4.72 / 4.76 ms, as two kernels take turns).
+  // The residual update is one kernel for both.
+  constexpr bool LONG_RING = NS >= 6, EITHER = LONG_RING && !is_residual(EPI);
+  if (!EITHER || (EPI == 3 ? p.split_steps : nk) >= NS)
+    return launch_kernel<WGM, WGN, WGK, TM, TN, NS, EPI, LONG_RING, GT>(p, grid, s, gt);
+  return launch_kernel<WGM, WGN, WGK, TM, TN, NS, EPI, LONG_RING && !EITHER, GT>(p, grid, s, gt);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -953,7 +964,6 @@ constexpr int64_t TWO_LAUNCHES_FROM = 4096;
 constexpr int TWO_LAUNCHES_K = 3072;
 
 int64_t tokens_in_front(int epilogue, int64_t N, int n, int k, int cus) {
-  if (N < TWO_LAUNCHES_FROM || k < TWO_LAUNCHES_K) return 0;
   const int64_t cols = (n + TILES[0].cols - 1) / TILES[0].cols, round = cus / cols * TILES[0].rows;
   const int64_t rows = (N + TILES[0].rows - 1) / TILES[0].rows;
   const int64_t front = rows * cols / cus * cus / cols * TILES[0].rows;   // whole rows of tiles
@@ -1174,7 +1184,7 @@ int launch_gemm(int epilogue, const GemmArgs &a, hipStream_t s) {
     return epilogue == 0 ? launch_epi<0>(tile, q, elements, s) : epilogue == 1 ? launch_epi<1>(tile, q, elements, s)
                                                                                 : launch_epi<2>(tile, q, elements, s);
   };
-  if (a.tile < 0) {
+  if (a.tile < 0 && p.N >= TWO_LAUNCHES_FROM && p.k >= TWO_LAUNCHES_K) {
     const int64_t front = tokens_in_front(epilogue == 2 && p.out ? RESIDUAL_COPY : epilogue, p.N, p.n, p.k, device_cus());
     if (front > 0) {
       GemmParams first = p;
@@ -1185,7 +1195,7 @@ int launch_gemm(int epilogue, const GemmArgs &a, hipStream_t s) {
       if (p.out) p.out += front * p.ld_out;
       if (p.resid) p.resid += front * p.n;
       p.N -= front;
-      p.tok0 = front;
+      p.tok0 = (unsigned)front;
     }
   }
   return launch(a.tile, p);
