@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "prefetch.hpp"
+
 typedef __bf16 bf16_t;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
@@ -29,35 +31,17 @@ __device__ __forceinline__ float wave_sum(float v) {
 }
 
 namespace ddit {
-// Weights that the launches after this one read.  Further rows of workgroups (blockIdx.y > 0), each as many as the launch's
-// own, read them once, in address order, so that they are in the memory-side cache by then.
-struct Prefetch {
-  const void *p[2];
-  unsigned pieces[2];   // of 16 bytes; none: no further row
-};
-// Rows of a grid of `blocks` workgroups: its own, and so many more that none reads over 48 KB, within what a grid may have
-// (weights of over 3.2 GB beside a single workgroup would ask for more).
-inline unsigned prefetch_rows(const Prefetch &f, int64_t blocks) {
-  const int64_t at_most = blocks * 3072, rows = 1 + ((int64_t)f.pieces[0] + f.pieces[1] + at_most - 1) / at_most;
-  return (unsigned)(rows < 65535 ? rows : 65535);
-}
-
 template <int THREADS>
 __device__ __forceinline__ void prefetch_share(const Prefetch &f) {
   constexpr unsigned AHEAD = 8;   // loads in flight per thread
 #pragma unroll
   for (int w = 0; w < 2; ++w) {
     const uint4 *src = reinterpret_cast<const uint4 *>(f.p[w]);
-    const unsigned n = f.pieces[w], readers = gridDim.x * (gridDim.y - 1);
-    const unsigned share = (n + readers - 1) / readers, from = ((blockIdx.y - 1) * gridDim.x + blockIdx.x) * share;
-    const unsigned end = from + share < n ? from + share : n;
-    for (unsigned at = from; at < end; at += THREADS * AHEAD) {
+    const PrefetchSpan span = prefetch_span(f.pieces[w], gridDim.x * (gridDim.y - 1), (blockIdx.y - 1) * gridDim.x + blockIdx.x);
+    for (unsigned at = span.from; at < span.end; at += THREADS * AHEAD) {
       uint4 v[AHEAD];
 #pragma unroll
-      for (unsigned j = 0; j < AHEAD; ++j) {
-        const unsigned i = at + j * THREADS + threadIdx.x;
-        v[j] = src[i < end ? i : end - 1];
-      }
+      for (unsigned j = 0; j < AHEAD; ++j) v[j] = src[prefetch_piece(span, at, j, THREADS, threadIdx.x)];
 #pragma unroll
       for (unsigned j = 0; j < AHEAD; ++j) asm volatile("" ::"v"(v[j].x), "v"(v[j].y), "v"(v[j].z), "v"(v[j].w));
     }

@@ -306,16 +306,6 @@ struct Taps {
 
 #define DDIT_TRY(expr) do { int rc_ = (expr); if (rc_ != DDIT_OK) return rc_; } while (0)
 
-// Up to this many tokens attention and LayerNorm, which leave the memory idle, have the weights of the launches after them
-// fetched.  A step reads every weight from memory (2.4 GB of them), and a linear fetches its own in pieces of one line from
-// all rows at once, which the memory serves slowly: at 2304 tokens fc1 takes 27.8 us instead of 32.2 once its weights are in
-// the memory-side cache, the out-projections 14.8 instead of 18.0, and the launches that fetch them 1-2 us more.  Without /
-// with, us a layer of a step: 16 tokens 80.7 / 79.3, 64 90.0 / 82.5, 128 89.2 / 85.0, 180 88.7 / 86.2, 200 87.4 / 89.9, 256
-// 92.5 / 90.1, 320 99.5 / 96.8, 400 97.5 / 97.7, 512 109.2 / 107.1, 702 115.0 / 113.6, 1200 145.2 / 141.0, 1728 158.2 / 154.4,
-// 2304 187.6 / 183.0, 3000 210.5 / 209.6, 3680 251.2 / 252.1, 5000 294.9 / 295.5; with 4 of the 16 heads: 64 81.1 / 76.2,
-// 1200 125.2 / 122.4, 2304 149.2 / 146.2, 3000 168.1 / 166.5.
-constexpr int64_t PREFETCH_UP_TO = 3200;
-
 // One layer on the fp32 stream x (in the workspace).
 // pending: a residual update of the layer before that has not been added to x yet (parts == 0: none); the layer
 // adds it and may leave its own last one
@@ -339,7 +329,7 @@ int run_layer(ddit_attn_kind kind, const Dims &d, const ddit_layer_weights &w, c
     g.u = u; g.ld_u = ld_u; g.W = W; g.bias = b; g.N = rows; g.n = n; g.k = k; g.tokens_per_sample = d.L;
   };
   auto weights_ahead = [&](const void *w0, int64_t n0, const void *w1 = nullptr, int64_t n1 = 0) {
-    if (N > PREFETCH_UP_TO) return Prefetch{};
+    if (!prefetch_pays(N, 2 * (n0 + n1))) return Prefetch{};
     return Prefetch{{w0, w1}, {(unsigned)(n0 / 8), (unsigned)(n1 / 8)}};
   };
   auto gated = [&](int row) {
