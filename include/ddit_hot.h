@@ -258,7 +258,8 @@ int ddit_self_attn_fwd(ddit_attn_kind kind, const ddit_shape *shape, void *q, vo
 /* ---- output tiles of the linear: for tuning and for parity tests of every compiled tile ----
  * The linear is compiled for a short list of output tiles (rows x cols of out per workgroup) and
  * ddit_linear_fwd takes, per call, the one that a cost model of the kernel prices cheapest for
- * (epilogue, N, n, k) on the current device.  None of the three calls below is on the hot path. */
+ * (epilogue, N, n, k) on the current device; a long contraction of many tokens may be two launches,
+ * each with its own tile (ddit_linear_front_tokens).  None of the calls below is on the hot path. */
 
 /* Number of compiled tiles; tile indices are 0 .. count-1. */
 int ddit_linear_tile_count(void);
@@ -271,7 +272,7 @@ int ddit_linear_tile_count(void);
 int ddit_linear_tile_info(int tile, int32_t *rows, int32_t *cols, int32_t *wavefronts,
                           int32_t *workgroups_per_cu);
 
-/* The tile ddit_linear_fwd would take for this problem on a device of compute_units CUs
+/* The tile ddit_linear_fwd would take for this problem, as one launch, on a device of compute_units CUs
  * (compute_units <= 0: the current device's count, 256 if there is no device) -> *tile_out.
  * epilogue: DDIT_EPI_RESIDUAL_F32 | DDIT_EPI_COPY for a residual update whose out is given.
  * predicted_us_host, if not NULL, is a HOST array of ddit_linear_tile_count() floats that
@@ -280,7 +281,12 @@ int ddit_linear_tile_info(int tile, int32_t *rows, int32_t *cols, int32_t *wavef
 int ddit_linear_tile_choice(int epilogue, int64_t N, int32_t n, int32_t k, int32_t compute_units,
                             int32_t *tile_out, float *predicted_us_host);
 
-/* ddit_linear_fwd with the tile fixed (tile < 0: the model's choice, i.e. ddit_linear_fwd itself).
+/* *tokens_out: 0 where ddit_linear_fwd is one launch with the tile above; else it is two, the first of so many tokens with
+ * tile 0 and the second of the others with the tile of a linear of that many tokens.  Arguments as above.  Host only;
+ * needs no GPU. */
+int ddit_linear_front_tokens(int epilogue, int64_t N, int32_t n, int32_t k, int32_t compute_units, int64_t *tokens_out);
+
+/* ddit_linear_fwd as one launch with the tile fixed (tile < 0: the model's choice, i.e. ddit_linear_fwd itself).
  * Every tile computes the same function for every valid shape; only the time differs. */
 int ddit_linear_fwd_tile(int tile, int epilogue, const void *u, int64_t ld_u, const void *W, const void *bias,
                          int64_t N, int32_t n, int32_t k, void *out, int64_t ld_out, float *resid,

@@ -109,6 +109,8 @@ int gemm_tile_info(int tile, int *rows, int *cols, int *wavefronts, int *wg_per_
 // the tile the launcher would take (cus <= 0: the current device's CU count); us_per_tile, if not
 // null, receives the model's time for each of the gemm_tile_count() tiles
 int gemm_tile_choice(int epilogue, bool copy, int64_t N, int n, int k, int cus, float *us_per_tile);
+// tokens of the first of the two launches that the launcher would make of this linear, 0 if it makes one
+int64_t gemm_tokens_in_front(int epilogue, bool copy, int64_t N, int n, int k, int cus);
 
 struct AttnArgs {
   const void *q, *k, *v; void *o; float *lse;

@@ -829,6 +829,16 @@ int ddit_linear_tile_choice(int epilogue, int64_t N, int32_t n, int32_t k, int32
   return DDIT_OK;
 }
 
+int ddit_linear_front_tokens(int epilogue, int64_t N, int32_t n, int32_t k, int32_t compute_units, int64_t *tokens_out) {
+  const bool copy = epilogue == (DDIT_EPI_RESIDUAL_F32 | DDIT_EPI_COPY);
+  if (copy) epilogue = DDIT_EPI_RESIDUAL_F32;
+  if (epilogue < 0 || epilogue > 2) { set_error("unknown epilogue %d", epilogue); return DDIT_ERR_INVALID_ARG; }
+  if (N < 0 || n < 1 || k < 1) { set_error("linear: N=%lld n=%d k=%d", (long long)N, n, k); return DDIT_ERR_INVALID_ARG; }
+  if (!tokens_out) { set_error("tokens_out is NULL"); return DDIT_ERR_INVALID_ARG; }
+  *tokens_out = gemm_tokens_in_front(epilogue, copy, N, n, k, compute_units);
+  return DDIT_OK;
+}
+
 int ddit_linear_fwd(int epilogue, const void *u, int64_t ld_u, const void *W, const void *bias, int64_t N,
                     int32_t n, int32_t k, void *out, int64_t ld_out, float *resid, const float *ada_table,
                     const float *c6, int gate_row, int64_t tokens_per_sample, void *hip_stream) {

@@ -44,7 +44,6 @@
 // also storing bf16(x).
 #include "ddit_common.hpp"
 
-#include <string.h>
 #include <cmath>
 #include <type_traits>
 
@@ -955,15 +954,19 @@ constexpr int64_t STREAM_WRITES_FROM = (int64_t)5 << 18, PLAIN_WRITES_FROM = (in
 // Two launches for a long contraction (fc2).  Its tiles read the tokens from memory rather than from the L2, the smaller
 // tiles more often, but the largest tile may fill the chip a few times and then a small part of it.  Then the tokens of the
 // full rounds are one launch of it, and the rest, at most three fifths of a round, another of whichever tile suits; where the
-// model sees a twentieth in that, which it is wont to overstate.  Returns the first one's tokens, or 0.  One launch / two,
+// model sees seven hundredths in that, of which it is wont to overstate as much (where it saw 6.4 of them, 1344 x 5376 and 16600
+// tokens, it was 230 / 232 us).  The rest may take a tile that sums k in two halves: a prediction's error against 64 bits is
+// 0.999-1.000 times that of one launch (16700 to 33600 tokens, six blocks).  Returns the first one's tokens, or 0.  One launch / two,
 // microseconds, 1152 x 4608: 16600 tokens 191 / 161, 18000 193 / 172, 20000 206 / 203, 22500 235 / 227, 33500 411 / 331, 36000
 // 422 / 362, 42000 429 / 417, 50200 602 / 494, 67000 701 / 639, 70000 704 / 664 (27000, where two thirds of a round are left,
-// 274 / 281); 1344 x 5376: 15000 223 / 210, 16600 230 / 232, 25500 405 / 363, 67000 975 / 906; 2048 x 8192: 9300 292 / 290,
+// 274 / 281); 1344 x 5376: 15000 223 / 210, 25500 405 / 363, 67000 975 / 906; 2048 x 8192: 9300 292 / 290,
 // 25500 801 / 754.  Contractions of 1152 gain nothing: the model sees up to a sixth, and -4 to +9 hundredths came of it.
 constexpr int64_t TWO_LAUNCHES_FROM = 4096;
 constexpr int TWO_LAUNCHES_K = 3072;
+constexpr float TWO_LAUNCHES_BELOW = 0.93f;
 
 int64_t tokens_in_front(int epilogue, int64_t N, int n, int k, int cus) {
+  if (N < TWO_LAUNCHES_FROM || k < TWO_LAUNCHES_K) return 0;
   const int64_t cols = (n + TILES[0].cols - 1) / TILES[0].cols, round = cus / cols * TILES[0].rows;
   const int64_t rows = (N + TILES[0].rows - 1) / TILES[0].rows;
   const int64_t front = rows * cols / cus * cus / cols * TILES[0].rows;   // whole rows of tiles
@@ -971,7 +974,7 @@ int64_t tokens_in_front(int epilogue, int64_t N, int n, int k, int cus) {
   const float one = predicted_us(cheapest_tile(epilogue, N, n, k, cus), epilogue, N, n, k, cus);
   const float two = predicted_us(0, epilogue, front, n, k, cus) +
                     predicted_us(cheapest_tile(epilogue, N - front, n, k, cus), epilogue, N - front, n, k, cus);
-  return two < 0.95f * one ? front : 0;
+  return two < TWO_LAUNCHES_BELOW * one ? front : 0;
 }
 
 int launch_residual_streaming(int tile, const GemmParams &p, hipStream_t s) {
@@ -1028,6 +1031,10 @@ int gemm_tile_choice(int epilogue, bool copy, int64_t N, int n, int k, int cus, 
   return cheapest_tile(epilogue, N, n, k, cus);
 }
 
+int64_t gemm_tokens_in_front(int epilogue, bool copy, int64_t N, int n, int k, int cus) {
+  return tokens_in_front(epilogue == 2 && copy ? RESIDUAL_COPY : epilogue, N, n, k, cus > 0 ? cus : device_cus());
+}
+
 template <int WGM, int WGN, int WGK, int TM, int TN, int NS>
 int launch_grouped_tile(const GemmParams &p, const GroupTable &gt, hipStream_t s) {
   return launch_one<WGM, WGN, WGK, TM, TN, NS, 0, GroupTable>(p, s, gt);
@@ -1057,15 +1064,12 @@ int launch_gemm_grouped(const GemmArgs &a, int G, const void *const *W, const vo
     gt.bias[g] = bias ? reinterpret_cast<const bf16_t *>(bias[g]) : nullptr;
     gt.out[g] = reinterpret_cast<bf16_t *>(out[g]);
   }
-  GemmParams p;
+  GemmParams p{};
   p.u = reinterpret_cast<const bf16_t *>(a.u); p.ld_u = a.ld_u;
   p.W = gt.W[0]; p.bias = gt.bias[0];
   p.N = a.N; p.n = n_all; p.k = a.k;
   p.out = gt.out[0]; p.ld_out = a.ld_out;
-  p.resid = nullptr; p.gate_tab = nullptr; p.gate_c6 = nullptr; p.gate_c6_stride = 0;
   p.tokens_per_sample = a.tokens_per_sample > 0 ? a.tokens_per_sample : 1;
-  p.tiles_m = 0; p.tiles_n = 0; p.group_w = 1; p.total_tiles = 0; p.rounds = 0; p.plain = 0;
-  p.split_steps = p.split_tiles = 0; p.split_stride = 0;
   switch (tile) {
     case 0: return launch_grouped_tile<2, 4, 1, 3, 3, 2>(p, gt, s);
     case 1: return launch_grouped_tile<2, 4, 1, 4, 2, 2>(p, gt, s);
@@ -1130,8 +1134,7 @@ int launch_gemm_partial(const GemmArgs &a, int parts, int tile, float *out, int6
     set_error("linear: n*k = %lld or N*ld_u = %lld exceeds the 31-bit index range", (long long)a.n * a.k, (long long)(a.N * a.ld_u));
     return -2;
   }
-  GemmParams p;
-  memset(&p, 0, sizeof(p));
+  GemmParams p{};
   p.u = reinterpret_cast<const bf16_t *>(a.u); p.ld_u = a.ld_u;
   p.W = reinterpret_cast<const bf16_t *>(a.W);
   p.bias = reinterpret_cast<const bf16_t *>(a.bias);
@@ -1163,7 +1166,7 @@ int launch_gemm(int epilogue, const GemmArgs &a, hipStream_t s) {
     set_error("linear: N*ld_u = %lld exceeds the 31-bit activation index range", (long long)(a.N * a.ld_u));
     return -2;
   }
-  GemmParams p;
+  GemmParams p{};
   p.u = reinterpret_cast<const bf16_t *>(a.u); p.ld_u = a.ld_u;
   p.W = reinterpret_cast<const bf16_t *>(a.W);
   p.bias = reinterpret_cast<const bf16_t *>(a.bias);
@@ -1172,31 +1175,26 @@ int launch_gemm(int epilogue, const GemmArgs &a, hipStream_t s) {
   p.resid = a.resid;
   p.gate_tab = a.gate_tab; p.gate_c6 = a.gate_c6; p.gate_c6_stride = a.gate_c6_stride;
   p.tokens_per_sample = a.tokens_per_sample > 0 ? a.tokens_per_sample : 1;
-  p.tiles_m = 0; p.tiles_n = 0; p.group_w = 1; p.total_tiles = 0; p.rounds = 0; p.plain = 0;
-  p.split_steps = p.split_tiles = 0; p.split_stride = 0;
   if (epilogue < 0 || epilogue > 2) {
     set_error("unknown epilogue %d", epilogue);
     return -1;
   }
-  p.tok0 = 0;
   const int64_t elements = p.N * (int64_t)p.n;
   auto launch = [&](int tile, const GemmParams &q) {
     return epilogue == 0 ? launch_epi<0>(tile, q, elements, s) : epilogue == 1 ? launch_epi<1>(tile, q, elements, s)
                                                                                 : launch_epi<2>(tile, q, elements, s);
   };
-  if (a.tile < 0 && p.N >= TWO_LAUNCHES_FROM && p.k >= TWO_LAUNCHES_K) {
-    const int64_t front = tokens_in_front(epilogue == 2 && p.out ? RESIDUAL_COPY : epilogue, p.N, p.n, p.k, device_cus());
-    if (front > 0) {
-      GemmParams first = p;
-      first.N = front;
-      const int rc = launch(0, first);
-      if (rc != 0) return rc;
-      p.u += front * p.ld_u;
-      if (p.out) p.out += front * p.ld_out;
-      if (p.resid) p.resid += front * p.n;
-      p.N -= front;
-      p.tok0 = (unsigned)front;
-    }
+  const int64_t front = a.tile < 0 ? gemm_tokens_in_front(epilogue, p.out != nullptr, p.N, p.n, p.k, 0) : 0;
+  if (front > 0) {
+    GemmParams first = p;
+    first.N = front;
+    const int rc = launch(0, first);
+    if (rc != 0) return rc;
+    p.u += front * p.ld_u;
+    if (p.out) p.out += front * p.ld_out;
+    if (p.resid) p.resid += front * p.n;
+    p.N -= front;
+    p.tok0 = (unsigned)front;
   }
   return launch(a.tile, p);
 }

@@ -174,6 +174,9 @@ static int do_linear(FILE *f) {
   printf("tile %d %d", rc, tile);
   for (int t = 0; t < nt; ++t) printf(" %.4f", us[t]);
   printf("\n");
+  int64_t front = -1;
+  printf("front %d", ddit_linear_front_tokens((int)v[0], v[1], (int32_t)v[2], (int32_t)v[3], (int32_t)v[4], &front));
+  printf(" %lld\n", (long long)front);
   // the linear's own validation: refused before any launch
   alignas(16) static unsigned char buf[64];
   printf("v linear_null %d\n", ddit_linear_fwd((int)v[0], nullptr, 8, buf, nullptr, 8, 8, 8, buf, 8, nullptr, nullptr, nullptr, -1, 1, nullptr));

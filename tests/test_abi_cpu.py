@@ -255,6 +255,18 @@ def test_linear_tile_list_and_cost_model(m):
             us = m.ddit_linear_tile_choice(epi, N, 1152, 1152, 256)[1]
             assert all(a >= b for a, b in zip(us, prev))
             prev = us
+    # two launches: only long contractions of many tokens, whole rounds of the largest tile in the first
+    front = C.c_int64(-7)
+    assert lib.ddit_linear_front_tokens(3, 100, 64, 64, 256, C.byref(front)) == -1
+    assert lib.ddit_linear_front_tokens(0, -1, 64, 64, 256, C.byref(front)) == -1
+    assert lib.ddit_linear_front_tokens(0, 100, 64, 64, 256, None) == -1
+    for epi in (0, 1, 2, 2 | m.DDIT_EPI_COPY):
+        assert m.ddit_linear_front_tokens(epi, 33000, 1152, 3072, 256) == 32640
+        for N, n, k in [(0, 1152, 4608), (100, 1152, 4608), (33000, 1152, 3064), (32640, 1152, 4608), (42433, 1152, 4608), (48600, 1152, 1152)]:
+            assert m.ddit_linear_front_tokens(epi, N, n, k, 256) == 0
+    for N, front in [(16600, 16320), (18000, 16320), (33500, 32640), (36000, 32640), (50200, 49152), (67000, 65472)]:   # measured gains
+        assert m.ddit_linear_front_tokens(2, N, 1152, 4608, 256) == front
+    assert m.ddit_linear_front_tokens(2, 16600, 1344, 5376, 256) == 0   # measured 230 / 232 us
     # fewer CUs: the same problem spreads over more rounds, so no tile gets cheaper
     a = m.ddit_linear_tile_choice(0, 20000, 1152, 1152, 256)[1]
     b = m.ddit_linear_tile_choice(0, 20000, 1152, 1152, 64)[1]

@@ -158,7 +158,7 @@ def test_validation_and_layout_under_sanitizers_equal_the_ordinary_build(exe, tm
         (0, 1, 1, 1, 1, 64, 1, 64, 1 << 24, 1, 1), (0, 1, 32768, 32768, 2, 64, 1, 64, 8, 1, 1),
     ]
     linears = [(e, N, n, k, cu) for e in (0, 1, 2) for N, n, k in ((48600, 1152, 1152), (2304, 4608, 1152), (300, 2304, 1152), (0, 8, 8),
-                                                                       (108000, 864, 1152)) for cu in (256, 0, 304)]
+                                                                       (108000, 864, 1152), (33000, 1152, 4608)) for cu in (256, 0, 304)]
     text = "".join("SHAPE %s\n" % " ".join(map(str, s)) for s in shapes) + "".join("LINEAR %d %d %d %d %d\n" % l for l in linears)
     out = _run(exe, text, tmp_path)
     # the same questions to the ordinary build, through ctypes
@@ -194,5 +194,6 @@ def test_validation_and_layout_under_sanitizers_equal_the_ordinary_build(exe, tm
         got = out[i].split(); i += 1
         assert got[:3] == ["tile", "0", str(tile)]
         assert [float(v) for v in got[3:]] == pytest.approx(us, rel=1e-4)
+        assert out[i].split() == ["front", "0", str(m.ddit_linear_front_tokens(e, N, n_, k, cu))]; i += 1
         assert out[i:i + 4] == ["v linear_null -1", "v linear_dims -2", "v linear_align -4", "v linear_zero_rows 0"]; i += 4
     assert i == len(out)
