@@ -391,8 +391,10 @@ int ddit_solver_step(float *z, const float *eps_c, const float *eps_u_or_null, f
  * y_uncond_or_null bf16 [B,Ly,D]: unconditional text input for guidance (its valid length is Ly).
  * cross_kv_or_null / cross_kv_uncond_or_null: caches from ddit_cross_kv_precompute for y and
  * y_uncond (kept by the caller across calls); with guidance either both or none are given.
- * With both, the two evaluations of a step run as one of twice the samples where the workspace has
- * the room: their sums may then be formed in another order than those of ddit_eps_theta.
+ * With both, the two evaluations of a step run as one of twice the samples where the workspace of
+ * one evaluation (ddit_io_workspace_bytes, however large the given one is) has the room, for at most
+ * 32 samples and without DDIT_FLAG_TAPS: their sums may then be formed in another order than those
+ * of ddit_eps_theta.
  * eps_scratch: device fp32, 2 * B * C_out * T * 2Hp * 2Wp floats. */
 int ddit_sample(const ddit_shape *shape, const ddit_step_weights *weights, const ddit_io_weights *io, float *z,
                 const void *y, const int32_t *y_valid_len_host, const void *y_uncond_or_null,

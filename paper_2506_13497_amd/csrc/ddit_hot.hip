@@ -463,6 +463,31 @@ int check_common(const Dims &d, const Layout &lo, const void *x_in, const void *
   return DDIT_OK;
 }
 
+// y may be null with a cache: it is not read when every layer's k|v is given
+int check_step(const ddit_shape *shape, const Dims &d, const Layout &lo, const ddit_step_weights *weights, const void *x_in,
+               const void *y, const void *cross_kv, const int32_t *valid_len, const void *x_out, void *ws, size_t ws_bytes) {
+  if (!weights) { set_error("weights is NULL"); return DDIT_ERR_INVALID_ARG; }
+  if (cross_kv && !aligned16(cross_kv)) { set_error("cross_kv must be 16-byte aligned"); return DDIT_ERR_ALIGNMENT; }
+  if (shape->n_blocks > 0 && !weights->blocks) { set_error("weights->blocks is NULL"); return DDIT_ERR_INVALID_ARG; }
+  DDIT_TRY(check_common(d, lo, x_in, y ? y : cross_kv, x_out, ws, ws_bytes));
+  DDIT_TRY(check_valid_len(valid_len, d));
+  for (int i = 0; i < shape->n_blocks; ++i) {
+    DDIT_TRY(check_layer_weights(weights->blocks[i].spatial, "spatial", shape->flags));
+    DDIT_TRY(check_layer_weights(weights->blocks[i].temporal, "temporal", shape->flags));
+  }
+  return DDIT_OK;
+}
+
+int check_conditioning(const ddit_step_weights *weights, bool temb_given) {
+  if (!weights->w_ada) { set_error("w_ada must not be NULL"); return DDIT_ERR_INVALID_ARG; }
+  if (!temb_given) {
+    if (!weights->w_t1 || !weights->w_t2) { set_error("w_t1 and w_t2 are required when no temb is given"); return DDIT_ERR_INVALID_ARG; }
+    if (!aligned16(weights->w_t1) || !aligned16(weights->w_t2)) { set_error("w_t1/w_t2 not 16-byte aligned"); return DDIT_ERR_ALIGNMENT; }
+  }
+  if (!aligned16(weights->w_ada)) { set_error("w_ada not 16-byte aligned"); return DDIT_ERR_ALIGNMENT; }
+  return DDIT_OK;
+}
+
 // ---- latent in / latent out ----------------------------------------------------------------
 struct IoLayout {
   size_t step;      // the step's own workspace starts at 0
@@ -500,6 +525,20 @@ void make_io_layout(const Dims &d, uint32_t flags, IoLayout *lo) {
   lo->cap = take((size_t)d.B * d.Ly * d.D * 2);
   lo->cond = take((size_t)d.B * (256 + 2 * d.D) * 4 + (size_t)d.B * 6 * d.D * 4);
   lo->total = off;
+}
+
+int check_embed_latent(const ddit_io_weights *io, const void *z, const void *x_out) {
+  if (!z || !x_out || !io->w_patch) { set_error("z, x_out and w_patch must not be NULL"); return DDIT_ERR_INVALID_ARG; }
+  if (!aligned16(z) || !aligned16(x_out) || !aligned16(io->w_patch)) {
+    set_error("z, x_out and w_patch must be 16-byte aligned"); return DDIT_ERR_ALIGNMENT;
+  }
+  return DDIT_OK;
+}
+
+int check_output_head(const ddit_io_weights *io, const void *x) {
+  if (!x || !io->final_table || !io->w_final) { set_error("x, final_table and w_final must not be NULL"); return DDIT_ERR_INVALID_ARG; }
+  if (!aligned16(x) || !aligned16(io->w_final)) { set_error("x and w_final must be 16-byte aligned"); return DDIT_ERR_ALIGNMENT; }
+  return DDIT_OK;
 }
 
 int check_ws(void *ws, size_t ws_bytes, size_t need) {
@@ -643,15 +682,11 @@ int ddit_timestep_conditioning(const ddit_shape *shape, const ddit_step_weights 
                                float *scratch, void *hip_stream) {
   Dims d;
   DDIT_TRY(check_shape(shape, &d));
-  if (!weights || !c6_out || !weights->w_ada) { set_error("weights, w_ada and c6_out must not be NULL"); return DDIT_ERR_INVALID_ARG; }
-  if (!temb_or_null) {
-    if (!timesteps_host || !weights->w_t1 || !weights->w_t2 || !scratch) {
-      set_error("timesteps_host, w_t1, w_t2 and scratch are required when no temb is given");
-      return DDIT_ERR_INVALID_ARG;
-    }
-    if (!aligned16(weights->w_t1) || !aligned16(weights->w_t2)) { set_error("w_t1/w_t2 not 16-byte aligned"); return DDIT_ERR_ALIGNMENT; }
+  if (!weights || !c6_out) { set_error("weights and c6_out must not be NULL"); return DDIT_ERR_INVALID_ARG; }
+  DDIT_TRY(check_conditioning(weights, temb_or_null != nullptr));
+  if (!temb_or_null && (!timesteps_host || !scratch)) {
+    set_error("timesteps_host and scratch are required when no temb is given"); return DDIT_ERR_INVALID_ARG;
   }
-  if (!aligned16(weights->w_ada)) { set_error("w_ada not 16-byte aligned"); return DDIT_ERR_ALIGNMENT; }
   CondArgs c;
   memset(&c, 0, sizeof(c));
   c.B = (int)d.B; c.D = (int)d.D;
@@ -701,18 +736,7 @@ int ddit_denoise_step_cached(const ddit_shape *shape, const ddit_step_weights *w
   DDIT_TRY(check_shape(shape, &d));
   Layout lo;
   make_layout(d, shape->flags, &lo);
-  if (!weights) { set_error("weights is NULL"); return DDIT_ERR_INVALID_ARG; }
-  if (cross_kv_or_null) {
-    if (!aligned16(cross_kv_or_null)) { set_error("cross_kv must be 16-byte aligned"); return DDIT_ERR_ALIGNMENT; }
-    if (!y) y = cross_kv_or_null;   // y is not read when every layer's k|v is cached; keep the checks below uniform
-  }
-  if (shape->n_blocks > 0 && !weights->blocks) { set_error("weights->blocks is NULL"); return DDIT_ERR_INVALID_ARG; }
-  DDIT_TRY(check_common(d, lo, x_in, y, x_out, workspace, workspace_bytes));
-  DDIT_TRY(check_valid_len(y_valid_len_host, d));
-  for (int i = 0; i < shape->n_blocks; ++i) {
-    DDIT_TRY(check_layer_weights(weights->blocks[i].spatial, "spatial", shape->flags));
-    DDIT_TRY(check_layer_weights(weights->blocks[i].temporal, "temporal", shape->flags));
-  }
+  DDIT_TRY(check_step(shape, d, lo, weights, x_in, y, cross_kv_or_null, y_valid_len_host, x_out, workspace, workspace_bytes));
   hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
   unsigned char *ws = reinterpret_cast<unsigned char *>(workspace);
   float *x = reinterpret_cast<float *>(ws + lo.x);
@@ -728,9 +752,6 @@ int ddit_denoise_step_cached(const ddit_shape *shape, const ddit_step_weights *w
   const unsigned char *kv = reinterpret_cast<const unsigned char *>(cross_kv_or_null);
   if (!kv && shape->n_blocks > 0) {
     // no cache given: the text k|v of every layer are formed here, in one grouped launch, into the workspace
-    for (int i = 0; i < shape->n_blocks; ++i)
-      for (const ddit_layer_weights *w : {&weights->blocks[i].spatial, &weights->blocks[i].temporal})
-        if (!w->w_ckv) { set_error("block %d: w_ckv is NULL", i); return DDIT_ERR_INVALID_ARG; }
     DDIT_TRY(project_text_kv(d, weights, y, ws + lo.kvc, s));
     kv = ws + lo.kvc;
   }
@@ -926,10 +947,7 @@ int ddit_embed_latent(const ddit_shape *shape, const ddit_io_weights *io, const 
   Dims d;
   DDIT_TRY(check_shape(shape, &d));
   DDIT_TRY(check_io(shape, d, io));
-  if (!z || !x_out || !io->w_patch) { set_error("z, x_out and w_patch must not be NULL"); return DDIT_ERR_INVALID_ARG; }
-  if (!aligned16(z) || !aligned16(x_out) || !aligned16(io->w_patch)) {
-    set_error("z, x_out and w_patch must be 16-byte aligned"); return DDIT_ERR_ALIGNMENT;
-  }
+  DDIT_TRY(check_embed_latent(io, z, x_out));
   IoLayout lo;
   make_io_layout(d, shape->flags, &lo);
   DDIT_TRY(check_ws(workspace, workspace_bytes, lo.total));
@@ -969,12 +987,26 @@ int ddit_output_head(const ddit_shape *shape, const ddit_io_weights *io, const v
   Dims d;
   DDIT_TRY(check_shape(shape, &d));
   DDIT_TRY(check_io(shape, d, io));
-  if (!x || !temb || !eps_out || !io->final_table || !io->w_final) {
-    set_error("x, temb, eps_out, final_table and w_final must not be NULL"); return DDIT_ERR_INVALID_ARG;
-  }
-  if (!aligned16(x) || !aligned16(io->w_final)) { set_error("x and w_final must be 16-byte aligned"); return DDIT_ERR_ALIGNMENT; }
+  if (!temb || !eps_out) { set_error("temb and eps_out must not be NULL"); return DDIT_ERR_INVALID_ARG; }
+  DDIT_TRY(check_output_head(io, x));
   return launch_output_head(x, temb, io->final_table, io->w_final, io->b_final, eps_out, shape->B, io->C_out, shape->T,
                             shape->Hp, shape->Wp, shape->D, shape->ln_eps, reinterpret_cast<hipStream_t>(hip_stream));
+}
+
+// Everything that the calls of one evaluation would refuse, in their order, before the first of them enqueues anything.
+static int check_eps_theta(const ddit_shape *shape, const Dims &d, const ddit_step_weights *weights, const ddit_io_weights *io,
+                           const float *z, const void *y, const void *cross_kv, const int32_t *valid_len,
+                           const float *timesteps, const float *eps_out, void *workspace, size_t workspace_bytes, IoLayout *lo) {
+  if (!weights || !timesteps || !eps_out) { set_error("weights, timesteps_host and eps_out must not be NULL"); return DDIT_ERR_INVALID_ARG; }
+  make_io_layout(d, shape->flags, lo);
+  DDIT_TRY(check_ws(workspace, workspace_bytes, lo->total));
+  const unsigned char *ws = reinterpret_cast<const unsigned char *>(workspace);
+  DDIT_TRY(check_embed_latent(io, z, ws + lo->x_tok));
+  DDIT_TRY(check_conditioning(weights, false));
+  Layout step;
+  make_layout(d, shape->flags, &step);
+  DDIT_TRY(check_step(shape, d, step, weights, ws + lo->x_tok, y, cross_kv, valid_len, ws + lo->x_res, workspace, workspace_bytes));
+  return check_output_head(io, ws + lo->x_res);
 }
 
 int ddit_eps_theta(const ddit_shape *shape, const ddit_step_weights *weights, const ddit_io_weights *io,
@@ -984,10 +1016,9 @@ int ddit_eps_theta(const ddit_shape *shape, const ddit_step_weights *weights, co
   Dims d;
   DDIT_TRY(check_shape(shape, &d));
   DDIT_TRY(check_io(shape, d, io));
-  if (!weights || !timesteps_host || !eps_out) { set_error("weights, timesteps_host and eps_out must not be NULL"); return DDIT_ERR_INVALID_ARG; }
   IoLayout lo;
-  make_io_layout(d, shape->flags, &lo);
-  DDIT_TRY(check_ws(workspace, workspace_bytes, lo.total));
+  DDIT_TRY(check_eps_theta(shape, d, weights, io, z, y, cross_kv_or_null, y_valid_len_host, timesteps_host, eps_out, workspace,
+                           workspace_bytes, &lo));
   unsigned char *ws = reinterpret_cast<unsigned char *>(workspace);
   void *x_tok = ws + lo.x_tok, *x_res = ws + lo.x_res;
   float *cond = reinterpret_cast<float *>(ws + lo.cond);
@@ -999,8 +1030,6 @@ int ddit_eps_theta(const ddit_shape *shape, const ddit_step_weights *weights, co
                                     workspace, workspace_bytes, hip_stream));
   return ddit_output_head(shape, io, x_res, temb, eps_out, hip_stream);
 }
-
-constexpr int64_t PAIR_UP_TO = 49000;   // tokens of both
 
 // eps_theta of one latent with two texts in one pass of twice the samples: half the launches, every weight read once, and
 // linears of twice the tokens.  Everything has been checked (ddit_sample); eps_out: the first text's predictions, then the
@@ -1032,30 +1061,21 @@ static int eps_theta_pair(const ddit_shape &shape, const Dims &d, const PairLayo
   return ddit_output_head(&shape, io, tokens, temb, eps_out, s);
 }
 
-// Whether the two evaluations of a guided step go side by side: where the caches are given and the workspace of one has the
-// room, and up to the tokens that were measured.  What would be refused is left for the evaluation one by one to refuse, and
-// a step that keeps taps keeps those of one evaluation.  A guided step, one by one / side by side, 28 blocks, both options:
-// 64 tokens 10.79 / 5.04 ms, 200 10.55 / 5.80, 702 13.17 / 8.37, 1152 15.68 / 10.44, 2304 21.36 / 16.22, 3680 28.46 / 26.14,
-// 5000 33.3 / 30.4, 6851 42.5 / 39.8, 9000 57.8 / 52.4, 12150 69.8 / 67.4, 16200 92.9 / 89.0, 24300 140.8 / 131.4; 4 of the 16
-// heads: 64 9.89 / 4.68, 2304 17.0 / 12.1.
-static bool pair_of_evaluations(const ddit_shape *shape, const Dims &d, const ddit_step_weights *weights, const ddit_io_weights *io,
-                                const float *z, const void *y, const void *y_second, const void *kv, const void *kv_second, const int32_t *valid_len,
-                                void *workspace, size_t workspace_bytes, ddit_shape *shape2, Dims *d2, PairLayout *lo) {
-  if (!kv || !kv_second || !weights || 2 * d.B > 64 || 2 * d.N > PAIR_UP_TO || (shape->flags & DDIT_FLAG_TAPS)) return false;
-  if (!io->w_patch || !io->final_table || !io->w_final || (shape->n_blocks > 0 && !weights->blocks)) return false;
-  for (const void *p : {(const void *)z, y, y_second, kv, kv_second, io->w_patch, io->w_final})
-    if (!aligned16(p)) return false;
+// Whether the two evaluations of a guided step go side by side: with both caches, where the workspace that one evaluation
+// asks for has the room, up to 64 samples and the 49000 tokens of both that were measured, and without taps, which are of one evaluation.  A guided step, one by one /
+// side by side, 28 blocks, both options: 64 tokens 10.79 / 5.04 ms, 200 10.55 / 5.80, 702 13.17 / 8.37, 1152 15.68 / 10.44, 2304
+// 21.36 / 16.22, 3680 28.46 / 26.14, 5000 33.3 / 30.4, 6851 42.5 / 39.8, 9000 57.8 / 52.4, 12150 69.8 / 67.4, 16200 92.9 / 89.0,
+// 24300 140.8 / 131.4; 4 of the 16
+// heads: 64 9.89 / 4.68, 2304 17.0 / 12.1.  At few tokens the linears of twice as many take other tiles and other parts of k
+// than one by one: against 64 bits the error of a step is 0.98-1.02 times that of one by one (64 to 3120 tokens, 16 and 4 heads).
+static bool pair_of_evaluations(const ddit_shape *shape, const Dims &d, const void *kv, const void *kv_second, ddit_shape *shape2,
+                                Dims *d2, PairLayout *lo) {
+  if (!kv || !kv_second || 2 * d.B > 64 || 2 * d.N > 49000 || (shape->flags & DDIT_FLAG_TAPS)) return false;
   *shape2 = *shape;
   shape2->B = 2 * shape->B;
+  if (check_shape(shape2, d2) != DDIT_OK) return false;
   IoLayout one;
   make_io_layout(d, shape->flags, &one);
-  if (check_ws(workspace, workspace_bytes, one.total) != DDIT_OK || check_valid_len(valid_len, d) != DDIT_OK ||
-      check_shape(shape2, d2) != DDIT_OK)
-    return false;
-  for (int i = 0; i < shape->n_blocks; ++i)
-    if (check_layer_weights(weights->blocks[i].spatial, "spatial", shape->flags) != DDIT_OK ||
-        check_layer_weights(weights->blocks[i].temporal, "temporal", shape->flags) != DDIT_OK)
-      return false;
   make_pair_layout(*d2, shape->flags, lo);
   return lo->step.total <= one.total;
 }
@@ -1092,8 +1112,16 @@ int ddit_sample(const ddit_shape *shape, const ddit_step_weights *weights, const
   ddit_shape shape2;
   Dims d2;
   PairLayout pair;
-  const bool together = y_uncond_or_null && pair_of_evaluations(shape, d, weights, io, z, y, y_uncond_or_null, cross_kv_or_null,
-                                                                cross_kv_uncond_or_null, y_valid_len_host, workspace, workspace_bytes, &shape2, &d2, &pair);
+  const bool together = y_uncond_or_null && pair_of_evaluations(shape, d, cross_kv_or_null, cross_kv_uncond_or_null, &shape2, &d2, &pair);
+  if (first_step < last_step) {   // an empty range does nothing and needs nothing
+    IoLayout lo;
+    const float any_time = 0.f;
+    DDIT_TRY(check_eps_theta(shape, d, weights, io, z, y, cross_kv_or_null, y_valid_len_host, &any_time, eps_c, workspace,
+                             workspace_bytes, &lo));
+    if (y_uncond_or_null)
+      DDIT_TRY(check_eps_theta(shape, d, weights, io, z, y_uncond_or_null, cross_kv_uncond_or_null, nullptr, &any_time, eps_u,
+                               workspace, workspace_bytes, &lo));
+  }
   int32_t valid[64];
   if (together)
     for (int b = 0; b < 2 * d.B; ++b) valid[b] = b < d.B && y_valid_len_host ? y_valid_len_host[b] : (int32_t)d.Ly;

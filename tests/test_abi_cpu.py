@@ -6,6 +6,7 @@ import os
 import re
 
 import pytest
+import torch
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 LIB = os.path.join(ROOT, "paper_2506_13497_amd", "libddit_hot.so")
@@ -376,3 +377,42 @@ def test_workspace_depends_on_the_shape_alone(m):
         N = T * S
         plain = sum(up(b) for b in (N * D * 4, N * D * 2, N * 3 * H * 72 * 2, N * H * 72 * 2, 2 * layer, N * 4608 * 2, 6 * D * 4, (256 + 2 * D) * 4))
         assert 0 <= ws(1) - plain <= 25 << 20
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="the pointers are not memory")
+def test_a_prediction_is_refused_before_anything_is_enqueued(m):
+    """Whatever any stage of an evaluation would refuse, the whole call refuses first: on a machine without a GPU a launch would
+    be a HIP error (-5) instead."""
+    lib, P, b = m.binding._lib, C.c_void_p, m.binding
+    sh, io = _shape(m, n_blocks=1), _io(m)
+    blocks, sw = (b.ddit_block_weights * 1)(), b.ddit_step_weights()
+    for name, _ in b.ddit_step_weights._fields_[:-1]:
+        setattr(sw, name, 0x1000)
+    sw.blocks = blocks
+    for layer in (blocks[0].spatial, blocks[0].temporal):
+        for name, _ in b.ddit_layer_weights._fields_:
+            setattr(layer, name, 0x1000)
+    for name, _ in b.ddit_io_weights._fields_[4:]:
+        setattr(io, name, 0x1000)
+    ts = (C.c_float * 1)(500.0)
+
+    def statuses(y=0x2000, y_uncond=0x2000, kv=0x3000, valid=None):
+        valid = None if valid is None else (C.c_int32 * 1)(valid)
+        return (lib.ddit_eps_theta(C.byref(sh), C.byref(sw), C.byref(io), P(0x4000), P(y), P(kv), valid, ts, P(0x5000), P(0x100000), 1 << 30, None),
+                lib.ddit_sample(C.byref(sh), C.byref(sw), C.byref(io), P(0x4000), P(y), valid, P(y_uncond), P(kv), P(kv),
+                                C.c_float(2.0), 4, 1, 2, P(0x5000), P(0x100000), 1 << 30, None))
+
+    for kv in (0x3000, None):
+        assert statuses(y=0x2002, kv=kv) == (-4, -4) and statuses(valid=17, kv=kv) == (-1, -1)
+        assert statuses(y_uncond=0x2002, kv=kv)[1] == -4
+        for obj, name in [(sw, "w_t1"), (sw, "w_t2"), (sw, "w_ada"), (io, "w_patch"), (io, "final_table"), (io, "w_final"),
+                          (blocks[0].spatial, "w_qkv"), (blocks[0].temporal, "w_fc2"), (blocks[0].temporal, "ada_table")]:
+            setattr(obj, name, None)
+            assert statuses(kv=kv) == (-1, -1), name
+            if name not in ("final_table",):
+                setattr(obj, name, 0x1008)
+                assert statuses(kv=kv) == (-4, -4), name
+            setattr(obj, name, 0x1000)
+    assert statuses(y=None, kv=None)[0] == -1
+    sw.blocks = None
+    assert statuses() == (-1, -1)
