@@ -18,7 +18,9 @@ namespace {
 // PARTS > 0: a residual update that came as so many partial sums is added to the row first, and the row written back.
 // Their number is known to the compiler so that all of a row's loads are in flight at once: in a loop over the parts each
 // addition waited for its load, some fifteen memory latencies one after the other (kernel trace, 1152 features: 200 rows in
-// three parts 10.4 -> 7.1 us, 2304 rows in two 12.4 -> 11.7; a layer of 64 tokens 92.7 -> 90.2 us, 200 89.8 -> 87.5).
+// three parts 10.4 -> 7.1 us, 2304 rows in two 12.4 -> 11.7; a layer of 64 tokens 92.7 -> 90.2 us, 200 89.8 -> 87.5).  Above 1280
+// features that takes 136 to 256 registers, and so few rows leave them free: a block of 64 tokens and 1536 features 187.8 -> 183.8
+// us, 2048 246.0 -> 240.1, 4096 461.3 -> 452.1; of 400 to 1200 tokens within 0.7 % either way.
 template <int CHUNKS, int ROWS, bool STREAM, int PARTS>
 __global__ __launch_bounds__(256) void k_modulated_layernorm(float *__restrict__ x,
                                                              const float *__restrict__ tab,

@@ -1065,7 +1065,7 @@ static int eps_theta_pair(const ddit_shape &shape, const Dims &d, const PairLayo
 // asks for has the room, up to 64 samples of both, and without taps, which are of one evaluation.  A guided step, one by one /
 // side by side, 28 blocks, both options: 64 tokens 10.79 / 5.04 ms, 200 10.55 / 5.80, 702 13.17 / 8.37, 1152 15.68 / 10.44, 2304
 // 21.36 / 16.22, 3680 28.46 / 26.14, 5000 33.3 / 30.4, 6851 42.5 / 39.8, 9000 57.8 / 52.4, 12150 69.8 / 67.4, 16200 92.9 / 89.0,
-// 24300 140.8 / 131.4, 26496 153.3 / 146.4, 29808 168.3 / 162.8, 33120 191.1 / 184.1 (from about 33500 on there is no room); 4 of the 16
+// 24300 140.8 / 131.4, 26496 153.3 / 146.4, 29808 168.3 / 162.8, 33120 191.1 / 184.1 (from about 33900 on there is no room); 4 of the 16
 // heads: 64 9.89 / 4.68, 2304 17.0 / 12.1.  At few tokens the linears of twice as many take other tiles and other parts of k
 // than one by one: against 64 bits the error of a step is 0.98-1.02 times that of one by one (64 to 3120 tokens, 16 and 4 heads).
 static bool pair_of_evaluations(const ddit_shape *shape, const Dims &d, const void *kv, const void *kv_second, ddit_shape *shape2,

@@ -32,10 +32,11 @@
 // The head dim is padded to the next multiple of 16 above it for Q K^T and to 96 rows for V^T
 // (rows past the head dim produce rows of O^T that are never stored); row 72 of V^T reads constant
 // pieces holding ones, so that the same MFMAs that form O also accumulate the softmax denominator
-// (of the bf16-rounded probabilities used).  The rows behind it read constant zeros: the chip runs
-// this kernel at its power limit (1367 of 1400 W), and multiplying the neighbouring row's data
-// there, which the reads would run on into, costs power and LDS clocks (720p 2335 -> 2285 us, 480p
-// 526 -> 516, cross-attention 102.5 -> 100.6).
+// (of the bf16-rounded probabilities used).  The rows behind it read constant zeros and not the
+// neighbouring row's data, which the reads would run on into: a quarter of the bank conflicts less (31.2 -> 23.4
+// million), and as many clocks (926 -> 931 thousand, the chain per key tile) at a higher clock, since the chip
+// runs this kernel at its power limit (1372-1379 of 1400 W in amd-smi metric --power while it runs back to
+// back) and products of zeros draw less (720p 2335 -> 2285 us, 480p 526 -> 516).
 //
 // Online softmax without per-score bookkeeping.  The first padding column of the contraction
 // (index dh) is put to work: K holds a one there (a constant 16-byte piece in LDS that the lanes

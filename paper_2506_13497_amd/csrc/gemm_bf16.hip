@@ -726,8 +726,9 @@ __global__ __launch_bounds__(WGM *WGN *WGK * 64, 2) void k_gemm_bf16(GemmParams 
     // The last k-steps of a tile, which fill no stage: DEFER, whose stages the epilogue uses.  Of a workgroup's last tile they
     // are all that the ring holds, as behind it there is nothing to fetch: loads of length zero cost as much as others to
     // issue.  DRAIN: where the ring is long and the contraction fills it (launch_one); with three or four stages it gave
-    // nothing, and of the large tiles the compiler would keep the accumulators twice (a layer of 16 / 64 / 128 / 256 / 512 /
-    // 1200 tokens 79.3 / 82.4 / 85.1 / 90.2 / 107.0 / 140.3 -> 78.9 / 81.8 / 84.2 / 89.2 / 106.4 / 139.5 us).
+    // nothing, and of the large tiles the compiler would keep the accumulators twice.  It is worth little: a step of 28 blocks
+    // without / with, ms: 16 tokens 4.56 / 4.57, 64 4.80 / 4.77, 128 4.85 / 4.87, 320 5.45 / 5.44, 512 6.02 / 6.00, 1200 7.77 / 7.70, 2304
+    // 10.14 / 10.14; 4 of the 16 heads 200 tokens 4.62 / 4.64, 1200 6.66 / 6.62, 2304 8.09 / 8.01.
     auto tail_steps = [&](auto n_tag) {
       constexpr int N = decltype(n_tag)::value;
       static_assert(N <= 8, "k_step calls");
@@ -854,7 +855,8 @@ int launch_one(const GemmParams &p0, hipStream_t s, const GT &gt = GT()) {
   p.rounds = ((p.total_tiles + 7) / 8 + grid / 8 - 1) / (grid / 8);
   // A contraction shorter than the ring has no k-steps to drain, and the kernel without them is the shorter one to fetch: a
   // block of hidden size 256, 16 / 64 / 576 tokens, one kernel for both / two, 109.4 / 105.1, 113.4 / 111.7, 124.1 / 123.7 us; 4 heads
-  // of 1152 features, 16 tokens 160.2 / 156.8 (a step of 28 blocks, 64 tokens, 4.72 / 4.76 ms, as two kernels take turns).
+  // of 1152 features, 16 tokens 160.2 / 156.8 (a step of 28 blocks, 64 tokens, 4.72 / 4.76 ms, as two kernels take turns; below 192
+  // tokens the one without for long contractions too: 64 tokens 4.77 / 4.82, 4 heads 4.32 / 4.39).
   // The residual update is one kernel for both.
   constexpr bool LONG_RING = NS >= 6, EITHER = LONG_RING && !is_residual(EPI);
   if (!EITHER || (EPI == 3 ? p.split_steps : nk) >= NS)
