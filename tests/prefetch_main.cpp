@@ -1,5 +1,5 @@
 // Reads "pays N bytes" and "span pieces0 pieces1 blocks threads" lines and answers each from csrc/prefetch.hpp: the rule's
-// verdict, or the rows of the grid, the most 16-byte pieces that a workgroup reads and whether every piece of both arrays is
+// answer, or the rows of the grid, the most 16-byte pieces that a workgroup reads and whether every piece of both arrays is
 // read by exactly one workgroup, none twice but an array's last ones of a workgroup, and nothing beyond them.
 #include <cstdio>
 #include <cstring>

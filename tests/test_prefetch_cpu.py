@@ -49,7 +49,7 @@ TIMES += [(N, _bytes(4096, 1024), a, b) for N, a, b in [(64, 0.913, 0.990), (256
 
 def test_rule_against_measured_steps(ask):
     """Fetched where a step was measured to gain, left alone where it was measured to lose, and never beyond what was measured."""
-    verdicts = ask(["pays %d %d" % (N, b) for N, b, _, _ in TIMES] + ["pays 3200 1000", "pays 3201 1000"])
-    for (N, b, without, with_), pays in zip(TIMES, verdicts):
+    answers = ask(["pays %d %d" % (N, b) for N, b, _, _ in TIMES] + ["pays 3200 1000", "pays 3201 1000"])
+    for (N, b, without, with_), pays in zip(TIMES, answers):
         assert int(pays) == (with_ < without), (N, b, without, with_)
-    assert verdicts[-2:] == ["1", "0"]
+    assert answers[-2:] == ["1", "0"]
