@@ -688,13 +688,21 @@ int launch_flash_attn(const AttnArgs &a, hipStream_t s) {
   }
   p.n_units = a.n_groups * a.H;
   p.n_chunks = 1; p.qtiles_per_chunk = 1;
-  // Short key sequences shared by long query sequences (cross-attention to the text): the resident
-  // form, when every workgroup gets a run of at least four query tiles to spread the one-off K/V
-  // fetch over.  One workgroup per CU: as many chunks per unit as that allows.
+  // Short key sequences (cross-attention to the text): the resident form, one workgroup per CU, as many chunks per unit
+  // as that allows.  It pays where every workgroup gets a run of at least four query tiles to spread the one-off K/V
+  // fetch over, and, with two key tiles and more, as soon as the streaming form's 128 queries a workgroup would put two of them on a
+  // CU: the keys are then fetched once for both, and all at once.  16 heads, streaming / resident, us: 300 keys, 1024 queries 9.3 / 11.1
+  // (64 CUs busy; stays streaming), 2304 13.3 / 12.0, 4600 22.0 / 19.0, 7360 26.8 / 21.4, 9720 44.5 / 38.1; 4 heads 2304 8.9 / 10.5
+  // (stays), 9720 12.7 / 11.5; 60 keys, 12960 queries 36.5 / 37.6 (stays); frames of 144 tokens, 160 units 14.4 / 12.4, 256
+  // 16.7 / 15.2.  Not where units of one query tile alone are more than the CUs (225 tokens, 512 units 35.6 / 40.4: each
+  // workgroup waits for its whole K and V with nothing beside it on the CU), nor where tiles of 256 queries are much emptier.
   const int res_qtiles = (a.Lq + 32 * RES_NW - 1) / (32 * RES_NW);
   int chunks = ddit::device_cus() / (p.n_units > 0 ? p.n_units : 1);
   if (chunks < 1) chunks = 1;
-  if (a.Lk_max <= RES_TILES * KT && res_qtiles >= 4 * chunks) {
+  const int tiles = (a.Lk_max + KT - 1) / KT, cus = ddit::device_cus(), qtiles = (a.Lq + 127) / 128;
+  const int64_t blocks128 = (int64_t)p.n_units * qtiles;
+  const bool shared = tiles >= 2 && p.n_units <= cus && blocks128 > cus && 14 * (int64_t)res_qtiles <= 8 * (int64_t)qtiles;
+  if (tiles <= RES_TILES && (res_qtiles >= 4 * chunks || shared)) {
     p.n_qtiles = res_qtiles;
     p.qtiles_per_chunk = (res_qtiles + chunks - 1) / chunks;
     p.n_chunks = (res_qtiles + p.qtiles_per_chunk - 1) / p.qtiles_per_chunk;
