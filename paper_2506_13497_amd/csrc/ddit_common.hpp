@@ -99,7 +99,9 @@ int launch_gemm(int epilogue, const GemmArgs &a, hipStream_t s);
 // The residual update as partial sums over parts of k, fp32 [N, n] each, for a later launch to add up.
 // In how many, at most max_parts (0: in one launch is cheaper), and with which tile; the launch.
 int gemm_partial_choice(int64_t N, int n, int k, int max_parts, int *tile_out);
-int launch_gemm_partial(const GemmArgs &a, int parts, int tile, float *out, int64_t part_stride, hipStream_t s);
+// few: in the form for few tokens, whatever the tile; whether it fits
+bool gemm_partial_few(int64_t N, int n, int k, int parts);
+int launch_gemm_partial(const GemmArgs &a, int parts, int tile, float *out, int64_t part_stride, hipStream_t s, bool few = false);
 // G problems that share u (a.W, a.bias, a.out are ignored; a.n is one problem's out-features): 0 = launched,
 // 1 = this shape cannot be grouped (nothing launched: launch them one by one), negative = error
 int launch_gemm_grouped(const GemmArgs &a, int G, const void *const *W, const void *const *bias, void *const *out,

@@ -398,7 +398,8 @@ int run_layer(ddit_attn_kind kind, const Dims &d, const ddit_layer_weights &w, c
   // and o were.
   if (lo.fc2_parts > 0) {
     *pending = PendingSum{lo.fc2_parts, reinterpret_cast<const float *>(qkv), N * D, g.gate_tab, g.gate_c6, g.gate_c6_stride};
-    DDIT_TRY(launch_gemm_partial(g, lo.fc2_parts, lo.fc2_tile, reinterpret_cast<float *>(qkv), N * D, s));
+    DDIT_TRY(launch_gemm_partial(g, lo.fc2_parts, lo.fc2_tile, reinterpret_cast<float *>(qkv), N * D, s,
+                                 gemm_partial_few(N, (int)D, (int)M, lo.fc2_parts)));
     if (tp.on) {   // the tap shows the stream after the layer: the same sum, formed here instead of by the next launch
       DDIT_TRY(launch_add_pending(x, *pending, N, d.L, (int)D, s));
       pending->parts = 0;

@@ -44,6 +44,7 @@
 // also storing bf16(x).
 #include "ddit_common.hpp"
 
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 
@@ -123,6 +124,13 @@ __device__ __forceinline__ void lds_read4_b128(uintx4 (&v)[4], unsigned a) {
       : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3])
       : "v"(a), "n"(STEP), "n"(2 * STEP), "n"(3 * STEP)
       : "memory");
+}
+// a lane's four fragments of 32 operand rows (see k_gemm_few)
+__device__ __forceinline__ void lds_read_frags(uintx4 (&v)[4], unsigned a0, unsigned a1, unsigned a2, unsigned a3) {
+  asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\ts_waitcnt lgkmcnt(0)"
+               : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3])
+               : "v"(a0), "v"(a1), "v"(a2), "v"(a3)
+               : "memory");
 }
 // the tile's bias for this lane: 4 consecutive features (8 bytes) at each of four 8-feature steps
 __device__ __forceinline__ void lds_read4_b64(uint2 (&v)[4], unsigned a) {
@@ -808,6 +816,228 @@ __global__ __launch_bounds__(WGM *WGN *WGK * 64, 2) void k_gemm_bf16(GemmParams 
 #undef DL_MFMAS
 }
 
+// ---------------------------------------------------------------------------------------------
+// Few tokens: output tiles of 32 x 32, 64 x 32 or 64 x 64, the k-steps dealt out to the wavefronts.
+//
+// What bounds such a launch is the path into a CU (105 bytes per ns when the lines are in the L2) and the time around it, not
+// the matrix cores: a 64 x 64 tile with k = 1152 fetches 295 KB through it, and at 64 tokens 18 of 256 CUs do all of the work.
+// A 32 x 32 tile fetches half of that, on four times as many CUs.  Every wavefront owns the whole tile for k-steps w, w + NW, ... and
+// a ring of NS stages of its own, so nothing synchronises until the partial tiles meet in LDS once, and with k = 1152
+// nearly all of a tile's operands are asked for before the first byte is waited for.
+// Launches in a step's state, us with an event pair's 3.5, best of the other tiles / this: 1152 x 1152, 64 tokens 11.8 / 8.6, with the
+// residual update and the bf16 copy 13.1 / 9.2; 192 tokens 11.2 / 8.6; 448 (64 x 32) 11.2 / 10.5; 3456 x 1152, 64 tokens 13.0 / 9.5; 256 x 256, 256
+// tokens 7.6 / 6.6, residual 10.3 / 7.0; 1152 x 4608, 128 tokens 29.4 / 17.4, 768 (64 x 64) 30.2 / 27.7.  A step of 28 blocks of 1152
+// features, ms: 16 tokens 4.58 / 3.36, 64 4.77 / 3.72, 200 4.98 / 4.45, 256 5.12 / 4.77, 512 6.00 / 5.81; 4 heads 64 4.35 / 3.43.
+// ---------------------------------------------------------------------------------------------
+template <int TM_, int TN_, int NW_, int NS_>
+struct FewCfg {
+  static constexpr int TM = TM_, TN = TN_, NW = NW_, NS = NS_;   // MFMA tiles of 32 x 32; wavefronts; stages of each
+  static constexpr int BM = 32 * TM, BN = 32 * TN;
+  static constexpr int STAGE = (BM + BN) * ROW, LU = BM / 8, LOADS = (BM + BN) / 8;   // wave-wide loads of a k-step
+  static constexpr int EG = NW >= 8 && TM * TN > 1 ? 2 : 1;      // groups of 256 threads that write out
+  static constexpr int UNITS = TM * TN / EG;                     // MFMA tiles that a group writes out
+  static constexpr int SMEM = NW * NS * STAGE;
+  static_assert(TM * TN * 4096 <= STAGE, "a partial tile lies in a stage");
+  static_assert(TM * TN % EG == 0 && EG * 256 <= NW * 64 && NS <= 3 && 2 * LOADS < 64 && SMEM <= 160 * 1024, "");
+};
+
+template <class C, int EPI>
+__global__ __launch_bounds__(64 * C::NW, (C::NW + 3) / 4) void k_gemm_few(GemmParams p) {
+  constexpr int TM = C::TM, TN = C::TN, NW = C::NW, UNITS = C::UNITS;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, lh = lane >> 5;
+  // tiles in runs per XCD, the token tiles of one set of columns next to each other (they share W)
+  const int xcd = blockIdx.x & 7, q8 = p.total_tiles >> 3, r8 = p.total_tiles & 7;
+  int tile = blockIdx.x >> 3;
+  if (tile >= q8 + (xcd < r8 ? 1 : 0)) return;
+  tile += xcd * q8 + (xcd < r8 ? xcd : r8);
+  int part = 0, k0 = 0, kend = p.k;
+  if constexpr (EPI == 3) {
+    part = tile / p.split_tiles;
+    tile -= part * p.split_tiles;
+    k0 = part * p.split_steps;
+    kend = (k0 + p.split_steps) * BK < p.k ? (k0 + p.split_steps) * BK : p.k;
+  }
+  const int tile_n = tile / p.tiles_m, tile_m = tile - tile_n * p.tiles_m;
+  const int row0 = tile_m * C::BM, col0 = tile_n * C::BN;
+  const int steps = (kend - k0 * BK + BK - 1) / BK;      // k-steps of the tile
+  const int ring = p.rounds;                             // stages of a wavefront
+
+  // A thread of the first EG * 256 writes four features of one token of UNITS MFMA tiles.  What it needs besides the sums is asked for
+  // ahead of the operands: loads complete in order, so the waits below count the operands alone.
+  const int group = tid >> 8, r = (tid >> 3) & 31;
+  float4 x[UNITS], gate[UNITS];
+  uint2 bias[UNITS];
+  auto place = [&](int i, int64_t &tok, int &f) {
+    const int u = group + C::EG * i, b = u / TN, a = u - b * TN;
+    tok = row0 + 32 * b + r;
+    f = col0 + 32 * a + (tid & 7) * 4;
+    return group < C::EG && tok < p.N && f < p.n;
+  };
+#pragma unroll
+  for (int i = 0; i < UNITS; ++i) {
+    int64_t tok; int f;
+    x[i] = make_float4(0.f, 0.f, 0.f, 0.f); gate[i] = make_float4(1.f, 1.f, 1.f, 1.f); bias[i] = make_uint2(0u, 0u);
+    if (place(i, tok, f)) {
+      if (p.bias && part == 0) bias[i] = *reinterpret_cast<const uint2 *>(p.bias + f);
+      if constexpr (is_residual(EPI)) {
+        x[i] = *reinterpret_cast<const float4 *>(p.resid + tok * p.n + f);
+        gate[i] = gate_vector(p, p.gate_tab && p.gate_c6 ? sample_of(p, tok) : 0, f);
+      }
+    }
+  }
+  asm volatile("" ::: "memory");
+
+  // Loads as in the large kernel: 8 rows of 128 bytes each, chunk c of row r at slot c ^ ((r >> 1) & 7); rows past the operands and
+  // the k tail are zeros by the buffers' lengths.
+  const __amdgpu_buffer_rsrc_t ru = __builtin_amdgcn_make_buffer_rsrc(
+      uniform_ptr(p.u + (int64_t)row0 * p.ld_u), 0,
+      __builtin_amdgcn_readfirstlane((int)(unsigned)(((p.N - row0 - 1) * p.ld_u + p.k) * 2)), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+      uniform_ptr(p.W + (int64_t)col0 * p.k), 0, __builtin_amdgcn_readfirstlane((int)(unsigned)((int64_t)(p.n - col0) * p.k * 2)), 0x00020000);
+  const int chunk0 = (lane & 7) ^ (lane >> 4);           // of rows 8 j + lane / 8, j even; j odd: chunk0 ^ 4
+  const unsigned row_u = (unsigned)(lane >> 3) * (unsigned)p.ld_u * 2u, row_w = (unsigned)(lane >> 3) * (unsigned)p.k * 2u;
+  unsigned char *const mem = smem + wave * (ring * C::STAGE);
+  auto issue = [&](int t, int st) {
+    const int at = (k0 + wave + t * NW) * BK;
+#pragma unroll
+    for (int o = 0; o < 2; ++o) {
+      const int kk = at + (chunk0 ^ (4 * o)) * 8;
+      const bool in = kk < kend;
+      const unsigned ou = in ? row_u + (unsigned)kk * 2u : 0u, ow = in ? row_w + (unsigned)kk * 2u : 0u;
+#pragma unroll
+      for (int j = o; j < C::LOADS; j += 2) {
+        const bool is_u = j < C::LU;
+        const unsigned to = is_u ? ou + (unsigned)(j * 16) * (unsigned)p.ld_u : ow + (unsigned)((j - C::LU) * 16) * (unsigned)p.k;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(is_u ? ru : rw, (lds_ptr_t)(mem + st * C::STAGE + j * 1024), 16, in ? to : 0xfffffff0u, 0, 0, 0);
+      }
+    }
+  };
+  const int mine_steps = (steps - wave + NW - 1) / NW;   // of this wavefront; none where k is short
+  for (int t = 0; t < ring; ++t)
+    if (t < mine_steps) issue(t, t);
+
+  floatx16 acc[TN][TM];
+#pragma unroll
+  for (int a = 0; a < TN; ++a)
+#pragma unroll
+    for (int b = 0; b < TM; ++b)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[a][b][e] = 0.f;
+  unsigned frag[4];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) frag[s] = lds_offset(mem) + l32 * ROW + (((2 * s + lh) ^ ((l32 >> 1) & 7)) << 4);
+  int st = 0;
+  for (int t = 0; t < mine_steps; ++t) {
+    const int behind = mine_steps - 1 - t < ring - 1 ? mine_steps - 1 - t : ring - 1;   // k-steps asked for after this one
+    if (behind >= 2) wait_vmcnt<2 * C::LOADS>();
+    else if (behind == 1) wait_vmcnt<C::LOADS>();
+    else wait_vmcnt<0>();
+    uintx4 fr[TM + TN][4];   // rows of 32 tokens, then of 32 features
+#pragma unroll
+    for (int i = 0; i < TM + TN; ++i) lds_read_frags(fr[i], frag[0] + st * C::STAGE + i * 32 * ROW, frag[1] + st * C::STAGE + i * 32 * ROW,
+                                                     frag[2] + st * C::STAGE + i * 32 * ROW, frag[3] + st * C::STAGE + i * 32 * ROW);
+    if (t + ring < mine_steps) issue(t + ring, st);
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int a = 0; a < TN; ++a)
+#pragma unroll
+        for (int b = 0; b < TM; ++b)
+          acc[a][b] = mfma32(__builtin_bit_cast(bf16x8, fr[TM + a][s]), __builtin_bit_cast(bf16x8, fr[b][s]), acc[a][b]);
+    st = st + 1 == ring ? 0 : st + 1;
+  }
+  // The partial tiles meet: every wavefront's lies where its first stage was, 16-byte pieces of a row swizzled like the operands'.
+  if (mine_steps > 0) {
+#pragma unroll
+    for (int a = 0; a < TN; ++a)
+#pragma unroll
+      for (int b = 0; b < TM; ++b)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          floatx4 v;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = acc[a][b][4 * g + e];
+          *reinterpret_cast<floatx4 *>(mem + (b * TN + a) * 4096 + l32 * ROW + (((2 * g + lh) ^ ((l32 >> 1) & 7)) << 4)) = v;
+        }
+  }
+  lds_barrier();
+  auto rounded = [](float4 v) { bf16x4 o; o[0] = (bf16_t)v.x; o[1] = (bf16_t)v.y; o[2] = (bf16_t)v.z; o[3] = (bf16_t)v.w; return o; };
+#pragma unroll
+  for (int i = 0; i < UNITS; ++i) {
+    int64_t tok; int f;
+    if (!place(i, tok, f)) continue;
+    float4 sum = make_float4(__uint_as_float(bias[i].x << 16), __uint_as_float(bias[i].x & 0xffff0000u), __uint_as_float(bias[i].y << 16),
+                             __uint_as_float(bias[i].y & 0xffff0000u));
+    const unsigned char *const from = smem + (group + C::EG * i) * 4096 + r * ROW + (((tid & 7) ^ ((r >> 1) & 7)) << 4);
+#pragma unroll
+    for (int w = 0; w < NW; ++w)
+      if (w < steps) {
+        const floatx4 v = *reinterpret_cast<const floatx4 *>(from + w * (ring * C::STAGE));
+        sum.x += v[0]; sum.y += v[1]; sum.z += v[2]; sum.w += v[3];
+      }
+    if constexpr (EPI < 2) {
+      if (EPI == 1) sum = make_float4(gelu_tanh_f(sum.x), gelu_tanh_f(sum.y), gelu_tanh_f(sum.z), gelu_tanh_f(sum.w));
+      *reinterpret_cast<bf16x4 *>(p.out + tok * p.ld_out + f) = rounded(sum);
+    } else if constexpr (EPI == 3) {
+      *reinterpret_cast<float4 *>(p.resid + part * p.split_stride + tok * p.n + f) = sum;
+    } else {
+      const float4 v = make_float4(x[i].x + gate[i].x * sum.x, x[i].y + gate[i].y * sum.y, x[i].z + gate[i].z * sum.z, x[i].w + gate[i].w * sum.w);
+      *reinterpret_cast<float4 *>(p.resid + tok * p.n + f) = v;
+      if (p.out) *reinterpret_cast<bf16x4 *>(p.out + tok * p.ld_out + f) = rounded(v);
+    }
+  }
+}
+
+template <class C, int EPI>
+int launch_few(const GemmParams &p0, hipStream_t s) {
+  GemmParams p = p0;
+  const int nk = EPI == 3 ? p.split_steps : (p.k + BK - 1) / BK;
+  p.tiles_m = (int)((p.N + C::BM - 1) / C::BM);
+  p.tiles_n = (p.n + C::BN - 1) / C::BN;
+  p.total_tiles = p.split_tiles = p.tiles_m * p.tiles_n;
+  if (EPI == 3) p.total_tiles *= ((p.k + BK - 1) / BK + p.split_steps - 1) / p.split_steps;
+  p.rounds = std::min(C::NS, (nk + C::NW - 1) / C::NW);   // no more stages than a wavefront has k-steps: the LDS holds further workgroups
+  static bool attr_set = false;  // benign race: the attribute is idempotent
+  if (!attr_set) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_few<C, EPI>), hipFuncAttributeMaxDynamicSharedMemorySize, C::SMEM);
+    if (e != hipSuccess) return ddit::hip_fail(e, "gemm hipFuncSetAttribute");
+    attr_set = true;
+  }
+  hipLaunchKernelGGL((k_gemm_few<C, EPI>), dim3((unsigned)((p.total_tiles + 7) & ~7)), dim3(64 * C::NW), C::NW * p.rounds * C::STAGE, s, p);
+  return ddit::hip_fail(hipGetLastError(), "gemm launch");
+}
+
+using Few32 = FewCfg<1, 1, 6, 3>;
+using Few64x32 = FewCfg<2, 1, 6, 2>;
+using Few64 = FewCfg<2, 2, 8, 1>;
+
+// Which of those forms a linear takes (0: none): the smallest tile whose grid, `parts` times as large with partial sums of `steps`
+// k-steps, finds room on the chip at once, which for short contractions is several workgroups a CU; beyond that the tiles of several
+// rounds fetch more than the larger ones (1152 x 1152, 32 x 32: 224 tokens, 252 tiles, 8.6 us, 256 tokens, 288 tiles, 11.3; 768 x 256:
+// 640 tokens, 480 tiles, 7.0 against 8.8).  64 x 64 only for long contractions: with 18 k-steps it is as fast as the other kernel's 64 x 64
+// (12.4 / 12.5 us), with 32 up to 6 % slower, with 72 7-9 % faster, with 128 8 %.  Over 462 linears of 16 to 1680 tokens the
+// rule takes 0.2 % more time than the best of all tiles and never more than without these forms.
+constexpr int FEW_LONG_STEPS = 47;
+template <class C>
+bool few_fits(int64_t N, int n, int steps, int parts, int cus) {
+  const int smem = C::NW * std::min(C::NS, (steps + C::NW - 1) / C::NW) * C::STAGE;
+  return (N + C::BM - 1) / C::BM * ((n + C::BN - 1) / C::BN) * parts <= (int64_t)cus * (160 * 1024 / smem);
+}
+int few_form(int64_t N, int n, int64_t ld_u, int k, int parts, int steps, int cus) {
+  if (ld_u >= 1 << 24 || k >= 1 << 24) return 0;
+  if (few_fits<Few32>(N, n, steps, parts, cus)) return 1;
+  if (few_fits<Few64x32>(N, n, steps, parts, cus)) return 2;
+  return steps >= FEW_LONG_STEPS && few_fits<Few64>(N, n, steps, parts, cus) ? 3 : 0;
+}
+
+template <int EPI>
+int launch_few_form(int form, const GemmParams &p, hipStream_t s) {
+  return form == 1 ? launch_few<Few32, EPI>(p, s) : form == 2 ? launch_few<Few64x32, EPI>(p, s) : launch_few<Few64, EPI>(p, s);
+}
+
 template <int WGM, int WGN, int WGK, int TM, int TN, int NS, int EPI, bool DRAIN, class GT>
 int launch_kernel(const GemmParams &p, int grid, hipStream_t s, const GT &gt) {
   using C = GemmCfg<WGM, WGN, WGK, TM, TN, NS>;
@@ -1127,6 +1357,10 @@ int gemm_partial_choice(int64_t N, int n, int k, int max_parts, int *tile_out) {
   return chosen;
 }
 
+bool gemm_partial_few(int64_t N, int n, int k, int parts) {
+  return few_form(N, n, k, k, parts, ((k + BK - 1) / BK + parts - 1) / parts, device_cus()) > 0;
+}
+
 int launch_partial_tile(int tile, const GemmParams &p, hipStream_t s) {
   switch (tile) {
     case 4: return launch_checked<4, 2, 1, 2, 2, 3, 3>(tile, p, s);
@@ -1140,7 +1374,7 @@ int launch_partial_tile(int tile, const GemmParams &p, hipStream_t s) {
   return -1;
 }
 
-int launch_gemm_partial(const GemmArgs &a, int parts, int tile, float *out, int64_t part_stride, hipStream_t s) {
+int launch_gemm_partial(const GemmArgs &a, int parts, int tile, float *out, int64_t part_stride, hipStream_t s, bool few) {
   if (a.N == 0 || a.n == 0) return 0;
   if ((int64_t)a.n * a.k >= (int64_t)1 << 31 || a.N * a.ld_u >= (int64_t)1 << 31) {
     set_error("linear: n*k = %lld or N*ld_u = %lld exceeds the 31-bit index range", (long long)a.n * a.k, (long long)(a.N * a.ld_u));
@@ -1161,6 +1395,7 @@ int launch_gemm_partial(const GemmArgs &a, int parts, int tile, float *out, int6
     return -2;
   }
   p.split_stride = part_stride;
+  if (few) return launch_few_form<3>(few_form(p.N, p.n, p.ld_u, p.k, parts, p.split_steps, device_cus()), p, s);
   return launch_partial_tile(tile, p, s);
 }
 
@@ -1196,6 +1431,8 @@ int launch_gemm(int epilogue, const GemmArgs &a, hipStream_t s) {
     return epilogue == 0 ? launch_epi<0>(tile, q, elements, s) : epilogue == 1 ? launch_epi<1>(tile, q, elements, s)
                                                                                 : launch_epi<2>(tile, q, elements, s);
   };
+  if (const int form = a.tile < 0 ? few_form(p.N, p.n, p.ld_u, p.k, 1, (p.k + BK - 1) / BK, device_cus()) : 0)
+    return epilogue == 0 ? launch_few_form<0>(form, p, s) : epilogue == 1 ? launch_few_form<1>(form, p, s) : launch_few_form<2>(form, p, s);
   const int64_t front = a.tile < 0 ? gemm_tokens_in_front(epilogue, p.out != nullptr, p.N, p.n, p.k, 0) : 0;
   if (front > 0) {
     GemmParams first = p;
