@@ -15,7 +15,8 @@
 // tokens of cross-attention): 8 wavefronts, one workgroup per CU; the unit's whole K and V are
 // fetched into LDS once and the workgroup walks over a run of 256-query tiles with no further tile
 // load and no barrier (480p cross-attention: 0.149 -> 0.109 ms; each further key tile then costs
-// what its MFMAs cost).
+// what its MFMAs cost).  Where there are fewer workgroups than CUs both forms also come with the key tiles dealt out to sets of
+// wavefronts, whose sums meet at the end.
 //
 // Matrix-core mapping (v_mfma_f32_32x32x16_bf16, 64-wide wavefronts).  Scores are
 // computed transposed, S^T = K Q^T: the K tile is the first operand (read from LDS, 16
@@ -141,13 +142,18 @@ struct BoolTag { static constexpr bool value = V; };
 // then the workgroup walks over its run of query tiles with no further tile load and no barrier;
 // what it saves is the per-query-tile prologue (with five key tiles that is a third of the time)
 // and four fifths of the K/V traffic.
-template <int DH, int NW, bool RES>
-__global__ __launch_bounds__(64 * NW, 2) void k_flash_attn(FlashParams p) {
+template <int DH, int QG, int KS, bool RES>
+__global__ __launch_bounds__(64 * QG * KS, 2) void k_flash_attn(FlashParams p) {
   using C = Cfg<DH>;
-  constexpr int QT = 32 * NW;              // queries per workgroup and query tile
-  constexpr int NST = RES ? RES_TILES : 2; // LDS stages
+  constexpr int NW = QG * KS;              // wavefronts: QG groups of 32 queries, KS sets of key tiles
+  constexpr bool WALK = RES && KS == 1;    // the workgroup walks over query tiles
+  constexpr int QT = 32 * QG;              // queries per workgroup and query tile
+  constexpr int NST = RES ? RES_TILES : 2 * KS; // LDS stages
+  constexpr int LW = RES ? NW : QG;        // wavefronts that fetch a tile together
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = KS > 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
+  const int qg = KS > 1 ? wave % QG : wave, kg = KS > 1 ? wave / QG : 0;   // this wavefront's queries and key tiles kg, kg + KS, ...
+  const int lw = RES ? wave : qg;
   const int l32 = lane & 31, lh = lane >> 5;
   if (blockIdx.y) {
     ddit::prefetch_share<64 * NW>(p.ahead);
@@ -170,7 +176,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_flash_attn(FlashParams p) {
   // (With only a few units that would leave XCDs idle; their K/V are then small enough for every
   // L2, and consecutive workgroups simply take consecutive query tiles.)
   int unit, qtile, qt_end;
-  if constexpr (RES) {
+  if constexpr (WALK) {
     unit = blockIdx.x / p.n_chunks;
     qtile = (blockIdx.x - unit * p.n_chunks) * p.qtiles_per_chunk;
     qt_end = qtile + p.qtiles_per_chunk < p.n_qtiles ? qtile + p.qtiles_per_chunk : p.n_qtiles;
@@ -182,7 +188,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_flash_attn(FlashParams p) {
     unit = (idx / p.n_qtiles) * 8 + xcd;
     qtile = idx % p.n_qtiles;
   }
-  if constexpr (!RES) qt_end = qtile + 1;
+  if constexpr (!WALK) qt_end = qtile + 1;
   if (unit >= p.n_units || qtile >= qt_end) return;
   const int h = unit % p.H, g = unit / p.H;
   const int g_out = g / p.g_inner, g_in = g - g_out * p.g_inner;
@@ -230,7 +236,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_flash_attn(FlashParams p) {
       }
     }
   };
-  load_q(qtile * QT + wave * 32);
+  load_q(qtile * QT + qg * 32);
   constexpr int KS_REF = DH / 16;                       // k-step of the reference column
   const bool ref_lane = (8 * lh == DH - 16 * KS_REF);   // lanes whose fragment of that k-step starts at column DH
 
@@ -261,11 +267,11 @@ __global__ __launch_bounds__(64 * NW, 2) void k_flash_attn(FlashParams p) {
 
   // ---- K and V tiles, global -> LDS: wave-wide load j fills LDS bytes [1024 j, 1024 j + 1024) of a
   // tile; this lane's piece is LDS chunk m = 64 j + lane = (key m / DCH, chunk slot m % DCH)
-  constexpr int TJ = (C::T_INSTR + NW - 1) / NW;   // loads per wave and tile (the last one only on some waves)
+  constexpr int TJ = (C::T_INSTR + LW - 1) / LW;   // loads per wave and tile (the last one only on some waves)
   int t_key[TJ], t_col[TJ];
 #pragma unroll
   for (int i = 0; i < TJ; ++i) {
-    const int m = 64 * (wave + NW * i) + lane;
+    const int m = 64 * (lw + LW * i) + lane;
     const int key = m / C::DCH, slot = m - key * C::DCH;
     t_key[i] = key;
     t_col[i] = (C::SWZ ? (slot ^ (key & 7)) : slot) * 8;
@@ -284,17 +290,17 @@ __global__ __launch_bounds__(64 * NW, 2) void k_flash_attn(FlashParams p) {
     if ((KEY0) + KT <= Lk) {                                                                            \
       const int64_t toff_ = (int64_t)(TILE_IDX) * KT * kv_row;                                          \
       _Pragma("unroll") for (int i = 0; i < TJ; ++i) {                                                  \
-        if (wave + NW * i < C::T_INSTR)                                                                 \
+        if (lw + LW * i < C::T_INSTR)                                                                 \
           __builtin_amdgcn_global_load_lds((gbl_ptr_t)(src_ + t_off[i] + toff_),                        \
-                                           (lds_ptr_t)(dst_ + (wave + NW * i) * 1024), 16, 0, 0);       \
+                                           (lds_ptr_t)(dst_ + (lw + LW * i) * 1024), 16, 0, 0);       \
       }                                                                                                 \
     } else {                                                                                            \
       _Pragma("unroll") for (int i = 0; i < TJ; ++i) {                                                  \
-        if (wave + NW * i < C::T_INSTR) {                                                               \
+        if (lw + LW * i < C::T_INSTR) {                                                               \
           int key_ = (KEY0) + t_key[i];                                                                 \
           if (key_ > Lk - 1) key_ = Lk - 1; /* tail keys re-read the last valid key; masked below */    \
           __builtin_amdgcn_global_load_lds((gbl_ptr_t)(src_ + key_ * kv_row + t_col[i]),                \
-                                           (lds_ptr_t)(dst_ + (wave + NW * i) * 1024), 16, 0, 0);       \
+                                           (lds_ptr_t)(dst_ + (lw + LW * i) * 1024), 16, 0, 0);       \
         }                                                                                               \
       }                                                                                                 \
     }                                                                                                   \
@@ -401,7 +407,8 @@ __global__ __launch_bounds__(64 * NW, 2) void k_flash_attn(FlashParams p) {
     static_assert(2 * KS_REF >= 4, "the reference column's k-step is issued after the decision");
     if (__builtin_amdgcn_ballot_w64(first || mx > p.rebase) != 0) {
       const float mq = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      const float m_new = (first || mq > p.rebase) ? (float)(bf16_t)(m_ref + mq) : m_ref;
+      // (of a set of tiles whose first holds nothing but -inf the reference stays: the other sets may have finite scores)
+      const float m_new = ((first && (KS == 1 || mq > -INFINITY)) || mq > p.rebase) ? (float)(bf16_t)(m_ref + mq) : m_ref;
       const float delta = m_new - m_ref;
       // (the first tile moves the reference from 0, possibly far down: O and the sum are still zero)
       const float alpha = first ? 1.0f : __builtin_amdgcn_exp2f(-delta * p.scale_log2);
@@ -514,6 +521,8 @@ __global__ __launch_bounds__(64 * NW, 2) void k_flash_attn(FlashParams p) {
   // after the barrier that ends tile it.  Both have a whole tile's time to land.
   // Resident form: every tile is fetched here, once, and stays.
   const int n_tiles = (Lk + KT - 1) / KT;
+  const int n_my = KS == 1 ? n_tiles : (n_tiles - kg + KS - 1) / KS;   // of this wavefront; may be none
+  auto tile_at = [&](int i) { return KS == 1 ? i : kg + i * KS; };
   if constexpr (RES) {
     for (int t = 0; t < n_tiles; ++t) {
       FA_LOAD(0, t * KT, t, t);
@@ -525,39 +534,100 @@ __global__ __launch_bounds__(64 * NW, 2) void k_flash_attn(FlashParams p) {
 
 #define FA_ITER(HAS_NEXT, S_CUR, S_NXT)                                                                 \
   do {                                                                                                  \
-    const int cur_ = RES ? it : (it & 1);                                                               \
+    const int cur_ = RES ? tile_at(it) : kg * 2 + (it & 1);                                             \
     if constexpr (!RES) {                                                                               \
-      if (it + 2 < n_tiles) FA_LOAD(0, (it + 2) * KT, cur_, it + 2);                                    \
+      if (it + 2 < n_my) FA_LOAD(0, tile_at(it + 2) * KT, cur_, tile_at(it + 2));                       \
     }                                                                                                   \
     FENCE();                                                                                            \
-    tile_step(BoolTag<HAS_NEXT>{}, it == 0, RES ? it + 1 : (cur_ ^ 1), cur_, S_CUR, S_NXT);             \
+    tile_step(BoolTag<HAS_NEXT>{}, it == 0, RES ? tile_at(it + 1) : (cur_ ^ 1), cur_, S_CUR, S_NXT);    \
     FENCE();                                                                                            \
     if constexpr (!RES) {                                                                               \
       if (HAS_NEXT) {                                                                                   \
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); /* K of tile it+2 (and V of tile it+1) has landed */ \
         lds_barrier(); /* V of tile it, K of tile it+1 are free; tile it+1's V and tile it+2's K complete */ \
-        if (it + 2 < n_tiles) FA_LOAD(1, (it + 2) * KT, cur_, it + 2);                                  \
+        if (it + 2 < n_my) FA_LOAD(1, tile_at(it + 2) * KT, cur_, tile_at(it + 2));                     \
       }                                                                                                 \
     }                                                                                                   \
   } while (0)
 
+  // Sums over the sets of key tiles: every set has its own reference.  The sets from the second on hand theirs over in LDS, in
+  // the place of the tiles, to the first, which weighs each by 2^(reference - largest reference).  A set without a
+  // term (no tile, or scores of -inf alone) has no say in the largest.
+  auto merge_sets = [&]() {
+    constexpr int PART = C::DT * 4 + 1;   // 16-byte pieces a lane hands over
+    static_assert((KS - 1) * QG * PART * 1024 <= NST * C::STAGE, "the sums fit the place of the tiles");
+    if (!C::ONES) l_run += __shfl_xor(l_run, 32, 64);
+    constexpr int one_reg = 4 * ((DH % 32) / 8);
+    const float l_set = C::ONES ? __shfl(oacc[DH / 32 < C::DT ? DH / 32 : 0][one_reg], l32, 64) : l_run;
+    lds_barrier();   // every wavefront is done with the tiles
+    if (kg > 0) {
+      unsigned char *const at = smem + ((kg - 1) * QG + qg) * (PART * 1024) + lane * 16;
+#pragma unroll
+      for (int d = 0; d < C::DT; ++d)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          floatx4 v;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = oacc[d][4 * g + e];
+          *reinterpret_cast<floatx4 *>(at + (d * 4 + g) * 1024) = v;
+        }
+      floatx4 v;
+      v[0] = m_ref; v[1] = l_set; v[2] = v[3] = 0.f;
+      *reinterpret_cast<floatx4 *>(at + C::DT * 4 * 1024) = v;
+    }
+    lds_barrier();
+    if (kg > 0) return;
+    float m_set[KS], l_of[KS], top = l_set > 0.f ? m_ref : -INFINITY;
+    m_set[0] = m_ref; l_of[0] = l_set;
+#pragma unroll
+    for (int k = 1; k < KS; ++k) {
+      const floatx4 v = *reinterpret_cast<const floatx4 *>(smem + ((k - 1) * QG + qg) * (PART * 1024) + lane * 16 + C::DT * 4 * 1024);
+      m_set[k] = v[0]; l_of[k] = v[1];
+      if (v[1] > 0.f) top = fmaxf(top, v[0]);
+    }
+    auto weight = [&](int k) { return l_of[k] == 0.f ? 0.f : __builtin_amdgcn_exp2f((m_set[k] - top) * p.scale_log2); };
+    const float w0 = weight(0);
+#pragma unroll
+    for (int d = 0; d < C::DT; ++d)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) oacc[d][e] *= w0;
+    float l_sum = l_set * w0;
+#pragma unroll
+    for (int k = 1; k < KS; ++k) {
+      const unsigned char *const at = smem + ((k - 1) * QG + qg) * (PART * 1024) + lane * 16;
+      const float w = weight(k);
+#pragma unroll
+      for (int d = 0; d < C::DT; ++d)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const floatx4 v = *reinterpret_cast<const floatx4 *>(at + (d * 4 + g) * 1024);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) oacc[d][4 * g + e] += v[e] * w;
+        }
+      l_sum += l_of[k] * w;
+    }
+    m_ref = top;
+    l_run = l_sum * 0.5f;   // both halves of a query add theirs up below
+  };
+
   for (;;) {   // over this workgroup's query tiles (the streaming form has one)
-    const int q0 = qtile * QT + wave * 32;
+    const int q0 = qtile * QT + qg * 32;
+    if (KS == 1 || n_my > 0) {
     if constexpr (!RES) {
-      FA_LOAD(0, 0, 0, 0);
-      FA_LOAD(1, 0, 0, 0);
-      if (n_tiles > 1) {
-        FA_LOAD(0, KT, 1, 1);
-        FA_LOAD(1, KT, 1, 1);
+      FA_LOAD(0, tile_at(0) * KT, kg * 2, tile_at(0));
+      FA_LOAD(1, tile_at(0) * KT, kg * 2, tile_at(0));
+      if (n_my > 1) {
+        FA_LOAD(0, tile_at(1) * KT, kg * 2 + 1, tile_at(1));
+        FA_LOAD(1, tile_at(1) * KT, kg * 2 + 1, tile_at(1));
       }
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // tile 0 has landed (once per kernel: also waits tile 1)
       lds_barrier();
     }
-    FA_QK(s_a, 0);
+    FA_QK(s_a, RES ? tile_at(0) : kg * 2);
     if constexpr (!RES) lds_barrier();                    // K of tile 0 may now be overwritten (by tile 2)
 
     int it = 0;
-    for (; it + 2 < n_tiles; it += 2) {
+    for (; it + 2 < n_my; it += 2) {
       FA_ITER(true, s_a, s_b);
       ++it;
       FA_ITER(true, s_b, s_a);
@@ -565,7 +635,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_flash_attn(FlashParams p) {
     }
     // ---- one or two tiles left; the last one masks the keys past the end
     auto mask_tail = [&](floatx16 (&sc)[2]) {
-      const int key0 = it * KT;
+      const int key0 = tile_at(it) * KT;
       if (key0 + KT > Lk) {
 #pragma unroll
         for (int kt = 0; kt < 2; ++kt)
@@ -576,7 +646,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_flash_attn(FlashParams p) {
           }
       }
     };
-    if (it + 1 < n_tiles) {
+    if (it + 1 < n_my) {
       FA_ITER(true, s_a, s_b);
       ++it;
       mask_tail(s_b);
@@ -584,6 +654,16 @@ __global__ __launch_bounds__(64 * NW, 2) void k_flash_attn(FlashParams p) {
     } else {
       mask_tail(s_a);
       FA_ITER(false, s_a, s_b);
+    }
+    }
+    if constexpr (KS > 1) {
+      // the other sets of key tiles: as many barriers as the one with the most tiles has passed
+      if constexpr (!RES) {
+        const int most = (n_tiles + KS - 1) / KS;
+        for (int i = n_my > 0 ? n_my : -1; i < most; ++i) lds_barrier();
+      }
+      merge_sets();
+      if (kg > 0) return;
     }
 
     // ---- row sum
@@ -614,7 +694,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_flash_attn(FlashParams p) {
         }
       if (p.lse && lh == 0) p.lse[tok * p.H + h] = m_ref * p.scale + __logf(l_tot);
     }
-    if constexpr (!RES) {
+    if constexpr (!WALK) {
       break;
     } else {
       if (++qtile >= qt_end) break;
@@ -622,7 +702,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_flash_attn(FlashParams p) {
       // (fetching them earlier, under the last key tile, costs 20 registers the kernel does not have:
       // measured with the spills it causes, 0.131 ms against 0.109 ms; the second wavefront of the
       // SIMD covers the wait instead)
-      load_q(qtile * QT + wave * 32);
+      load_q(qtile * QT + qg * 32);
 #pragma unroll
       for (int d = 0; d < C::DT; ++d)
 #pragma unroll
@@ -637,20 +717,20 @@ __global__ __launch_bounds__(64 * NW, 2) void k_flash_attn(FlashParams p) {
 #undef FA_LOAD
 }
 
-template <int DH, int NW, bool RES>
+template <int DH, int QG, int KS, bool RES>
 int launch_dh(const FlashParams &p, int64_t blocks, hipStream_t s) {
   using C = Cfg<DH>;
-  constexpr int smem = (RES ? RES_TILES : 2) * C::STAGE;
+  constexpr int smem = (RES ? RES_TILES : 2 * KS) * C::STAGE;
   static_assert(smem <= 160 * 1024, "the stages must fit the LDS");
   static bool attr_set = false;
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_flash_attn<DH, NW, RES>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_flash_attn<DH, QG, KS, RES>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     if (e != hipSuccess) return ddit::hip_fail(e, "flash hipFuncSetAttribute");
     attr_set = true;
   }
   if (blocks > 0x7fffffff) { ddit::set_error("attention: too many workgroups"); return -2; }
-  hipLaunchKernelGGL((k_flash_attn<DH, NW, RES>), dim3((unsigned)blocks, ddit::prefetch_rows(p.ahead, blocks)), dim3(64 * NW), smem, s, p);
+  hipLaunchKernelGGL((k_flash_attn<DH, QG, KS, RES>), dim3((unsigned)blocks, ddit::prefetch_rows(p.ahead, blocks)), dim3(64 * QG * KS), smem, s, p);
   return ddit::hip_fail(hipGetLastError(), "flash attention launch");
 }
 
@@ -708,8 +788,26 @@ int launch_flash_attn(const AttnArgs &a, hipStream_t s) {
     p.n_chunks = (res_qtiles + p.qtiles_per_chunk - 1) / p.qtiles_per_chunk;
     p.spread = 0;
     const int64_t blocks = (int64_t)p.n_units * p.n_chunks;
-    if (a.dh == 72) return launch_dh<72, RES_NW, true>(p, blocks, s);
-    if (a.dh == 64) return launch_dh<64, RES_NW, true>(p, blocks, s);
+    if (a.dh == 72) return launch_dh<72, RES_NW, 1, true>(p, blocks, s);
+    if (a.dh == 64) return launch_dh<64, RES_NW, 1, true>(p, blocks, s);
+  }
+  // Fewer workgroups than CUs: the wavefronts of a workgroup share the keys as well (see merge_sets).  Up to five key tiles, all fetched at once,
+  // two groups of 32 queries and four sets of tiles; from twelve on, four groups and two sets, each with its own two-stage
+  // ring.  What is saved is the chain of tiles (1.2 us a tile for a wavefront alone on its SIMD); what it costs is the CU's other workgroups,
+  // among them those that fetch weights ahead, hence not up to the last CU.  16 heads, 300 keys, not split / split, a step of 28
+  // blocks, ms: 256 tokens 4.82 / 4.77, 512 5.86 / 5.81, 640 6.13 / 6.05, 768 6.27 / 6.30, 1024 7.07 / 7.31 (192 and 256 workgroups);
+  // one frame of 1000 tokens 21.9 / 20.4 us, of 3600 tokens and 4 heads 58.8 / 47.7 (a step 11.46 / 11.14 ms); two sets of one tile each
+  // (128 tokens, 128 units) made a step 1 % longer.
+  const bool split_res = tiles >= 2 && tiles <= RES_TILES && (int64_t)p.n_units * ((a.Lq + 63) / 64) * 8 <= 5 * (int64_t)cus;
+  const bool split_stream = tiles >= 12 && blocks128 * 4 <= 3 * (int64_t)cus;
+  if (split_res || split_stream) {
+    p.n_qtiles = split_res ? (a.Lq + 63) / 64 : qtiles;
+    p.spread = p.n_units < 64;
+    const int64_t blocks = (p.spread ? (int64_t)p.n_units : (int64_t)((p.n_units + 7) / 8) * 8) * p.n_qtiles;
+    if (split_res && a.dh == 72) return launch_dh<72, 2, 4, true>(p, blocks, s);
+    if (split_res && a.dh == 64) return launch_dh<64, 2, 4, true>(p, blocks, s);
+    if (split_stream && a.dh == 72) return launch_dh<72, 4, 2, false>(p, blocks, s);
+    if (split_stream && a.dh == 64) return launch_dh<64, 4, 2, false>(p, blocks, s);
   }
   // Up to 64 queries (one tile of keys: temporal attention of 33 to 64 frames) half of a workgroup of 128 would
   // be idle and take a CU's slots: 64 queries per workgroup, three workgroups per CU instead of two.  128 / 64
@@ -720,10 +818,10 @@ int launch_flash_attn(const AttnArgs &a, hipStream_t s) {
   p.n_qtiles = (a.Lq + 32 * nw - 1) / (32 * nw);
   p.spread = p.n_units < 64;
   const int64_t blocks = (p.spread ? (int64_t)p.n_units : (int64_t)((p.n_units + 7) / 8) * 8) * p.n_qtiles;
-  if (nw == SHORT_NW && a.dh == 72) return launch_dh<72, SHORT_NW, false>(p, blocks, s);
-  if (nw == SHORT_NW && a.dh == 64) return launch_dh<64, SHORT_NW, false>(p, blocks, s);
-  if (a.dh == 72) return launch_dh<72, STREAM_NW, false>(p, blocks, s);
-  if (a.dh == 64) return launch_dh<64, STREAM_NW, false>(p, blocks, s);
+  if (nw == SHORT_NW && a.dh == 72) return launch_dh<72, SHORT_NW, 1, false>(p, blocks, s);
+  if (nw == SHORT_NW && a.dh == 64) return launch_dh<64, SHORT_NW, 1, false>(p, blocks, s);
+  if (a.dh == 72) return launch_dh<72, STREAM_NW, 1, false>(p, blocks, s);
+  if (a.dh == 64) return launch_dh<64, STREAM_NW, 1, false>(p, blocks, s);
   set_error("dh=%d: supported head dims are 64 and 72", a.dh);
   return -2;
 }
