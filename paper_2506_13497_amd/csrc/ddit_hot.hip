@@ -332,6 +332,9 @@ int run_layer(ddit_attn_kind kind, const Dims &d, const ddit_layer_weights &w, c
     if (!prefetch_pays(N, 2 * (n0 + n1))) return Prefetch{};
     return Prefetch{{w0, w1}, {(unsigned)(n0 / 8), (unsigned)(n1 / 8)}};
   };
+  // text keys and values of this layer (of the first cache, if there are two) that its first launch fetches: elements
+  int64_t text_ahead = kvc_cached && N <= PREFETCH_TEXT_UP_TO ? (kvc_second ? d.B / 2 : d.B) * d.Ly * 2 * A : 0;
+  if (!prefetch_pays(N, 2 * (3 * A * D + text_ahead))) text_ahead = 0;
   auto gated = [&](int row) {
     g.resid = x;
     if (row >= 0) { g.gate_tab = w.ada_table + (int64_t)row * D; g.gate_c6 = c6 + (int64_t)row * D; g.gate_c6_stride = 6 * D; }
@@ -339,7 +342,7 @@ int run_layer(ddit_attn_kind kind, const Dims &d, const ddit_layer_weights &w, c
 
   // self-attention branch
   DDIT_TRY(launch_modulated_layernorm(x, w.ada_table, c6, 0, N, d.L, (int)D, eps, xh, s, pending,
-                                      weights_ahead(w.w_qkv, 3 * A * D)));
+                                      weights_ahead(w.w_qkv, 3 * A * D, kvc, text_ahead)));
   pending->parts = 0;
   DDIT_TRY(tp.keep(DDIT_TAP_XH_MSA, xh));
   base(xh, D, w.w_qkv, w.b_qkv, N, (int)(3 * A), (int)D); g.out = qkv; g.ld_out = 3 * A;

@@ -1,4 +1,4 @@
-// Weights fetched ahead: which launches do it, and which workgroup reads what.  Plain C++, for the host and the device.
+// Weights and text keys fetched ahead: which launches do it, and which workgroup reads what.  Plain C++, for the host and the device.
 #pragma once
 #include <stdint.h>
 
@@ -29,7 +29,11 @@ struct Prefetch {
 // A caller of single blocks walks over the layers in the same way (28 blocks, 64 tokens 5.41 / 5.12 ms, 2304 11.22 / 10.92); one
 // that calls the same block again finds its weights in the cache and pays for the fetch (64 tokens 170 / 176 us a block, 4 heads
 // 160 / 163), which nothing in the call tells apart.
-constexpr int64_t PREFETCH_UP_TO = 3200, PREFETCH_SMALL_TILES_UP_TO = 768;
+// The text's keys and values of a layer, which its few workgroups of cross-attention read at once (16 heads, 64 tokens: 4.2 us of its
+// 9.7 wait for them), come with a layer's first launch up to 1024 tokens.  A step without / with it, ms: 16 heads 64 tokens
+// 3.72 / 3.69, 128 4.13 / 4.07, 180 4.30 / 4.27, 256 4.77 / 4.75, 512 5.81 / 5.80, 1024 7.07 / 7.05; 4 heads 64 3.44 / 3.37, 256 4.08 / 4.05;
+// beyond, 2304 9.78 / 9.83, 3000 11.38 / 11.43.
+constexpr int64_t PREFETCH_UP_TO = 3200, PREFETCH_SMALL_TILES_UP_TO = 768, PREFETCH_TEXT_UP_TO = 1024;
 constexpr bool prefetch_pays(int64_t N, int64_t bytes) {
   if (N > PREFETCH_UP_TO) return false;
   const int64_t last = N % 64;
