@@ -68,6 +68,8 @@ constexpr int KT = 64;         // keys per LDS tile
 typedef __attribute__((address_space(3))) void *lds_ptr_t;
 typedef __attribute__((address_space(1))) const void *gbl_ptr_t;
 typedef short shortx4 __attribute__((ext_vector_type(4)));
+typedef unsigned int uintx2 __attribute__((ext_vector_type(2)));
+typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) shortx4 *lds_s4_ptr_t;
 
 struct FlashParams {
@@ -677,21 +679,32 @@ __global__ __launch_bounds__(64 * QG * KS, 2) void k_flash_attn(FlashParams p) {
     }
     const float inv = 1.0f / l_tot;
     const int qi = q0 + l32;
+    // A lane and lane ^ 32 hold the two halves of each 16-byte piece of a row: after exchanging them the lower lanes store the even
+    // pieces and the upper lanes the odd ones.
+    constexpr int NP = DH / 8;
+    uintx4 piece[(NP + 1) / 2];
+    auto half_piece = [&](int q) {
+      bf16x4 ov;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) ov[e] = (bf16_t)(oacc[q >> 2][4 * (q & 3) + e] * inv);
+      return __builtin_bit_cast(uintx2, ov);
+    };
+#pragma unroll
+    for (int q = 0; q < NP; q += 2) {
+      const uintx2 a = half_piece(q), b = half_piece(q + 1 < NP ? q + 1 : q);
+#pragma unroll
+      for (int w = 0; w < 2; ++w) {
+        const auto r = __builtin_amdgcn_permlane32_swap(a[w], b[w], false, false);
+        piece[q / 2][w] = r[0];
+        piece[q / 2][2 + w] = r[1];
+      }
+    }
     if (qi < p.Lq) {
       const int64_t tok = q_tok0 + (int64_t)qi * p.q_tok_step;
       bf16_t *orow = p.o + tok * p.ld_o + h * DH;
 #pragma unroll
-      for (int d = 0; d < C::DT; ++d)
-#pragma unroll
-        for (int gq = 0; gq < 4; ++gq) {
-          const int d0 = 32 * d + 8 * gq + 4 * lh;
-          if (d0 < DH) {
-            bf16x4 ov;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) ov[e] = (bf16_t)(oacc[d][4 * gq + e] * inv);
-            *reinterpret_cast<bf16x4 *>(orow + d0) = ov;
-          }
-        }
+      for (int q = 0; q < NP; q += 2)
+        if (q + lh < NP) *reinterpret_cast<uintx4 *>(orow + (q + lh) * 8) = piece[q / 2];
       if (p.lse && lh == 0) p.lse[tok * p.H + h] = m_ref * p.scale + __logf(l_tot);
     }
     if constexpr (!WALK) {
