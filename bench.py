@@ -439,15 +439,14 @@ class Workload:
         return table, total_ms
 
     def gemm_tiles(self):
-        """The output tile the launcher's model takes for each linear of this workload (rows x cols; two if it is two launches)."""
+        """The output tile the launcher takes for each linear of this workload (rows x cols; two if it is two launches)."""
         m, sh = self.m, self.sh
         out = {}
         for name, epi, n, k in (("qkv", m.DDIT_EPI_BF16, 3 * sh.A, sh.D), ("attn_out", m.DDIT_EPI_RESIDUAL_F32 | m.DDIT_EPI_COPY, sh.D, sh.A),
                                 ("cross_q", m.DDIT_EPI_BF16, sh.A, sh.D), ("cross_out", m.DDIT_EPI_RESIDUAL_F32, sh.D, sh.A),
                                 ("fc1", m.DDIT_EPI_GELU_BF16, sh.M, sh.D), ("fc2", m.DDIT_EPI_RESIDUAL_F32, sh.D, sh.M)):
             front = m.ddit_linear_front_tokens(epi, sh.N, n, k)   # > 0: two launches, the first with the largest tile
-            picks = ([0] if front else []) + [m.ddit_linear_tile_choice(epi, sh.N - front, n, k)[0]]
-            out[name] = "+".join("%(rows)dx%(cols)d" % m.ddit_linear_tile_info(t) for t in picks)
+            out[name] = ("%(rows)dx%(cols)d+" % m.ddit_linear_tile_info(0) if front else "") + "%dx%d" % m.ddit_linear_form(epi, sh.N - front, n, k)
         return out
 
 

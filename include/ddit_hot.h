@@ -272,7 +272,7 @@ int ddit_linear_tile_count(void);
 int ddit_linear_tile_info(int tile, int32_t *rows, int32_t *cols, int32_t *wavefronts,
                           int32_t *workgroups_per_cu);
 
-/* The tile ddit_linear_fwd would take for this problem, as one launch, on a device of compute_units CUs
+/* The tile of the list that is cheapest for this problem, as one launch, on a device of compute_units CUs
  * (compute_units <= 0: the current device's count, 256 if there is no device) -> *tile_out.
  * epilogue: DDIT_EPI_RESIDUAL_F32 | DDIT_EPI_COPY for a residual update whose out is given.
  * predicted_us_host, if not NULL, is a HOST array of ddit_linear_tile_count() floats that
@@ -281,8 +281,13 @@ int ddit_linear_tile_info(int tile, int32_t *rows, int32_t *cols, int32_t *wavef
 int ddit_linear_tile_choice(int epilogue, int64_t N, int32_t n, int32_t k, int32_t compute_units,
                             int32_t *tile_out, float *predicted_us_host);
 
-/* *tokens_out: 0 where ddit_linear_fwd is one launch with the tile above; else it is two, the first of so many tokens with
- * tile 0 and the second of the others with the tile of a linear of that many tokens.  Arguments as above.  Host only;
+/* Rows and columns of the output tiles that ddit_linear_fwd (with ld_u == k) takes for this problem, as one launch: that tile, or one of the
+ * forms outside the list (few tokens; 320 x 256).  Arguments as above.  Host only; needs no GPU. */
+int ddit_linear_form(int epilogue, int64_t N, int32_t n, int32_t k, int32_t compute_units, int32_t *rows_out,
+                     int32_t *cols_out);
+
+/* *tokens_out: 0 where ddit_linear_fwd is one launch with the tiles above; else it is two, the first of so many tokens with
+ * tile 0 and the second of the others with those of a linear of that many tokens.  Arguments as above.  Host only;
  * needs no GPU. */
 int ddit_linear_front_tokens(int epilogue, int64_t N, int32_t n, int32_t k, int32_t compute_units, int64_t *tokens_out);
 

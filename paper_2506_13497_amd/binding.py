@@ -29,7 +29,7 @@ EXPORTS = ["ddit_abi_version", "ddit_status_string", "ddit_last_error", "ddit_wo
            "ddit_linear_fwd", "ddit_timestep_conditioning", "ddit_io_workspace_bytes", "ddit_embed_latent",
            "ddit_embed_caption", "ddit_output_head", "ddit_eps_theta", "ddit_solver_step", "ddit_sample",
            "ddit_cross_kv_bytes", "ddit_cross_kv_precompute", "ddit_denoise_step_cached", "ddit_linear_tile_count",
-           "ddit_linear_tile_info", "ddit_linear_tile_choice", "ddit_linear_front_tokens", "ddit_linear_fwd_tile",
+           "ddit_linear_tile_info", "ddit_linear_tile_choice", "ddit_linear_form", "ddit_linear_front_tokens", "ddit_linear_fwd_tile",
            "ddit_linear_partial_choice", "ddit_linear_partial_fwd", "ddit_qk_norm_rope_fwd", "ddit_self_attn_fwd", "ddit_optimal_dop",
            "ddit_buddy_create", "ddit_buddy_alloc", "ddit_buddy_release", "ddit_buddy_free_gpus", "ddit_buddy_destroy",
            "ddit_sched_simulate", "ddit_probe_mfma_bf16", "ddit_probe_stream_copy", "ddit_probe_stream_read", "ddit_probe_residual_stream"]
@@ -146,6 +146,7 @@ def _load() -> C.CDLL:
     lib.ddit_linear_tile_info.argtypes = [C.c_int] + [C.POINTER(C.c_int32)] * 4
     lib.ddit_linear_tile_choice.argtypes = [C.c_int, C.c_int64, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32),
                                             C.POINTER(C.c_float)]
+    lib.ddit_linear_form.argtypes = [C.c_int, C.c_int64, C.c_int32, C.c_int32, C.c_int32] + [C.POINTER(C.c_int32)] * 2
     lib.ddit_linear_front_tokens.argtypes = [C.c_int, C.c_int64, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int64)]
     lib.ddit_linear_partial_choice.argtypes = [C.c_int64, C.c_int32, C.c_int32, C.c_int32] + [C.POINTER(C.c_int32)] * 2
     lib.ddit_linear_partial_fwd.argtypes = [C.c_int, C.c_int32, C.c_void_p, C.c_int64, C.c_void_p, C.c_void_p, C.c_int64,
@@ -385,6 +386,13 @@ def ddit_linear_tile_choice(epilogue: int, N: int, n: int, k: int, compute_units
     us = (C.c_float * ddit_linear_tile_count())()
     _check(_lib.ddit_linear_tile_choice(epilogue, N, n, k, compute_units, C.byref(tile), us))
     return tile.value, list(us)
+
+
+def ddit_linear_form(epilogue: int, N: int, n: int, k: int, compute_units: int = 0):
+    """-> (rows, columns) of the output tiles that the launch takes."""
+    v = [C.c_int32() for _ in range(2)]
+    _check(_lib.ddit_linear_form(epilogue, N, n, k, compute_units, *[C.byref(x) for x in v]))
+    return v[0].value, v[1].value
 
 
 def ddit_linear_front_tokens(epilogue: int, N: int, n: int, k: int, compute_units: int = 0) -> int:

@@ -854,6 +854,18 @@ int ddit_linear_tile_choice(int epilogue, int64_t N, int32_t n, int32_t k, int32
   return DDIT_OK;
 }
 
+int ddit_linear_form(int epilogue, int64_t N, int32_t n, int32_t k, int32_t compute_units, int32_t *rows_out, int32_t *cols_out) {
+  const bool copy = epilogue == (DDIT_EPI_RESIDUAL_F32 | DDIT_EPI_COPY);
+  if (copy) epilogue = DDIT_EPI_RESIDUAL_F32;
+  if (epilogue < 0 || epilogue > 2) { set_error("unknown epilogue %d", epilogue); return DDIT_ERR_INVALID_ARG; }
+  if (N < 0 || n < 1 || k < 1) { set_error("linear: N=%lld n=%d k=%d", (long long)N, n, k); return DDIT_ERR_INVALID_ARG; }
+  if (!rows_out || !cols_out) { set_error("rows_out and cols_out must not be NULL"); return DDIT_ERR_INVALID_ARG; }
+  int rows, cols;
+  gemm_form(epilogue, copy, N, n, k, compute_units, &rows, &cols);
+  *rows_out = rows; *cols_out = cols;
+  return DDIT_OK;
+}
+
 int ddit_linear_front_tokens(int epilogue, int64_t N, int32_t n, int32_t k, int32_t compute_units, int64_t *tokens_out) {
   const bool copy = epilogue == (DDIT_EPI_RESIDUAL_F32 | DDIT_EPI_COPY);
   if (copy) epilogue = DDIT_EPI_RESIDUAL_F32;

@@ -1136,11 +1136,20 @@ constexpr TileModel TILES[N_TILES] = {
     {64, 128, 8, 6, 0.364f, {1.42f, 1.92f, 2.78f, 4.25f}, 0.000f, {0.85f, 2.25f}},
     {64, 64, 8, 8, 0.232f, {0.82f, 1.30f, 1.80f, 2.32f}, 0.087f, {0.00f, 2.16f}},
 };
-// One more for the grouped text projections, whose rows are a few hundred text tokens: the 300 of a prompt are one row of its tiles (6 % of
-// the matrix work on nothing, W through the L2 once) where they are two of 192 rows (22 %, twice).  300 tokens, 56 layers of 2304 features: 125
-// -> 92 us; 600 tokens 203 -> 174; 900 282 -> 262; 1200 and 2400 as before.  As a tile of the other linears it would be the best of all for one
-// in seventeen, by up to 13 %.
-constexpr TileModel TEXT_TILE = {320, 256, 8, 2, 1.50f, {5.2f}, 0.310f, {}};
+// One more, outside the list that callers can force a tile from: 142 flop per byte fetched (192 x 384: 128), ten MFMA tiles a wavefront, 234
+// registers.  Its constants are fitted to two sweeps (1164 linears of 500 to 108000 tokens, hidden 1152 with 16 and 4 heads, 2048); taken
+// where its price is two hundredths below the best one's it makes the sweeps' linears 2.7 % of their time shorter, by 8 to 18 % on average where a
+// width is 432 to 864, 512 or 2048: fc1 of 12960 tokens 134.5 -> 123.0 us, 48600 448 -> 428, 108000 967 -> 945; 2048 features, 48600
+// tokens, q|k|v 974 -> 907.  On a third sweep (256, 512, 768 features, 2 heads of 1152), which the fit has not seen, the same but for residual updates of
+// short contractions (k = 256 1.07 times the other tile's time, 512 with the copy 1.10, 512 without 0.92, 768 0.94) and for columns that
+// do not fill a tile (144: 1.03).  For the grouped text projections the 300 tokens of a prompt are one row of its tiles (6 % of the
+// matrix work on nothing, W through the L2 once) where they are two of 192 rows (22 %, twice): 56 layers of 2304 features, 300
+// tokens 125 -> 92 us, 600 203 -> 174, 900 282 -> 262, 1200 and 2400 as before.
+// (256 x 192, 384 x 192 and 192 x 128 were swept too: what the model took them for was 0.1 to 0.4 % shorter on average, with one in
+// twenty 3 % and more longer.)
+constexpr TileModel WIDE_TILE = {320, 256, 8, 2, 1.372f, {3.51f, 5.69f, 16.35f, 20.81f}, 0.255f, {0.00f, 14.90f}};
+constexpr float WIDE_BELOW = 0.98f;
+constexpr int WIDE_K = 256, WIDE_K_RESIDUAL = 768;
 constexpr int RESIDUAL_COPY = 3;   // the model's index of the residual update that also writes bf16(x)
 constexpr float LAUNCH_US = 2.71f;
 constexpr int CHIP_CUS = 256;
@@ -1168,6 +1177,13 @@ int cheapest_tile(int epilogue, int64_t N, int n, int k, int cus) {
     if (us < best_us) { best_us = us; best = t; }
   }
   return best;
+}
+
+// what the launcher takes: cheapest_tile's, or N_TILES for the wide one
+int tile_to_launch(int epilogue, int64_t N, int n, int k, int cus) {
+  const int best = cheapest_tile(epilogue, N, n, k, cus);
+  if (n < WIDE_TILE.cols || k < (epilogue < 2 ? WIDE_K : WIDE_K_RESIDUAL)) return best;
+  return predicted_us(WIDE_TILE, epilogue, N, n, k, cus) < WIDE_BELOW * predicted_us(best, epilogue, N, n, k, cus) ? N_TILES : best;
 }
 
 template <int WGM, int WGN, int WGK, int TM, int TN, int NS, int EPI>
@@ -1231,7 +1247,7 @@ int launch_residual_streaming(int tile, const GemmParams &p, hipStream_t s) {
 // elements: of the whole residual stream
 template <int EPI>
 int launch_epi(int tile, const GemmParams &p, int64_t elements, hipStream_t s) {
-  if (tile < 0) tile = cheapest_tile(EPI == 2 && p.out ? RESIDUAL_COPY : EPI, p.N, p.n, p.k, ddit::device_cus());
+  if (tile < 0) tile = tile_to_launch(EPI == 2 && p.out ? RESIDUAL_COPY : EPI, p.N, p.n, p.k, ddit::device_cus());
   if (EPI == 2 && tile >= FIRST_SMALL_TILE && tile < N_TILES && elements >= STREAM_WRITES_FROM && elements < PLAIN_WRITES_FROM)
     return launch_residual_streaming(tile, p, s);
   switch (tile) {
@@ -1245,6 +1261,7 @@ int launch_epi(int tile, const GemmParams &p, int64_t elements, hipStream_t s) {
     case 7: return launch_checked<2, 2, 2, 1, 3, 4, EPI>(tile, p, s);
     case 8: return launch_checked<2, 2, 2, 1, 2, 6, EPI>(tile, p, s);
     case 9: return launch_checked<2, 2, 2, 1, 1, 8, EPI>(tile, p, s);
+    case N_TILES: return launch_one<2, 4, 1, 5, 2, 2, EPI>(p, s);
   }
   ddit::set_error("linear: no tile %d (there are %d)", tile, N_TILES);
   return -1;
@@ -1269,6 +1286,15 @@ int gemm_tile_choice(int epilogue, bool copy, int64_t N, int n, int k, int cus, 
   if (us_per_tile)
     for (int t = 0; t < N_TILES; ++t) us_per_tile[t] = predicted_us(t, epilogue, N, n, k, cus);
   return cheapest_tile(epilogue, N, n, k, cus);
+}
+
+void gemm_form(int epilogue, bool copy, int64_t N, int n, int k, int cus, int *rows, int *cols) {
+  if (epilogue == 2 && copy) epilogue = RESIDUAL_COPY;
+  if (cus <= 0) cus = device_cus();
+  const int few = few_form(N, n, k, k, 1, (k + BK - 1) / BK, cus), tile = tile_to_launch(epilogue, N, n, k, cus);
+  const TileModel &t = tile < N_TILES ? TILES[tile] : WIDE_TILE;
+  *rows = few ? (few == 1 ? 32 : 64) : t.rows;
+  *cols = few ? (few == 3 ? 64 : 32) : t.cols;
 }
 
 int64_t gemm_tokens_in_front(int epilogue, bool copy, int64_t N, int n, int k, int cus) {
@@ -1296,7 +1322,7 @@ int launch_gemm_grouped(const GemmArgs &a, int G, const void *const *W, const vo
     const float us = predicted_us(t, 0, a.N, n_all, a.k, cus);
     if (tile < 0 || us < best) { tile = t; best = us; }
   }
-  if (a.n % TEXT_TILE.cols == 0 && predicted_us(TEXT_TILE, 0, a.N, n_all, a.k, cus) < best) tile = N_TILES;
+  if (a.n % WIDE_TILE.cols == 0 && predicted_us(WIDE_TILE, 0, a.N, n_all, a.k, cus) < best) tile = N_TILES;
   if (tile < 0) return 1;
   GroupTable gt;
   gt.group_n = a.n;
@@ -1322,7 +1348,7 @@ int launch_gemm_grouped(const GemmArgs &a, int G, const void *const *W, const vo
     case 7: return launch_grouped_tile<2, 2, 2, 1, 3, 4>(p, gt, s);
     case 8: return launch_grouped_tile<2, 2, 2, 1, 2, 6>(p, gt, s);
     case 9: return launch_grouped_tile<2, 2, 2, 1, 1, 8>(p, gt, s);
-    default: return launch_grouped_tile<2, 4, 1, 5, 2, 2>(p, gt, s);   // TEXT_TILE
+    default: return launch_grouped_tile<2, 4, 1, 5, 2, 2>(p, gt, s);   // WIDE_TILE
   }
 }
 
