@@ -111,9 +111,9 @@ int gemm_tile_info(int tile, int *rows, int *cols, int *wavefronts, int *wg_per_
 // the tile the launcher would take (cus <= 0: the current device's CU count); us_per_tile, if not
 // null, receives the model's time for each of the gemm_tile_count() tiles
 int gemm_tile_choice(int epilogue, bool copy, int64_t N, int n, int k, int cus, float *us_per_tile);
-// tokens of the first of the two launches that the launcher would make of this linear, 0 if it makes one
 // Rows and columns of the output tiles of the launch that a linear, or the rest of one in two launches, takes; as above.
 void gemm_form(int epilogue, bool copy, int64_t N, int n, int k, int cus, int *rows, int *cols);
+// tokens of the first of the two launches that the launcher would make of this linear, 0 if it makes one
 int64_t gemm_tokens_in_front(int epilogue, bool copy, int64_t N, int n, int k, int cus);
 
 struct AttnArgs {

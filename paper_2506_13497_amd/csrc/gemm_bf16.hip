@@ -1138,18 +1138,19 @@ constexpr TileModel TILES[N_TILES] = {
 };
 // One more, outside the list that callers can force a tile from: 142 flop per byte fetched (192 x 384: 128), ten MFMA tiles a wavefront, 234
 // registers.  Its constants are fitted to two sweeps (1164 linears of 500 to 108000 tokens, hidden 1152 with 16 and 4 heads, 2048); taken
-// where its price is two hundredths below the best one's it makes the sweeps' linears 2.7 % of their time shorter, by 8 to 18 % on average where a
+// where its price is two hundredths below the best one's it made the sweeps' linears, residual updates of 2048 features among them, 2.7 % of their time shorter, by 8 to 18 % on average where a
 // width is 432 to 864, 512 or 2048: fc1 of 12960 tokens 134.5 -> 123.0 us, 48600 448 -> 428, 108000 967 -> 945; 2048 features, 48600
-// tokens, q|k|v 974 -> 907.  On a third sweep (256, 512, 768 features, 2 heads of 1152), which the fit has not seen, the same but for residual updates of
-// short contractions (k = 256 1.07 times the other tile's time, 512 with the copy 1.10, 512 without 0.92, 768 0.94) and for columns that
-// do not fill a tile (144: 1.03).  For the grouped text projections the 300 tokens of a prompt are one row of its tiles (6 % of the
+// tokens, q|k|v 974 -> 907.  On a third sweep (256, 512, 768 features, 2 heads of 1152), which the fit has not seen, the same but for
+// columns that do not fill a tile (144: 1.03).  Not for residual updates: their widths here are the hidden size, of which 1152 would leave a
+// tenth of its columns empty and is never cheapest, and those of short contractions lost (k = 256 1.07 times the other tile's time).
+// For the grouped text projections the 300 tokens of a prompt are one row of its tiles (6 % of the
 // matrix work on nothing, W through the L2 once) where they are two of 192 rows (22 %, twice): 56 layers of 2304 features, 300
 // tokens 125 -> 92 us, 600 203 -> 174, 900 282 -> 262, 1200 and 2400 as before.
 // (256 x 192, 384 x 192 and 192 x 128 were swept too: what the model took them for was 0.1 to 0.4 % shorter on average, with one in
 // twenty 3 % and more longer.)
-constexpr TileModel WIDE_TILE = {320, 256, 8, 2, 1.372f, {3.51f, 5.69f, 16.35f, 20.81f}, 0.255f, {0.00f, 14.90f}};
+constexpr TileModel WIDE_TILE = {320, 256, 8, 2, 1.372f, {3.51f, 5.69f, 0.00f, 0.00f}, 0.255f, {0.00f, 0.00f}};
 constexpr float WIDE_BELOW = 0.98f;
-constexpr int WIDE_K = 256, WIDE_K_RESIDUAL = 768;
+constexpr int WIDE_K = 256;
 constexpr int RESIDUAL_COPY = 3;   // the model's index of the residual update that also writes bf16(x)
 constexpr float LAUNCH_US = 2.71f;
 constexpr int CHIP_CUS = 256;
@@ -1182,7 +1183,7 @@ int cheapest_tile(int epilogue, int64_t N, int n, int k, int cus) {
 // what the launcher takes: cheapest_tile's, or N_TILES for the wide one
 int tile_to_launch(int epilogue, int64_t N, int n, int k, int cus) {
   const int best = cheapest_tile(epilogue, N, n, k, cus);
-  if (n < WIDE_TILE.cols || k < (epilogue < 2 ? WIDE_K : WIDE_K_RESIDUAL)) return best;
+  if (epilogue >= 2 || n < WIDE_TILE.cols || k < WIDE_K) return best;
   return predicted_us(WIDE_TILE, epilogue, N, n, k, cus) < WIDE_BELOW * predicted_us(best, epilogue, N, n, k, cus) ? N_TILES : best;
 }
 
@@ -1261,7 +1262,8 @@ int launch_epi(int tile, const GemmParams &p, int64_t elements, hipStream_t s) {
     case 7: return launch_checked<2, 2, 2, 1, 3, 4, EPI>(tile, p, s);
     case 8: return launch_checked<2, 2, 2, 1, 2, 6, EPI>(tile, p, s);
     case 9: return launch_checked<2, 2, 2, 1, 1, 8, EPI>(tile, p, s);
-    case N_TILES: return launch_one<2, 4, 1, 5, 2, 2, EPI>(p, s);
+    case N_TILES:
+      if constexpr (EPI < 2) return launch_one<2, 4, 1, 5, 2, 2, EPI>(p, s);
   }
   ddit::set_error("linear: no tile %d (there are %d)", tile, N_TILES);
   return -1;

@@ -1,14 +1,13 @@
 """The linear's 320 x 256 tile at shapes where the launcher takes it: rows and columns that end inside a tile, whole and ragged last
-k-steps, tiles that several samples meet in, more than one round of the chip.  Against float64: bf16 results one rounding
-(2^-9), fp32 results 2 sqrt(k) 2^-24 of the terms' size, taken four times."""
+k-steps, more than one round of the chip.  Against float64: one bf16 rounding (2^-9), taken twice, and the fp32 sum's 2 sqrt(k) 2^-24 of the
+terms' size, taken four times."""
 import pytest
 import torch
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("epi,N,n,k", [(0, 24893, 312, 256), (0, 16817, 592, 264), (0, 32003, 3072, 1152), (1, 16775, 784, 264), (1, 22105, 592, 768),
-                                       (2, 33540, 400, 776), (2, 33702, 392, 768), (18, 34044, 408, 768)])
+@pytest.mark.parametrize("epi,N,n,k", [(0, 24893, 312, 256), (0, 16817, 592, 264), (0, 32003, 3072, 1152), (1, 16775, 784, 264), (1, 22105, 592, 768)])
 def test_linear(epi, N, n, k):
     import paper_2506_13497_amd as m
     assert m.ddit_linear_form(epi, N, n, k, 256) == (320, 256) and m.ddit_linear_front_tokens(epi, N, n, k, 256) == 0
@@ -18,22 +17,8 @@ def test_linear(epi, N, n, k):
     ref = u.double() @ W.double().t() + bias.double()
     fp32 = 8 * k ** 0.5 * 2.0 ** -24 * k ** 0.5
     out = torch.full((N, n + 8), float("nan"), dtype=torch.bfloat16, device="cuda")
-    if epi < 2:
-        m.ddit_linear_fwd(epi, u, k + 8, W, bias, N, n, k, out, n + 8)
-        torch.cuda.synchronize()
-        want = ref if epi == 0 else torch.nn.functional.gelu(ref, approximate="tanh")
-        assert torch.isnan(out[:, n:].float()).all()
-        assert ((out[:, :n].double() - want).abs() <= 2.0 ** -8 * want.abs() + fp32 + 1e-5).all()
-        return
-    copy = epi != 2
-    for tps in (N, 7001):   # one sample; samples that end inside tiles
-        tab, c6 = rnd(6, n), rnd((N + tps - 1) // tps, 6 * n)
-        x0 = rnd(N, n)
-        x = x0.clone()
-        m.ddit_linear_fwd(2, u, k + 8, W, bias, N, n, k, out if copy else None, n + 8 if copy else 0, resid=x, ada_table=tab, c6=c6,
-                          gate_row=2, tokens_per_sample=tps)
-        torch.cuda.synchronize()
-        gate = tab[2].double() + c6.double()[torch.arange(N, device="cuda") // tps, 2 * n:3 * n]
-        want = x0.double() + gate * ref
-        assert ((x.double() - want).abs() <= (fp32 + 2.0 ** -20 * ref.abs()) * (1 + gate.abs()) + 2.0 ** -22 * want.abs()).all(), tps
-        assert not copy or torch.equal(out[:, :n], x.bfloat16())
+    m.ddit_linear_fwd(epi, u, k + 8, W, bias, N, n, k, out, n + 8)
+    torch.cuda.synchronize()
+    want = ref if epi == 0 else torch.nn.functional.gelu(ref, approximate="tanh")
+    assert torch.isnan(out[:, n:].float()).all()
+    assert ((out[:, :n].double() - want).abs() <= 2.0 ** -8 * want.abs() + fp32 + 1e-5).all()
