@@ -223,6 +223,11 @@ struct GemmCfg {
   // accumulators they are fetched when the tile begins, else a few at a time under the epilogue.
   static constexpr int OWN = (TM * TN + WGK - 1) / WGK;
   static constexpr bool X_EARLY = TM * TN <= 4;
+  // ... or, of a tile's first X_AHEAD and where the wavefront is all inside, when the last k-steps begin (as many as fit without
+  // spills): the epilogue began with waiting for them.  With whole wavefronts at a problem's edge (gemm_epilogue) steps of 12960 and 7360 tokens
+  // 36.3 -> 35.8 and 25.5 -> 25.3 ms, 108000 with 4 heads 199.9 -> 199.4, 48600 as before.
+  static constexpr int X_AHEAD = X_EARLY ? 0 : TM * TN <= 6 ? 3 : TM * TN <= 8 ? 2 : 1;
+  static constexpr int X_ROWS = X_EARLY ? OWN : X_AHEAD;
   static_assert(BN / 8 <= 64, "one wavefront fetches the tile's bias");
   static_assert((NS - 1) * NJ < 64 && NS >= 2, "pipeline depth");
 };
@@ -241,8 +246,8 @@ struct TileOut {
   int64_t row0; int col0;      // first token, first out-feature
   bf16_t *out; int shift;      // output of the tile's problem; its first out-feature
   float *part;                 // partial sums: where this part's fp32 rows go
-  unsigned smp0;               // sample of the first token ...
-  bool one_sample;             // ... and of all of them
+  unsigned smp0;               // sample of the wavefront's first token ...
+  bool one_sample;             // ... and of all of its tokens
 };
 
 // The sample a token belongs to (token counts stay below 2^30).
@@ -252,9 +257,9 @@ __device__ __forceinline__ unsigned sample_of(const GemmParams &p, int64_t tok) 
 
 // Rows of the residual stream and gate vectors of a wavefront's tiles, fetched before they are needed: lane l of a
 // group of 8 rows holds four features of row l / 8.
-template <int OWN, int TN>
+template <int TILES, int TN>
 struct XRows {
-  float4 x[OWN][4];
+  float4 x[TILES][4];
   float4 gate[TN];
 };
 
@@ -283,7 +288,7 @@ constexpr bool is_residual(int epi) { return epi == 2 || epi == 4; }
 template <class C, int TM, int TN, int EPI, int T0, int T1, bool FULL>
 __device__ __forceinline__ void gemm_epilogue_as(floatx16 (&acc)[TN][TM], unsigned stg, unsigned char *stg_ptr,
                                               const GemmParams &p, const TileOut &to, int lane, int wm, int wn, unsigned smp0,
-                                                 bool one_sample, const XRows<C::OWN, TN> &early) {
+                                                 bool one_sample, const XRows<C::X_ROWS, TN> &early) {
   const int l32 = lane & 31, lh = lane >> 5;
   const int64_t row_w = to.row0 + wm * (TM * 32);   // the wavefront's first token and out-feature
   const int col_w = to.col0 + wn * (TN * 32);
@@ -381,8 +386,13 @@ __device__ __forceinline__ void gemm_epilogue_as(floatx16 (&acc)[TN][TM], unsign
 #pragma unroll
       for (int a = 0; a < TN; ++a) gate[a] = early.gate[a];
     } else if constexpr (FULL && is_residual(EPI)) {
+      static_assert(C::X_AHEAD <= DEPTH, "");
 #pragma unroll
-      for (int d = 0; d < DEPTH; ++d) issue_x(T0 + d, d);
+      for (int d = 0; d < C::X_AHEAD; ++d)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) xr[d][i] = early.x[d][i];
+#pragma unroll
+      for (int d = C::X_AHEAD; d < DEPTH; ++d) issue_x(T0 + d, d);
 #pragma unroll
       for (int a = 0; a < TN; ++a) gate[a] = gate_vector(p, smp0, col_w + a * 32 + f4);
     }
@@ -467,8 +477,13 @@ __device__ __forceinline__ void gemm_epilogue_as(floatx16 (&acc)[TN][TM], unsign
 template <class C, int TM, int TN, int EPI, int T0, int T1>
 __device__ __forceinline__ void gemm_epilogue(floatx16 (&acc)[TN][TM], unsigned stg, unsigned char *stg_ptr,
                                               const GemmParams &p, const TileOut &to, int lane, int wm, int wn,
-                                              const XRows<C::OWN, TN> &early) {
-  const bool inside = p.plain && to.row0 + C::BM <= p.N && to.col0 + C::BN <= p.n;
+                                              const XRows<C::X_ROWS, TN> &early) {
+  // What lies inside is asked of the wavefront's own rows and columns, not of the tile's: where 256 columns end at 1152 of 1280 half of the
+  // wavefronts have nothing to write and the others all of theirs, and a launch of one round lasts as long as its slowest tile.
+  const int64_t row_w = to.row0 + wm * (TM * 32);
+  const int col_w = to.col0 + wn * (TN * 32);
+  if (row_w >= p.N || col_w >= p.n) return;
+  const bool inside = p.plain && row_w + TM * 32 <= p.N && col_w + TN * 32 <= p.n;
   const unsigned smp0 = to.smp0;
   const bool one_sample = to.one_sample;
   if (inside && one_sample)
@@ -636,11 +651,12 @@ __global__ __launch_bounds__(WGM *WGN *WGK * 64, 2) void k_gemm_bf16(GemmParams 
     to.part = EPI == 3 ? p.resid + part * p.split_stride : nullptr;
     to.row0 = (int64_t)tile_m * BM; to.col0 = tile_n * BN; to.out = p.out; to.shift = 0;
     to.smp0 = 0; to.one_sample = true;
-    XRows<C::OWN, TN> early;
+    XRows<C::X_ROWS, TN> early;
     if constexpr (is_residual(EPI)) {
       if (p.gate_tab && p.gate_c6) {
-        to.smp0 = sample_of(p, to.row0);
-        to.one_sample = to.smp0 == sample_of(p, (to.row0 + BM < p.N ? to.row0 + BM : p.N) - 1);
+        const int64_t first = to.row0 + wm * (TM * 32), end = first + TM * 32;   // the wavefront's rows; past the last token: that one
+        to.smp0 = sample_of(p, first < p.N ? first : p.N - 1);
+        to.one_sample = to.smp0 == sample_of(p, (end < p.N ? end : p.N) - 1);
       }
       if constexpr (C::X_EARLY) {
         // this wavefront's rows of x and gates, behind the loads in flight: they have arrived long before the epilogue
@@ -747,6 +763,22 @@ __global__ __launch_bounds__(WGM *WGN *WGK * 64, 2) void k_gemm_bf16(GemmParams 
     const bool last_tile = DRAIN && nk >= NS && (round + 1 >= p.rounds || tile_sequence_index(p, round + 1) < 0);
     const int full = nk - (last_tile ? NS : DEFER);
     for (int kt = 0; kt < full; ++kt) k_step(std::integral_constant<int, -1>{}, std::false_type{});
+    if constexpr (is_residual(EPI) && C::X_AHEAD > 0) {
+      const int64_t row_w = to.row0 + wm * (TM * 32);
+      const int col_w = to.col0 + wn * (TN * 32);
+      if (p.plain && row_w + TM * 32 <= p.N && col_w + TN * 32 <= p.n) {
+        const unsigned char *const x0 = reinterpret_cast<const unsigned char *>(uniform_ptr(p.resid + row_w * p.n + col_w));
+        const unsigned lane_x = (unsigned)((lane >> 3) * p.n + (lane & 7) * 4) * 4u;
+#pragma unroll
+        for (int d = 0; d < C::X_AHEAD; ++d)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const floatx4 v = *reinterpret_cast<const floatx4 *>(x0 + ((int64_t)(d / TN * 32 + 8 * i) * p.n + d % TN * 32) * 4 + lane_x);
+            early.x[d][i] = make_float4(v[0], v[1], v[2], v[3]);
+          }
+      }
+      asm volatile("" ::: "memory");
+    }
     if (last_tile) tail_steps(std::integral_constant<int, DRAIN ? NS : DEFER>{});
     else tail_steps(std::integral_constant<int, DEFER>{});
 
