@@ -222,11 +222,12 @@ struct GemmCfg {
   // Residual update: a wavefront writes OWN MFMA tiles; where their rows of x fit the registers beside the
   // accumulators they are fetched when the tile begins, else a few at a time under the epilogue.
   static constexpr int OWN = (TM * TN + WGK - 1) / WGK;
-  static constexpr bool X_EARLY = TM * TN <= 4;
+  static constexpr bool X_EARLY = TM * TN <= 4 && NW <= 8;
   // ... or, of a tile's first X_AHEAD and where the wavefront is all inside, when the last k-steps begin (as many as fit without
   // spills): the epilogue began with waiting for them.  With whole wavefronts at a problem's edge (gemm_epilogue) steps of 12960 and 7360 tokens
   // 36.3 -> 35.8 and 25.5 -> 25.3 ms, 108000 with 4 heads 199.9 -> 199.4, 48600 as before.
-  static constexpr int X_AHEAD = X_EARLY ? 0 : TM * TN <= 6 ? 3 : TM * TN <= 8 ? 2 : 1;
+  static constexpr int X_AHEAD = X_EARLY ? 0 : NW > 8 ? 2 : TM * TN <= 6 ? 3 : TM * TN <= 8 ? 2 : 1;
+  static constexpr int X_DEPTH = NW > 8 ? 2 : 3;             // tiles whose rows are in flight under the epilogue
   static constexpr int X_ROWS = X_EARLY ? OWN : X_AHEAD;
   static_assert(BN / 8 <= 64, "one wavefront fetches the tile's bias");
   static_assert((NS - 1) * NJ < 64 && NS >= 2, "pipeline depth");
@@ -351,7 +352,7 @@ __device__ __forceinline__ void gemm_epilogue_as(floatx16 (&acc)[TN][TM], unsign
     // the tiles processed while they are in flight, and waiting for them never waits for a store.
     // Partial sums (EPI 3) leave the same way, fp32 rows as they are, with no stream to read.
     constexpr bool EARLY = is_residual(EPI) && C::X_EARLY;
-    constexpr int DEPTH = EPI == 3 ? 1 : EARLY ? T1 - T0 : !FULL ? 1 : (T1 - T0 < 3 ? T1 - T0 : 3);
+    constexpr int DEPTH = EPI == 3 ? 1 : EARLY ? T1 - T0 : !FULL ? 1 : T1 - T0 < C::X_DEPTH ? T1 - T0 : C::X_DEPTH;
     int r8 = lane >> 3, f4 = (lane & 7) * 4;
     // this wavefront's corner of the stream and of its bf16 copy, and this lane's place in a group of 8 rows
     unsigned char *const x0 = reinterpret_cast<unsigned char *>(uniform_ptr((EPI == 3 ? to.part : p.resid) + row_w * p.n + col_w));
@@ -496,7 +497,7 @@ typedef __attribute__((address_space(3))) void *lds_ptr_t;
 typedef __attribute__((address_space(1))) const void *gbl_ptr_t;
 
 template <int WGM, int WGN, int WGK, int TM, int TN, int NS, int EPI, bool DRAIN, class GT>
-__global__ __launch_bounds__(WGM *WGN *WGK * 64, 2) void k_gemm_bf16(GemmParams p, GT gt) {
+__device__ __forceinline__ void gemm_tiles(GemmParams p, GT gt) {
   using C = GemmCfg<WGM, WGN, WGK, TM, TN, NS>;
   constexpr bool GROUPED = !std::is_same<GT, NoGroups>::value;
   static_assert(!GROUPED || EPI < 2, "grouped launches write bf16 outputs");
@@ -848,6 +849,16 @@ __global__ __launch_bounds__(WGM *WGN *WGK * 64, 2) void k_gemm_bf16(GemmParams 
 #undef DL_MFMAS
 }
 
+template <int WGM, int WGN, int WGK, int TM, int TN, int NS, int EPI, bool DRAIN, class GT>
+__global__ __launch_bounds__(WGM *WGN *WGK * 64, 2) void k_gemm_bf16(GemmParams p, GT gt) {
+  gemm_tiles<WGM, WGN, WGK, TM, TN, NS, EPI, DRAIN, GT>(p, gt);
+}
+// 192 x 192 on twelve wavefronts, three a SIMD, each with 96 x 32 of it: eight could not share its 36 MFMA tiles evenly.
+template <int EPI>
+__global__ __launch_bounds__(768, 3) void k_gemm_twelve(GemmParams p) {
+  gemm_tiles<2, 6, 1, 3, 1, 3, EPI, false, NoGroups>(p, NoGroups());
+}
+
 // ---------------------------------------------------------------------------------------------
 // Few tokens: output tiles of 32 x 32, 64 x 32 or 64 x 64, the k-steps dealt out to the wavefronts.
 //
@@ -1073,14 +1084,19 @@ int launch_few_form(int form, const GemmParams &p, hipStream_t s) {
 template <int WGM, int WGN, int WGK, int TM, int TN, int NS, int EPI, bool DRAIN, class GT>
 int launch_kernel(const GemmParams &p, int grid, hipStream_t s, const GT &gt) {
   using C = GemmCfg<WGM, WGN, WGK, TM, TN, NS>;
+  constexpr bool TWELVE = C::NW == 12;
+  auto kernel = [] {
+    if constexpr (TWELVE) return &k_gemm_twelve<EPI>;
+    else return &k_gemm_bf16<WGM, WGN, WGK, TM, TN, NS, EPI, DRAIN, GT>;
+  }();
   static bool attr_set = false;  // benign race: the attribute is idempotent
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_bf16<WGM, WGN, WGK, TM, TN, NS, EPI, DRAIN, GT>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, C::SMEM);
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, C::SMEM);
     if (e != hipSuccess) return ddit::hip_fail(e, "gemm hipFuncSetAttribute");
     attr_set = true;
   }
-  hipLaunchKernelGGL((k_gemm_bf16<WGM, WGN, WGK, TM, TN, NS, EPI, DRAIN, GT>), dim3((unsigned)grid), dim3(C::NT), C::SMEM, s, p, gt);
+  if constexpr (TWELVE) hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(C::NT), C::SMEM, s, p);
+  else hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(C::NT), C::SMEM, s, p, gt);
   return ddit::hip_fail(hipGetLastError(), "gemm launch");
 }
 
@@ -1183,6 +1199,17 @@ constexpr TileModel TILES[N_TILES] = {
 constexpr TileModel WIDE_TILE = {320, 256, 8, 2, 1.372f, {3.51f, 5.69f, 0.00f, 0.00f}, 0.255f, {0.00f, 0.00f}};
 constexpr float WIDE_BELOW = 0.98f;
 constexpr int WIDE_K = 256;
+// And 192 x 192, which is one round of the chip up to 8064 tokens of 1152 features, where from 7200 on 192 x 256 leaves a tenth of its
+// columns and a quarter of the CUs empty, and in the same place for other widths.  Fitted to a sweep of the same layers with it forced;
+// taken where it is one round and its price a hundredth below the best one's: 20 of the sweep's 918 linears, 0.88 of the other tile's time on
+// average and never more.  (Over several rounds the model overrates it: steps of 14800 to 56800 tokens 0 to 2 % longer; at equal
+// prices, fc1 of 1600 tokens, a step was 0.5 % longer.)  7756 tokens, us with an event pair's 3.5: fc2
+// 115.5 -> 86.1, out-projection with the copy 52.8 -> 42.2, without 40.4 -> 32.1, cross-attention q 31.2 -> 26.8; q|k|v of 2440 tokens 33.4 -> 27.6.
+// A step of six blocks: 2496 tokens 2.30 -> 2.26 ms, 5440 4.03 -> 3.96, 6848 4.72 -> 4.63, 7360 5.35 -> 4.94; 4 heads 7360 3.78 -> 3.42.
+// Wavefronts of 32 x 96 are as fast but spill; four of 96 x 96 take 1.04 times the time.
+constexpr TileModel SQUARE_TILE = {192, 192, 12, 3, 0.512f, {3.07f, 2.67f, 6.25f, 8.00f}, 0.703f, {0.00f, 3.88f}};
+constexpr float SQUARE_BELOW = 0.99f;
+constexpr int WIDE = N_TILES, SQUARE = N_TILES + 1;   // what tile_to_launch calls them
 constexpr int RESIDUAL_COPY = 3;   // the model's index of the residual update that also writes bf16(x)
 constexpr float LAUNCH_US = 2.71f;
 constexpr int CHIP_CUS = 256;
@@ -1212,11 +1239,21 @@ int cheapest_tile(int epilogue, int64_t N, int n, int k, int cus) {
   return best;
 }
 
-// what the launcher takes: cheapest_tile's, or N_TILES for the wide one
+const TileModel &tile_model(int tile) { return tile == WIDE ? WIDE_TILE : tile == SQUARE ? SQUARE_TILE : TILES[tile]; }
+
+// what the launcher takes: cheapest_tile's, or one of the two beside the list
 int tile_to_launch(int epilogue, int64_t N, int n, int k, int cus) {
-  const int best = cheapest_tile(epilogue, N, n, k, cus);
-  if (epilogue >= 2 || n < WIDE_TILE.cols || k < WIDE_K) return best;
-  return predicted_us(WIDE_TILE, epilogue, N, n, k, cus) < WIDE_BELOW * predicted_us(best, epilogue, N, n, k, cus) ? N_TILES : best;
+  int tile = cheapest_tile(epilogue, N, n, k, cus);
+  const float listed = predicted_us(tile, epilogue, N, n, k, cus);
+  float best = listed;
+  auto consider = [&](int other, float below) {
+    const float t = predicted_us(tile_model(other), epilogue, N, n, k, cus);
+    if (t < below * listed && t < best) { tile = other; best = t; }
+  };
+  if (epilogue < 2 && n >= WIDE_TILE.cols && k >= WIDE_K) consider(WIDE, WIDE_BELOW);
+  if (n >= SQUARE_TILE.cols && (N + SQUARE_TILE.rows - 1) / SQUARE_TILE.rows * ((n + SQUARE_TILE.cols - 1) / SQUARE_TILE.cols) <= cus)
+    consider(SQUARE, SQUARE_BELOW);
+  return tile;
 }
 
 template <int WGM, int WGN, int WGK, int TM, int TN, int NS, int EPI>
@@ -1294,7 +1331,8 @@ int launch_epi(int tile, const GemmParams &p, int64_t elements, hipStream_t s) {
     case 7: return launch_checked<2, 2, 2, 1, 3, 4, EPI>(tile, p, s);
     case 8: return launch_checked<2, 2, 2, 1, 2, 6, EPI>(tile, p, s);
     case 9: return launch_checked<2, 2, 2, 1, 1, 8, EPI>(tile, p, s);
-    case N_TILES:
+    case SQUARE: return launch_one<2, 6, 1, 3, 1, 3, EPI>(p, s);
+    case WIDE:
       if constexpr (EPI < 2) return launch_one<2, 4, 1, 5, 2, 2, EPI>(p, s);
   }
   ddit::set_error("linear: no tile %d (there are %d)", tile, N_TILES);
@@ -1325,8 +1363,8 @@ int gemm_tile_choice(int epilogue, bool copy, int64_t N, int n, int k, int cus, 
 void gemm_form(int epilogue, bool copy, int64_t N, int n, int k, int cus, int *rows, int *cols) {
   if (epilogue == 2 && copy) epilogue = RESIDUAL_COPY;
   if (cus <= 0) cus = device_cus();
-  const int few = few_form(N, n, k, k, 1, (k + BK - 1) / BK, cus), tile = tile_to_launch(epilogue, N, n, k, cus);
-  const TileModel &t = tile < N_TILES ? TILES[tile] : WIDE_TILE;
+  const int few = few_form(N, n, k, k, 1, (k + BK - 1) / BK, cus);
+  const TileModel &t = tile_model(tile_to_launch(epilogue, N, n, k, cus));
   *rows = few ? (few == 1 ? 32 : 64) : t.rows;
   *cols = few ? (few == 3 ? 64 : 32) : t.cols;
 }
@@ -1356,7 +1394,7 @@ int launch_gemm_grouped(const GemmArgs &a, int G, const void *const *W, const vo
     const float us = predicted_us(t, 0, a.N, n_all, a.k, cus);
     if (tile < 0 || us < best) { tile = t; best = us; }
   }
-  if (a.n % WIDE_TILE.cols == 0 && predicted_us(WIDE_TILE, 0, a.N, n_all, a.k, cus) < best) tile = N_TILES;
+  if (a.n % WIDE_TILE.cols == 0 && predicted_us(WIDE_TILE, 0, a.N, n_all, a.k, cus) < best) tile = WIDE;
   if (tile < 0) return 1;
   GroupTable gt;
   gt.group_n = a.n;
