@@ -409,8 +409,7 @@ __global__ __launch_bounds__(64 * QG * KS, 2) void k_flash_attn(FlashParams p) {
     static_assert(2 * KS_REF >= 4, "the reference column's k-step is issued after the decision");
     if (__builtin_amdgcn_ballot_w64(first || mx > p.rebase) != 0) {
       const float mq = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      // (of a set of tiles whose first holds nothing but -inf the reference stays: the other sets may have finite scores)
-      const float m_new = ((first && (KS == 1 || mq > -INFINITY)) || mq > p.rebase) ? (float)(bf16_t)(m_ref + mq) : m_ref;
+      const float m_new = (first || mq > p.rebase) ? (float)(bf16_t)(m_ref + mq) : m_ref;
       const float delta = m_new - m_ref;
       // (the first tile moves the reference from 0, possibly far down: O and the sum are still zero)
       const float alpha = first ? 1.0f : __builtin_amdgcn_exp2f(-delta * p.scale_log2);
@@ -541,7 +540,7 @@ __global__ __launch_bounds__(64 * QG * KS, 2) void k_flash_attn(FlashParams p) {
       if (it + 2 < n_my) FA_LOAD(0, tile_at(it + 2) * KT, cur_, tile_at(it + 2));                       \
     }                                                                                                   \
     FENCE();                                                                                            \
-    tile_step(BoolTag<HAS_NEXT>{}, it == 0, RES ? tile_at(it + 1) : (cur_ ^ 1), cur_, S_CUR, S_NXT);    \
+    tile_step(BoolTag<HAS_NEXT>{}, KS == 1 && it == 0, RES ? tile_at(it + 1) : (cur_ ^ 1), cur_, S_CUR, S_NXT);    \
     FENCE();                                                                                            \
     if constexpr (!RES) {                                                                               \
       if (HAS_NEXT) {                                                                                   \
@@ -552,9 +551,34 @@ __global__ __launch_bounds__(64 * QG * KS, 2) void k_flash_attn(FlashParams p) {
     }                                                                                                   \
   } while (0)
 
-  // Sums over the sets of key tiles: every set has its own reference.  The sets from the second on hand theirs over in LDS, in
+  // The sets of key tiles begin with one reference, the largest score of all their first tiles: with one of its own a set whose first
+  // tile lies far below the others' would give weight to scores that have none (the bf16 reference of a score of -1e6 is off by
+  // thousands, and in s - m_ref a huge m_ref leaves nothing of an ordinary s).  A query's largest scores meet behind the stages; if
+  // all are -inf the reference stays 0.
+  float *const first_max = reinterpret_cast<float *>(smem + NST * C::STAGE) + qg * 32 + l32;   // of set k: [k * QT]
+  auto first_reference = [&](floatx16 (&sc)[2]) {
+    float mx = sc[0][0];
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[kt][r]);
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    if (lh == 0) first_max[kg * QT] = mx;
+    lds_barrier();
+#pragma unroll
+    for (int k = 0; k < KS; ++k) mx = fmaxf(mx, first_max[k * QT]);
+    if (mx > -INFINITY) m_ref = (float)(bf16_t)mx;
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sc[kt][r] -= m_ref;
+    if (ref_lane) qf[KS_REF][0] = (bf16_t)(-m_ref);
+  };
+
+  // Sums over the sets of key tiles, whose references may have moved apart.  The sets from the second on hand theirs over in LDS, in
   // the place of the tiles, to the first, which weighs each by 2^(reference - largest reference).  A set without a
-  // term (no tile, or scores of -inf alone) has no say in the largest.
+  // term (no tile, or scores of -inf alone) has no say in the largest; one whose sums are infinite only for its reference's rounding, far
+  // below another's, has no weight: it is left out, since infinity times zero would be NaN.
   auto merge_sets = [&]() {
     constexpr int PART = C::DT * 4 + 1;   // 16-byte pieces a lane hands over
     static_assert((KS - 1) * QG * PART * 1024 <= NST * C::STAGE, "the sums fit the place of the tiles");
@@ -588,25 +612,37 @@ __global__ __launch_bounds__(64 * QG * KS, 2) void k_flash_attn(FlashParams p) {
       if (v[1] > 0.f) top = fmaxf(top, v[0]);
     }
     auto weight = [&](int k) { return l_of[k] == 0.f ? 0.f : __builtin_amdgcn_exp2f((m_set[k] - top) * p.scale_log2); };
+    auto left_out = [&](int k, float w) { return w == 0.f && l_of[k] == INFINITY; };
     const float w0 = weight(0);
+    if (__builtin_amdgcn_ballot_w64(left_out(0, w0)) != 0) {
+#pragma unroll
+      for (int d = 0; d < C::DT; ++d)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) oacc[d][e] = left_out(0, w0) ? 0.f : oacc[d][e];
+    }
 #pragma unroll
     for (int d = 0; d < C::DT; ++d)
 #pragma unroll
       for (int e = 0; e < 16; ++e) oacc[d][e] *= w0;
-    float l_sum = l_set * w0;
+    float l_sum = left_out(0, w0) ? 0.f : l_set * w0;
 #pragma unroll
     for (int k = 1; k < KS; ++k) {
       const unsigned char *const at = smem + ((k - 1) * QG + qg) * (PART * 1024) + lane * 16;
       const float w = weight(k);
+      const bool out = left_out(k, w), any_out = __builtin_amdgcn_ballot_w64(out) != 0;
 #pragma unroll
       for (int d = 0; d < C::DT; ++d)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-          const floatx4 v = *reinterpret_cast<const floatx4 *>(at + (d * 4 + g) * 1024);
+          floatx4 v = *reinterpret_cast<const floatx4 *>(at + (d * 4 + g) * 1024);
+          if (any_out) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = out ? 0.f : v[e];
+          }
 #pragma unroll
           for (int e = 0; e < 4; ++e) oacc[d][4 * g + e] += v[e] * w;
         }
-      l_sum += l_of[k] * w;
+      l_sum += out ? 0.f : l_of[k] * w;
     }
     m_ref = top;
     l_run = l_sum * 0.5f;   // both halves of a query add theirs up below
@@ -653,17 +689,8 @@ __global__ __launch_bounds__(64 * QG * KS, 2) void k_flash_attn(FlashParams p) {
       lds_barrier();
     }
     FA_QK(s_a, RES ? tile_at(0) : kg * 2);
-    if constexpr (!RES) lds_barrier();                    // K of tile 0 may now be overwritten (by tile 2)
-
     int it = 0;
-    for (; it + 2 < n_my; it += 2) {
-      FA_ITER(true, s_a, s_b);
-      ++it;
-      FA_ITER(true, s_b, s_a);
-      --it;
-    }
-    // ---- one or two tiles left; the last one masks the keys past the end
-    auto mask_tail = [&](floatx16 (&sc)[2]) {
+    auto mask_tail = [&](floatx16 (&sc)[2]) {             // the keys past the end
       const int key0 = tile_at(it) * KT;
       if (key0 + KT > Lk) {
 #pragma unroll
@@ -675,21 +702,39 @@ __global__ __launch_bounds__(64 * QG * KS, 2) void k_flash_attn(FlashParams p) {
           }
       }
     };
+    if constexpr (KS > 1) {
+      if (n_my == 1) mask_tail(s_a);
+      first_reference(s_a);                               // (with a barrier that is the next line's as well)
+    } else if constexpr (!RES) {
+      lds_barrier();                                      // K of tile 0 may now be overwritten (by tile 2)
+    }
+
+    for (; it + 2 < n_my; it += 2) {
+      FA_ITER(true, s_a, s_b);
+      ++it;
+      FA_ITER(true, s_b, s_a);
+      --it;
+    }
+    // ---- one or two tiles left; the last one masks the keys past the end
     if (it + 1 < n_my) {
       FA_ITER(true, s_a, s_b);
       ++it;
       mask_tail(s_b);
       FA_ITER(false, s_b, s_a);
     } else {
-      mask_tail(s_a);
+      if (KS == 1 || it > 0) mask_tail(s_a);
       FA_ITER(false, s_a, s_b);
     }
     }
     if constexpr (KS > 1) {
-      // the other sets of key tiles: as many barriers as the one with the most tiles has passed
+      // The other sets of key tiles: as many barriers as the one with the most tiles has passed.  A set without a tile has no first
+      // tile's largest score either.
+      if (n_my == 0 && lh == 0) first_max[kg * QT] = -INFINITY;
       if constexpr (!RES) {
         const int most = (n_tiles + KS - 1) / KS;
         for (int i = n_my > 0 ? n_my : -1; i < most; ++i) lds_barrier();
+      } else if (n_my == 0) {
+        lds_barrier();
       }
       merge_sets();
       if (kg > 0) return;
@@ -760,7 +805,7 @@ __global__ __launch_bounds__(64 * QG * KS, 2) void k_flash_attn(FlashParams p) {
 template <int DH, int QG, int KS, bool RES>
 int launch_dh(const FlashParams &p, int64_t blocks, hipStream_t s) {
   using C = Cfg<DH>;
-  constexpr int smem = (RES ? RES_TILES : 2 * KS) * C::STAGE;
+  constexpr int smem = (RES ? RES_TILES : 2 * KS) * C::STAGE + (KS > 1 ? QG * KS * 32 * (int)sizeof(float) : 0);
   static_assert(smem <= 160 * 1024, "the stages must fit the LDS");
   static bool attr_set = false;
   if (!attr_set) {
@@ -836,8 +881,8 @@ int launch_flash_attn(const AttnArgs &a, hipStream_t s) {
   // ring.  What is saved is the chain of tiles (1.2 us a tile for a wavefront alone on its SIMD); what it costs is the CU's other workgroups,
   // among them those that fetch weights ahead, hence not up to the last CU.  16 heads, 300 keys, not split / split, a step of 28
   // blocks, ms: 256 tokens 4.82 / 4.77, 512 5.86 / 5.81, 640 6.13 / 6.05, 768 6.27 / 6.30, 1024 7.07 / 7.31 (192 and 256 workgroups);
-  // one frame of 1000 tokens 21.9 / 20.4 us, of 3600 tokens and 4 heads 58.8 / 47.7 (a step 11.46 / 11.14 ms); two sets of one tile each
-  // (128 tokens, 128 units) made a step 1 % longer.
+  // one frame of 1000 tokens 19.0 / 16.7 us back to back, of 3600 tokens and 4 heads 53.8 / 38.7 (the common reference is 0.6 of it); two sets
+  // of one tile each (128 tokens, 128 units) made a step 1 % longer.
   const bool split_res = tiles >= 2 && tiles <= RES_TILES && (int64_t)p.n_units * ((a.Lq + 63) / 64) * 8 <= 5 * (int64_t)cus;
   const bool split_stream = tiles >= 12 && blocks128 * 4 <= 3 * (int64_t)cus;
   if (split_res || split_stream) {

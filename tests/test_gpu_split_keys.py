@@ -80,3 +80,60 @@ def test_scores_of_minus_infinity_in_one_set(Ly):
     o, _ = run(m.DDIT_ATTN_CROSS, sh, {"q": q.cuda(), "k": cut.cuda(), "v": v.cuda()})
     o_ref, _ = ora.cross_attention(*(t.double().numpy() for t in (q, k[:, keep], v[:, keep])), np.array([len(keep)]))
     assert_parity(o, o_ref, "-inf in one set")
+
+
+def attend(q, k, v, keep=None):
+    """The kernel's output and log-sum-exp of one sample of cross-attention, and the oracle's over the keys kept."""
+    import paper_2506_13497_amd as m
+    L, Ly, H, dh = q.shape[1], k.shape[1], q.shape[2], q.shape[3]
+    o, lse = run(m.DDIT_ATTN_CROSS, syn.Shape(1, 1, 1, L, H * dh, H, dh, 64, Ly, 1), {"q": q.cuda(), "k": k.cuda(), "v": v.cuda()})
+    keep = list(range(Ly)) if keep is None else keep
+    o_ref, lse_ref = ora.cross_attention(*(t.double().numpy() for t in (q, k[:, keep], v[:, keep])), np.array([len(keep)]))
+    return o, lse, o_ref, lse_ref.reshape(lse.shape)
+
+
+def operands_with_a_bias(Ly, H, dh, seed):
+    """q, k, v ~ N(0,1); the first two columns of q are ones and those of k zero, so that they add to a key's scores."""
+    rng = np.random.default_rng(seed)
+    q, k, v = (torch.from_numpy(rng.standard_normal(s)).to(torch.bfloat16) for s in ((1, 96, H, dh), (1, Ly, H, dh), (1, Ly, H, dh)))
+    q[..., :2], k[..., :2] = 1.0, 0.0
+    return q, k, v
+
+
+@pytest.mark.parametrize("H,dh", [(4, 72), (4, 64)])
+@pytest.mark.parametrize("level", [-1e6, -1e9, -3.3e38])
+@pytest.mark.parametrize("Ly,tiles", [(300, (0,)), (300, (1,)), (300, (2,)), (300, (3,)), (300, (4,)), (300, (1, 2, 3)), (90, (1,)),
+                                      (720, (0,)), (720, (1,)), (720, (2,)), (720, (3,)), (720, (1, 3, 5, 7, 9, 11)), (720, (11,)), (705, (1,))])
+def test_whole_tiles_far_below(Ly, tiles, level, H, dh):
+    """Key tiles whose scores lie far below the others' have no weight, whichever set has them and whether or not their level is a
+    bf16 number (it is off the nearest one by 1.5e-3 of it)."""
+    q, k, v = operands_with_a_bias(Ly, H, dh, 7)
+    for t in tiles:
+        k[:, 64 * t:64 * t + 64, :, 0], k[:, 64 * t:64 * t + 64, :, 1] = level, -1.5e-3 * level
+    o, lse, o_ref, lse_ref = attend(q, k, v)
+    assert_parity(o, o_ref, "%s at %g" % (tiles, level))
+    assert np.abs(lse - lse_ref).max() <= 2e-2
+
+
+@pytest.mark.parametrize("Ly,cut", [(300, (1,)), (300, (0, 1, 2)), (300, (0, 1, 2, 3)), (720, (0,)), (720, (1,)), (720, (1, 3, 5, 7, 9, 11))])
+def test_first_tiles_of_minus_infinity_and_the_rest_far_below_zero(Ly, cut):
+    """A set whose first tile holds -inf alone begins with the others' reference, not with zero.  (Where all sets' first tiles do, the
+    reference is zero and the rest is near it.)"""
+    q, k, v = operands_with_a_bias(Ly, 4, 72, 8)
+    k[..., 0] = 0.0 if cut == (0, 1, 2, 3) else -1200.0
+    for t in cut:
+        k[:, 64 * t:64 * t + 64, :, 0] = float("-inf")
+    o, lse, o_ref, lse_ref = attend(q, k, v, [j for j in range(Ly) if j // 64 not in cut])
+    assert_parity(o, o_ref, "-inf in %s" % (cut,))
+    assert np.abs(lse - lse_ref).max() <= 2e-2
+
+
+@pytest.mark.parametrize("high,lower", [(2, 3), (3, 2), (10, 11), (6, 3)])
+def test_a_later_tile_far_below_another_sets(high, lower):
+    """Two tiles far above the first ones, in different sets: the lower one's sums overflow for its reference's rounding and have no
+    weight.  (At 3e5 a score's fp32 sum is rounded to 1/32, a weight by a few thousandths.)"""
+    q, k, v = operands_with_a_bias(720, 4, 72, 9)
+    k[:, 64 * high:64 * high + 64, :, 0] = 299008.0
+    k[:, 64 * lower:64 * lower + 64, :, 0], k[:, 64 * lower:64 * lower + 64, :, 1] = 266240.0, 1000.0
+    o, _, o_ref, _ = attend(q, k, v)
+    assert_parity(o, o_ref, "tile %d above tile %d" % (high, lower))
