@@ -1258,6 +1258,10 @@ int tile_to_launch(int epilogue, int64_t N, int n, int k, int cus) {
   return tile;
 }
 
+float launch_price(int epilogue, int64_t N, int n, int k, int cus) {
+  return predicted_us(tile_model(tile_to_launch(epilogue, N, n, k, cus)), epilogue, N, n, k, cus);
+}
+
 template <int WGM, int WGN, int WGK, int TM, int TN, int NS, int EPI>
 int launch_checked(int tile, const GemmParams &p, hipStream_t s) {
   using C = GemmCfg<WGM, WGN, WGK, TM, TN, NS>;
@@ -1281,7 +1285,8 @@ constexpr int64_t STREAM_WRITES_FROM = (int64_t)5 << 18, PLAIN_WRITES_FROM = (in
 
 // Two launches for a long contraction (fc2).  Its tiles read the tokens from memory rather than from the L2, the smaller
 // tiles more often, but the largest tile may fill the chip a few times and then a small part of it.  Then the tokens of the
-// full rounds are one launch of it, and the rest, at most three fifths of a round, another of whichever tile suits; where the
+// full rounds are one launch of it, and the rest, at most three fifths of a round, another of whichever form suits (few tokens
+// included: 16401 tokens 177 / 173 us with the listed tile / 32 x 32, 16600 171.5 / 167.7); where the
 // model sees seven hundredths in that, of which it is wont to overstate as much (where it saw 6.4 of them, 1344 x 5376 and 16600
 // tokens, it was 230 / 232 us).  The rest may take a tile that sums k in two halves: a prediction's error against 64 bits is
 // 0.999-1.000 times that of one launch (16700 to 33600 tokens, six blocks).  Returns the first one's tokens, or 0.  One launch / two,
@@ -1289,9 +1294,13 @@ constexpr int64_t STREAM_WRITES_FROM = (int64_t)5 << 18, PLAIN_WRITES_FROM = (in
 // 422 / 362, 42000 429 / 417, 50200 602 / 494, 67000 701 / 639, 70000 704 / 664 (27000, where two thirds of a round are left,
 // 274 / 281); 1344 x 5376: 15000 223 / 210, 25500 405 / 363, 67000 975 / 906; 2048 x 8192: 9300 292 / 290,
 // 25500 801 / 754.  Contractions of 1152 gain nothing: the model sees up to a sixth, and -4 to +9 hundredths came of it.
+// Those prices are of the listed tiles.  Where one launch is of the 320 x 256 tile (bf16 outputs) it is taken instead if its price is 3.5
+// hundredths below the two launches': two / one, us, 1024 x 3072: 16674 tokens 102 / 90, 51098 294 / 285; 1536 x 4096: 12371 133 / 119, 38851
+// 384 / 373; 2048 x 3072: 10054 119 / 97; 72 linears of 768 to 3072 features 0.82 to 1.00 times the time.  Nearer than that the two are
+// faster: 3072 x 3072, 55401 tokens, priced 0.99 of the two, 848 / 901.
 constexpr int64_t TWO_LAUNCHES_FROM = 4096;
 constexpr int TWO_LAUNCHES_K = 3072;
-constexpr float TWO_LAUNCHES_BELOW = 0.93f;
+constexpr float TWO_LAUNCHES_BELOW = 0.93f, ONE_LAUNCH_BELOW = 0.965f;
 
 int64_t tokens_in_front(int epilogue, int64_t N, int n, int k, int cus) {
   if (N < TWO_LAUNCHES_FROM || k < TWO_LAUNCHES_K) return 0;
@@ -1299,10 +1308,10 @@ int64_t tokens_in_front(int epilogue, int64_t N, int n, int k, int cus) {
   const int64_t rows = (N + TILES[0].rows - 1) / TILES[0].rows;
   const int64_t front = rows * cols / cus * cus / cols * TILES[0].rows;   // whole rows of tiles
   if (front <= 0 || front >= N || (N - front) * 5 > round * 3) return 0;
-  const float one = predicted_us(cheapest_tile(epilogue, N, n, k, cus), epilogue, N, n, k, cus);
-  const float two = predicted_us(0, epilogue, front, n, k, cus) +
-                    predicted_us(cheapest_tile(epilogue, N - front, n, k, cus), epilogue, N - front, n, k, cus);
-  return two < TWO_LAUNCHES_BELOW * one ? front : 0;
+  auto listed = [&](int64_t tokens) { return predicted_us(cheapest_tile(epilogue, tokens, n, k, cus), epilogue, tokens, n, k, cus); };
+  const float first = predicted_us(0, epilogue, front, n, k, cus);
+  if (first + listed(N - front) >= TWO_LAUNCHES_BELOW * listed(N)) return 0;
+  return launch_price(epilogue, N, n, k, cus) < ONE_LAUNCH_BELOW * (first + launch_price(epilogue, N - front, n, k, cus)) ? 0 : front;
 }
 
 int launch_residual_streaming(int tile, const GemmParams &p, hipStream_t s) {
@@ -1528,11 +1537,11 @@ int launch_gemm(int epilogue, const GemmArgs &a, hipStream_t s) {
   }
   const int64_t elements = p.N * (int64_t)p.n;
   auto launch = [&](int tile, const GemmParams &q) {
+    if (const int form = tile < 0 ? few_form(q.N, q.n, q.ld_u, q.k, 1, (q.k + BK - 1) / BK, device_cus()) : 0)
+      return epilogue == 0 ? launch_few_form<0>(form, q, s) : epilogue == 1 ? launch_few_form<1>(form, q, s) : launch_few_form<2>(form, q, s);
     return epilogue == 0 ? launch_epi<0>(tile, q, elements, s) : epilogue == 1 ? launch_epi<1>(tile, q, elements, s)
                                                                                 : launch_epi<2>(tile, q, elements, s);
   };
-  if (const int form = a.tile < 0 ? few_form(p.N, p.n, p.ld_u, p.k, 1, (p.k + BK - 1) / BK, device_cus()) : 0)
-    return epilogue == 0 ? launch_few_form<0>(form, p, s) : epilogue == 1 ? launch_few_form<1>(form, p, s) : launch_few_form<2>(form, p, s);
   const int64_t front = a.tile < 0 ? gemm_tokens_in_front(epilogue, p.out != nullptr, p.N, p.n, p.k, 0) : 0;
   if (front > 0) {
     GemmParams first = p;

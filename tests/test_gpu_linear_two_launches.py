@@ -47,3 +47,25 @@ def test_linear_in_two_launches(epilogue, N, front, per_sample):
     if epilogue != RESIDUAL:
         assert ((out[:N, :M].float() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-4).all()
         assert torch.isnan(out[N:]).all() and torch.isnan(out[:, M:]).all()
+
+
+@pytest.mark.parametrize("epilogue,N,form", [(RESIDUAL, 16401, (32, 32)), (RESIDUAL, 17100, (64, 64)), (COPY, 16700, (64, 32)), (GELU, 32700, (32, 32)),
+                                             (0, 32990, (64, 32))])
+def test_the_rest_takes_the_form_of_so_few_tokens(epilogue, N, form):
+    """The second launch is the one that a linear of its tokens takes, which ddit_linear_form says: the same bits."""
+    import paper_2506_13497_amd as m
+    k = 4608
+    front = m.ddit_linear_front_tokens(epilogue, N, M, k, 256)
+    assert front in (16320, 32640) and m.ddit_linear_form(epilogue, N - front, M, k, 256) == form
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    rnd = lambda *s: torch.randn(s, generator=gen, device="cuda")
+    u, W, b, x0 = rnd(N, k).bfloat16(), (rnd(M, k) / k ** 0.5).bfloat16(), rnd(M).bfloat16(), rnd(N, M)
+    got = []
+    for first in (0, front):
+        x, out = x0[first:].clone(), torch.full((N - first, M), float("nan"), dtype=torch.bfloat16, device="cuda")
+        m.ddit_linear_fwd(epilogue & 3, u[first:], k, W, b, N - first, M, k, None if epilogue == RESIDUAL else out, M,
+                          resid=x if epilogue & 2 else None, tokens_per_sample=N)
+        got.append((x[front - first:], out[front - first:]))
+    torch.cuda.synchronize()
+    for a, b in zip(*got):
+        assert torch.equal(a, b) or (torch.isnan(a).all() and torch.isnan(b).all())

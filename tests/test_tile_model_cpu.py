@@ -36,3 +36,19 @@ def test_split_of_fc2_against_measured_layers(m, N):
     parts = m.ddit_linear_partial_choice(N, 1152, 4608)[0]
     assert us[max(parts - 1, 0)] <= min(us) + 2.0
     assert parts == 0 or us[parts - 1] < us[0]
+
+
+# microseconds of linears (epilogue, tokens, out-features, in-features) whose largest tile leaves a small part of a round: in two launches and
+# in one of the tile that ddit_linear_form says
+TWO_OR_ONE_TIMES = {(0, 24618, 768, 3072): (115.0, 107.8), (1, 54077, 768, 4096): (289.1, 267.0), (0, 19653, 1024, 3072): (114.2, 97.0),
+                    (1, 51098, 1024, 4096): (375.3, 361.9), (0, 12371, 1344, 3072): (100.2, 88.1), (1, 26273, 1536, 4096): (262.1, 248.1),
+                    (0, 10054, 2048, 3072): (118.6, 96.7), (1, 25280, 2048, 4096): (366.0, 340.0), (0, 6413, 3072, 4096): (136.2, 124.8),
+                    (0, 55401, 3072, 3072): (848.6, 901.2), (1, 49774, 3072, 3072): (781.9, 825.2), (0, 50105, 3072, 4096): (969.3, 1009.0)}
+
+
+@pytest.mark.parametrize("linear", sorted(TWO_OR_ONE_TIMES))
+def test_two_launches_or_one_of_the_wide_tile(m, linear):
+    epi, N, n, k = linear
+    two, one = TWO_OR_ONE_TIMES[linear]
+    assert m.ddit_linear_form(epi, N, n, k, 256) == (320, 256)
+    assert (m.ddit_linear_front_tokens(epi, N, n, k, 256) == 0) == (one < two)
