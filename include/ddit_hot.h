@@ -161,6 +161,12 @@ int ddit_attn_fwd(ddit_attn_kind kind, const ddit_shape *shape, const void *q, c
                   int64_t ld_q, int64_t ld_kv, const int32_t *kv_valid_len_host, void *o, int64_t ld_o,
                   float *lse_or_null, void *workspace, size_t workspace_bytes, void *hip_stream);
 
+/* How ddit_attn_fwd splits that work on a device of compute_units CUs (<= 0: the current device's count, 256 if there is no
+ * device) -> queries of a workgroup (0: the kernel for short temporal sequences takes the call), sets of wavefronts that share a
+ * sequence's keys, and whether all keys are fetched at once (1) or tile by tile (0).  Host only; needs no GPU. */
+int ddit_attn_form(ddit_attn_kind kind, const ddit_shape *shape, int32_t compute_units, int32_t *queries_out,
+                   int32_t *key_sets_out, int32_t *resident_out);
+
 /* One block of the model of section 2.2 (a "spatial" Transformer layer, which mixes the tokens of one temporal
  * index, followed by a "temporal" one, which mixes the tokens of one spatial location; each with its
  * "cross-attention" to the conditioning text): spatial layer then temporal layer on x_in bf16 [B,T,S,D] with text y bf16
@@ -207,6 +213,9 @@ int ddit_denoise_step(const ddit_shape *shape, const ddit_step_weights *weights,
 int ddit_cross_kv_bytes(const ddit_shape *shape, size_t *bytes_out);
 int ddit_cross_kv_precompute(const ddit_shape *shape, const ddit_step_weights *weights, const void *y,
                              void *cross_kv_out, void *hip_stream);
+/* Rows and columns of the output tiles of ddit_cross_kv_precompute's launches, of up to 128 layers each; 0 and 0 where it projects layer by
+ * layer.  compute_units as for ddit_attn_form.  Host only; needs no GPU. */
+int ddit_cross_kv_form(const ddit_shape *shape, int32_t compute_units, int32_t *rows_out, int32_t *cols_out);
 int ddit_denoise_step_cached(const ddit_shape *shape, const ddit_step_weights *weights, const void *x_in,
                              const void *y, const void *cross_kv_or_null, const int32_t *y_valid_len_host,
                              const float *timesteps_host, const float *temb_or_null, void *x_out,
@@ -256,9 +265,10 @@ int ddit_self_attn_fwd(ddit_attn_kind kind, const ddit_shape *shape, void *q, vo
                        int64_t ld_o, float *lse_or_null, void *hip_stream);
 
 /* ---- output tiles of the linear: for tuning and for parity tests of every compiled tile ----
- * The linear is compiled for a short list of output tiles (rows x cols of out per workgroup) and
- * ddit_linear_fwd takes, per call, the one that a cost model of the kernel prices cheapest for
- * (epilogue, N, n, k) on the current device; a long contraction of many tokens may be two launches,
+ * The linear is compiled for a short list of output tiles (rows x cols of out per workgroup), which callers can force, and for
+ * a few forms beside the list.  ddit_linear_fwd takes, per call, a form for few tokens where its grid finds room on the device
+ * at once, else the tile that a cost model of the kernel prices cheapest for (epilogue, N, n, k), of the list or, where its price
+ * is lower by a margin, 320 x 256 or 192 x 192; a long contraction of many tokens may be two launches,
  * each with its own tile (ddit_linear_front_tokens).  None of the calls below is on the hot path. */
 
 /* Number of compiled tiles; tile indices are 0 .. count-1. */
@@ -281,10 +291,15 @@ int ddit_linear_tile_info(int tile, int32_t *rows, int32_t *cols, int32_t *wavef
 int ddit_linear_tile_choice(int epilogue, int64_t N, int32_t n, int32_t k, int32_t compute_units,
                             int32_t *tile_out, float *predicted_us_host);
 
-/* Rows and columns of the output tiles that ddit_linear_fwd (with ld_u == k) takes for this problem, as one launch: that tile, or one of the
- * forms outside the list (few tokens; 320 x 256).  Arguments as above.  Host only; needs no GPU. */
+/* Rows and columns of the output tiles that ddit_linear_fwd (with ld_u == k) takes for this problem, as one launch: that tile, or one
+ * beside the list (320 x 256; 192 x 192; for few tokens 32 x 32, 64 x 32, 64 x 64, which ddit_linear_few_form tells from the listed
+ * 64 x 64).  Arguments as above.  Host only; needs no GPU. */
 int ddit_linear_form(int epilogue, int64_t N, int32_t n, int32_t k, int32_t compute_units, int32_t *rows_out,
                      int32_t *cols_out);
+
+/* The form for few tokens that a linear (parts = 1), or its partial sums in `parts` parts inside a step, takes -> *form_out: 0 none, 1 tiles of
+ * 32 x 32, 2 of 64 x 32, 3 of 64 x 64.  Arguments as above.  Host only; needs no GPU. */
+int ddit_linear_few_form(int64_t N, int32_t n, int32_t k, int32_t parts, int32_t compute_units, int32_t *form_out);
 
 /* *tokens_out: 0 where ddit_linear_fwd is one launch with the tiles above; else it is two, the first of so many tokens with
  * tile 0 and the second of the others with those of a linear of that many tokens.  Arguments as above.  Host only;

@@ -29,7 +29,7 @@ EXPORTS = ["ddit_abi_version", "ddit_status_string", "ddit_last_error", "ddit_wo
            "ddit_linear_fwd", "ddit_timestep_conditioning", "ddit_io_workspace_bytes", "ddit_embed_latent",
            "ddit_embed_caption", "ddit_output_head", "ddit_eps_theta", "ddit_solver_step", "ddit_sample",
            "ddit_cross_kv_bytes", "ddit_cross_kv_precompute", "ddit_denoise_step_cached", "ddit_linear_tile_count",
-           "ddit_linear_tile_info", "ddit_linear_tile_choice", "ddit_linear_form", "ddit_linear_front_tokens", "ddit_linear_fwd_tile",
+           "ddit_linear_tile_info", "ddit_linear_tile_choice", "ddit_linear_form", "ddit_linear_few_form", "ddit_attn_form", "ddit_cross_kv_form", "ddit_linear_front_tokens", "ddit_linear_fwd_tile",
            "ddit_linear_partial_choice", "ddit_linear_partial_fwd", "ddit_qk_norm_rope_fwd", "ddit_self_attn_fwd", "ddit_optimal_dop",
            "ddit_buddy_create", "ddit_buddy_alloc", "ddit_buddy_release", "ddit_buddy_free_gpus", "ddit_buddy_destroy",
            "ddit_sched_simulate", "ddit_probe_mfma_bf16", "ddit_probe_stream_copy", "ddit_probe_stream_read", "ddit_probe_residual_stream"]
@@ -147,6 +147,9 @@ def _load() -> C.CDLL:
     lib.ddit_linear_tile_choice.argtypes = [C.c_int, C.c_int64, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32),
                                             C.POINTER(C.c_float)]
     lib.ddit_linear_form.argtypes = [C.c_int, C.c_int64, C.c_int32, C.c_int32, C.c_int32] + [C.POINTER(C.c_int32)] * 2
+    lib.ddit_linear_few_form.argtypes = [C.c_int64, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32)]
+    lib.ddit_attn_form.argtypes = [C.c_int, C.POINTER(ddit_shape), C.c_int32] + [C.POINTER(C.c_int32)] * 3
+    lib.ddit_cross_kv_form.argtypes = [C.POINTER(ddit_shape), C.c_int32] + [C.POINTER(C.c_int32)] * 2
     lib.ddit_linear_front_tokens.argtypes = [C.c_int, C.c_int64, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int64)]
     lib.ddit_linear_partial_choice.argtypes = [C.c_int64, C.c_int32, C.c_int32, C.c_int32] + [C.POINTER(C.c_int32)] * 2
     lib.ddit_linear_partial_fwd.argtypes = [C.c_int, C.c_int32, C.c_void_p, C.c_int64, C.c_void_p, C.c_void_p, C.c_int64,
@@ -392,6 +395,27 @@ def ddit_linear_form(epilogue: int, N: int, n: int, k: int, compute_units: int =
     """-> (rows, columns) of the output tiles that the launch takes."""
     v = [C.c_int32() for _ in range(2)]
     _check(_lib.ddit_linear_form(epilogue, N, n, k, compute_units, *[C.byref(x) for x in v]))
+    return v[0].value, v[1].value
+
+
+def ddit_linear_few_form(N: int, n: int, k: int, parts: int = 1, compute_units: int = 0) -> int:
+    """0, or the form for few tokens: 1 tiles of 32 x 32, 2 of 64 x 32, 3 of 64 x 64."""
+    form = C.c_int32()
+    _check(_lib.ddit_linear_few_form(N, n, k, parts, compute_units, C.byref(form)))
+    return form.value
+
+
+def ddit_attn_form(kind: int, shape, compute_units: int = 0):
+    """-> (queries of a workgroup, sets of wavefronts that share the keys, whether all keys are fetched at once)."""
+    v = [C.c_int32() for _ in range(3)]
+    _check(_lib.ddit_attn_form(kind, C.byref(shape), compute_units, *[C.byref(x) for x in v]))
+    return v[0].value, v[1].value, bool(v[2].value)
+
+
+def ddit_cross_kv_form(shape, compute_units: int = 0):
+    """-> (rows, columns) of the output tiles of the grouped launch; (0, 0) where the layers are projected one by one."""
+    v = [C.c_int32() for _ in range(2)]
+    _check(_lib.ddit_cross_kv_form(C.byref(shape), compute_units, *[C.byref(x) for x in v]))
     return v[0].value, v[1].value
 
 

@@ -99,8 +99,7 @@ int launch_gemm(int epilogue, const GemmArgs &a, hipStream_t s);
 // The residual update as partial sums over parts of k, fp32 [N, n] each, for a later launch to add up.
 // In how many, at most max_parts (0: in one launch is cheaper), and with which tile; the launch.
 int gemm_partial_choice(int64_t N, int n, int k, int max_parts, int *tile_out);
-// few: in the form for few tokens, whatever the tile; whether it fits
-bool gemm_partial_few(int64_t N, int n, int k, int parts);
+// few: in the form for few tokens, whatever the tile (where there is one: gemm_few_form)
 int launch_gemm_partial(const GemmArgs &a, int parts, int tile, float *out, int64_t part_stride, hipStream_t s, bool few = false);
 // G problems that share u (a.W, a.bias, a.out are ignored; a.n is one problem's out-features): 0 = launched,
 // 1 = this shape cannot be grouped (nothing launched: launch them one by one), negative = error
@@ -113,6 +112,10 @@ int gemm_tile_info(int tile, int *rows, int *cols, int *wavefronts, int *wg_per_
 int gemm_tile_choice(int epilogue, bool copy, int64_t N, int n, int k, int cus, float *us_per_tile);
 // Rows and columns of the output tiles of the launch that a linear, or the rest of one in two launches, takes; as above.
 void gemm_form(int epilogue, bool copy, int64_t N, int n, int k, int cus, int *rows, int *cols);
+// The form for few tokens that a linear (parts = 1), or its partial sums in so many parts, takes: 0 none, 1 32 x 32, 2 64 x 32, 3 64 x 64.
+int gemm_few_form(int64_t N, int n, int k, int parts, int cus);
+// Rows and columns of the output tiles of a grouped launch; 0 where the problems are launched one by one.
+void gemm_grouped_form(int64_t N, int n, int k, int G, int cus, int *rows, int *cols);
 // tokens of the first of the two launches that the launcher would make of this linear, 0 if it makes one
 int64_t gemm_tokens_in_front(int epilogue, bool copy, int64_t N, int n, int k, int cus);
 
@@ -136,6 +139,13 @@ struct AttnArgs {
   const void *k2, *v2; int split;
 };
 int launch_flash_attn(const AttnArgs &a, hipStream_t s);
+// How launch_flash_attn splits the work for units (groups x heads) of Lq queries and at most Lk keys.
+struct FlashForm {
+  int queries;    // per workgroup (of the resident form that walks over query tiles: per tile)
+  int key_sets;   // sets of wavefronts that share the keys
+  bool resident;  // all keys are fetched at once
+};
+FlashForm flash_form(int Lq, int Lk, int64_t units, int cus);
 int temporal_attn_max_T();   // longest sequence the dedicated temporal kernel takes
 // g_q/g_k (per-head RMS-norm scales, both or neither) and rope_table ([T, dh/2] (cos, sin)) may be null:
 // when given, q and k are normalised / rotated inside the kernel on their way in

@@ -402,7 +402,7 @@ int run_layer(ddit_attn_kind kind, const Dims &d, const ddit_layer_weights &w, c
   if (lo.fc2_parts > 0) {
     *pending = PendingSum{lo.fc2_parts, reinterpret_cast<const float *>(qkv), N * D, g.gate_tab, g.gate_c6, g.gate_c6_stride};
     DDIT_TRY(launch_gemm_partial(g, lo.fc2_parts, lo.fc2_tile, reinterpret_cast<float *>(qkv), N * D, s,
-                                 gemm_partial_few(N, (int)D, (int)M, lo.fc2_parts)));
+                                 gemm_few_form(N, (int)D, (int)M, lo.fc2_parts, 0) > 0));
     if (tp.on) {   // the tap shows the stream after the layer: the same sum, formed here instead of by the next launch
       DDIT_TRY(launch_add_pending(x, *pending, N, d.L, (int)D, s));
       pending->parts = 0;
@@ -423,17 +423,17 @@ int finish_stream(const Dims &d, const float *x, const PendingSum &pending, void
 // Text k|v projections of all 2 * n_blocks layers: y [B*Ly, D] against every layer's w_ckv, layer l's result at
 // out + l * (B*Ly*2A*2 bytes).  One grouped launch where the shape allows it (the projections share y and are
 // far too small, one by one, for the chip), else layer by layer.
+constexpr int TEXT_LAYERS_A_LAUNCH = 128;
 int project_text_kv(const Dims &d, const ddit_step_weights *weights, const void *y, unsigned char *out, hipStream_t s) {
   const size_t per_layer = (size_t)d.B * d.Ly * 2 * d.A * 2;
   const int layers = (int)(2 * d.n_blocks);
   GemmArgs g;
   memset(&g, 0, sizeof(g)); g.tile = -1;
   g.u = y; g.ld_u = d.D; g.N = d.B * d.Ly; g.n = (int)(2 * d.A); g.k = (int)d.D; g.ld_out = 2 * d.A; g.tokens_per_sample = d.Ly;
-  constexpr int CHUNK = 128;
-  for (int l0 = 0; l0 < layers; l0 += CHUNK) {
-    const int G = layers - l0 < CHUNK ? layers - l0 : CHUNK;
-    const void *W[CHUNK], *bias[CHUNK];
-    void *o[CHUNK];
+  for (int l0 = 0; l0 < layers; l0 += TEXT_LAYERS_A_LAUNCH) {
+    const int G = layers - l0 < TEXT_LAYERS_A_LAUNCH ? layers - l0 : TEXT_LAYERS_A_LAUNCH;
+    const void *W[TEXT_LAYERS_A_LAUNCH], *bias[TEXT_LAYERS_A_LAUNCH];
+    void *o[TEXT_LAYERS_A_LAUNCH];
     for (int j = 0; j < G; ++j) {
       const int l = l0 + j;
       const ddit_layer_weights &w = (l & 1) ? weights->blocks[l >> 1].temporal : weights->blocks[l >> 1].spatial;
@@ -626,6 +626,23 @@ int ddit_attn_fwd(ddit_attn_kind kind, const ddit_shape *shape, const void *q, c
                        lse_or_null, reinterpret_cast<hipStream_t>(hip_stream));
 }
 
+int ddit_attn_form(ddit_attn_kind kind, const ddit_shape *shape, int32_t compute_units, int32_t *queries_out, int32_t *key_sets_out,
+                   int32_t *resident_out) {
+  Dims d;
+  DDIT_TRY(check_shape(shape, &d));
+  if (kind != DDIT_ATTN_SPATIAL && kind != DDIT_ATTN_TEMPORAL && kind != DDIT_ATTN_CROSS) {
+    set_error("unknown attention kind %d", (int)kind); return DDIT_ERR_INVALID_ARG;
+  }
+  if (!queries_out || !key_sets_out || !resident_out) { set_error("queries_out, key_sets_out and resident_out must not be NULL"); return DDIT_ERR_INVALID_ARG; }
+  FlashForm f = {0, 0, false};
+  const int cus = compute_units > 0 ? compute_units : device_cus();
+  if (kind == DDIT_ATTN_SPATIAL) f = flash_form((int)d.S, (int)d.S, d.B * d.T * d.H, cus);
+  else if (kind == DDIT_ATTN_CROSS) f = flash_form((int)d.L, (int)d.Ly, d.B * d.H, cus);
+  else if (d.T > temporal_attn_max_T()) f = flash_form((int)d.T, (int)d.T, d.B * d.S * d.H, cus);
+  *queries_out = f.queries; *key_sets_out = f.key_sets; *resident_out = f.resident;
+  return DDIT_OK;
+}
+
 // One block in a workspace laid out as `lo`
 static int block_fwd(const ddit_shape *shape, const Dims &d, const Layout &lo, const ddit_block_weights *weights, const void *x_in,
                      const void *y, const int32_t *y_valid_len_host, const float *c6, void *x_out, void *workspace,
@@ -722,6 +739,16 @@ int ddit_cross_kv_precompute(const ddit_shape *shape, const ddit_step_weights *w
       if (!aligned16(w->w_ckv) || (w->b_ckv && !aligned16(w->b_ckv))) { set_error("block %d: w_ckv/b_ckv not 16-byte aligned", i); return DDIT_ERR_ALIGNMENT; }
     }
   return project_text_kv(d, weights, y, reinterpret_cast<unsigned char *>(cross_kv_out), reinterpret_cast<hipStream_t>(hip_stream));
+}
+
+int ddit_cross_kv_form(const ddit_shape *shape, int32_t compute_units, int32_t *rows_out, int32_t *cols_out) {
+  Dims d;
+  DDIT_TRY(check_shape(shape, &d));
+  if (!rows_out || !cols_out) { set_error("rows_out and cols_out must not be NULL"); return DDIT_ERR_INVALID_ARG; }
+  int rows, cols;
+  gemm_grouped_form(d.B * d.Ly, (int)(2 * d.A), (int)d.D, (int)std::min<int64_t>(2 * d.n_blocks, TEXT_LAYERS_A_LAUNCH), compute_units, &rows, &cols);
+  *rows_out = rows; *cols_out = cols;
+  return DDIT_OK;
 }
 
 int ddit_denoise_step(const ddit_shape *shape, const ddit_step_weights *weights, const void *x_in,
@@ -863,6 +890,13 @@ int ddit_linear_form(int epilogue, int64_t N, int32_t n, int32_t k, int32_t comp
   int rows, cols;
   gemm_form(epilogue, copy, N, n, k, compute_units, &rows, &cols);
   *rows_out = rows; *cols_out = cols;
+  return DDIT_OK;
+}
+
+int ddit_linear_few_form(int64_t N, int32_t n, int32_t k, int32_t parts, int32_t compute_units, int32_t *form_out) {
+  if (N < 0 || n < 1 || k < 1 || parts < 1) { set_error("linear: N=%lld n=%d k=%d parts=%d", (long long)N, n, k, parts); return DDIT_ERR_INVALID_ARG; }
+  if (!form_out) { set_error("form_out must not be NULL"); return DDIT_ERR_INVALID_ARG; }
+  *form_out = gemm_few_form(N, n, k, parts, compute_units);
   return DDIT_OK;
 }
 

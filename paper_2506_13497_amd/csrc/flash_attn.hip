@@ -57,6 +57,8 @@
 // threaded through the exponentials by hand: see tile_step.
 #include "ddit_common.hpp"
 
+#include <algorithm>
+
 namespace {
 
 constexpr int STREAM_NW = 4;   // wavefronts per workgroup of the streaming form (two workgroups per CU)
@@ -823,6 +825,37 @@ int launch_dh(const FlashParams &p, int64_t blocks, hipStream_t s) {
 
 namespace ddit {
 
+FlashForm flash_form(int Lq, int Lk, int64_t units, int cus) {
+  // Short key sequences (cross-attention to the text): the resident form, one workgroup per CU, as many chunks per unit
+  // as that allows.  It pays where every workgroup gets a run of at least four query tiles to spread the one-off K/V
+  // fetch over, and, with two key tiles and more, as soon as the streaming form's 128 queries a workgroup would put two of them on a
+  // CU: the keys are then fetched once for both, and all at once.  16 heads, streaming / resident, us: 300 keys, 1024 queries 9.3 / 11.1
+  // (64 CUs busy; stays streaming), 2304 13.3 / 12.0, 4600 22.0 / 19.0, 7360 26.8 / 21.4, 9720 44.5 / 38.1; 4 heads 2304 8.9 / 10.5
+  // (stays), 9720 12.7 / 11.5; 60 keys, 12960 queries 36.5 / 37.6 (stays); frames of 144 tokens, 160 units 14.4 / 12.4, 256
+  // 16.7 / 15.2.  Not where units of one query tile alone are more than the CUs (225 tokens, 512 units 35.6 / 40.4: each
+  // workgroup waits for its whole K and V with nothing beside it on the CU), nor where tiles of 256 queries are much emptier.
+  const int64_t res_qtiles = (Lq + 32 * RES_NW - 1) / (32 * RES_NW), qtiles = (Lq + 127) / 128;
+  const int64_t chunks = units > 0 && units < cus ? cus / units : 1, blocks128 = units * qtiles;
+  const int tiles = (Lk + KT - 1) / KT;
+  const bool shared = tiles >= 2 && units <= cus && blocks128 > cus && 14 * res_qtiles <= 8 * qtiles;
+  if (tiles <= RES_TILES && (res_qtiles >= 4 * chunks || shared)) return {32 * RES_NW, 1, true};
+  // Fewer workgroups than CUs: the wavefronts of a workgroup share the keys as well (see merge_sets).  Up to five key tiles, all fetched at once,
+  // two groups of 32 queries and four sets of tiles; from twelve on, four groups and two sets, each with its own two-stage
+  // ring.  What is saved is the chain of tiles (1.2 us a tile for a wavefront alone on its SIMD); what it costs is the CU's other workgroups,
+  // among them those that fetch weights ahead, hence not up to the last CU.  16 heads, 300 keys, not split / split, a step of 28
+  // blocks, ms: 256 tokens 4.82 / 4.77, 512 5.86 / 5.81, 640 6.13 / 6.05, 768 6.27 / 6.30, 1024 7.07 / 7.31 (192 and 256 workgroups);
+  // one frame of 1000 tokens 19.0 / 16.7 us back to back, of 3600 tokens and 4 heads 53.8 / 38.7 (the common reference is 0.6 of it); two sets
+  // of one tile each (128 tokens, 128 units) made a step 1 % longer.
+  if (tiles >= 2 && tiles <= RES_TILES && units * ((Lq + 63) / 64) * 8 <= 5 * (int64_t)cus) return {64, 4, true};
+  if (tiles >= 12 && blocks128 * 4 <= 3 * (int64_t)cus) return {128, 2, false};
+  // Up to 64 queries (one tile of keys: temporal attention of 33 to 64 frames) half of a workgroup of 128 would
+  // be idle and take a CU's slots: 64 queries per workgroup, three workgroups per CU instead of two.  128 / 64
+  // queries, d_h = 72: 405 locations x 16 heads, T = 51 71.9 / 57.6 us, T = 64 69.5 / 64.1; 920 x 4, T = 33
+  // 36.0 / 27.5; 129 to 192 queries, where the last 128 are half empty too: no difference (144 queries, 256 units
+  // 12.8 / 12.7 us; 192, 480 units 22.6 / 22.8).
+  return {32 * (Lq <= 32 * SHORT_NW ? SHORT_NW : STREAM_NW), 1, false};
+}
+
 int launch_flash_attn(const AttnArgs &a, hipStream_t s) {
   if (a.n_groups == 0 || a.Lq == 0) return 0;
   FlashParams p;
@@ -853,58 +886,28 @@ int launch_flash_attn(const AttnArgs &a, hipStream_t s) {
   }
   p.n_units = a.n_groups * a.H;
   p.n_chunks = 1; p.qtiles_per_chunk = 1;
-  // Short key sequences (cross-attention to the text): the resident form, one workgroup per CU, as many chunks per unit
-  // as that allows.  It pays where every workgroup gets a run of at least four query tiles to spread the one-off K/V
-  // fetch over, and, with two key tiles and more, as soon as the streaming form's 128 queries a workgroup would put two of them on a
-  // CU: the keys are then fetched once for both, and all at once.  16 heads, streaming / resident, us: 300 keys, 1024 queries 9.3 / 11.1
-  // (64 CUs busy; stays streaming), 2304 13.3 / 12.0, 4600 22.0 / 19.0, 7360 26.8 / 21.4, 9720 44.5 / 38.1; 4 heads 2304 8.9 / 10.5
-  // (stays), 9720 12.7 / 11.5; 60 keys, 12960 queries 36.5 / 37.6 (stays); frames of 144 tokens, 160 units 14.4 / 12.4, 256
-  // 16.7 / 15.2.  Not where units of one query tile alone are more than the CUs (225 tokens, 512 units 35.6 / 40.4: each
-  // workgroup waits for its whole K and V with nothing beside it on the CU), nor where tiles of 256 queries are much emptier.
-  const int res_qtiles = (a.Lq + 32 * RES_NW - 1) / (32 * RES_NW);
-  int chunks = ddit::device_cus() / (p.n_units > 0 ? p.n_units : 1);
-  if (chunks < 1) chunks = 1;
-  const int tiles = (a.Lk_max + KT - 1) / KT, cus = ddit::device_cus(), qtiles = (a.Lq + 127) / 128;
-  const int64_t blocks128 = (int64_t)p.n_units * qtiles;
-  const bool shared = tiles >= 2 && p.n_units <= cus && blocks128 > cus && 14 * (int64_t)res_qtiles <= 8 * (int64_t)qtiles;
-  if (tiles <= RES_TILES && (res_qtiles >= 4 * chunks || shared)) {
-    p.n_qtiles = res_qtiles;
-    p.qtiles_per_chunk = (res_qtiles + chunks - 1) / chunks;
-    p.n_chunks = (res_qtiles + p.qtiles_per_chunk - 1) / p.qtiles_per_chunk;
+  const FlashForm form = flash_form(a.Lq, a.Lk_max, p.n_units, device_cus());
+  p.n_qtiles = (a.Lq + form.queries - 1) / form.queries;
+  if (form.resident && form.key_sets == 1) {
+    const int chunks = std::max(1, device_cus() / std::max(1, p.n_units));   // workgroups per unit, at one per CU
+    p.qtiles_per_chunk = (p.n_qtiles + chunks - 1) / chunks;
+    p.n_chunks = (p.n_qtiles + p.qtiles_per_chunk - 1) / p.qtiles_per_chunk;
     p.spread = 0;
     const int64_t blocks = (int64_t)p.n_units * p.n_chunks;
     if (a.dh == 72) return launch_dh<72, RES_NW, 1, true>(p, blocks, s);
     if (a.dh == 64) return launch_dh<64, RES_NW, 1, true>(p, blocks, s);
   }
-  // Fewer workgroups than CUs: the wavefronts of a workgroup share the keys as well (see merge_sets).  Up to five key tiles, all fetched at once,
-  // two groups of 32 queries and four sets of tiles; from twelve on, four groups and two sets, each with its own two-stage
-  // ring.  What is saved is the chain of tiles (1.2 us a tile for a wavefront alone on its SIMD); what it costs is the CU's other workgroups,
-  // among them those that fetch weights ahead, hence not up to the last CU.  16 heads, 300 keys, not split / split, a step of 28
-  // blocks, ms: 256 tokens 4.82 / 4.77, 512 5.86 / 5.81, 640 6.13 / 6.05, 768 6.27 / 6.30, 1024 7.07 / 7.31 (192 and 256 workgroups);
-  // one frame of 1000 tokens 19.0 / 16.7 us back to back, of 3600 tokens and 4 heads 53.8 / 38.7 (the common reference is 0.6 of it); two sets
-  // of one tile each (128 tokens, 128 units) made a step 1 % longer.
-  const bool split_res = tiles >= 2 && tiles <= RES_TILES && (int64_t)p.n_units * ((a.Lq + 63) / 64) * 8 <= 5 * (int64_t)cus;
-  const bool split_stream = tiles >= 12 && blocks128 * 4 <= 3 * (int64_t)cus;
-  if (split_res || split_stream) {
-    p.n_qtiles = split_res ? (a.Lq + 63) / 64 : qtiles;
-    p.spread = p.n_units < 64;
-    const int64_t blocks = (p.spread ? (int64_t)p.n_units : (int64_t)((p.n_units + 7) / 8) * 8) * p.n_qtiles;
-    if (split_res && a.dh == 72) return launch_dh<72, 2, 4, true>(p, blocks, s);
-    if (split_res && a.dh == 64) return launch_dh<64, 2, 4, true>(p, blocks, s);
-    if (split_stream && a.dh == 72) return launch_dh<72, 4, 2, false>(p, blocks, s);
-    if (split_stream && a.dh == 64) return launch_dh<64, 4, 2, false>(p, blocks, s);
-  }
-  // Up to 64 queries (one tile of keys: temporal attention of 33 to 64 frames) half of a workgroup of 128 would
-  // be idle and take a CU's slots: 64 queries per workgroup, three workgroups per CU instead of two.  128 / 64
-  // queries, d_h = 72: 405 locations x 16 heads, T = 51 71.9 / 57.6 us, T = 64 69.5 / 64.1; 920 x 4, T = 33
-  // 36.0 / 27.5; 129 to 192 queries, where the last 128 are half empty too: no difference (144 queries, 256 units
-  // 12.8 / 12.7 us; 192, 480 units 22.6 / 22.8).
-  const int nw = a.Lq <= 32 * SHORT_NW ? SHORT_NW : STREAM_NW;
-  p.n_qtiles = (a.Lq + 32 * nw - 1) / (32 * nw);
   p.spread = p.n_units < 64;
   const int64_t blocks = (p.spread ? (int64_t)p.n_units : (int64_t)((p.n_units + 7) / 8) * 8) * p.n_qtiles;
-  if (nw == SHORT_NW && a.dh == 72) return launch_dh<72, SHORT_NW, 1, false>(p, blocks, s);
-  if (nw == SHORT_NW && a.dh == 64) return launch_dh<64, SHORT_NW, 1, false>(p, blocks, s);
+  if (form.key_sets > 1) {
+    if (form.resident && a.dh == 72) return launch_dh<72, 2, 4, true>(p, blocks, s);
+    if (form.resident && a.dh == 64) return launch_dh<64, 2, 4, true>(p, blocks, s);
+    if (!form.resident && a.dh == 72) return launch_dh<72, 4, 2, false>(p, blocks, s);
+    if (!form.resident && a.dh == 64) return launch_dh<64, 4, 2, false>(p, blocks, s);
+  }
+  const bool few = form.queries == 32 * SHORT_NW;
+  if (few && a.dh == 72) return launch_dh<72, SHORT_NW, 1, false>(p, blocks, s);
+  if (few && a.dh == 64) return launch_dh<64, SHORT_NW, 1, false>(p, blocks, s);
   if (a.dh == 72) return launch_dh<72, STREAM_NW, 1, false>(p, blocks, s);
   if (a.dh == 64) return launch_dh<64, STREAM_NW, 1, false>(p, blocks, s);
   set_error("dh=%d: supported head dims are 64 and 72", a.dh);

@@ -1380,6 +1380,10 @@ void gemm_form(int epilogue, bool copy, int64_t N, int n, int k, int cus, int *r
   *cols = few ? (few == 3 ? 64 : 32) : t.cols;
 }
 
+int gemm_few_form(int64_t N, int n, int k, int parts, int cus) {
+  return few_form(N, n, k, k, parts, ((k + BK - 1) / BK + parts - 1) / parts, cus > 0 ? cus : device_cus());
+}
+
 int64_t gemm_tokens_in_front(int epilogue, bool copy, int64_t N, int n, int k, int cus) {
   return tokens_in_front(epilogue == 2 && copy ? RESIDUAL_COPY : epilogue, N, n, k, cus > 0 ? cus : device_cus());
 }
@@ -1389,23 +1393,35 @@ int launch_grouped_tile(const GemmParams &p, const GroupTable &gt, hipStream_t s
   return launch_one<WGM, WGN, WGK, TM, TN, NS, 0, GroupTable>(p, s, gt);
 }
 
+// The cheapest tile whose columns divide a problem's out-features (a tile must lie inside one problem), or -1.
+static int grouped_tile(int64_t N, int n, int k, int G, int cus) {
+  const int n_all = G * n;
+  int tile = -1;
+  float best = 0.f;
+  for (int t = 0; t < N_TILES; ++t) {
+    if (n % TILES[t].cols) continue;
+    const float us = predicted_us(t, 0, N, n_all, k, cus);
+    if (tile < 0 || us < best) { tile = t; best = us; }
+  }
+  return n % WIDE_TILE.cols == 0 && predicted_us(WIDE_TILE, 0, N, n_all, k, cus) < best ? WIDE : tile;
+}
+
+static bool can_group(int64_t N, int n, int64_t ld_u, int k, int G) {
+  return G >= 2 && G <= MAX_GROUPS && (int64_t)G * n < (int64_t)1 << 30 && (int64_t)n * k < (int64_t)1 << 31 && N * ld_u < (int64_t)1 << 31;
+}
+
+void gemm_grouped_form(int64_t N, int n, int k, int G, int cus, int *rows, int *cols) {
+  const int tile = can_group(N, n, k, k, G) ? grouped_tile(N, n, k, G, cus > 0 ? cus : device_cus()) : -1;
+  *rows = tile < 0 ? 0 : tile_model(tile).rows;
+  *cols = tile < 0 ? 0 : tile_model(tile).cols;
+}
+
 // One launch for G problems that share u: out[g] = u W[g]^T + bias[g], every W[g] of shape [a.n, a.k].
 // Returns 1 (nothing launched) when the shape cannot be grouped: the caller then launches them one by one.
 int launch_gemm_grouped(const GemmArgs &a, int G, const void *const *W, const void *const *bias, void *const *out,
                         hipStream_t s) {
   if (a.N == 0 || a.n == 0 || G == 0) return 0;
-  if (G < 2 || G > MAX_GROUPS || (int64_t)G * a.n >= (int64_t)1 << 30) return 1;
-  if ((int64_t)a.n * a.k >= (int64_t)1 << 31 || a.N * a.ld_u >= (int64_t)1 << 31) return 1;
-  // cheapest tile whose columns divide a problem's out-features (a tile must lie inside one problem)
-  const int n_all = G * a.n, cus = device_cus();
-  int tile = -1;
-  float best = 0.f;
-  for (int t = 0; t < N_TILES; ++t) {
-    if (a.n % TILES[t].cols) continue;
-    const float us = predicted_us(t, 0, a.N, n_all, a.k, cus);
-    if (tile < 0 || us < best) { tile = t; best = us; }
-  }
-  if (a.n % WIDE_TILE.cols == 0 && predicted_us(WIDE_TILE, 0, a.N, n_all, a.k, cus) < best) tile = WIDE;
+  const int tile = can_group(a.N, a.n, a.ld_u, a.k, G) ? grouped_tile(a.N, a.n, a.k, G, device_cus()) : -1;
   if (tile < 0) return 1;
   GroupTable gt;
   gt.group_n = a.n;
@@ -1417,7 +1433,7 @@ int launch_gemm_grouped(const GemmArgs &a, int G, const void *const *W, const vo
   GemmParams p{};
   p.u = reinterpret_cast<const bf16_t *>(a.u); p.ld_u = a.ld_u;
   p.W = gt.W[0]; p.bias = gt.bias[0];
-  p.N = a.N; p.n = n_all; p.k = a.k;
+  p.N = a.N; p.n = G * a.n; p.k = a.k;
   p.out = gt.out[0]; p.ld_out = a.ld_out;
   p.tokens_per_sample = a.tokens_per_sample > 0 ? a.tokens_per_sample : 1;
   switch (tile) {
@@ -1464,10 +1480,6 @@ int gemm_partial_choice(int64_t N, int n, int k, int max_parts, int *tile_out) {
     }
   }
   return chosen;
-}
-
-bool gemm_partial_few(int64_t N, int n, int k, int parts) {
-  return few_form(N, n, k, k, parts, ((k + BK - 1) / BK + parts - 1) / parts, device_cus()) > 0;
 }
 
 int launch_partial_tile(int tile, const GemmParams &p, hipStream_t s) {

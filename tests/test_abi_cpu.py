@@ -416,3 +416,46 @@ def test_a_prediction_is_refused_before_anything_is_enqueued(m):
     assert statuses(y=None, kv=None)[0] == -1
     sw.blocks = None
     assert statuses() == (-1, -1)
+
+
+def test_which_form_takes_a_call(m):
+    """The host-only queries of the forms beside the tile list: arguments are validated, answers agree with each other, and the
+    boundaries of the forms lie where a change of the rules would move them."""
+    lib = m.binding._lib
+    v = [C.c_int32(-7) for _ in range(3)]
+    P = [C.byref(x) for x in v]
+    bad_shape = m.make_shape(1, 4, 8, 8, 256, 4, 80, 1024, 16, 1)
+    assert lib.ddit_linear_form(3, 100, 64, 64, 256, *P[:2]) == -1 and lib.ddit_linear_form(0, -1, 64, 64, 256, *P[:2]) == -1
+    assert lib.ddit_linear_form(0, 100, 0, 64, 256, *P[:2]) == -1 and lib.ddit_linear_form(0, 100, 64, 0, 256, *P[:2]) == -1
+    assert lib.ddit_linear_form(0, 100, 64, 64, 256, None, P[1]) == -1 and lib.ddit_linear_form(0, 100, 64, 64, 256, P[0], None) == -1
+    assert lib.ddit_linear_few_form(-1, 64, 64, 1, 256, P[0]) == -1 and lib.ddit_linear_few_form(1, 64, 64, 0, 256, P[0]) == -1
+    assert lib.ddit_linear_few_form(1, 64, 64, 1, 256, None) == -1
+    sh = _shape(m)
+    assert lib.ddit_attn_form(3, C.byref(sh), 256, *P) == -1 and lib.ddit_attn_form(0, C.byref(bad_shape), 256, *P) == -2
+    assert lib.ddit_attn_form(0, C.byref(sh), 256, None, P[1], P[2]) == -1 and lib.ddit_attn_form(0, None, 256, *P) == -1
+    assert lib.ddit_cross_kv_form(C.byref(sh), 256, None, P[1]) == -1 and lib.ddit_cross_kv_form(C.byref(bad_shape), 256, *P[:2]) == -2
+    assert all(x.value == -7 for x in v)
+    listed = {(t["rows"], t["cols"]) for t in (m.ddit_linear_tile_info(i) for i in range(m.ddit_linear_tile_count()))}
+    for epi in (0, 1, 2, 2 | m.DDIT_EPI_COPY):
+        for N in (1, 40, 224, 225, 441, 513, 900, 2400, 5000, 7700, 13111, 20000, 48600, 108000):
+            for n, k in ((8, 8), (256, 256), (512, 1152), (1152, 1152), (1152, 4608), (3456, 1152), (4608, 1152)):
+                form, few = m.ddit_linear_form(epi, N, n, k, 256), m.ddit_linear_few_form(N, n, k, 1, 256)
+                if few:
+                    assert form == {1: (32, 32), 2: (64, 32), 3: (64, 64)}[few]
+                else:
+                    tile = m.ddit_linear_tile_info(m.ddit_linear_tile_choice(epi, N, n, k, 256)[0])
+                    assert form in ((tile["rows"], tile["cols"]), (192, 192)) or (form == (320, 256) and epi < 2)
+    assert listed.isdisjoint({(320, 256), (192, 192), (32, 32), (64, 32)})
+    assert [m.ddit_linear_few_form(N, 1152, 1152, 1, 256) for N in (224, 225, 448, 449)] == [1, 2, 2, 0]
+    assert [m.ddit_linear_few_form(N, 1152, k, 1, 256) for N, k in ((896, 3008), (897, 3008), (896, 2944))] == [3, 0, 0]
+    assert [m.ddit_linear_form(2, N, 1152, 1152, 256) == (192, 192) for N in (7168, 7169, 8064, 8065)] == [False, True, True, False]
+    attn = lambda kind, T, S, H, Ly=300, B=1: m.ddit_attn_form(kind, m.make_shape(B, T, 1, S, H * 72, H, 72, 64, Ly, 1), 256)
+    assert attn(m.DDIT_ATTN_TEMPORAL, 32, 9, 4) == (0, 0, False) and attn(m.DDIT_ATTN_TEMPORAL, 33, 9, 4) == (64, 1, False)
+    assert attn(m.DDIT_ATTN_CROSS, 30, 1620, 16, 287) == (256, 1, True)
+    assert attn(m.DDIT_ATTN_SPATIAL, 30, 1620, 16) == (128, 1, False)
+    assert [attn(m.DDIT_ATTN_CROSS, 1, 640, 16, Ly) for Ly in (64, 65, 320, 321, 704, 705)] == [
+        (128, 1, False), (64, 4, True), (64, 4, True), (128, 1, False), (128, 1, False), (128, 2, False)]
+    assert [attn(m.DDIT_ATTN_CROSS, 1, L, 16) for L in (640, 641)] == [(64, 4, True), (128, 1, False)]
+    assert [attn(m.DDIT_ATTN_CROSS, 1, L, 16, 1000)[1] for L in (1536, 1537)] == [2, 1]
+    text = lambda Ly, H=16, blocks=28: m.ddit_cross_kv_form(m.make_shape(1, 1, 1, 2, 1152, H, 72, 4608, Ly, blocks), 256)
+    assert text(300) == (320, 256) and text(300, H=7) == (0, 0) and text(300, H=2) == (192, 288) and text(300, blocks=0) == (0, 0)
