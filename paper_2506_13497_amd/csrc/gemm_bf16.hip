@@ -1201,6 +1201,13 @@ constexpr TileModel TILES[N_TILES] = {
 constexpr TileModel WIDE_TILE = {320, 256, 8, 2, 1.372f, {3.51f, 5.69f, 0.00f, 0.00f}, 0.255f, {0.00f, 0.00f}};
 constexpr float WIDE_BELOW = 0.98f;
 constexpr int WIDE_K = 256;
+// Over several rounds of a contraction below 1024 the price is too low, a tile being mostly epilogue.  Where it lay 2 to 6.5 hundredths
+// below the listed tile's, the linears took 1.00 to 1.18 times that tile's time, and bf16 outputs with k below 512 gained nothing from
+// three rounds on (29 linears 0.94-1.07, 1.01 on average; they are bound by writing): 768 x 256, 35058 tokens, 23.3 -> 27.4 us, 74891 43.4 -> 46.3,
+// 256 x 256, 101426 tokens, 26.4 -> 29.8; grouped, 56 layers of 512 features with k = 256, 1600 text tokens 35.5 -> 41.8.  Of 193 linears with k = 256 to 768
+// 65 are listed tiles by that, 1.03 times as long with this one, and 128 are this tile, 0.97.
+constexpr float WIDE_BELOW_SHORT = 0.935f;
+constexpr int WIDE_SHORT_K = 1024, WIDE_PLAIN_K = 512;
 // And 192 x 192, which is one round of the chip up to 8064 tokens of 1152 features, where from 7200 on 192 x 256 leaves a tenth of its
 // columns and a quarter of the CUs empty, and in the same place for other widths.  Fitted to a sweep of the same layers with it forced;
 // taken where it is one round and its price a hundredth below the best one's: 20 of the sweep's 918 linears, 0.88 of the other tile's time on
@@ -1243,6 +1250,13 @@ int cheapest_tile(int epilogue, int64_t N, int n, int k, int cus) {
 
 const TileModel &tile_model(int tile) { return tile == WIDE ? WIDE_TILE : tile == SQUARE ? SQUARE_TILE : TILES[tile]; }
 
+// what the 320 x 256 tile's price has to be below, of the best listed one's; `margin` where its price is right
+float wide_below(float margin, int epilogue, int64_t N, int n, int k, int cus) {
+  const int64_t tiles = (N + WIDE_TILE.rows - 1) / WIDE_TILE.rows * ((n + WIDE_TILE.cols - 1) / WIDE_TILE.cols);
+  if (tiles <= cus || k >= WIDE_SHORT_K) return margin;
+  return epilogue == 0 && k < WIDE_PLAIN_K && tiles > 2 * cus ? 0.f : WIDE_BELOW_SHORT;
+}
+
 // what the launcher takes: cheapest_tile's, or one of the two beside the list
 int tile_to_launch(int epilogue, int64_t N, int n, int k, int cus) {
   int tile = cheapest_tile(epilogue, N, n, k, cus);
@@ -1252,7 +1266,7 @@ int tile_to_launch(int epilogue, int64_t N, int n, int k, int cus) {
     const float t = predicted_us(tile_model(other), epilogue, N, n, k, cus);
     if (t < below * listed && t < best) { tile = other; best = t; }
   };
-  if (epilogue < 2 && n >= WIDE_TILE.cols && k >= WIDE_K) consider(WIDE, WIDE_BELOW);
+  if (epilogue < 2 && n >= WIDE_TILE.cols && k >= WIDE_K) consider(WIDE, wide_below(WIDE_BELOW, epilogue, N, n, k, cus));
   if (n >= SQUARE_TILE.cols && (N + SQUARE_TILE.rows - 1) / SQUARE_TILE.rows * ((n + SQUARE_TILE.cols - 1) / SQUARE_TILE.cols) <= cus)
     consider(SQUARE, SQUARE_BELOW);
   return tile;
@@ -1403,7 +1417,7 @@ static int grouped_tile(int64_t N, int n, int k, int G, int cus) {
     const float us = predicted_us(t, 0, N, n_all, k, cus);
     if (tile < 0 || us < best) { tile = t; best = us; }
   }
-  return n % WIDE_TILE.cols == 0 && predicted_us(WIDE_TILE, 0, N, n_all, k, cus) < best ? WIDE : tile;
+  return n % WIDE_TILE.cols == 0 && predicted_us(WIDE_TILE, 0, N, n_all, k, cus) < wide_below(1.f, 0, N, n_all, k, cus) * best ? WIDE : tile;
 }
 
 static bool can_group(int64_t N, int n, int64_t ld_u, int k, int G) {

@@ -1,5 +1,5 @@
 """Text k|v projections of all layers at the token counts where the launcher takes a tile of 320 rows: one row of tiles, full and
-ragged, a ragged second, the first token of a third; and the first count behind one row, which another tile takes.  Enough layers to fill the chip with it.  Against fp32 PyTorch on the
+ragged, and a ragged second; and the first counts behind one row and two, which other tiles take.  Enough layers to fill the chip with it.  Against fp32 PyTorch on the
 same bf16 operands: one bf16 rounding (2^-9 of the value) and fp32 sums over k = 256."""
 import pytest
 import torch
@@ -10,13 +10,13 @@ from helpers import dict_dev, to_dev
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("Ly", [289, 300, 320, 321, 400, 620, 641])
+@pytest.mark.parametrize("Ly", [289, 300, 320, 321, 620, 641])
 def test_text_projection(Ly):
     import paper_2506_13497_amd as m
     D, H, dh, blocks = 256, 4, 64, 64
     sh = syn.Shape(1, 1, 1, 2, D, H, dh, 64, Ly, blocks)
     shape = m.make_shape(1, 1, 1, 2, D, H, dh, 64, Ly, blocks)
-    assert m.ddit_cross_kv_form(shape, 256) == ((192, 256) if Ly == 321 else (320, 256))
+    assert m.ddit_cross_kv_form(shape, 256) == {321: (192, 256), 641: (256, 256)}.get(Ly, (320, 256))
     dsw = {k: to_dev(v) for k, v in syn.make_step_weights(sh, 62).items()}
     dblocks = [dict_dev(syn.make_block_weights(sh, 62, 0, table_std=0.1)) for _ in range(blocks)]
     g = torch.Generator(device="cuda").manual_seed(Ly)

@@ -52,3 +52,23 @@ def test_two_launches_or_one_of_the_wide_tile(m, linear):
     two, one = TWO_OR_ONE_TIMES[linear]
     assert m.ddit_linear_form(epi, N, n, k, 256) == (320, 256)
     assert (m.ddit_linear_front_tokens(epi, N, n, k, 256) == 0) == (one < two)
+
+
+# microseconds of short contractions of many tokens (epilogue, tokens, out-features, in-features) with the best listed tile and with 320 x 256
+SHORT_TIMES = {(0, 101426, 256, 256): (26.4, 29.8), (0, 72024, 256, 256): (20.8, 18.5), (0, 35058, 768, 256): (23.3, 27.4), (0, 61654, 768, 256): (38.6, 44.3),
+               (0, 48295, 768, 256): (32.2, 29.6), (0, 74891, 768, 256): (43.3, 46.2), (1, 103073, 1024, 256): (91.9, 93.9), (1, 56225, 1024, 256): (51.6, 48.2),
+               (0, 102646, 1024, 384): (102.9, 110.0), (0, 37559, 1024, 384): (41.0, 37.2), (1, 96119, 1536, 384): (143.9, 151.2), (1, 90202, 1536, 384): (142.8, 133.1),
+               (0, 95692, 1536, 512): (161.4, 169.0), (0, 77392, 1536, 512): (143.0, 130.7), (1, 63057, 2048, 512): (152.9, 158.4), (1, 50247, 2048, 512): (132.0, 117.1),
+               (0, 87984, 768, 768): (105.3, 110.3), (0, 51933, 2304, 768): (177.8, 164.1)}
+
+
+@pytest.mark.parametrize("linear", sorted(SHORT_TIMES))
+def test_short_contractions_take_the_wide_tile_where_it_is_faster(m, linear):
+    listed, wide = SHORT_TIMES[linear]
+    assert (m.ddit_linear_form(*linear, 256) == (320, 256)) == (wide < listed)
+
+
+def test_text_projections_of_short_contractions(m):
+    """56 layers of 512 features, k = 256: 600 text tokens 18.3 us with the best listed tile, 16.6 with 320 x 256; 1600 35.2 and 41.8; 2000 42.7 and 49.3."""
+    form = lambda Ly, B: m.ddit_cross_kv_form(m.make_shape(B, 1, 1, 2, 256, 4, 64, 64, Ly, 28), 256)
+    assert form(300, 2) == (320, 256) and form(200, 8) != (320, 256) and form(500, 4) != (320, 256)
