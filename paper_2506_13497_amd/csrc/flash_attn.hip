@@ -614,37 +614,42 @@ __global__ __launch_bounds__(64 * QG * KS, 2) void k_flash_attn(FlashParams p) {
       if (v[1] > 0.f) top = fmaxf(top, v[0]);
     }
     auto weight = [&](int k) { return l_of[k] == 0.f ? 0.f : __builtin_amdgcn_exp2f((m_set[k] - top) * p.scale_log2); };
-    auto left_out = [&](int k, float w) { return w == 0.f && l_of[k] == INFINITY; };
-    const float w0 = weight(0);
-    if (__builtin_amdgcn_ballot_w64(left_out(0, w0)) != 0) {
 #pragma unroll
-      for (int d = 0; d < C::DT; ++d)
+    for (int k = 0; k < KS; ++k) {
+      const bool out = l_of[k] == INFINITY && weight(k) == 0.f;
+      if (__builtin_amdgcn_ballot_w64(out) == 0) continue;
+      if (out) {
+        l_of[k] = 0.f;
+        if (k == 0) {
 #pragma unroll
-        for (int e = 0; e < 16; ++e) oacc[d][e] = left_out(0, w0) ? 0.f : oacc[d][e];
+          for (int d = 0; d < C::DT; ++d)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) oacc[d][e] = 0.f;
+        } else {
+          for (int i = 0; i < C::DT * 4; ++i)
+            *reinterpret_cast<floatx4 *>(smem + ((k - 1) * QG + qg) * (PART * 1024) + i * 1024 + lane * 16) = floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+      }
     }
+    const float w0 = weight(0);
 #pragma unroll
     for (int d = 0; d < C::DT; ++d)
 #pragma unroll
       for (int e = 0; e < 16; ++e) oacc[d][e] *= w0;
-    float l_sum = left_out(0, w0) ? 0.f : l_set * w0;
+    float l_sum = l_of[0] * w0;
 #pragma unroll
     for (int k = 1; k < KS; ++k) {
       const unsigned char *const at = smem + ((k - 1) * QG + qg) * (PART * 1024) + lane * 16;
       const float w = weight(k);
-      const bool out = left_out(k, w), any_out = __builtin_amdgcn_ballot_w64(out) != 0;
 #pragma unroll
       for (int d = 0; d < C::DT; ++d)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-          floatx4 v = *reinterpret_cast<const floatx4 *>(at + (d * 4 + g) * 1024);
-          if (any_out) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = out ? 0.f : v[e];
-          }
+          const floatx4 v = *reinterpret_cast<const floatx4 *>(at + (d * 4 + g) * 1024);
 #pragma unroll
           for (int e = 0; e < 4; ++e) oacc[d][4 * g + e] += v[e] * w;
         }
-      l_sum += out ? 0.f : l_of[k] * w;
+      l_sum += l_of[k] * w;
     }
     m_ref = top;
     l_run = l_sum * 0.5f;   // both halves of a query add theirs up below
@@ -844,7 +849,7 @@ FlashForm flash_form(int Lq, int Lk, int64_t units, int cus) {
   // ring.  What is saved is the chain of tiles (1.2 us a tile for a wavefront alone on its SIMD); what it costs is the CU's other workgroups,
   // among them those that fetch weights ahead, hence not up to the last CU.  16 heads, 300 keys, not split / split, a step of 28
   // blocks, ms: 256 tokens 4.82 / 4.77, 512 5.86 / 5.81, 640 6.13 / 6.05, 768 6.27 / 6.30, 1024 7.07 / 7.31 (192 and 256 workgroups);
-  // one frame of 1000 tokens 19.0 / 16.7 us back to back, of 3600 tokens and 4 heads 53.8 / 38.7 (the common reference is 0.6 of it); two sets
+  // one frame of 1000 tokens 19.0 / 16.3 us back to back, of 3600 tokens and 4 heads 53.8 / 38.5 (the common reference is 0.3 of it); two sets
   // of one tile each (128 tokens, 128 units) made a step 1 % longer.
   if (tiles >= 2 && tiles <= RES_TILES && units * ((Lq + 63) / 64) * 8 <= 5 * (int64_t)cus) return {64, 4, true};
   if (tiles >= 12 && blocks128 * 4 <= 3 * (int64_t)cus) return {128, 2, false};
