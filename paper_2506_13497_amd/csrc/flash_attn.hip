@@ -579,8 +579,9 @@ __global__ __launch_bounds__(64 * QG * KS, 2) void k_flash_attn(FlashParams p) {
 
   // Sums over the sets of key tiles, whose references may have moved apart.  The sets from the second on hand theirs over in LDS, in
   // the place of the tiles, to the first, which weighs each by 2^(reference - largest reference).  A set without a
-  // term (no tile, or scores of -inf alone) has no say in the largest; one whose sums are infinite only for its reference's rounding, far
-  // below another's, has no weight: it is left out, since infinity times zero would be NaN.
+  // term (no tile, or scores of -inf alone) has no say in the largest; one whose sums are infinite only for the rounding of a reference far
+  // below another's has no weight: it is left out, since infinity times zero would be NaN.  (Not in the resident form: only the fifth tile
+  // follows a set's first there, and one set alone, which sees that tile last, would have overflowed before it too.)
   auto merge_sets = [&]() {
     constexpr int PART = C::DT * 4 + 1;   // 16-byte pieces a lane hands over
     static_assert((KS - 1) * QG * PART * 1024 <= NST * C::STAGE, "the sums fit the place of the tiles");
@@ -614,21 +615,25 @@ __global__ __launch_bounds__(64 * QG * KS, 2) void k_flash_attn(FlashParams p) {
       if (v[1] > 0.f) top = fmaxf(top, v[0]);
     }
     auto weight = [&](int k) { return l_of[k] == 0.f ? 0.f : __builtin_amdgcn_exp2f((m_set[k] - top) * p.scale_log2); };
+    if constexpr (!RES) {
+      bool infinite = false;
 #pragma unroll
-    for (int k = 0; k < KS; ++k) {
-      const bool out = l_of[k] == INFINITY && weight(k) == 0.f;
-      if (__builtin_amdgcn_ballot_w64(out) == 0) continue;
-      if (out) {
-        l_of[k] = 0.f;
-        if (k == 0) {
+      for (int k = 0; k < KS; ++k) infinite |= l_of[k] == INFINITY;
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(infinite) != 0, 0)) {
 #pragma unroll
-          for (int d = 0; d < C::DT; ++d)
+        for (int k = 0; k < KS; ++k)
+          if (l_of[k] == INFINITY && weight(k) == 0.f) {
+            l_of[k] = 0.f;
+            if (k == 0) {
 #pragma unroll
-            for (int e = 0; e < 16; ++e) oacc[d][e] = 0.f;
-        } else {
-          for (int i = 0; i < C::DT * 4; ++i)
-            *reinterpret_cast<floatx4 *>(smem + ((k - 1) * QG + qg) * (PART * 1024) + i * 1024 + lane * 16) = floatx4{0.f, 0.f, 0.f, 0.f};
-        }
+              for (int d = 0; d < C::DT; ++d)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) oacc[d][e] = 0.f;
+            } else {
+              for (int i = 0; i < C::DT * 4; ++i)
+                *reinterpret_cast<floatx4 *>(smem + ((k - 1) * QG + qg) * (PART * 1024) + i * 1024 + lane * 16) = floatx4{0.f, 0.f, 0.f, 0.f};
+            }
+          }
       }
     }
     const float w0 = weight(0);
@@ -849,7 +854,7 @@ FlashForm flash_form(int Lq, int Lk, int64_t units, int cus) {
   // ring.  What is saved is the chain of tiles (1.2 us a tile for a wavefront alone on its SIMD); what it costs is the CU's other workgroups,
   // among them those that fetch weights ahead, hence not up to the last CU.  16 heads, 300 keys, not split / split, a step of 28
   // blocks, ms: 256 tokens 4.82 / 4.77, 512 5.86 / 5.81, 640 6.13 / 6.05, 768 6.27 / 6.30, 1024 7.07 / 7.31 (192 and 256 workgroups);
-  // one frame of 1000 tokens 19.0 / 16.3 us back to back, of 3600 tokens and 4 heads 53.8 / 38.5 (the common reference is 0.3 of it); two sets
+  // one frame of 1000 tokens 19.0 / 16.3 us back to back, of 3600 tokens and 4 heads 53.8 / 38.5 (the common reference is 0.2 of it); two sets
   // of one tile each (128 tokens, 128 units) made a step 1 % longer.
   if (tiles >= 2 && tiles <= RES_TILES && units * ((Lq + 63) / 64) * 8 <= 5 * (int64_t)cus) return {64, 4, true};
   if (tiles >= 12 && blocks128 * 4 <= 3 * (int64_t)cus) return {128, 2, false};
