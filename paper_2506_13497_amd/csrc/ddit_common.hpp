@@ -107,7 +107,7 @@ int launch_gemm_grouped(const GemmArgs &a, int G, const void *const *W, const vo
                         hipStream_t s);
 int gemm_tile_count();
 int gemm_tile_info(int tile, int *rows, int *cols, int *wavefronts, int *wg_per_cu);
-// the tile the launcher would take (cus <= 0: the current device's CU count); us_per_tile, if not
+// the cheapest tile of the list, which is what the launcher takes where no form beside the list is (gemm_form; cus <= 0: the current device's CU count); us_per_tile, if not
 // null, receives the model's time for each of the gemm_tile_count() tiles
 int gemm_tile_choice(int epilogue, bool copy, int64_t N, int n, int k, int cus, float *us_per_tile);
 // Rows and columns of the output tiles of the launch that a linear, or the rest of one in two launches, takes; as above.

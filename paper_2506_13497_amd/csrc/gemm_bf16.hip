@@ -1061,8 +1061,9 @@ using Few64 = FewCfg<2, 2, 8, 1>;
 // k-steps, finds room on the chip at once, which for short contractions is several workgroups a CU; beyond that the tiles of several
 // rounds fetch more than the larger ones (1152 x 1152, 32 x 32: 224 tokens, 252 tiles, 8.6 us, 256 tokens, 288 tiles, 11.3; 768 x 256:
 // 640 tokens, 480 tiles, 7.0 against 8.8).  64 x 64 only for long contractions: with 18 k-steps it is as fast as the other kernel's 64 x 64
-// (12.4 / 12.5 us), with 32 up to 6 % slower, with 72 7-9 % faster, with 128 8 %.  Over 462 linears of 16 to 1680 tokens the
-// rule takes 0.2 % more time than the best of all tiles and never more than without these forms.
+// (12.4 / 12.5 us), with 32 up to 6 % slower, with 72 7-9 % faster, with 128 8 %.  Over 600 linears of 16 to 1624 tokens
+// (profiles/gemm_few_tokens_sweep.txt) the launcher takes 0.3 % more time than the best of all forms; the 443 that take these are 0.78 times the best
+// other tile's time on average, 1.03 at worst.
 constexpr int FEW_LONG_STEPS = 47;
 template <class C>
 bool few_fits(int64_t N, int n, int steps, int parts, int cus) {
@@ -1109,9 +1110,10 @@ int launch_one(const GemmParams &p0, hipStream_t s, const GT &gt = GT()) {
   p.tiles_m = (int)tiles_m;
   p.tiles_n = (p.n + C::BN - 1) / C::BN;
   // width of an out-feature group: at most 4 tiles (their W, about 3.5 MB at k = 1152, stays in an XCD's 4 MB L2 next to the token panels
-  // streaming through), as even as the tile count allows.  All of them where large tiles are 5 or 6 to a row of no more features
+  // streaming through), as even as the tile count allows.  All of them where large tiles are 5 to 8 to a row of no more features
   // than 4 of the largest: the tokens then pass once (steps of 7360 tokens 22.88 -> 22.72 ms, 12960 36.01 -> 35.86, six blocks of 8800
-  // 6.36 -> 6.33).  Wider groups for every tile: 3600 tokens 1.3 % longer, 1600 1 %.
+  // 6.36 -> 6.33; 361 linears of 1160 to 1536 features, by count of tiles: 5 0.99 of the time in groups of 4, 6 0.98, 7 0.98, 8 0.98, and 1.00 where
+  // 6 or 8 fill 1536).  Wider groups for every tile: 3600 tokens 1.3 % longer, 1600 1 %.
   const int max_w = C::BM >= 192 && C::BN >= 192 && p.tiles_n * C::BN <= 1536 ? p.tiles_n : 4;
   const int n_groups = (p.tiles_n + max_w - 1) / max_w;
   p.group_w = (p.tiles_n + n_groups - 1) / n_groups;
@@ -1145,10 +1147,11 @@ int launch_one(const GemmParams &p0, hipStream_t s, const GT &gt = GT()) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Tile choice.  Ten output tiles are compiled.  Which is fastest depends on how the tile grid divides over
+// Tile choice.  Ten output tiles make up the list that callers can force (ddit_linear_fwd_tile); 320 x 256 and 192 x 192 stand beside it,
+// below, and the forms for few tokens above.  Which is fastest depends on how the tile grid divides over
 // the CUs far more than on the tile's own efficiency (a 192 x 384 tile does twice the work per byte
 // fetched of a 128 x 192 one, but 60 of them leave 196 CUs idle).  The launcher therefore prices every tile
-// with a small model of the kernel and takes the cheapest.  With  tiles = ceil(N / rows) * ceil(n / cols),
+// with a small model of the kernel and takes the cheapest of the list, or one beside it whose price is lower by a margin.  With  tiles = ceil(N / rows) * ceil(n / cols),
 // q = ceil(tiles / CUs)  tiles on the busiest CU and  steps = ceil(k / 64),
 //     t = (a * steps + e[epilogue]) * q * (1 + s * min(1, tiles / CUs)) + 2.71      [microseconds]
 //         (+ f[copy] * min(1, tiles / CUs) for the residual update)
@@ -1158,7 +1161,7 @@ int launch_one(const GemmParams &p0, hipStream_t s, const GT &gt = GT()) {
 // (bench.py --tile-sweep, kept in profiles/gemm_tile_sweep.txt) of whole layers with every tile forced in turn, so that
 // operands, weights and the residual stream are where a step leaves them: hidden 1152 with 16, 8, 4 and 2 heads of 72, 256
 // and 2048, 31 token counts from 96 to 98316, twice.  Over that sweep the picks cost 0.5 % more than the best tile
-// everywhere, 1.15 times at worst (1.1 % and 1.29 with constants that had been fitted to launches with everything evicted),
+// everywhere, 1.17 times at worst (1.1 % and 1.29 with constants that had been fitted to launches with everything evicted),
 // and as much on the token counts that a fit to every other one has not seen.  The residual update that also writes
 // bf16(x) has constants of its own: at 12288 tokens, 1152 x 288, the largest tile takes 52.2 us with the copy and 31.6
 // without, 256 x 128 39.6 and 35.1.
@@ -1208,10 +1211,11 @@ constexpr int WIDE_K = 256;
 // 65 are listed tiles by that, 1.03 times as long with this one, and 128 are this tile, 0.97.
 constexpr float WIDE_BELOW_SHORT = 0.935f;
 constexpr int WIDE_SHORT_K = 1024, WIDE_PLAIN_K = 512;
+// In profiles/gemm_forms_sweep.txt, a sweep that the fit has not seen, 67 of 662 linears take it: 0.92 times the listed pick's time on average, 1.05 at worst.
 // And 192 x 192, which is one round of the chip up to 8064 tokens of 1152 features, where from 7200 on 192 x 256 leaves a tenth of its
 // columns and a quarter of the CUs empty, and in the same place for other widths.  Fitted to a sweep of the same layers with it forced;
-// taken where it is one round and its price a hundredth below the best one's: 20 of the sweep's 918 linears, 0.88 of the other tile's time on
-// average and never more.  (Over several rounds the model overrates it: steps of 14800 to 56800 tokens 0 to 2 % longer; at equal
+// taken where it is one round and its price a hundredth below the best one's: 20 linears of profiles/gemm_forms_sweep.txt, 0.90 of the other tile's
+// time on average, 1.05 at worst.  (Over several rounds the model overrates it: steps of 14800 to 56800 tokens 0 to 2 % longer; at equal
 // prices, fc1 of 1600 tokens, a step was 0.5 % longer.)  7756 tokens, us with an event pair's 3.5: fc2
 // 115.5 -> 86.1, out-projection with the copy 52.8 -> 42.2, without 40.4 -> 32.1, cross-attention q 31.2 -> 26.8; q|k|v of 2440 tokens 33.4 -> 27.6.
 // A step of six blocks: 2496 tokens 2.30 -> 2.26 ms, 5440 4.03 -> 3.96, 6848 4.72 -> 4.63, 7360 5.35 -> 4.94; 4 heads 7360 3.78 -> 3.42.

@@ -72,3 +72,19 @@ def test_text_projections_of_short_contractions(m):
     """56 layers of 512 features, k = 256: 600 text tokens 18.3 us with the best listed tile, 16.6 with 320 x 256; 1600 35.2 and 41.8; 2000 42.7 and 49.3."""
     form = lambda Ly, B: m.ddit_cross_kv_form(m.make_shape(B, 1, 1, 2, 256, 4, 64, 64, Ly, 28), 256)
     assert form(300, 2) == (320, 256) and form(200, 8) != (320, 256) and form(500, 4) != (320, 256)
+
+
+@pytest.mark.parametrize("table,forms,mean,worst", [("gemm_forms_sweep.txt", {(320, 256): 10}, 0.94, 1.06), ("gemm_forms_sweep.txt", {(192, 192): 11}, 0.92, 1.06),
+                                                    ("gemm_few_tokens_sweep.txt", {1: 12, 2: 13, 3: 14}, 0.79, 1.04)])
+def test_forms_beside_the_list_against_their_recorded_sweeps(m, table, forms, mean, worst):
+    """Where the launcher takes a form beside the list, the form's recorded time over that of the best listed tile."""
+    import bench
+    rows, tiles = bench.read_tile_sweep(os.path.join(ROOT, "profiles", table))
+    count = m.ddit_linear_tile_count()
+    ratio = []
+    for epi, n, k, N, us in rows:
+        few = m.ddit_linear_few_form(N, n, k, 1, 256)
+        column = forms.get(few or m.ddit_linear_form(epi, N, n, k, 256))
+        if column is not None:
+            ratio.append(us[column] / min(us[:count]))
+    assert len(ratio) >= 15 and sum(ratio) / len(ratio) <= mean and max(ratio) <= worst
