@@ -124,6 +124,11 @@ static int do_shape(FILE *f) {
   printf("shape ws %d %zu\n", rc, rc == 0 ? bytes : (size_t)0);
   const int rk = ddit_cross_kv_bytes(&s, &kv);
   printf("shape kv %d %zu\n", rk, rk == 0 ? kv : (size_t)0);
+  for (int kind = 0; kind < 4; ++kind) {   // kind 3: the text projections
+    int32_t q = -1, sets = -1, resident = -1;
+    const int rf = kind < 3 ? ddit_attn_form((ddit_attn_kind)kind, &s, 256, &q, &sets, &resident) : ddit_cross_kv_form(&s, 256, &q, &sets);
+    printf("form %d %d %d %d %d\n", kind, rf, q, sets, resident);
+  }
   if (s.flags & DDIT_FLAG_TAPS) {
     for (int layer = 0; layer < 2; ++layer)
       for (int t = 0; t < DDIT_TAP_COUNT; ++t) {
@@ -177,6 +182,11 @@ static int do_linear(FILE *f) {
   int64_t front = -1;
   printf("front %d", ddit_linear_front_tokens((int)v[0], v[1], (int32_t)v[2], (int32_t)v[3], (int32_t)v[4], &front));
   printf(" %lld\n", (long long)front);
+  int32_t rows = -1, cols = -1, few = -1;
+  printf("form %d", ddit_linear_form((int)v[0], v[1], (int32_t)v[2], (int32_t)v[3], (int32_t)v[4], &rows, &cols));
+  printf(" %d %d", rows, cols);
+  printf(" %d", ddit_linear_few_form(v[1], (int32_t)v[2], (int32_t)v[3], 1, (int32_t)v[4], &few));
+  printf(" %d\n", few);
   // the linear's own validation: refused before any launch
   alignas(16) static unsigned char buf[64];
   printf("v linear_null %d\n", ddit_linear_fwd((int)v[0], nullptr, 8, buf, nullptr, 8, 8, 8, buf, 8, nullptr, nullptr, nullptr, -1, 1, nullptr));

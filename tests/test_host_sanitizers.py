@@ -171,6 +171,11 @@ def test_validation_and_layout_under_sanitizers_equal_the_ordinary_build(exe, tm
         assert out[i] == "shape ws %d %d" % (rc, n.value if rc == 0 else 0), (s, out[i]); i += 1
         rc = lib.ddit_cross_kv_bytes(C.byref(shp), C.byref(n))
         assert out[i] == "shape kv %d %d" % (rc, n.value if rc == 0 else 0); i += 1
+        for kind in range(4):
+            v = [C.c_int32(-1) for _ in range(3)]
+            at = [C.byref(x) for x in v]
+            rc = lib.ddit_attn_form(kind, C.byref(shp), 256, *at) if kind < 3 else lib.ddit_cross_kv_form(C.byref(shp), 256, *at[:2])
+            assert out[i].split() == ["form", str(kind), str(rc)] + [str(x.value) for x in v]; i += 1
         if s[0] & 1:
             for layer in range(2):
                 for t in range(len(m.TAP_NAMES)):
@@ -195,5 +200,7 @@ def test_validation_and_layout_under_sanitizers_equal_the_ordinary_build(exe, tm
         assert got[:3] == ["tile", "0", str(tile)]
         assert [float(v) for v in got[3:]] == pytest.approx(us, rel=1e-4)
         assert out[i].split() == ["front", "0", str(m.ddit_linear_front_tokens(e, N, n_, k, cu))]; i += 1
+        form = m.ddit_linear_form(e, N, n_, k, cu)
+        assert out[i].split() == ["form", "0", str(form[0]), str(form[1]), "0", str(m.ddit_linear_few_form(N, n_, k, 1, cu))]; i += 1
         assert out[i:i + 4] == ["v linear_null -1", "v linear_dims -2", "v linear_align -4", "v linear_zero_rows 0"]; i += 4
     assert i == len(out)
