@@ -161,7 +161,7 @@ int ddit_attn_fwd(ddit_attn_kind kind, const ddit_shape *shape, const void *q, c
                   int64_t ld_q, int64_t ld_kv, const int32_t *kv_valid_len_host, void *o, int64_t ld_o,
                   float *lse_or_null, void *workspace, size_t workspace_bytes, void *hip_stream);
 
-/* How ddit_attn_fwd splits that work on a device of compute_units CUs (<= 0: the current device's count, 256 if there is no
+/* How ddit_attn_fwd splits that work, with all keys valid, on a device of compute_units CUs (<= 0: the current device's count, 256 if there is no
  * device) -> queries of a workgroup (0: the kernel for short temporal sequences takes the call), sets of wavefronts that share a
  * sequence's keys, and whether all keys are fetched at once (1) or tile by tile (0).  Host only; needs no GPU. */
 int ddit_attn_form(ddit_attn_kind kind, const ddit_shape *shape, int32_t compute_units, int32_t *queries_out,

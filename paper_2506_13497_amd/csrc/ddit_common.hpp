@@ -139,13 +139,13 @@ struct AttnArgs {
   const void *k2, *v2; int split;
 };
 int launch_flash_attn(const AttnArgs &a, hipStream_t s);
-// How launch_flash_attn splits the work for units (groups x heads) of Lq queries and at most Lk keys.
+// How launch_flash_attn splits the work for units (groups x heads) of Lq queries and at most Lk keys, of which the longest has `longest`.
 struct FlashForm {
   int queries;    // per workgroup (of the resident form that walks over query tiles: per tile)
   int key_sets;   // sets of wavefronts that share the keys
   bool resident;  // all keys are fetched at once
 };
-FlashForm flash_form(int Lq, int Lk, int64_t units, int cus);
+FlashForm flash_form(int Lq, int Lk, int longest, int64_t units, int cus);
 int temporal_attn_max_T();   // longest sequence the dedicated temporal kernel takes
 // g_q/g_k (per-head RMS-norm scales, both or neither) and rope_table ([T, dh/2] (cos, sin)) may be null:
 // when given, q and k are normalised / rotated inside the kernel on their way in

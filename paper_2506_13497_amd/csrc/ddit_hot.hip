@@ -636,9 +636,9 @@ int ddit_attn_form(ddit_attn_kind kind, const ddit_shape *shape, int32_t compute
   if (!queries_out || !key_sets_out || !resident_out) { set_error("queries_out, key_sets_out and resident_out must not be NULL"); return DDIT_ERR_INVALID_ARG; }
   FlashForm f = {0, 0, false};
   const int cus = compute_units > 0 ? compute_units : device_cus();
-  if (kind == DDIT_ATTN_SPATIAL) f = flash_form((int)d.S, (int)d.S, d.B * d.T * d.H, cus);
-  else if (kind == DDIT_ATTN_CROSS) f = flash_form((int)d.L, (int)d.Ly, d.B * d.H, cus);
-  else if (d.T > temporal_attn_max_T()) f = flash_form((int)d.T, (int)d.T, d.B * d.S * d.H, cus);
+  if (kind == DDIT_ATTN_SPATIAL) f = flash_form((int)d.S, (int)d.S, (int)d.S, d.B * d.T * d.H, cus);
+  else if (kind == DDIT_ATTN_CROSS) f = flash_form((int)d.L, (int)d.Ly, (int)d.Ly, d.B * d.H, cus);
+  else if (d.T > temporal_attn_max_T()) f = flash_form((int)d.T, (int)d.T, (int)d.T, d.B * d.S * d.H, cus);
   *queries_out = f.queries; *key_sets_out = f.key_sets; *resident_out = f.resident;
   return DDIT_OK;
 }

@@ -835,7 +835,7 @@ int launch_dh(const FlashParams &p, int64_t blocks, hipStream_t s) {
 
 namespace ddit {
 
-FlashForm flash_form(int Lq, int Lk, int64_t units, int cus) {
+FlashForm flash_form(int Lq, int Lk, int longest, int64_t units, int cus) {
   // Short key sequences (cross-attention to the text): the resident form, one workgroup per CU, as many chunks per unit
   // as that allows.  It pays where every workgroup gets a run of at least four query tiles to spread the one-off K/V
   // fetch over, and, with two key tiles and more, as soon as the streaming form's 128 queries a workgroup would put two of them on a
@@ -856,8 +856,13 @@ FlashForm flash_form(int Lq, int Lk, int64_t units, int cus) {
   // blocks, ms: 256 tokens 4.82 / 4.77, 512 5.86 / 5.81, 640 6.13 / 6.05, 768 6.27 / 6.30, 1024 7.07 / 7.31 (192 and 256 workgroups);
   // one frame of 1000 tokens 19.0 / 16.3 us back to back, of 3600 tokens and 4 heads 53.8 / 38.5 (the common reference is 0.2 of it); two sets
   // of one tile each (128 tokens, 128 units) made a step 1 % longer.
-  if (tiles >= 2 && tiles <= RES_TILES && units * ((Lq + 63) / 64) * 8 <= 5 * (int64_t)cus) return {64, 4, true};
-  if (tiles >= 12 && blocks128 * 4 <= 3 * (int64_t)cus) return {128, 2, false};
+  // With few tiles there is little to share and a meeting to pay for, so it is asked of the longest sequence that there is, and where 65 to 128
+  // queries are one workgroup of the streaming form and two here it takes a tile more.  Kernel trace, not split / split, us, by valid keys: 16
+  // heads, 300 queries, 40 keys 6.5 / 7.5, 100 7.7 / 7.8, 170 8.7 / 8.7, 230 9.6 / 9.2, 300 10.3 / 9.7; 4 heads 6.5 / 7.2, 7.6 / 7.4, 8.5 / 8.2, 9.5 / 8.5, 10.2 / 9.2;
+  // 16 heads, 72 queries 6.2 / 7.5, 7.4 / 7.8, 8.3 / 8.6, 9.3 / 9.0, 10.0 / 9.5; frames of 80 tokens 7.3 / 7.8, of 144 8.6 / 8.5, of 200 9.8 / 9.6.
+  const int longest_tiles = (longest + KT - 1) / KT;
+  if (tiles <= RES_TILES && longest_tiles >= (Lq > 64 && Lq <= 128 ? 4 : 3) && units * ((Lq + 63) / 64) * 8 <= 5 * (int64_t)cus) return {64, 4, true};
+  if (longest_tiles >= 12 && blocks128 * 4 <= 3 * (int64_t)cus) return {128, 2, false};
   // Up to 64 queries (one tile of keys: temporal attention of 33 to 64 frames) half of a workgroup of 128 would
   // be idle and take a CU's slots: 64 queries per workgroup, three workgroups per CU instead of two.  128 / 64
   // queries, d_h = 72: 405 locations x 16 heads, T = 51 71.9 / 57.6 us, T = 64 69.5 / 64.1; 920 x 4, T = 33
@@ -896,7 +901,9 @@ int launch_flash_attn(const AttnArgs &a, hipStream_t s) {
   }
   p.n_units = a.n_groups * a.H;
   p.n_chunks = 1; p.qtiles_per_chunk = 1;
-  const FlashForm form = flash_form(a.Lq, a.Lk_max, p.n_units, device_cus());
+  int longest = a.Lk_max;
+  if (a.use_kv_len) longest = *std::max_element(a.kv_len, a.kv_len + std::min(a.n_groups / a.g_inner, 64));
+  const FlashForm form = flash_form(a.Lq, a.Lk_max, longest, p.n_units, device_cus());
   p.n_qtiles = (a.Lq + form.queries - 1) / form.queries;
   if (form.resident && form.key_sets == 1) {
     const int chunks = std::max(1, device_cus() / std::max(1, p.n_units));   // workgroups per unit, at one per CU

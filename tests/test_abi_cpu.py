@@ -453,8 +453,9 @@ def test_which_form_takes_a_call(m):
     assert attn(m.DDIT_ATTN_TEMPORAL, 32, 9, 4) == (0, 0, False) and attn(m.DDIT_ATTN_TEMPORAL, 33, 9, 4) == (64, 1, False)
     assert attn(m.DDIT_ATTN_CROSS, 30, 1620, 16, 287) == (256, 1, True)
     assert attn(m.DDIT_ATTN_SPATIAL, 30, 1620, 16) == (128, 1, False)
-    assert [attn(m.DDIT_ATTN_CROSS, 1, 640, 16, Ly) for Ly in (64, 65, 320, 321, 704, 705)] == [
+    assert [attn(m.DDIT_ATTN_CROSS, 1, 640, 16, Ly) for Ly in (128, 129, 320, 321, 704, 705)] == [
         (128, 1, False), (64, 4, True), (64, 4, True), (128, 1, False), (128, 1, False), (128, 2, False)]
+    assert [attn(m.DDIT_ATTN_CROSS, 1, L, 16, 192)[1] for L in (64, 65, 128, 129)] == [4, 1, 1, 4]
     assert [attn(m.DDIT_ATTN_CROSS, 1, L, 16) for L in (640, 641)] == [(64, 4, True), (128, 1, False)]
     assert [attn(m.DDIT_ATTN_CROSS, 1, L, 16, 1000)[1] for L in (1536, 1537)] == [2, 1]
     text = lambda Ly, H=16, blocks=28: m.ddit_cross_kv_form(m.make_shape(1, 1, 1, 2, 1152, H, 72, 4608, Ly, blocks), 256)

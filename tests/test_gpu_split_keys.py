@@ -13,8 +13,8 @@ from oracle import stdit_oracle as ora
 pytestmark = pytest.mark.gpu
 
 
-def sets_of(keys):
-    return 4 if 64 < keys <= 320 else 2 if keys > 704 else 1
+def sets_of(keys, queries):
+    return 4 if (192 if 64 < queries <= 128 else 128) < keys <= 320 else 2 if keys > 704 else 1
 
 
 def run(kind, sh, d, sets, valid=None):
@@ -31,26 +31,26 @@ def run(kind, sh, d, sets, valid=None):
 
 @pytest.mark.parametrize("H,dh", [(5, 72), (4, 64)])
 @pytest.mark.parametrize("Ly,valid,L", [(300, [300, 1, 64], 65), (320, [65, 320, 129], 64), (321, [321, 2, 200], 129),
-                                        (700, [700, 640, 63], 33), (128, [128, 65, 66], 1), (705, [705, 64, 65], 33),
+                                        (700, [700, 640, 63], 33), (128, [128, 65, 66], 1), (192, [192, 65, 129], 1), (129, [129, 128, 64], 200), (193, [193, 192, 1], 128), (300, [60, 64, 1], 65), (705, [705, 64, 65], 33),
                                         (720, [720, 128, 129], 33), (1031, [1031, 1, 700], 130), (768, [768, 767, 705], 96)])
 def test_cross(Ly, valid, L, H, dh):
     import paper_2506_13497_amd as m
     sh = syn.Shape(3, 1, 1, L, H * dh, H, dh, 64, Ly, 1)
     d = syn.make_attn_inputs("cross", sh, 71, q_scale=3.0, Lq=L)
     o_ref, lse_ref = ora.cross_attention(*(to_f64(d[k]) for k in "qkv"), np.array(valid))
-    o, lse = run(m.DDIT_ATTN_CROSS, sh, d, sets_of(Ly), valid)
+    o, lse = run(m.DDIT_ATTN_CROSS, sh, d, sets_of(Ly, L), valid)
     assert_parity(o, o_ref.reshape(o.shape), "cross %d %s" % (Ly, valid))
     assert np.abs(lse - lse_ref.reshape(lse.shape)).max() <= 2e-2
 
 
 @pytest.mark.parametrize("H,dh", [(4, 72), (4, 64)])
-@pytest.mark.parametrize("S", [65, 192, 193, 320, 321, 450, 704, 705, 832, 1031])
+@pytest.mark.parametrize("S", [65, 129, 192, 193, 320, 321, 450, 704, 705, 832, 1031])
 def test_spatial(S, H, dh):
     import paper_2506_13497_amd as m
     sh = syn.Shape(1, 2, 1, S, H * dh, H, dh, 64, 8, 1)
     d = syn.make_attn_inputs("spatial", sh, 72, q_scale=2.0)
     o_ref, lse_ref = ora.spatial_attention(*(to_f64(d[k]) for k in "qkv"))
-    o, lse = run(m.DDIT_ATTN_SPATIAL, sh, d, sets_of(S))
+    o, lse = run(m.DDIT_ATTN_SPATIAL, sh, d, sets_of(S, S))
     assert_parity(o, o_ref, "spatial %d" % S)
     assert np.abs(lse - lse_ref.reshape(lse.shape)).max() <= 2e-2
 
@@ -66,7 +66,7 @@ def test_a_dominant_key_in_one_set(Ly, at):
     k = -4.0 * np.abs(rng.standard_normal((1, Ly, H, dh)))
     k[:, at] = 4.0
     q, k, v = (torch.from_numpy(a).to(torch.bfloat16) for a in (q, k, rng.standard_normal((1, Ly, H, dh))))
-    o, lse = run(m.DDIT_ATTN_CROSS, sh, {"q": q.cuda(), "k": k.cuda(), "v": v.cuda()}, sets_of(Ly))
+    o, lse = run(m.DDIT_ATTN_CROSS, sh, {"q": q.cuda(), "k": k.cuda(), "v": v.cuda()}, sets_of(Ly, L))
     o_ref, lse_ref = ora.cross_attention(*(t.double().numpy() for t in (q, k, v)), np.array([Ly]))
     assert_parity(o, o_ref, "dominant key %d" % at)
     assert np.abs(lse / lse_ref.reshape(lse.shape) - 1).max() <= 1e-2
@@ -85,7 +85,7 @@ def test_scores_of_minus_infinity_in_one_set(Ly, at):
     cut = k.clone()
     cut[:, list(at), :, 0] = float("-inf")
     keep = [j for j in range(Ly) if j not in set(at)]
-    o, _ = run(m.DDIT_ATTN_CROSS, sh, {"q": q.cuda(), "k": cut.cuda(), "v": v.cuda()}, sets_of(Ly))
+    o, _ = run(m.DDIT_ATTN_CROSS, sh, {"q": q.cuda(), "k": cut.cuda(), "v": v.cuda()}, sets_of(Ly, L))
     o_ref, _ = ora.cross_attention(*(t.double().numpy() for t in (q, k[:, keep], v[:, keep])), np.array([len(keep)]))
     assert_parity(o, o_ref, "-inf in one set")
 
@@ -94,7 +94,7 @@ def attend(q, k, v, keep=None):
     """The kernel's output and log-sum-exp of one sample of cross-attention, and the oracle's over the keys kept."""
     import paper_2506_13497_amd as m
     L, Ly, H, dh = q.shape[1], k.shape[1], q.shape[2], q.shape[3]
-    o, lse = run(m.DDIT_ATTN_CROSS, syn.Shape(1, 1, 1, L, H * dh, H, dh, 64, Ly, 1), {"q": q.cuda(), "k": k.cuda(), "v": v.cuda()}, sets_of(Ly))
+    o, lse = run(m.DDIT_ATTN_CROSS, syn.Shape(1, 1, 1, L, H * dh, H, dh, 64, Ly, 1), {"q": q.cuda(), "k": k.cuda(), "v": v.cuda()}, sets_of(Ly, L))
     keep = list(range(Ly)) if keep is None else keep
     o_ref, lse_ref = ora.cross_attention(*(t.double().numpy() for t in (q, k[:, keep], v[:, keep])), np.array([len(keep)]))
     return o, lse, o_ref, lse_ref.reshape(lse.shape)
@@ -110,7 +110,7 @@ def operands_with_a_bias(Ly, H, dh, seed):
 
 @pytest.mark.parametrize("H,dh", [(4, 72), (4, 64)])
 @pytest.mark.parametrize("level", [-1e6, -1e9, -3.3e38])
-@pytest.mark.parametrize("Ly,tiles", [(300, (0,)), (300, (1,)), (300, (2,)), (300, (3,)), (300, (4,)), (300, (1, 2, 3)), (90, (1,)),
+@pytest.mark.parametrize("Ly,tiles", [(300, (0,)), (300, (1,)), (300, (2,)), (300, (3,)), (300, (4,)), (300, (1, 2, 3)), (200, (1,)),
                                       (720, (0,)), (720, (1,)), (720, (2,)), (720, (3,)), (720, (1, 3, 5, 7, 9, 11)), (720, (11,)), (705, (1,))])
 def test_whole_tiles_far_below(Ly, tiles, level, H, dh):
     """Key tiles whose scores lie far below the others' have no weight, whichever set has them and whether or not their level is a

@@ -88,3 +88,19 @@ def test_forms_beside_the_list_against_their_recorded_sweeps(m, table, forms, me
         if column is not None:
             ratio.append(us[column] / min(us[:count]))
     assert len(ratio) >= 15 and sum(ratio) / len(ratio) <= mean and max(ratio) <= worst
+
+
+# kernel times of attention of few units (kind, heads, frames, queries of a unit, keys), microseconds, the keys shared by four sets of wavefronts or not
+SPLIT_KEYS_TIMES = {("cross", 4, 1, 36, 100): (6.64, 6.04), ("cross", 4, 1, 36, 170): (7.48, 8.10), ("cross", 4, 1, 72, 170): (8.20, 7.28), ("cross", 4, 1, 160, 230): (8.60, 9.48),
+                    ("cross", 4, 1, 512, 300): (9.10, 10.26), ("cross", 16, 1, 36, 300): (9.08, 11.60), ("cross", 16, 1, 72, 100): (7.82, 7.40), ("cross", 16, 1, 72, 170): (8.60, 8.26),
+                    ("cross", 16, 1, 72, 230): (8.98, 9.34), ("cross", 16, 1, 640, 100): (8.16, 7.84), ("cross", 16, 1, 640, 300): (10.12, 10.58), ("spatial", 4, 2, 144, 144): (8.08, 8.48),
+                    ("spatial", 16, 2, 80, 80): (7.82, 7.32), ("spatial", 16, 5, 128, 128): (8.04, 7.66), ("spatial", 16, 1, 300, 300): (9.72, 10.28), ("spatial", 4, 1, 128, 128): (7.36, 6.38)}
+
+
+@pytest.mark.parametrize("case", sorted(SPLIT_KEYS_TIMES))
+def test_keys_are_shared_where_that_was_faster(m, case):
+    kind, H, T, L, keys = case
+    split, whole = SPLIT_KEYS_TIMES[case]
+    shape = m.make_shape(1, T, 1, L, H * 72, H, 72, 64, keys, 1)
+    form = m.ddit_attn_form(m.DDIT_ATTN_CROSS if kind == "cross" else m.DDIT_ATTN_SPATIAL, shape, 256)
+    assert (form[1] == 4) == (split < whole)
