@@ -843,11 +843,14 @@ FlashForm flash_form(int Lq, int Lk, int longest, int64_t units, int cus) {
   // (64 CUs busy; stays streaming), 2304 13.3 / 12.0, 4600 22.0 / 19.0, 7360 26.8 / 21.4, 9720 44.5 / 38.1; 4 heads 2304 8.9 / 10.5
   // (stays), 9720 12.7 / 11.5; 60 keys, 12960 queries 36.5 / 37.6 (stays); frames of 144 tokens, 160 units 14.4 / 12.4, 256
   // 16.7 / 15.2.  Not where units of one query tile alone are more than the CUs (225 tokens, 512 units 35.6 / 40.4: each
-  // workgroup waits for its whole K and V with nothing beside it on the CU), nor where tiles of 256 queries are much emptier.
+  // workgroup waits for its whole K and V with nothing beside it on the CU), nor where tiles of 256 queries are much emptier, nor, for the
+  // same wait, where units of one query tile fill most of the chip: frames of 256 tokens, 160 units 13.0 / 13.0, 176 13.4 / 13.9, 240 15.0 / 16.4,
+  // 256 15.2 / 16.9; 200 tokens, 144 units 12.8 / 11.7, 256 14.8 / 14.9; 192 tokens, 176 11.3 / 11.2, 240 12.4 / 12.9; 144 tokens, 256 12.7 / 12.2.
   const int64_t res_qtiles = (Lq + 32 * RES_NW - 1) / (32 * RES_NW), qtiles = (Lq + 127) / 128;
   const int64_t chunks = units > 0 && units < cus ? cus / units : 1, blocks128 = units * qtiles;
   const int tiles = (Lk + KT - 1) / KT;
-  const bool shared = tiles >= 2 && units <= cus && blocks128 > cus && 14 * res_qtiles <= 8 * qtiles;
+  const bool shared = tiles >= 2 && units <= cus && blocks128 > cus && 14 * res_qtiles <= 8 * qtiles &&
+                      (res_qtiles > 1 || units * Lq * 8 <= 5 * 32 * RES_NW * (int64_t)cus);
   if (tiles <= RES_TILES && (res_qtiles >= 4 * chunks || shared)) return {32 * RES_NW, 1, true};
   // Fewer workgroups than CUs: the wavefronts of a workgroup share the keys as well (see merge_sets).  Up to five key tiles, all fetched at once,
   // two groups of 32 queries and four sets of tiles; from twelve on, four groups and two sets, each with its own two-stage

@@ -104,3 +104,16 @@ def test_keys_are_shared_where_that_was_faster(m, case):
     shape = m.make_shape(1, T, 1, L, H * 72, H, 72, 64, keys, 1)
     form = m.ddit_attn_form(m.DDIT_ATTN_CROSS if kind == "cross" else m.DDIT_ATTN_SPATIAL, shape, 256)
     assert (form[1] == 4) == (split < whole)
+
+
+# kernel times of one frame after the other (heads, frames, tokens of a frame), 64 keys a tile through a ring or all keys fetched at once
+RESIDENT_TIMES = {(16, 16, 144): (12.68, 12.18), (16, 16, 160): (12.80, 12.50), (16, 16, 192): (12.92, 13.30), (16, 16, 256): (15.20, 16.92), (16, 15, 240): (15.22, 16.12),
+                  (16, 13, 160): (11.84, 11.20), (16, 13, 224): (14.00, 14.36), (16, 11, 200): (13.22, 12.66), (16, 11, 256): (13.40, 13.92), (16, 9, 256): (13.14, 12.60),
+                  (4, 51, 130): (11.20, 10.22), (4, 51, 250): (14.24, 15.04), (4, 40, 224): (13.04, 12.74), (4, 64, 224): (15.04, 15.86)}
+
+
+@pytest.mark.parametrize("case", sorted(RESIDENT_TIMES))
+def test_keys_are_fetched_at_once_where_that_was_faster(m, case):
+    H, T, S = case
+    ring, resident = RESIDENT_TIMES[case]
+    assert m.ddit_attn_form(m.DDIT_ATTN_SPATIAL, m.make_shape(1, T, 1, S, H * 72, H, 72, 64, 8, 1), 256)[2] == (resident < ring)
